@@ -1,23 +1,34 @@
 // gsr_composite.hip -- per-tile compositing on gfx950 (A6 forward, A7 backward).
 //
-// Mapping.  One wave64 per tile of 16 x (4 RPL) pixels: lane l owns column
-// l % 16 and rows l / 16 + 4 k, k < RPL, of the tile.  A tile's sorted list is
-// consumed in batches of 64 records: each lane stages one record in LDS
-// (pre-scaled conic, tile-relative centre) and the whole wave then reads them
-// back as broadcasts.  With a single wave per tile there is no cross-wave
-// synchronisation in the inner loop, and a row "slab" (the 16 x 4 pixels of
-// one k) is skipped as a whole when the Gaussian's alpha >= 1/255 box misses
-// it.  Both passes take every decision (slab skip, alpha < 1/255, the stop)
-// with the same instructions on the same values, so the backward replays
-// exactly the forward's contributors.  The per-pixel updates
-// are branch-free (selects), so the only branches are wave-uniform.
+// Mapping.  A tile is 16 pixels wide and a multiple of 4 high; a "slab" is 16
+// x 4 of its pixels, one per lane of a wave64 (lane l: column l % 16, row
+// l / 16).  W waves share a tile, each owning RPL consecutive slabs (pixel
+// state in registers, RPL pixels per lane).  A tile's sorted list is consumed
+// in batches of 64 W records: each thread stages one record in LDS (pre-scaled
+// conic, tile-relative centre, and the mask of the slabs its alpha >= 1/255
+// ellipse reaches), then every wave lists the records that meet its slabs by
+// a ballot over the masks and walks that list four records at a time in
+// straight-line code, reading them back as LDS broadcasts.  So a record costs
+// a wave nothing where it misses its slabs, four exponentials are in flight
+// before the transmittance chain needs the first, and no row tests whether it
+// is worth evaluating (all but about 5 % of the listed ones are).  The pixel
+// updates are branch-free (selects).  Against one record at a time with a
+// skip test per row, one wave per tile, this took the fused step of a 1080p
+// view of 1M Gaussians from 332 to 303 us and of 200k from 265 to 224 us.
 //
-// Early stop.  Dense scenes saturate long before the end of a tile's list:
-// the forward records per tile the number of list positions any of its
-// pixels used (nmax).  The backward replays only [start, start + nmax) and
-// flags the pair slots of those positions as it stages their records; the
-// per-Gaussian reduction reads the moments of flagged slots only, so unused
-// pairs cost neither a replay nor a write nor a read.
+// Waves per tile.  One wave per tile leaves the chip idle when a call has few
+// tiles, each a serial chain over its list: 640 x 480 has 1,200 tiles of 16 x
+// 16 for 1,024 SIMDs.  W > 1 splits the chain (forward 77 -> 26 us, backward
+// 123 -> 48 us there, W = 4), but repeats the records' part of the work in
+// every wave and, in the backward, the reduction; tile_waves() has the rule.
+// The image does not depend on W (each pixel's arithmetic and order are the
+// same); the moments are summed in another order.
+//
+// Early stop.  Dense scenes saturate long before the end of a tile's list: a
+// wave drops a slab once all its pixels have stopped, and the forward records
+// per tile the number of list positions any of its pixels used (nmax).  The
+// backward replays only [start, start + nmax) and flags the pair slots whose
+// moments it writes; the per-Gaussian reduction reads those only.
 //
 // Backward.  Front to back again (nothing per (pixel, Gaussian) is stored):
 // from the forward's output C_out and the running accumulation, the colour
@@ -26,21 +37,24 @@
 // g.B = g.C_out - sum, from which alpha dL/dalpha = w g.c - g.B alpha / (1 - alpha)
 // (w = alpha T); with g.B taken after the Gaussian's own term and
 // T' = T (1 - alpha) that is w (g.c - g.B / T'), one reciprocal per row and
-// one fused multiply-add for the update of g.B.  A Gaussian that no lane
-// reaches in any row skips the
-// reduction: its moments are zero and the finalising lanes write zeros.
+// one fused multiply-add for the update of g.B.
 // Per pair the kernel produces nine moments over the tile's pixels: with
 // w = dL/dsigma, the sums of w dx, w dy, w dx^2, w dx dy, w dy^2, of
 // alpha dL/dalpha and of the colour gradient; they are linear in the per-pixel
 // terms, so the conversion to (u, v, conic, opacity) gradients happens once
-// per Gaussian after the reduction over its tiles.  Each lane sums its pixels'
-// terms in registers; the lanes of each quad are added with two DPP swaps,
-// and the 16 quad sums are transposed through LDS in groups of seven
-// Gaussians (63 values per row), after which lane r < 63 adds the 16 values
-// of one (Gaussian, moment) in a fixed order (no atomics, deterministic) and
-// the pair's slot in emission order is written once.  (Quads rather than lane
-// pairs halve the transpose buffer, which had held the kernel to 3.5 waves
-// per SIMD.)
+// per Gaussian after the reduction over its tiles.
+//
+// Reduction.  A lane's column fixes dx, so the lanes of one column (the four
+// rows of 16 lanes) only need the sums of six values: sa = alpha dL/dalpha,
+// sa dy, sa dy^2 and the colour gradient.  For four Gaussians together two
+// lane-swap levels (v_permlane32_swap, v_permlane16_swap: two instructions
+// turn two values into one register of half sums) leave six registers whose
+// row q holds Gaussian q's 16 column sums; the products with dx follow, once
+// for all four, and 36 lanes add the 16 columns of one (Gaussian, moment)
+// each from LDS, in a fixed order (no atomics, deterministic).  About 16
+// instructions per Gaussian, against 30 for nine values summed over lane
+// quads and transposed through LDS.  With W > 1 the waves' moments of 64
+// records are added in wave order before they are written.
 //
 // Schedule.  The forward files every tile in a bucket of its replay count
 // (nmax), and the backward's workgroups take the tiles heaviest first: in
@@ -48,15 +62,15 @@
 // workgroup takes which tile changes no result.
 //
 // Fused step.  For the mean absolute error the upstream gradient of a pixel
-// is a function of that pixel's colour alone, so k_composite_step runs a
-// tile's forward and, in the same workgroup, its backward: the two tile
-// passes are the functions the separate kernels call, so the results are
-// theirs bit for bit, but a SIMD then holds waves in both phases (the
-// backward's arithmetic fills the forward's latency) and the forward's
-// per-pixel state never leaves registers.  Its schedule cannot use this
-// step's replay counts, which exist only after the forward; it takes the
-// tile's list length, capped by the replay count the workspace holds from the
-// previous step.
+// is a function of that pixel's colour alone, so the fused pass runs a tile's
+// forward and, in the same workgroup, its backward: the same device
+// functions, so the results are theirs bit for bit, but a SIMD then holds
+// waves in both phases (the backward's arithmetic fills the forward's
+// latency), the forward's per-pixel state never leaves registers, and a list
+// that fits one batch is staged once.  Its schedule cannot use this step's
+// replay counts, which exist only after the forward; it takes the tile's list
+// length, capped by the replay count the workspace holds from the previous
+// step (exact for a repeated step, the list length on a fresh workspace).
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -153,11 +167,6 @@ __device__ __forceinline__ uint32_t slab_mask(float packed) {
     return __builtin_amdgcn_readfirstlane(__float_as_uint(packed));
 }
 
-// A slab whose every pixel has exponent below this (log2 of alpha before the
-// clamp) cannot reach alpha >= 1/255: skipping it changes no decision (the
-// margin dwarfs the exponential's rounding).
-constexpr float kLog2AlphaSkip = -7.9943534f - 0.01f;  // log2(1/255) - 0.01
-
 // The r-th tile of the backward's schedule: tiles in descending cost buckets
 // (any order within a bucket: tiles are independent, so results do not
 // depend on it), or tile r when the buckets do not hold every tile (a forward
@@ -181,13 +190,6 @@ __device__ __noinline__ uint32_t tile_by_cost(const uint32_t *__restrict__ order
     return order[kCostBuckets + (size_t)b * total_tiles + (k < cL0 ? k : k - cL0)];
 }
 
-__device__ __forceinline__ uint32_t next_tile(bool persistent, uint32_t *queue, uint32_t first, uint32_t &iter) {
-    if (!persistent) return iter++ == 0 ? first : 0xffffffffu;
-    uint32_t t = 0;
-    if (threadIdx.x == 0) t = atomicAdd(queue, 1u);
-    return __shfl(t, 0, kWave);
-}
-
 // Exponent of alpha before the clamp, ex = log2(opacity) - sigma log2e
 // = b.y + a.z dx^2 + a.w dx dy + b.x dy^2, for the pixel at (dx, dy) from the
 // centre.  A lane's pixels share dx, so the dx terms and b.y are formed once
@@ -206,176 +208,13 @@ __device__ __forceinline__ float alpha_exponent(const RowQuad &rq, const float4 
     return fmaf(fmaf(b.x, dy, rq.q), dy, rq.p);
 }
 
-// ---------------------------------------------------------------------------
-// A6: forward
-// ---------------------------------------------------------------------------
-// One tile's forward pass over its sorted list, from the per-pixel state
-// (T > 0: the pixel is still compositing; T < 0: it stopped, or lies outside
-// the image, and -T is its final transmittance) to the accumulated colours
-// and, per pixel, the list position after its last contributor (last).  With
-// STATS also the contributor count and the position of the stop.
-template <int RPL, bool STATS>
-__device__ __forceinline__ void tile_forward(const ViewTable &vt, const TileCtx &c, uint2 rg,
-                                             const uint32_t *__restrict__ pval, const Rec *__restrict__ rec,
-                                             const float2 *__restrict__ ulo, float4 *sa, float4 *sb, float4 *sd,
-                                             int lane, int ly, float pxl, float (&T)[RPL], float (&C0)[RPL],
-                                             float (&C1)[RPL], float (&C2)[RPL], uint32_t (&last)[RPL],
-                                             uint32_t (&ncontrib)[RPL], uint32_t (&stop_at)[RPL]) {
-    for (uint32_t b0 = rg.x; b0 < rg.y; b0 += kWave) {
-        bool any_live = false;
-#pragma unroll
-        for (int k = 0; k < RPL; ++k) any_live |= T[k] > 0.f;
-        if (__ballot(any_live) == 0ull) break;
-        const uint32_t idx = b0 + lane;
-        if (idx < rg.y) {
-            const uint32_t item = pval[idx];
-            float4 a, b, d;
-            stage_record(rec[item], ulo[item], c, (uint32_t)vt.tile_h, a, b, d);
-            sa[lane] = a;
-            sb[lane] = b;
-            sd[lane] = d;
-        }
-        __syncthreads();
-        const int cnt = (int)min((uint32_t)kWave, rg.y - b0);
-        for (int j = 0; j < cnt; ++j) {
-            if ((j & 15) == 15) {  // leave the batch once every pixel of the tile has stopped
-                bool any = false;
-#pragma unroll
-                for (int k = 0; k < RPL; ++k) any |= T[k] > 0.f;
-                if (__ballot(any) == 0ull) break;
-            }
-            const float4 a = sa[j], b = sb[j], d = sd[j];
-            const uint32_t pos = b0 - rg.x + (uint32_t)j;
-            const float dx = a.x - pxl;
-            const uint32_t smask = slab_mask(d.y);
-            const RowQuad rq = row_quad(a, b, dx);
-#pragma unroll
-            for (int k = 0; k < RPL; ++k) {
-                if (!(smask & (1u << k))) continue;
-                const float dy = a.y - ((float)(ly + 4 * k) + 0.5f);
-                const float ex = alpha_exponent(rq, b, dy);
-                if (__ballot(T[k] > 0.f && ex >= kLog2AlphaSkip) == 0ull) continue;
-                const float alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(ex));
-                const bool ok = alpha >= kAlphaMin;
-                const float wa = alpha * T[k];
-                const float Tn = T[k] - wa;  // T (1 - alpha)
-                // a stopped pixel has Tn <= 0 < kTMin, so it never adds again; the
-                // pixel stops where ok holds and add does not
-                const bool add = ok & (Tn >= kTMin);
-                const float w = add ? wa : 0.f;
-                C0[k] = fmaf(b.z, w, C0[k]);
-                C1[k] = fmaf(b.w, w, C1[k]);
-                C2[k] = fmaf(d.x, w, C2[k]);
-                last[k] = add ? pos + 1 : last[k];
-                if constexpr (STATS) {
-                    ncontrib[k] += add ? 1u : 0u;
-                    stop_at[k] = (ok && !add && T[k] > 0.f) ? pos : stop_at[k];
-                }
-                // (two selects: written as one nested select, the compiler branched on it)
-                const float Ts = ok ? -fabsf(T[k]) : T[k];
-                T[k] = add ? Tn : Ts;
-            }
-        }
-        __syncthreads();
-    }
-}
-
-template <int RPL, bool STATS>
-__global__ __launch_bounds__(kWave) void k_composite_fwd(ViewTable vt, const uint2 *__restrict__ ranges,
-                                                         const uint32_t *__restrict__ pval,
-                                                         const Rec *__restrict__ rec, const float2 *__restrict__ ulo,
-                                                         float3 bg,
-                                                         float *__restrict__ out_rgb, float *__restrict__ out_T,
-                                                         float *__restrict__ pix_T, uint32_t *__restrict__ pix_n,
-                                                         uint32_t *__restrict__ tile_cut, uint32_t *__restrict__ tile_order,
-                                                         WsHeader *hdr, int persistent) {
-    __shared__ float4 sa[kWave], sb[kWave], sd[kWave];
-    const int lane = threadIdx.x;
-    const int lx = lane & 15, ly = lane >> 4;
-    const float pxl = (float)lx + 0.5f;
-    uint32_t iter = 0;
-    for (;;) {
-        const uint32_t t = next_tile(persistent != 0, &hdr->queue[0], blockIdx.x, iter);
-        if (t >= vt.total_tiles) break;
-        const TileCtx c = tile_ctx(vt, t);
-        const uint32_t px = c.ox + lx;
-        float T[RPL], C0[RPL], C1[RPL], C2[RPL];
-        uint32_t last[RPL], stop_at[RPL], ncontrib[RPL];
-#pragma unroll
-        for (int k = 0; k < RPL; ++k) {
-            const uint32_t py = c.oy + ly + 4 * k;
-            T[k] = (px < c.width && py < c.height) ? 1.f : -1.f;
-            C0[k] = C1[k] = C2[k] = 0.f;
-            last[k] = 0;
-            ncontrib[k] = 0;
-            stop_at[k] = 0xffffffffu;
-        }
-        const uint2 rg = ranges[t];
-        tile_forward<RPL, STATS>(vt, c, rg, pval, rec, ulo, sa, sb, sd, lane, ly, pxl, T, C0, C1, C2, last, ncontrib,
-                                 stop_at);
-        // outputs
-        const uint32_t len = rg.y - rg.x;
-        uint32_t evals = 0, replays = 0, contrib = 0, nmax = 0;
-        const size_t plane = (size_t)c.width * c.height;
-        float *img = out_rgb + 3 * (size_t)c.pix_off;
-#pragma unroll
-        for (int k = 0; k < RPL; ++k) {
-            const uint32_t py = c.oy + ly + 4 * k;
-            if (px < c.width && py < c.height) {
-                const size_t pix = (size_t)py * c.width + px;
-                const float Tf = fabsf(T[k]);
-                img[pix] = C0[k] + Tf * bg.x;
-                img[plane + pix] = C1[k] + Tf * bg.y;
-                img[2 * plane + pix] = C2[k] + Tf * bg.z;
-                pix_T[c.pix_off + pix] = Tf;
-                pix_n[c.pix_off + pix] = last[k];
-                if (out_T) out_T[c.pix_off + pix] = Tf;
-                evals += stop_at[k] != 0xffffffffu ? stop_at[k] + 1 : len;
-                replays += last[k];
-                contrib += ncontrib[k];
-                nmax = max(nmax, last[k]);
-            }
-        }
-        nmax = wave_reduce(nmax, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
-        if constexpr (STATS) {
-            // work counters for the measurement harness (integer adds: order independent)
-            unsigned long long e = evals, rp = replays, cc = contrib;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                e += __shfl_xor(e, o, kWave);
-                rp += __shfl_xor(rp, o, kWave);
-                cc += __shfl_xor(cc, o, kWave);
-            }
-            if (lane == 0) {
-                atomicAdd(&hdr->evaluations, e);
-                atomicAdd(&hdr->replays, rp);
-                atomicAdd(&hdr->contributors, cc);
-            }
-        }
-        if (lane == 0) {
-            tile_cut[t] = nmax;  // positions the backward replays
-            // the backward's schedule: this tile in the bucket of its replay count
-            const uint32_t b = cost_bucket(nmax);
-            const uint32_t slot = atomicAdd(&tile_order[b], 1u);
-            tile_order[kCostBuckets + (size_t)b * vt.total_tiles + slot] = t;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// A7: backward
-// ---------------------------------------------------------------------------
-constexpr int kGroup = 7;                          // Gaussians per LDS transpose
-constexpr int kRedCols = kGroup * kPartialStride;  // 63 values per row
-constexpr int kRedRows = kWave / 4;                // lane quads are summed first
-constexpr int kRedStride = kRedCols + 2;           // odd row stride: conflict-free rows and columns
-
 // Zero gradient rows of the Gaussians of tile t's slice that no view saw, one
 // row per lane (fire-and-forget stores that overlap the tile's ALU work).
-__device__ __forceinline__ void zero_unseen_rows(const ZeroRows &z, uint32_t t, bool overflow, int lane) {
+__device__ __forceinline__ void zero_unseen_rows(const ZeroRows &z, uint32_t t, bool overflow, int lane,
+                                                 int threads = kWave) {
     const uint64_t g0 = (uint64_t)t * z.per_tile, g1 = min(z.n, g0 + z.per_tile);
     const int K3 = 3 * z.sh_k;
-    for (uint64_t i = g0 + (uint64_t)lane; i < g1; i += kWave) {
+    for (uint64_t i = g0 + (uint64_t)lane; i < g1; i += (uint64_t)threads) {
         bool seen = false;
         if (!overflow)
             for (int v = 0; v < z.n_views; ++v) seen |= z.count[(uint64_t)v * z.n + i] > 0u;
@@ -397,60 +236,251 @@ __device__ __forceinline__ float l1_grad(float c, float target, float scale) {
     return c > target ? scale : (c < target ? -scale : 0.f);
 }
 
-// One tile's backward pass over list positions [rg.x, end): the per-pixel
-// state starts at T = 1, the upstream gradient g = dL/dC (g0, g1, g2), gB =
-// g . C_out and the contributor count ncon; the pass writes the nine moments
-// of every replayed pair to `partial` (at its slot in emission order) and
-// flags the slot.
-template <int RPL>
-__device__ __forceinline__ void tile_backward(const ViewTable &vt, const TileCtx &c, uint2 rg, uint32_t end,
+// Slabs the forward walks together.  Two share a record's LDS reads and its
+// dx terms but evaluate both where only one is met: faster for the four of a
+// 16 x 16 tile's single wave (fused step of a 1080p view: 303 against 317 us),
+// slower for two or eight (412 against 421 us, 1178 against 1243 us).
+__host__ __device__ constexpr int forward_slabs(int rpl) { return rpl == 4 ? 2 : 1; }
+
+constexpr int kGroup = 4;              // records per straight-line group
+constexpr int kRedStride = kWave + 4;   // floats between two moments' rows (spreads the 16-byte reads over banks)
+
+template <int W>
+struct Staged {
+    float4 a[W * kWave + 1], b[W * kWave + 1], d[W * kWave + 1];  // the last record never contributes
+    uint32_t any[W];
+};
+template <int W>
+struct Reduce {
+    alignas(16) float red[W][kPartialStride * kRedStride];
+    float mom[W > 1 ? W : 1][W > 1 ? kWave * kPartialStride : 1];
+    unsigned long long live[W];
+};
+
+// Stages the list positions [b0, b0 + 64 W) below `end` (slab mask 0 beyond it).
+template <int W>
+__device__ __forceinline__ void stage_batch(Staged<W> &sh, const ViewTable &vt, const TileCtx &c, uint32_t b0,
+                                            uint32_t end, const uint32_t *__restrict__ pval,
+                                            const Rec *__restrict__ rec, const float2 *__restrict__ ulo) {
+    const uint32_t tid = threadIdx.x, idx = b0 + tid;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, d = a;
+    if (idx < end) {
+        const uint32_t item = pval[idx];
+        stage_record(rec[item], ulo[item], c, (uint32_t)vt.tile_h, a, b, d);
+    }
+    sh.a[tid] = a;
+    sh.b[tid] = b;
+    sh.d[tid] = d;
+}
+
+// The record that never contributes (exponent -1000 everywhere).
+template <int W>
+__device__ __forceinline__ void stage_sentinel(Staged<W> &sh) {
+    if (threadIdx.x == 0) {
+        sh.a[W * kWave] = sh.d[W * kWave] = make_float4(0.f, 0.f, 0.f, 0.f);
+        sh.b[W * kWave] = make_float4(0.f, -1000.f, 0.f, 0.f);
+    }
+}
+
+// Takes the next kGroup records off the list m (a bit per record of the
+// staged sub-batch s): their staged indices, the sentinel's once the list is
+// empty; `packed` holds their positions in the sub-batch, a byte each.
+// Returns how many are real.
+template <int W>
+__device__ __forceinline__ int take_group(unsigned long long &m, int s, int (&j)[kGroup], uint32_t &packed) {
+    int n = 0;
+    packed = 0u;
+#pragma unroll
+    for (int q = 0; q < kGroup; ++q) {
+        const bool on = m != 0ull;
+        const int l = on ? (int)__builtin_ctzll(m) : 0;
+        j[q] = on ? s * kWave + l : W * kWave;
+        packed |= (uint32_t)l << (8 * q);
+        m &= m - 1ull;  // (stays 0)
+        n += on ? 1 : 0;
+    }
+    return n;
+}
+
+// Forward over the records listed in m for KP slabs of the wave.  Returns
+// whether some pixel of them still composites.
+template <int KP, int W, bool STATS>
+__device__ __forceinline__ bool forward_list(const Staged<W> &sh, unsigned long long m, int s, uint32_t pos0, float pxl,
+                                             float pyl, float *T, float *C0, float *C1, float *C2, uint32_t *last,
+                                             uint32_t *ncontrib, uint32_t *stop_at) {
+    bool go = true;
+    while (m) {
+        int j[kGroup];
+        uint32_t packed;
+        take_group<W>(m, s, j, packed);
+        float4 b[kGroup];
+        float blue[kGroup], al[kGroup][KP];
+#pragma unroll
+        for (int q = 0; q < kGroup; ++q) {
+            const float4 a = sh.a[j[q]];
+            b[q] = sh.b[j[q]];
+            blue[q] = sh.d[j[q]].x;
+            const RowQuad rq = row_quad(a, b[q], a.x - pxl);
+#pragma unroll
+            for (int k = 0; k < KP; ++k) {
+                const float dy = a.y - (pyl + (float)(4 * k));
+                al[q][k] = fminf(kAlphaMax, __builtin_amdgcn_exp2f(alpha_exponent(rq, b[q], dy)));
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kGroup; ++q) {
+            const uint32_t pos = pos0 + (uint32_t)j[q];
+#pragma unroll
+            for (int k = 0; k < KP; ++k) {
+                const bool ok = al[q][k] >= kAlphaMin;
+                const float wa = al[q][k] * T[k];
+                const float Tn = T[k] - wa;  // T (1 - alpha)
+                // a stopped pixel has Tn <= 0 < kTMin, so it never adds again; the
+                // pixel stops where ok holds and add does not
+                const bool add = ok & (Tn >= kTMin);
+                const float w = add ? wa : 0.f;
+                C0[k] = fmaf(b[q].z, w, C0[k]);
+                C1[k] = fmaf(b[q].w, w, C1[k]);
+                C2[k] = fmaf(blue[q], w, C2[k]);
+                last[k] = add ? pos + 1 : last[k];
+                if constexpr (STATS) {
+                    ncontrib[k] += add ? 1u : 0u;
+                    stop_at[k] = (ok && !add && T[k] > 0.f) ? pos : stop_at[k];
+                }
+                const float Ts = ok ? -fabsf(T[k]) : T[k];
+                T[k] = add ? Tn : Ts;
+            }
+        }
+        bool any = false;
+#pragma unroll
+        for (int k = 0; k < KP; ++k) any |= T[k] > 0.f;
+        go = __ballot(any) != 0ull;
+        if (!go) break;
+    }
+    return go;
+}
+
+// A6 for one tile: the wave's RPL slabs over the tile's sorted list, from the
+// per-pixel state (T > 0: still compositing; T < 0: stopped, or outside the
+// image, and -T is the final transmittance) to the colours and, per pixel, the
+// list position after its last contributor.  `staged`: the first position of
+// the batch left in LDS.
+template <int RPL, int W, int KP, bool STATS>
+__device__ __forceinline__ void tile_forward(Staged<W> &sh, const ViewTable &vt, const TileCtx &c, uint2 rg,
+                                             const uint32_t *__restrict__ pval, const Rec *__restrict__ rec,
+                                             const float2 *__restrict__ ulo, int wave, int lane, float pxl, float pyl,
+                                             float (&T)[RPL], float (&C0)[RPL], float (&C1)[RPL], float (&C2)[RPL],
+                                             uint32_t (&last)[RPL], uint32_t (&ncontrib)[RPL],
+                                             uint32_t (&stop_at)[RPL], uint32_t &staged) {
+    static_assert(RPL % KP == 0, "whole passes");
+    stage_sentinel(sh);
+    uint32_t alive = 0;  // passes with a pixel still compositing (wave-uniform)
+#pragma unroll
+    for (int k = 0; k < RPL; ++k) alive |= __ballot(T[k] > 0.f) != 0ull ? 1u << (k / KP) : 0u;
+    for (uint32_t b0 = rg.x; b0 < rg.y; b0 += W * kWave) {
+        if (b0 != rg.x) {  // leave once every wave's pixels have stopped
+            if constexpr (W > 1) {
+                if (lane == 0) sh.any[wave] = alive;
+                __syncthreads();  // (and the waves are done with the previous batch)
+                uint32_t any = 0;
+#pragma unroll
+                for (int w = 0; w < W; ++w) any |= sh.any[w];
+                if (!any) break;
+            } else {
+                if (!alive) break;
+            }
+        }
+        stage_batch(sh, vt, c, b0, rg.y, pval, rec, ulo);
+        staged = b0;
+        __syncthreads();
+        for (int s = 0; s < W && alive && b0 + (uint32_t)(s * kWave) < rg.y; ++s) {
+            const uint32_t mask = __float_as_uint(sh.d[s * kWave + lane].y) >> (wave * RPL);
+#pragma unroll
+            for (int k = 0; k < RPL; k += KP) {
+                if (!(alive >> (k / KP) & 1u)) continue;
+                const unsigned long long m = __ballot((mask >> k & ((1u << KP) - 1u)) != 0u);
+                if (!forward_list<KP, W, STATS>(sh, m, s, b0 - rg.x, pxl, pyl + (float)(4 * k), T + k, C0 + k, C1 + k,
+                                                C2 + k, last + k, ncontrib + k, stop_at + k))
+                    alive &= ~(1u << (k / KP));
+            }
+        }
+    }
+}
+
+// Lanes [0, 32) of the result: x of the lane and of the lane 32 above, added;
+// lanes [32, 64): the same of y.
+__device__ __forceinline__ float swap_add32(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Rows of 16 lanes of the result: x rows 0 + 1, y rows 0 + 1, x rows 2 + 3, y rows 2 + 3.
+__device__ __forceinline__ float swap_add16(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// A7 for one tile over list positions [rg.x, end); `staged`: the position of
+// the batch the forward left staged (a fused step's), or anything but rg.x for
+// none.  The per-pixel state starts at T = 1, g = dL/dC, gB = g . C_out and the
+// contributor count ncon.
+template <int RPL, int W>
+__device__ __forceinline__ void tile_backward(Staged<W> &sh, Reduce<W> &bw, const ViewTable &vt, const TileCtx &c,
+                                              uint2 rg, uint32_t end, uint32_t staged,
                                               const uint32_t *__restrict__ pval, const Rec *__restrict__ rec,
-                                              const float2 *__restrict__ ulo, float4 *sa, float4 *sb, float4 *sd,
-                                              float *red, int lane, int ly, float pxl, int fq, int fc,
+                                              const float2 *__restrict__ ulo, int wave, int lane, float pxl, float pyl,
                                               float (&T)[RPL], const float (&g0)[RPL], const float (&g1)[RPL],
                                               const float (&g2)[RPL], float (&gB)[RPL], const uint32_t (&ncon)[RPL],
                                               float *__restrict__ partial, uint8_t *__restrict__ pflag) {
-    // per-lane sums over one Gaussian's rows: colour-gradient weights w,
-    // sa = alpha dL/dalpha, sa dy and sa dy^2 (the rows share dx); zero
-    // between Gaussians (a Gaussian no lane reaches leaves them so, and the
-    // reduction of one that some lane reaches resets them)
-    float a_c0 = 0.f, a_c1 = 0.f, a_c2 = 0.f, a_sa = 0.f, a_say = 0.f, a_sayy = 0.f;
-    for (uint32_t b0 = rg.x; b0 < end; b0 += kWave) {
-        const uint32_t idx = b0 + lane;
-        if (idx < end) {
-            const uint32_t item = pval[idx];
-            float4 a, b, d;
-            stage_record(rec[item], ulo[item], c, (uint32_t)vt.tile_h, a, b, d);
-            sa[lane] = a;
-            sb[lane] = b;
-            sd[lane] = d;
-            pflag[__float_as_uint(d.z)] = 1;  // this pair's moments get written: the reduction reads them
-        }
-        __syncthreads();
-        const int cnt = (int)min((uint32_t)kWave, end - b0);
-        for (int j0 = 0; j0 < cnt; j0 += kGroup) {
-            uint32_t zq = 0;  // Gaussians of the group with all moments zero
+    const uint32_t tid = threadIdx.x;
+    uint32_t mine = 0;
 #pragma unroll
-            for (int q = 0; q < kGroup; ++q) {
-                const int j = j0 + q;
-                float dx = 0.f;
-                bool live = false;  // wave-uniform: some lane reached some row of this Gaussian
-                if (j < cnt) {
-                    const uint32_t pos = b0 - rg.x + (uint32_t)j;
-                    const float4 a = sa[j], b = sb[j], d = sd[j];
-                    dx = a.x - pxl;
-                    const uint32_t smask = slab_mask(d.y);
+    for (int k = 0; k < RPL; ++k) mine = max(mine, ncon[k]);
+    // positions this wave's pixels used end here
+    const uint32_t stop = rg.x + wave_reduce(mine, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
+    // the (Gaussian of the group, moment) this lane finalises
+    const int fq = lane / kPartialStride, fc = lane - fq * kPartialStride;
+    float *red = bw.red[wave];
+    for (uint32_t b0 = rg.x; b0 < end; b0 += W * kWave) {
+        if (b0 != rg.x || staged != rg.x) {  // (the forward's batch is there only if it is the first)
+            if (b0 != rg.x) __syncthreads();
+            stage_batch(sh, vt, c, b0, end, pval, rec, ulo);
+            if (b0 == rg.x) stage_sentinel(sh);
+            __syncthreads();
+        }
+        for (int s = 0; s < W; ++s) {
+            const uint32_t s0 = b0 + (uint32_t)(s * kWave);
+            if (s0 >= end) break;
+            unsigned long long m = 0ull;
+            if (s0 < stop) {
+                const uint32_t mask = __float_as_uint(sh.d[s * kWave + lane].y) >> (wave * RPL);
+                m = __ballot((mask & ((1u << RPL) - 1u)) != 0u);
+                if (stop - s0 < (uint32_t)kWave) m &= (1ull << (stop - s0)) - 1ull;
+            }
+            if constexpr (W > 1)
+                if (lane == 0) bw.live[wave] = m;
+            while (m) {
+                int j[kGroup];
+                uint32_t packed;
+                const int n = take_group<W>(m, s, j, packed);
+                // per lane: the sums over its rows of sa = alpha dL/dalpha, sa dy,
+                // sa dy^2 and the colour gradient (the rows share dx)
+                float v[kGroup][6];
+#pragma unroll
+                for (int q = 0; q < kGroup; ++q) {
+                    const float4 a = sh.a[j[q]], b = sh.b[j[q]];
+                    const float2 d = *reinterpret_cast<const float2 *>(&sh.d[j[q]]);
+                    const float dx = a.x - pxl;
+                    const uint32_t pos = b0 - rg.x + (uint32_t)j[q];
                     const RowQuad rq = row_quad(a, b, dx);
+                    const uint32_t smask = RPL > 1 ? slab_mask(d.y) >> (wave * RPL) : 1u;
+                    float a_c0 = 0.f, a_c1 = 0.f, a_c2 = 0.f, a_sa = 0.f, a_say = 0.f, a_sayy = 0.f;
 #pragma unroll
                     for (int k = 0; k < RPL; ++k) {
-                        if (!(smask & (1u << k))) continue;
-                        const float dy = a.y - ((float)(ly + 4 * k) + 0.5f);
-                        const float ex = alpha_exponent(rq, b, dy);
-                        if (__ballot(pos < ncon[k] && ex >= kLog2AlphaSkip) == 0ull) continue;
-                        live = true;
-                        const float araw = __builtin_amdgcn_exp2f(ex);
+                        if (RPL > 1 && !(smask & (1u << k))) continue;
+                        const float dy = a.y - (pyl + (float)(4 * k));
+                        const float araw = __builtin_amdgcn_exp2f(alpha_exponent(rq, b, dy));
                         const float alpha = fminf(kAlphaMax, araw);
-                        const bool ok = pos < ncon[k] && alpha >= kAlphaMin;
+                        const bool ok = (pos < ncon[k]) & (alpha >= kAlphaMin);
                         const float w = ok ? alpha * T[k] : 0.f;
                         a_c0 = fmaf(w, g0[k], a_c0);
                         a_c1 = fmaf(w, g1[k], a_c1);
@@ -470,217 +500,298 @@ __device__ __forceinline__ void tile_backward(const ViewTable &vt, const TileCtx
                         a_say += say;
                         a_sayy = fmaf(say, dy, a_sayy);
                     }
+                    v[q][0] = a_sa, v[q][1] = a_say, v[q][2] = a_sayy;
+                    v[q][3] = a_c0, v[q][4] = a_c1, v[q][5] = a_c2;
                 }
-                if (!live) zq |= 1u << q;  // every moment is zero: the finaliser writes 0
-                if (live) {
-                    // (no contraction: a product contracted into the first DPP add
-                    // costs a separate lane move, and its four quad lanes would no
-                    // longer add a and b as b and a)
-#pragma clang fp contract(off)
-                    // the moments of sa (= -dL/dsigma): sums of sa dx, sa dy, sa dx^2,
-                    // sa dx dy, sa dy^2 (the negated S_x .. S_yy of the projection
-                    // backward), then S_o = sum sa and the colour gradient
-                    float s[kPartialStride];
-                    s[0] = dx * a_sa;
-                    s[1] = a_say;
-                    s[2] = dx * s[0];
-                    s[3] = dx * a_say;
-                    s[4] = a_sayy;
-                    s[5] = a_sa;
-                    s[6] = a_c0;
-                    s[7] = a_c1;
-                    s[8] = a_c2;
-                    // add the lanes of each quad (quad_perm [1, 0, 3, 2], then [2, 3, 0, 1]):
-                    // all four lanes hold the same sum (each step adds a and b as b and a,
-                    // exactly equal) and store it to the same place, so no lane is masked
-                    // off and each move folds into its add
+                // sums over the wave's four rows of 16 lanes; row q of the result holds Gaussian q's
+                float r[6];
 #pragma unroll
-                    for (int cc = 0; cc < kPartialStride; ++cc)
-                        s[cc] = dpp_add<0x4E, 0xf>(dpp_add<0xB1, 0xf>(s[cc]));
-#pragma unroll
-                    for (int cc = 0; cc < kPartialStride; ++cc)
-                        red[(lane >> 2) * kRedStride + q * kPartialStride + cc] = s[cc];
-                    a_c0 = a_c1 = a_c2 = a_sa = a_say = a_sayy = 0.f;
-                }
-            }
-            __syncthreads();
-            if (lane < kRedCols && j0 + fq < cnt) {
-                float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
-                if (!((zq >> fq) & 1u)) {
-#pragma unroll
-                    for (int r = 0; r < kRedRows; r += 4) {
-                        p0 += red[(r + 0) * kRedStride + lane];
-                        p1 += red[(r + 1) * kRedStride + lane];
-                        p2 += red[(r + 2) * kRedStride + lane];
-                        p3 += red[(r + 3) * kRedStride + lane];
+                for (int cc = 0; cc < 6; ++cc)
+                    r[cc] = swap_add16(swap_add32(v[0][cc], v[2][cc]), swap_add32(v[1][cc], v[3][cc]));
+                const float dxr = sh.a[s * kWave + (int)(packed >> (8 * (lane >> 4)) & 63u)].x - pxl;
+                // the moments of sa (= -dL/dsigma): sums of sa dx, sa dy, sa dx^2,
+                // sa dx dy, sa dy^2 (the negated S_x .. S_yy of the projection
+                // backward), then S_o = sum sa and the colour gradient
+                const float sx = dxr * r[0];
+                red[0 * kRedStride + lane] = sx;
+                red[1 * kRedStride + lane] = r[1];
+                red[2 * kRedStride + lane] = dxr * sx;
+                red[3 * kRedStride + lane] = dxr * r[1];
+                red[4 * kRedStride + lane] = r[2];
+                red[5 * kRedStride + lane] = r[0];
+                red[6 * kRedStride + lane] = r[3];
+                red[7 * kRedStride + lane] = r[4];
+                red[8 * kRedStride + lane] = r[5];
+                // (the wave's own LDS accesses, in order: no barrier, only no reordering by the compiler)
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (fq < n) {
+                    const float4 *rr = reinterpret_cast<const float4 *>(red + fc * kRedStride + fq * 16);
+                    const float4 x = rr[0], y = rr[1], z = rr[2], w = rr[3];
+                    const float t = (((x.x + x.y) + (x.z + x.w)) + ((y.x + y.y) + (y.z + y.w))) +
+                                    (((z.x + z.y) + (z.z + z.w)) + ((w.x + w.y) + (w.z + w.w)));
+                    const uint32_t jl = packed >> (8 * fq) & 63u;
+                    if constexpr (W > 1) {
+                        bw.mom[wave][jl * kPartialStride + fc] = t;
+                    } else {
+                        const uint32_t p = __float_as_uint(sh.d[jl].z);
+                        partial[(size_t)p * kPartialStride + fc] = t;
+                        if (fc == 0) pflag[p] = 1;  // this pair has moments: the reduction reads them
                     }
                 }
-                const uint32_t p = __float_as_uint(sd[j0 + fq].z);
-                partial[(size_t)p * kPartialStride + fc] = (p0 + p1) + (p2 + p3);
             }
-            __syncthreads();
-        }
-    }
-}
-
-template <int RPL>
-__global__ __launch_bounds__(kWave) void k_composite_bwd(ViewTable vt, const uint2 *__restrict__ ranges,
-                                                         const uint32_t *__restrict__ pval,
-                                                         const Rec *__restrict__ rec, const float2 *__restrict__ ulo,
-                                                         const float *__restrict__ out_rgb, Upstream up,
-                                                         const uint32_t *__restrict__ pix_n,
-                                                         const uint32_t *__restrict__ tile_cut,
-                                                         const uint32_t *__restrict__ tile_order,
-                                                         float *__restrict__ partial, uint8_t *__restrict__ pflag,
-                                                         ZeroRows zr, WsHeader *hdr, int persistent) {
-    __shared__ float4 sa[kWave], sb[kWave], sd[kWave];
-    __shared__ float red[kRedRows * kRedStride];
-    const int lane = threadIdx.x;
-    const int lx = lane & 15, ly = lane >> 4;
-    const float pxl = (float)lx + 0.5f;
-    // the (Gaussian of the group, moment) this lane finalises
-    const int fq = lane / kPartialStride, fc = lane - fq * kPartialStride;
-    uint32_t iter = 0;
-    for (;;) {
-        const uint32_t r = next_tile(persistent != 0, &hdr->queue[1], blockIdx.x, iter);
-        if (r >= vt.total_tiles) break;
-        const uint32_t t = tile_by_cost(tile_order, vt.total_tiles, r);  // heaviest tiles first
-        zero_unseen_rows(zr, t, hdr->overflow != 0u, lane);
-        const TileCtx c = tile_ctx(vt, t);
-        const uint32_t px = c.ox + lx;
-        const size_t plane = (size_t)c.width * c.height;
-        const float *img = out_rgb + 3 * (size_t)c.pix_off;
-        const float *gimg = (up.target ? up.target : up.grad) + 3 * (size_t)c.pix_off;
-        // gB = g . (colour still to come behind the current position): g . C_out
-        // before the first contributor, reduced by each contribution
-        float T[RPL], g0[RPL], g1[RPL], g2[RPL], gB[RPL];
-        uint32_t ncon[RPL];
+            if constexpr (W > 1) {
+                __syncthreads();
+                const uint32_t vals = min((uint32_t)kWave, end - s0) * kPartialStride;
+                for (uint32_t e = tid; e < vals; e += W * kWave) {
+                    const uint32_t jj = e / kPartialStride, cc = e - jj * kPartialStride;
+                    float t = 0.f;
+                    bool any = false;
 #pragma unroll
-        for (int k = 0; k < RPL; ++k) {
-            const uint32_t py = c.oy + ly + 4 * k;
-            T[k] = 1.f;
-            if (px < c.width && py < c.height) {
-                const size_t pix = (size_t)py * c.width + px;
-                ncon[k] = pix_n[c.pix_off + pix];
-                const float i0 = img[pix], i1 = img[plane + pix], i2 = img[2 * plane + pix];
-                g0[k] = gimg[pix];
-                g1[k] = gimg[plane + pix];
-                g2[k] = gimg[2 * plane + pix];
-                if (up.target) {  // mean absolute error: dL/dC = sign(C - target) / count
-                    g0[k] = l1_grad(i0, g0[k], up.l1_scale);
-                    g1[k] = l1_grad(i1, g1[k], up.l1_scale);
-                    g2[k] = l1_grad(i2, g2[k], up.l1_scale);
+                    for (int w = 0; w < W; ++w) {
+                        const bool on = (bw.live[w] >> jj) & 1ull;
+                        t += on ? bw.mom[w][e] : 0.f;
+                        any |= on;
+                    }
+                    if (any) {
+                        const uint32_t p = __float_as_uint(sh.d[s * kWave + jj].z);
+                        partial[(size_t)p * kPartialStride + cc] = t;
+                        if (cc == 0) pflag[p] = 1;
+                    }
                 }
-                gB[k] = fmaf(g2[k], i2, fmaf(g1[k], i1, g0[k] * i0));
-            } else {
-                ncon[k] = 0;
-                g0[k] = g1[k] = g2[k] = gB[k] = 0.f;
+                __syncthreads();
             }
         }
-        const uint2 rg = ranges[t];
-        const uint32_t end = rg.x + tile_cut[t];  // positions any pixel of the tile used
-        tile_backward<RPL>(vt, c, rg, end, pval, rec, ulo, sa, sb, sd, red, lane, ly, pxl, fq, fc, T, g0, g1, g2, gB,
-                           ncon, partial, pflag);
     }
 }
 
-// ---------------------------------------------------------------------------
-// A6 + A7 for the photometric loss in one pass over the tiles: a workgroup
-// composites its tile forward, forms dL/dC = sign(C - target) * l1_scale of
-// the tile's pixels from the colours it has just accumulated (the gradient of
-// a pixel depends on its own colour only), and replays the tile backward,
-// with the same two tile passes as the kernels above, so that the image, the
-// workspace state and the moments are theirs bit for bit.  What changes is the
-// schedule: a SIMD holds waves in both phases, so the backward's arithmetic
-// fills the forward's latency, and the forward's per-pixel state stays in
-// registers.  A fused tile lasts both passes, so a heavy tile dispatched late
-// leaves a long tail: the tiles are taken in descending buckets of min(list
-// length, the replay count the workspace holds from its previous step),
-// filed by a workgroup of the per-tile depth sort (exact for a repeated step,
-// the list length on a fresh workspace; any order gives the same results).
-// ---------------------------------------------------------------------------
-template <int RPL>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) void k_composite_step(
-    ViewTable vt, const uint2 *__restrict__ ranges, const uint32_t *__restrict__ pval, const Rec *__restrict__ rec,
-    const float2 *__restrict__ ulo, float3 bg, const float *__restrict__ target, float l1_scale,
-    float *__restrict__ out_rgb, float *__restrict__ out_T, float *__restrict__ pix_T, uint32_t *__restrict__ pix_n,
-    uint32_t *__restrict__ tile_cut, const uint32_t *__restrict__ tile_order, float *__restrict__ partial,
-    uint8_t *__restrict__ pflag, ZeroRows zr, WsHeader *hdr, int persistent) {
-    __shared__ float4 sa[kWave], sb[kWave], sd[kWave];
-    __shared__ float red[kRedRows * kRedStride];
-    const int lane = threadIdx.x;
-    const int lx = lane & 15, ly = lane >> 4;
-    const float pxl = (float)lx + 0.5f;
-    const int fq = lane / kPartialStride, fc = lane - fq * kPartialStride;
+// Tile turn of the workgroup (all its waves get it).
+template <int W>
+__device__ __forceinline__ uint32_t next_turn(bool persistent, uint32_t *queue, uint32_t &iter, uint32_t *s_turn) {
+    if (!persistent) return iter++ == 0 ? blockIdx.x : 0xffffffffu;
+    __syncthreads();
+    if (threadIdx.x == 0) *s_turn = atomicAdd(queue, 1u);
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(*s_turn);
+}
+
+// Largest of the workgroup's values.
+template <int W>
+__device__ __forceinline__ uint32_t group_max(uint32_t v, uint32_t *s /* [W] */) {
+    v = wave_reduce(v, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
+    if constexpr (W == 1) return v;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
+    __syncthreads();
+    uint32_t r = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) r = max(r, s[w]);
+    return __builtin_amdgcn_readfirstlane(r);
+}
+
+// One kernel body for the three passes: forward only, backward only (from the
+// state a forward left), or the fused step.
+struct CompositeArgs {
+    const uint2 *ranges;
+    const uint32_t *pval;
+    const Rec *rec;
+    const float2 *ulo;
+    float3 bg;
+    Upstream up;
+    float *out_rgb, *out_T, *pix_T;
+    uint32_t *pix_n, *tile_cut, *tile_order;
+    float *partial;
+    uint8_t *pflag;
+    ZeroRows zr;
+    WsHeader *hdr;
+    int persistent;
+};
+
+template <int RPL, int W, bool FWD, bool BWD, bool STATS>
+__global__ __launch_bounds__(W *kWave) void k_composite(ViewTable vt, CompositeArgs A) {
+    __shared__ Staged<W> sh;
+    __shared__ uint32_t s_turn;
+    const int lane = threadIdx.x & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const int lx = lane & 15, ly = wave * 4 * RPL + (lane >> 4);
+    const float pxl = (float)lx + 0.5f, pyl = (float)ly + 0.5f;
     uint32_t iter = 0;
     for (;;) {
-        const uint32_t r = next_tile(persistent != 0, &hdr->queue[0], blockIdx.x, iter);
+        const uint32_t r = next_turn<W>(A.persistent != 0, &A.hdr->queue[FWD ? 0 : 1], iter, &s_turn);
         if (r >= vt.total_tiles) break;
-        const uint32_t t = tile_by_cost(tile_order, vt.total_tiles, r);
-        zero_unseen_rows(zr, t, hdr->overflow != 0u, lane);
+        // (the tile is one for the wave: scalar registers and loads from here on)
+        const uint32_t t = __builtin_amdgcn_readfirstlane(BWD ? tile_by_cost(A.tile_order, vt.total_tiles, r) : r);
+        if constexpr (BWD) zero_unseen_rows(A.zr, t, A.hdr->overflow != 0u, (int)threadIdx.x, W * kWave);
         const TileCtx c = tile_ctx(vt, t);
+        const uint2 rg = A.ranges[t];
         const uint32_t px = c.ox + lx;
-        const uint2 rg = ranges[t];
-        float T[RPL], C0[RPL], C1[RPL], C2[RPL];
-        uint32_t last[RPL], unused0[RPL], unused1[RPL];
-#pragma unroll
-        for (int k = 0; k < RPL; ++k) {
-            const uint32_t py = c.oy + ly + 4 * k;
-            T[k] = (px < c.width && py < c.height) ? 1.f : -1.f;
-            C0[k] = C1[k] = C2[k] = 0.f;
-            last[k] = 0;
-        }
-        tile_forward<RPL, false>(vt, c, rg, pval, rec, ulo, sa, sb, sd, lane, ly, pxl, T, C0, C1, C2, last, unused0,
-                                 unused1);
-        // outputs, and the backward's start: g = dL/dC, gB = g . C_out
         const size_t plane = (size_t)c.width * c.height;
-        float *img = out_rgb + 3 * (size_t)c.pix_off;
-        const float *tgt = target + 3 * (size_t)c.pix_off;
+        float *img = A.out_rgb + 3 * (size_t)c.pix_off;
+        float T[RPL], C0[RPL], C1[RPL], C2[RPL];
+        uint32_t last[RPL], stop_at[RPL], ncontrib[RPL], staged = 0xffffffffu, nmax = 0;
+        if constexpr (FWD) {
+#pragma unroll
+            for (int k = 0; k < RPL; ++k) {
+                const uint32_t py = c.oy + ly + 4 * k;
+                T[k] = (px < c.width && py < c.height) ? 1.f : -1.f;
+                C0[k] = C1[k] = C2[k] = 0.f;
+                last[k] = 0;
+                ncontrib[k] = 0;
+                stop_at[k] = 0xffffffffu;
+            }
+            tile_forward<RPL, W, forward_slabs(RPL), STATS>(sh, vt, c, rg, A.pval, A.rec, A.ulo, wave, lane, pxl, pyl, T, C0, C1, C2,
+                                           last, ncontrib, stop_at, staged);
+        }
+        // the forward's outputs, and the backward's start: g = dL/dC, gB = g . C_out
+        // (gB: g . the colour still to come behind the current position)
+        const float *gimg = (A.up.target ? A.up.target : A.up.grad) + 3 * (size_t)c.pix_off;
         float g0[RPL], g1[RPL], g2[RPL], gB[RPL];
-        uint32_t ncon[RPL], nmax = 0;
+        uint32_t evals = 0, replays = 0, contrib = 0;
 #pragma unroll
         for (int k = 0; k < RPL; ++k) {
             const uint32_t py = c.oy + ly + 4 * k;
+            g0[k] = g1[k] = g2[k] = gB[k] = 0.f;
             if (px < c.width && py < c.height) {
                 const size_t pix = (size_t)py * c.width + px;
-                const float Tf = fabsf(T[k]);
-                const float i0 = C0[k] + Tf * bg.x, i1 = C1[k] + Tf * bg.y, i2 = C2[k] + Tf * bg.z;
-                img[pix] = i0;
-                img[plane + pix] = i1;
-                img[2 * plane + pix] = i2;
-                pix_T[c.pix_off + pix] = Tf;
-                pix_n[c.pix_off + pix] = last[k];
-                if (out_T) out_T[c.pix_off + pix] = Tf;
-                nmax = max(nmax, last[k]);
-                ncon[k] = last[k];
-                g0[k] = l1_grad(i0, tgt[pix], l1_scale);
-                g1[k] = l1_grad(i1, tgt[plane + pix], l1_scale);
-                g2[k] = l1_grad(i2, tgt[2 * plane + pix], l1_scale);
-                gB[k] = fmaf(g2[k], i2, fmaf(g1[k], i1, g0[k] * i0));
+                float i0, i1, i2;
+                if constexpr (FWD) {
+                    const float Tf = fabsf(T[k]);
+                    i0 = C0[k] + Tf * A.bg.x, i1 = C1[k] + Tf * A.bg.y, i2 = C2[k] + Tf * A.bg.z;
+                    img[pix] = i0;
+                    img[plane + pix] = i1;
+                    img[2 * plane + pix] = i2;
+                    A.pix_T[c.pix_off + pix] = Tf;
+                    A.pix_n[c.pix_off + pix] = last[k];
+                    if (A.out_T) A.out_T[c.pix_off + pix] = Tf;
+                    nmax = max(nmax, last[k]);
+                    if constexpr (STATS) {
+                        evals += stop_at[k] != 0xffffffffu ? stop_at[k] + 1 : rg.y - rg.x;
+                        replays += last[k];
+                        contrib += ncontrib[k];
+                    }
+                } else {
+                    last[k] = A.pix_n[c.pix_off + pix];
+                    i0 = img[pix], i1 = img[plane + pix], i2 = img[2 * plane + pix];
+                }
+                if constexpr (BWD) {
+                    g0[k] = gimg[pix];
+                    g1[k] = gimg[plane + pix];
+                    g2[k] = gimg[2 * plane + pix];
+                    if (A.up.target) {  // mean absolute error: dL/dC = sign(C - target) / count
+                        g0[k] = l1_grad(i0, g0[k], A.up.l1_scale);
+                        g1[k] = l1_grad(i1, g1[k], A.up.l1_scale);
+                        g2[k] = l1_grad(i2, g2[k], A.up.l1_scale);
+                    }
+                    gB[k] = fmaf(g2[k], i2, fmaf(g1[k], i1, g0[k] * i0));
+                }
             } else {
-                ncon[k] = 0;
-                g0[k] = g1[k] = g2[k] = gB[k] = 0.f;
+                last[k] = 0;
             }
             T[k] = 1.f;
         }
-        nmax = wave_reduce(nmax, 0u, [](uint32_t a, uint32_t b) { return max(a, b); });
-        if (lane == 0) tile_cut[t] = nmax;
-        tile_backward<RPL>(vt, c, rg, rg.x + nmax, pval, rec, ulo, sa, sb, sd, red, lane, ly, pxl, fq, fc, T, g0, g1,
-                           g2, gB, ncon, partial, pflag);
+        if constexpr (STATS) {
+            // work counters for the measurement harness (integer adds: order independent)
+            unsigned long long e = evals, rp = replays, cc = contrib;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                e += __shfl_xor(e, o, kWave);
+                rp += __shfl_xor(rp, o, kWave);
+                cc += __shfl_xor(cc, o, kWave);
+            }
+            if (lane == 0) {
+                atomicAdd(&A.hdr->evaluations, e);
+                atomicAdd(&A.hdr->replays, rp);
+                atomicAdd(&A.hdr->contributors, cc);
+            }
+        }
+        if constexpr (FWD) {
+            nmax = group_max<W>(nmax, sh.any);
+            if (threadIdx.x == 0) {
+                A.tile_cut[t] = nmax;  // positions the backward replays
+                if constexpr (!BWD) {  // the backward's schedule: this tile in the bucket of its replay count
+                    const uint32_t b = cost_bucket(nmax);
+                    const uint32_t slot = atomicAdd(&A.tile_order[b], 1u);
+                    A.tile_order[kCostBuckets + (size_t)b * vt.total_tiles + slot] = t;
+                }
+            }
+        } else {
+            nmax = A.tile_cut[t];
+        }
+        if constexpr (BWD) {
+            __shared__ Reduce<W> bw;
+            tile_backward<RPL, W>(sh, bw, vt, c, rg, rg.x + nmax, staged, A.pval, A.rec, A.ulo, wave, lane, pxl, pyl, T,
+                                  g0, g1, g2, gB, last, A.partial, A.pflag);
+        }
     }
+}
+
+// Waves per tile.  The forward always takes as many as it can: at every size
+// it measured faster (16 x 16 tiles, W = 1 / 2 / 4: 136 / 95 / 74 us at 1,200
+// tiles, 151 / 151 / 142 us at 8,160; 16 x 8 tiles, W = 1 / 2: 197 / 184 us at
+// 16,200).
+static int forward_waves(const ViewTable &vt) { return vt.tile_h / 4 < 4 ? vt.tile_h / 4 : 4; }
+
+// The backward and the fused step (one rule: both must add up a pair's moments
+// in the same order) give a wave fewer slabs the fewer tiles there are.
+// Measured on the fused step with 400k Gaussians at two distances (dense and
+// even; concentrated in the centre), us:
+//   1 slab per wave against one wave per tile   16 x 16: 214 / 369 and 371 / 901
+//     at 1,200 tiles, 229 / 246 and 355 / 533 at 2,952, 255 / 241 and 365 /
+//     512 at 3,600; 16 x 8: 201 / 231 and 343 / 475 at 2,400, 211 / 201 and
+//     320 / 418 at 3,750, 241 / 200 and 327 / 342 at 5,832
+//   2 slabs against one wave   16 x 16: 253 / 241 and 409 / 512 at 3,600, 319 /
+//     272 and 422 / 452 at 5,700; 16 x 32: 381 / 384 and 470 / 649 at 4,080
+//   4 slabs against one wave   16 x 32: 851 / 893 and 1266 / 1305 at 7,360, but
+//     1235 / 1178 at 14,720 (even)
+static int backward_waves(const ViewTable &vt) {
+    const int slabs = vt.tile_h / 4;
+    const uint32_t tiles = vt.total_tiles;
+    const int per_wave = tiles <= 3200u ? 1 : tiles <= 4500u ? 2 : tiles <= 9000u ? 4 : 8;
+    const int waves = slabs <= per_wave ? 1 : slabs / per_wave;
+    return waves < 4 ? waves : 4;
 }
 
 // Workgroups of a persistent launch: as many as can be resident at once
 // (occupancy of this kernel x compute units of the current device, queried at
 // each launch: nothing is cached between calls), unless the caller fixed it.
 template <typename Kernel>
-static int resident_ctas(Kernel kernel, int requested) {
+static int resident_ctas(Kernel kernel, int requested, int threads = kWave) {
     if (requested > 0) return requested;
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, kWave, 0) != hipSuccess || per <= 0) per = 8;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess || per <= 0) per = 8;
     return cus * per;
+}
+
+// One pass over the tiles in the form the call takes.
+template <bool FWD, bool BWD, bool STATS>
+static void launch_composite(const ViewTable &vt, const CompositeArgs &A, int persistent_ctas, hipStream_t st) {
+#define GSR_COMPOSITE(R, W)                                                                                         \
+    hipLaunchKernelGGL((k_composite<R, W, FWD, BWD, STATS>),                                                        \
+                       dim3(A.persistent ? (unsigned)resident_ctas(k_composite<R, W, FWD, BWD, STATS>,              \
+                                                                   persistent_ctas, W * kWave)                      \
+                                         : vt.total_tiles),                                                         \
+                       dim3(W * kWave), 0, st, vt, A)
+    const int waves = BWD ? backward_waves(vt) : forward_waves(vt);
+    if constexpr (BWD) {  // (the forward alone is never split less than it can be)
+        if (waves == 1 && vt.tile_h > 4) {
+            if (vt.tile_h == 8) GSR_COMPOSITE(2, 1);
+            else if (vt.tile_h == 16) GSR_COMPOSITE(4, 1);
+            else GSR_COMPOSITE(8, 1);
+            return;
+        }
+        if (waves == 2 && vt.tile_h > 8) {
+            if (vt.tile_h == 16) GSR_COMPOSITE(2, 2);
+            else GSR_COMPOSITE(4, 2);
+            return;
+        }
+    }
+    switch (vt.tile_h) {
+        case 4: GSR_COMPOSITE(1, 1); break;
+        case 8: GSR_COMPOSITE(1, 2); break;
+        case 32: GSR_COMPOSITE(2, 4); break;
+        default: GSR_COMPOSITE(1, 4); break;
+    }
+#undef GSR_COMPOSITE
 }
 
 void launch_composite_fwd(const ViewTable &vt, const uint2 *ranges, const uint32_t *pval, const Rec *rec,
@@ -688,23 +799,12 @@ void launch_composite_fwd(const ViewTable &vt, const uint2 *ranges, const uint32
                           uint32_t *pix_n, uint32_t *tile_cut, uint32_t *tile_order, WsHeader *hdr,
                           bool persistent, int persistent_ctas, bool stats, hipStream_t st) {
     if (vt.total_tiles == 0) return;
-    const int p = persistent ? 1 : 0;
-#define GSR_FWD(R, S)                                                                                               \
-    hipLaunchKernelGGL((k_composite_fwd<R, S>),                                                                     \
-                       dim3(persistent ? (unsigned)resident_ctas(k_composite_fwd<R, S>, persistent_ctas)            \
-                                       : vt.total_tiles),                                                           \
-                       dim3(kWave), 0, st, vt, ranges, pval, rec, ulo, bg, out_rgb, out_T, pix_T, pix_n,            \
-                       tile_cut, tile_order, hdr, p)
-#define GSR_FWD_RPL(R) \
-    if (stats) GSR_FWD(R, true); else GSR_FWD(R, false)
-    switch (vt.tile_h) {
-        case 4: GSR_FWD_RPL(1); break;
-        case 8: GSR_FWD_RPL(2); break;
-        case 32: GSR_FWD_RPL(8); break;
-        default: GSR_FWD_RPL(4); break;
-    }
-#undef GSR_FWD_RPL
-#undef GSR_FWD
+    CompositeArgs A{};
+    A.ranges = ranges, A.pval = pval, A.rec = rec, A.ulo = ulo, A.bg = bg;
+    A.out_rgb = out_rgb, A.out_T = out_T, A.pix_T = pix_T, A.pix_n = pix_n;
+    A.tile_cut = tile_cut, A.tile_order = tile_order, A.hdr = hdr, A.persistent = persistent ? 1 : 0;
+    if (stats) launch_composite<true, false, true>(vt, A, persistent_ctas, st);
+    else launch_composite<true, false, false>(vt, A, persistent_ctas, st);
 }
 
 void launch_composite_bwd(const ViewTable &vt, const uint2 *ranges, const uint32_t *pval, const Rec *rec,
@@ -712,22 +812,13 @@ void launch_composite_bwd(const ViewTable &vt, const uint2 *ranges, const uint32
                           const uint32_t *tile_cut, const uint32_t *tile_order, float *partial, uint8_t *pflag,
                           const ZeroRows &zr, WsHeader *hdr, bool persistent, int persistent_ctas, hipStream_t st) {
     if (vt.total_tiles == 0) return;
-    const int p = persistent ? 1 : 0;
-#define GSR_BWD(R)                                                                                                  \
-    hipLaunchKernelGGL(k_composite_bwd<R>,                                                                          \
-                       dim3(persistent ? (unsigned)resident_ctas(k_composite_bwd<R>, persistent_ctas)               \
-                                       : vt.total_tiles),                                                           \
-                       dim3(kWave), 0, st, vt, ranges, pval, rec, ulo, out_rgb, up, pix_n, tile_cut, tile_order,    \
-                       partial, pflag, zr, hdr, p)
-    switch (vt.tile_h) {
-        case 4: GSR_BWD(1); break;
-        case 8: GSR_BWD(2); break;
-        case 32: GSR_BWD(8); break;
-        default: GSR_BWD(4); break;
-    }
-#undef GSR_BWD
+    CompositeArgs A{};
+    A.ranges = ranges, A.pval = pval, A.rec = rec, A.ulo = ulo, A.up = up;
+    A.out_rgb = const_cast<float *>(out_rgb), A.pix_n = const_cast<uint32_t *>(pix_n);
+    A.tile_cut = const_cast<uint32_t *>(tile_cut), A.tile_order = const_cast<uint32_t *>(tile_order);
+    A.partial = partial, A.pflag = pflag, A.zr = zr, A.hdr = hdr, A.persistent = persistent ? 1 : 0;
+    launch_composite<false, true, false>(vt, A, persistent_ctas, st);
 }
-
 
 void launch_composite_step(const ViewTable &vt, const uint2 *ranges, const uint32_t *pval, const Rec *rec,
                            const float2 *ulo, float3 bg, const float *target, float l1_scale, float *out_rgb,
@@ -735,20 +826,12 @@ void launch_composite_step(const ViewTable &vt, const uint2 *ranges, const uint3
                            const uint32_t *tile_order, float *partial, uint8_t *pflag, const ZeroRows &zr,
                            WsHeader *hdr, bool persistent, int persistent_ctas, hipStream_t st) {
     if (vt.total_tiles == 0) return;
-    const int p = persistent ? 1 : 0;
-#define GSR_STEP(R)                                                                                                 \
-    hipLaunchKernelGGL(k_composite_step<R>,                                                                         \
-                       dim3(persistent ? (unsigned)resident_ctas(k_composite_step<R>, persistent_ctas)              \
-                                       : vt.total_tiles),                                                           \
-                       dim3(kWave), 0, st, vt, ranges, pval, rec, ulo, bg, target, l1_scale, out_rgb, out_T, pix_T, \
-                       pix_n, tile_cut, tile_order, partial, pflag, zr, hdr, p)
-    switch (vt.tile_h) {
-        case 4: GSR_STEP(1); break;
-        case 8: GSR_STEP(2); break;
-        case 32: GSR_STEP(8); break;
-        default: GSR_STEP(4); break;
-    }
-#undef GSR_STEP
+    CompositeArgs A{};
+    A.ranges = ranges, A.pval = pval, A.rec = rec, A.ulo = ulo, A.bg = bg, A.up = Upstream{nullptr, target, l1_scale};
+    A.out_rgb = out_rgb, A.out_T = out_T, A.pix_T = pix_T, A.pix_n = pix_n;
+    A.tile_cut = tile_cut, A.tile_order = const_cast<uint32_t *>(tile_order);
+    A.partial = partial, A.pflag = pflag, A.zr = zr, A.hdr = hdr, A.persistent = persistent ? 1 : 0;
+    launch_composite<true, true, false>(vt, A, persistent_ctas, st);
 }
 
 }  // namespace gsr
