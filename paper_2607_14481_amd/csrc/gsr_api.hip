@@ -913,7 +913,7 @@ int gsr_gather_gaussians(const gsr_gaussians *src, const int32_t *index, int64_t
 namespace {
 
 struct BaLayout {
-    size_t obs_rec, lm_rec, S, dc, obs_cam, free_slot, slot_cam, block_ab, block_off, pairs, rec_pos, total;
+    size_t lm_rec, lm_sum, S, dc, pose_old, obs_cam, free_slot, slot_cam, block_ab, block_off, pairs, total;
 };
 
 BaLayout ba_layout(int n_cams, int n_free, int K, int M) {
@@ -926,17 +926,17 @@ BaLayout ba_layout(int n_cams, int n_free, int K, int M) {
     };
     const size_t D = 6 * (size_t)n_free + 1, nblk = (size_t)n_free * (n_free + 1) / 2;
     const size_t max_pairs = (size_t)K * ((size_t)M + (size_t)M * (M - 1) / 2);
-    L.obs_rec = take((size_t)K * M * gsr::kBaRecStride * sizeof(double));
     L.lm_rec = take((size_t)K * gsr::kBaLmStride * sizeof(double));
+    L.lm_sum = take(4 * gsr::ba_lm_blocks(K) * sizeof(double));
     L.S = take(gsr::kBaAsmSplit * (D + 1) * (D + 1) * sizeof(double));   // partial systems (pitch D + 1) + rhs + cost
     L.dc = take(D * sizeof(double));
+    L.pose_old = take((12 * (size_t)n_free + 1) * sizeof(double));
     L.obs_cam = take((size_t)K * M * sizeof(int32_t));
     L.free_slot = take((size_t)n_cams * sizeof(int32_t));
     L.slot_cam = take((size_t)(n_free > 0 ? n_free : 1) * sizeof(int32_t));
     L.block_ab = take((nblk > 0 ? nblk : 1) * sizeof(int2));
     L.block_off = take((nblk + 1) * sizeof(uint32_t));
-    L.pairs = take((max_pairs > 0 ? max_pairs : 1) * sizeof(int2));
-    L.rec_pos = take((size_t)K * M * sizeof(int32_t));
+    L.pairs = take((max_pairs > 0 ? max_pairs : 1) * sizeof(uint32_t));
     L.total = off;
     return L;
 }
@@ -1013,8 +1013,9 @@ int gsr_ba_plan_create(int32_t n_cams, const int32_t *free_slot, int32_t n_landm
     const size_t lds = ba_lds_bytes(D);
     if (lds > (size_t)lds_max) return fail(GSR_ERR_UNSUPPORTED, "reduced system needs %zu bytes of LDS (%d available)", lds, lds_max);
     if ((rc = check_hip(ba_allow_lds(D), "LDS attribute"))) return rc;
-    // observation-pair lists of the reduced system's blocks (a <= b), each in landmark order
-    std::vector<std::vector<int2>> lists((size_t)nblk);
+    // lists of the reduced system's blocks (a <= b), each in landmark order:
+    // a diagonal block's observations, an off-diagonal one's shared landmarks
+    std::vector<std::vector<uint32_t>> lists((size_t)nblk);
     auto block_of = [F](int a, int b) { return a * F - a * (a - 1) / 2 + (b - a); };
     int slot[kBaMaxObs];
     for (int j = 0; j < K; ++j) {
@@ -1024,26 +1025,14 @@ int gsr_ba_plan_create(int32_t n_cams, const int32_t *free_slot, int32_t n_landm
         }
         for (int k1 = 0; k1 < M; ++k1) {
             if (slot[k1] < 0) continue;
-            const int o1 = j * M + k1;
-            lists[block_of(slot[k1], slot[k1])].push_back(make_int2(o1, o1));
-            for (int k2 = k1 + 1; k2 < M; ++k2) {
-                if (slot[k2] < 0) continue;
-                const int o2 = j * M + k2;
-                if (slot[k1] < slot[k2]) lists[block_of(slot[k1], slot[k2])].push_back(make_int2(o1, o2));
-                else lists[block_of(slot[k2], slot[k1])].push_back(make_int2(o2, o1));
-            }
+            lists[block_of(slot[k1], slot[k1])].push_back((uint32_t)(j * M + k1));
+            for (int k2 = k1 + 1; k2 < M; ++k2)
+                if (slot[k2] >= 0)
+                    lists[block_of(std::min(slot[k1], slot[k2]), std::max(slot[k1], slot[k2]))].push_back((uint32_t)j);
         }
     }
-    // records are stored keyframe-major (free slot, then landmark): a diagonal
-    // block's list is then one contiguous run of records, and the two sides of
-    // an off-diagonal block's pairs advance through two runs
-    std::vector<int32_t> rec_pos((size_t)K * M, -1);
-    int32_t next_rec = 0;
-    for (int a = 0; a < F; ++a)
-        for (const int2 &e : lists[block_of(a, a)]) rec_pos[e.x] = next_rec++;
-    for (auto &l : lists)
-        for (int2 &e : l) e = make_int2(rec_pos[e.x], rec_pos[e.y]);
-    std::vector<int2> block_ab(nblk > 0 ? nblk : 1), pairs;
+    std::vector<uint32_t> pairs;
+    std::vector<int2> block_ab(nblk > 0 ? nblk : 1);
     std::vector<uint32_t> block_off(nblk + 1, 0);
     for (int a = 0, b = 0; a < F; ++a)
         for (int q = a; q < F; ++q, ++b) {
@@ -1052,7 +1041,7 @@ int gsr_ba_plan_create(int32_t n_cams, const int32_t *free_slot, int32_t n_landm
             pairs.insert(pairs.end(), lists[b].begin(), lists[b].end());
         }
     block_off[nblk] = (uint32_t)pairs.size();
-    if (pairs.empty()) pairs.push_back(make_int2(0, 0));
+    if (pairs.empty()) pairs.push_back(0u);
     hipStream_t st = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
     const struct {
@@ -1064,8 +1053,7 @@ int gsr_ba_plan_create(int32_t n_cams, const int32_t *free_slot, int32_t n_landm
               {L.slot_cam, slot_cam.data(), slot_cam.size() * 4},
               {L.block_ab, block_ab.data(), block_ab.size() * sizeof(int2)},
               {L.block_off, block_off.data(), block_off.size() * 4},
-              {L.pairs, pairs.data(), pairs.size() * sizeof(int2)},
-              {L.rec_pos, rec_pos.data(), rec_pos.size() * 4}};
+              {L.pairs, pairs.data(), pairs.size() * sizeof(uint32_t)}};
     for (const auto &u : up)
         if ((rc = check_hip(hipMemcpyAsync(ws + u.off, u.src, u.bytes, hipMemcpyHostToDevice, st), "structure upload")))
             return rc;
@@ -1101,11 +1089,11 @@ int gsr_ba_solve(const gsr_ba_plan *plan, double *poses, double *focal, double c
     A.free_slot = reinterpret_cast<const int32_t *>(ws + L.free_slot);
     A.slot_cam = reinterpret_cast<const int32_t *>(ws + L.slot_cam);
     A.block_ab = reinterpret_cast<const int2 *>(ws + L.block_ab);
-    A.pairs = reinterpret_cast<const int2 *>(ws + L.pairs);
-    A.rec_pos = reinterpret_cast<const int32_t *>(ws + L.rec_pos);
+    A.pairs = reinterpret_cast<const uint32_t *>(ws + L.pairs);
     A.block_off = reinterpret_cast<const uint32_t *>(ws + L.block_off);
-    A.obs_rec = reinterpret_cast<double *>(ws + L.obs_rec);
     A.lm_rec = reinterpret_cast<double *>(ws + L.lm_rec);
+    A.lm_sum = reinterpret_cast<double *>(ws + L.lm_sum);
+    A.pose_old = reinterpret_cast<double *>(ws + L.pose_old);
     A.S = reinterpret_cast<double *>(ws + L.S);
     A.dc = reinterpret_cast<double *>(ws + L.dc);
     A.costs = costs;

@@ -11,32 +11,37 @@
 // taken unconditionally:
 //
 //   k_ba_landmark   one 8-lane group per landmark, one lane per observation
-//                   slot: residual and Jacobians, the landmark's 3x3 block
-//                   (damped, inverted in closed form), and for every
-//                   observation in a free keyframe the pieces of the Schur
-//                   complement it contributes (below);
+//                   slot: takes the previous step's landmark update (back-
+//                   substitution at the previous linearisation point), then
+//                   residual and Jacobians at the new one and the landmark's
+//                   3x3 block (damped, inverted in closed form); writes one
+//                   128-byte record per landmark;
 //   k_ba_assemble   workgroups per block (a, b) of the reduced camera
 //                   system, each walking its part of a host-built list of
-//                   observation pairs in a fixed order (deterministic, no
-//                   atomics) into a partial system, plus workgroups for the
-//                   focal-length entry and the cost; the records are stored
-//                   keyframe-major, so a diagonal block reads one contiguous
-//                   run of them;
-//   k_ba_solve      one workgroup: adds the partial systems, then a blocked
-//                   Cholesky in LDS with the forward solve riding along, and
-//                   the backward solve in one wave;
-//   k_ba_update     landmark back-substitution and update, and the SE(3)
-//                   retraction of the free poses and the focal step.
+//                   the landmarks the two keyframes share in a fixed order
+//                   (deterministic, no atomics) into a partial system, plus
+//                   workgroups for the focal-length entry and the cost;
+//   k_ba_solve      one workgroup: adds the partial systems, a blocked
+//                   L D L^T on the FP64 matrix cores, the two triangular
+//                   solves, the SE(3) retraction of the free poses and the
+//                   focal step.
 //
-// The pieces per observation o (landmark j, free keyframe a), with
-// B_o = Jx^T Jp (6x3), Hinv the inverse of the damped landmark block,
-// Y_o = B_o Hinv, b_f = sum over the landmark's observations of Jf^T Jp and
-// g_p the landmark gradient:
-//   D_o = Jx^T Jx - Y_o B_o^T   (diagonal block, damping added from dg_o),
-//   dg_o = diag(Jx^T Jx),  c_o = Jx^T Jf - Y_o b_f,  s_o = Jx^T r - Y_o g_p;
-// and per landmark y_f = Hinv b_f, h_g = Hinv g_p, Jf^T Jf, y_f . b_f,
-// Jf^T r - y_f . g_p and its share of the cost.  Off-diagonal blocks are
-// -sum over shared landmarks of Y_{o_a} B_{o_b}^T.
+// Nothing is stored per observation.  With H^-1 the inverse of the damped
+// landmark block, a pair of observations o (keyframe a) and q (keyframe b) of
+// one landmark contributes
+//   Jx_o^T M Jx_q,  M = -Jp_o H^-1 Jp_q^T  (2 x 2)
+// to block (a, b), and an observation to the diagonal block, the focal column
+// and the right-hand side
+//   Jx^T (I - Jp H^-1 Jp^T) Jx,  Jx^T (Jf - Jp H^-1 b_f),  Jx^T (r - Jp H^-1 g_p)
+// (b_f = sum over the landmark's observations of Jf^T Jp, g_p the landmark
+// gradient; the damping lambda diag(Jx^T Jx) is added per block).  The
+// assembly evaluates the Jacobians again from the landmark's record (its
+// position, H^-1, b_f, g_p: one cache line) and the block's two poses, which
+// the whole workgroup shares: about 200 FP64 operations per pair instead of
+// reading 288 bytes of stored factors.  At 20 keyframes x 10,000 landmarks
+// (49,891 observations) an iteration so moves about 10 MB instead of 69 MB;
+// with 24 MB less to write, the landmark pass (the update included) takes 6.2
+// instead of 16 + 5 us and the assembly 12.3 instead of 19.6 us.
 #include "gsr_ba.h"
 
 namespace gsr {
@@ -45,12 +50,14 @@ namespace {
 
 constexpr int kLanesPerLm = kBaMaxObs;   // 8
 constexpr int kBaThreads = 256;
-constexpr int kSolveThreads = 512;    // the solve: 2 waves per SIMD to overlap its dependent chains
+constexpr int kLmPerBlock = kBaThreads / kLanesPerLm;
+constexpr int kAsmThreads = 512;
+constexpr int kSolveThreads = 1024;
+constexpr int kTile = 16;                // rows and columns of a matrix-core tile
+constexpr int kMaxTiles = (6 * kBaMaxFree + 2 + kTile - 1) / kTile;   // 8: tile rows of the largest system
 
-// offsets inside an observation record
-constexpr int kRB = 0, kRY = 18, kRD = 36, kRDg = 57, kRC = 63, kRS = 69;
-// offsets inside a landmark record
-constexpr int kLYf = 0, kLHg = 3, kLFf = 6, kLFs = 7, kLSf = 8, kLCost = 9;
+// offsets inside a landmark record: position, inverse block (00 01 02 11 12 22), b_f, g_p
+constexpr int kQP = 0, kQH = 3, kQB = 9, kQG = 12;
 
 // One DPP step on a double (both 32-bit halves moved alike): v + v moved
 // across lanes by `ctrl`, only in the rows enabled by `row_mask` (others add 0).
@@ -85,75 +92,125 @@ __device__ __forceinline__ double group_sum(double v) {
     return dpp_add_d<0x141, 0xf>(v);  // row_half_mirror
 }
 
-// Sum over the 64 lanes of a wave in a fixed order: quad swaps, half-row and
-// row mirrors leave each lane with its 16-lane row's sum, two row broadcasts
-// gather the rows into row 3; lane 63's total is returned to every lane.
-__device__ __forceinline__ double wave_sum_d(double v) {
-    v = dpp_add_d<0xB1, 0xf>(v);   // quad_perm [1, 0, 3, 2]
-    v = dpp_add_d<0x4E, 0xf>(v);   // quad_perm [2, 3, 0, 1]
-    v = dpp_add_d<0x141, 0xf>(v);  // row_half_mirror
-    v = dpp_add_d<0x140, 0xf>(v);  // row_mirror
-    v = dpp_add_d<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-    v = dpp_add_d<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-    return readlane_d(v, 63);
+// Lane swaps of a double (both halves): swap32(x, y)'s lanes [0, 32) hold x
+// of the lane plus x of the lane 32 above, lanes [32, 64) the same of y;
+// swap16's rows of 16 lanes hold x rows 0 + 1, y rows 0 + 1, x rows 2 + 3,
+// y rows 2 + 3.
+struct Halves {
+    unsigned lo, hi;
+};
+__device__ __forceinline__ Halves halves(double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    return Halves{(unsigned)b, (unsigned)(b >> 32)};
+}
+__device__ __forceinline__ double whole(unsigned lo, unsigned hi) {
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double swap_add32_d(double x, double y) {
+    const Halves a = halves(x), b = halves(y);
+    const auto l = __builtin_amdgcn_permlane32_swap(a.lo, b.lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(a.hi, b.hi, false, false);
+    return whole(l[0], h[0]) + whole(l[1], h[1]);
+}
+__device__ __forceinline__ double swap_add16_d(double x, double y) {
+    const Halves a = halves(x), b = halves(y);
+    const auto l = __builtin_amdgcn_permlane16_swap(a.lo, b.lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(a.hi, b.hi, false, false);
+    return whole(l[0], h[0]) + whole(l[1], h[1]);
 }
 
-// Sum of N per-thread accumulators over the 256-thread block in a fixed
-// order (deterministic): wave sums, then thread t adds the four waves' value
-// t in wave order.  red: 5 N doubles of LDS; returns the N sums (in LDS,
-// valid for every thread).
-template <int N>
+// Sum of N per-thread accumulators over a block of WAVES waves in a fixed
+// order (deterministic).  Four values at a time: two lane-swap levels leave
+// one register whose rows of 16 lanes hold values 0, 2, 1 and 3, four DPP
+// steps add each row (5 cross-lane steps per value instead of 18); then
+// thread t adds the waves' value t in wave order.  red: WAVES + 1 times (N
+// rounded up to 4) doubles of LDS; returns the N sums (in LDS, valid for every thread).
+template <int WAVES, int N>
 __device__ __forceinline__ const double *block_sum(const double (&acc)[N], double *red) {
+    constexpr int R = (N + 3) / 4 * 4;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int row = lane >> 4, pick = row == 1 ? 2 : (row == 2 ? 1 : row);
 #pragma unroll
-    for (int t = 0; t < N; ++t) {
-        const double v = wave_sum_d(acc[t]);
-        if (lane == 0) red[w * N + t] = v;
+    for (int t = 0; t < R; t += 4) {
+        const double v0 = acc[t], v1 = t + 1 < N ? acc[t + 1 < N ? t + 1 : 0] : 0.0;
+        const double v2 = t + 2 < N ? acc[t + 2 < N ? t + 2 : 0] : 0.0, v3 = t + 3 < N ? acc[t + 3 < N ? t + 3 : 0] : 0.0;
+        double v = swap_add16_d(swap_add32_d(v0, v1), swap_add32_d(v2, v3));
+        v = dpp_add_d<0xB1, 0xf>(v);   // quad_perm [1, 0, 3, 2]
+        v = dpp_add_d<0x4E, 0xf>(v);   // quad_perm [2, 3, 0, 1]
+        v = dpp_add_d<0x141, 0xf>(v);  // row_half_mirror
+        v = dpp_add_d<0x140, 0xf>(v);  // row_mirror
+        if ((lane & 15) == 0) red[w * R + t + pick] = v;
     }
     __syncthreads();
     if (threadIdx.x < N) {
         const int t = threadIdx.x;
-        red[4 * N + t] = ((red[t] + red[N + t]) + red[2 * N + t]) + red[3 * N + t];
+        double v = red[t];
+#pragma unroll
+        for (int q = 1; q < WAVES; ++q) v += red[q * R + t];
+        red[WAVES * R + t] = v;
     }
     __syncthreads();
-    return red + 4 * N;
+    return red + WAVES * R;
 }
 
 // A partial system: D rows of pitch D + 1 (even, as D = 6F + 1 is odd, so rows
 // are 16-byte aligned), then the right-hand side (D), the cost and a pad.
 __device__ __forceinline__ size_t part_stride(int D) { return (size_t)(D + 1) * (D + 1); }
 
+// Camera-frame point of an observation and the derivatives of its projection:
+// d pi / dX = [[a, 0, b], [0, a, c]].
 struct ObsGeom {
-    double r[2], jx[2][6], jf[2], jp[2][3];
+    double x, y, z, xn, yn, a, b, c;
 };
 
-// Residual and Jacobians of one observation.
-__device__ __forceinline__ ObsGeom observe(const double *__restrict__ T, const double p[3], double f, double cx, double cy,
-                                           const double uv[2]) {
+__device__ __forceinline__ ObsGeom observe(const double *__restrict__ T, const double p[3], double f) {
     ObsGeom o;
-    const double x = fma(T[0], p[0], fma(T[1], p[1], fma(T[2], p[2], T[3])));
-    const double y = fma(T[4], p[0], fma(T[5], p[1], fma(T[6], p[2], T[7])));
-    const double z = fma(T[8], p[0], fma(T[9], p[1], fma(T[10], p[2], T[11])));
-    const double iz = 1.0 / z, xn = x * iz, yn = y * iz;
-    o.r[0] = fma(f, xn, cx) - uv[0];
-    o.r[1] = fma(f, yn, cy) - uv[1];
-    const double a = f * iz, b = -a * xn, c = -a * yn;   // d pi / dX = [[a, 0, b], [0, a, c]]
-    // dX/drho = I, dX/dphi = -[X]x (left perturbation)
-    o.jx[0][0] = a;   o.jx[0][1] = 0.0; o.jx[0][2] = b;
-    o.jx[0][3] = b * y; o.jx[0][4] = a * z - b * x; o.jx[0][5] = -a * y;
-    o.jx[1][0] = 0.0; o.jx[1][1] = a;   o.jx[1][2] = c;
-    o.jx[1][3] = c * y - a * z; o.jx[1][4] = -c * x; o.jx[1][5] = a * x;
-    o.jf[0] = xn;
-    o.jf[1] = yn;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        o.jp[0][k] = fma(a, T[k], b * T[8 + k]);
-        o.jp[1][k] = fma(a, T[4 + k], c * T[8 + k]);
-    }
+    o.x = fma(T[0], p[0], fma(T[1], p[1], fma(T[2], p[2], T[3])));
+    o.y = fma(T[4], p[0], fma(T[5], p[1], fma(T[6], p[2], T[7])));
+    o.z = fma(T[8], p[0], fma(T[9], p[1], fma(T[10], p[2], T[11])));
+    const double iz = 1.0 / o.z;
+    o.xn = o.x * iz;
+    o.yn = o.y * iz;
+    o.a = f * iz;
+    o.b = -o.a * o.xn;
+    o.c = -o.a * o.yn;
     return o;
 }
 
-__global__ void __launch_bounds__(kBaThreads) k_ba_landmark(BaArgs A, int cost_only) {
+// Jacobian rows with respect to the pose's left twist: dX/drho = I, dX/dphi = -[X]x.
+__device__ __forceinline__ void pose_rows(const ObsGeom &o, double (&j0)[6], double (&j1)[6]) {
+    j0[0] = o.a;  j0[1] = 0.0;  j0[2] = o.b;
+    j0[3] = o.b * o.y;  j0[4] = o.a * o.z - o.b * o.x;  j0[5] = -o.a * o.y;
+    j1[0] = 0.0;  j1[1] = o.a;  j1[2] = o.c;
+    j1[3] = o.c * o.y - o.a * o.z;  j1[4] = -o.c * o.x;  j1[5] = o.a * o.x;
+}
+
+// Jacobian rows with respect to the landmark.
+__device__ __forceinline__ void point_rows(const ObsGeom &o, const double *__restrict__ T, double (&j0)[3], double (&j1)[3]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        j0[k] = fma(o.a, T[k], o.b * T[8 + k]);
+        j1[k] = fma(o.a, T[4 + k], o.c * T[8 + k]);
+    }
+}
+
+// h (packed symmetric 3x3) times v
+__device__ __forceinline__ void sym3(const double *h, const double v[3], double (&o)[3]) {
+    o[0] = fma(h[0], v[0], fma(h[1], v[1], h[2] * v[2]));
+    o[1] = fma(h[1], v[0], fma(h[3], v[1], h[4] * v[2]));
+    o[2] = fma(h[2], v[0], fma(h[4], v[1], h[5] * v[2]));
+}
+
+__device__ __forceinline__ double dot3(const double a[3], const double b[3]) {
+    return fma(a[0], b[0], fma(a[1], b[1], a[2] * b[2]));
+}
+
+// flags: kUpdate: first take the landmark update of the step the solve has
+// just finished; kCostOnly: nothing but the cost after that.
+constexpr int kUpdate = 1, kCostOnly = 2;
+
+__global__ void __launch_bounds__(kBaThreads) k_ba_landmark(BaArgs A, int flags) {
+    __shared__ double red[5 * 4];
     const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
     const uint32_t j = gid / kLanesPerLm;
     const int k = (int)(gid % kLanesPerLm);
@@ -161,128 +218,113 @@ __global__ void __launch_bounds__(kBaThreads) k_ba_landmark(BaArgs A, int cost_o
     const uint64_t o = (uint64_t)j * A.M + k;
     const int cam = (lm_ok && k < A.M) ? A.obs_cam[o] : -1;
     const double f = A.focal[0];
-    ObsGeom g = {};
+    double p[3] = {0.0, 0.0, 1.0};
+    if (lm_ok)
+        for (int u = 0; u < 3; ++u) p[u] = A.landmarks[3 * (uint64_t)j + u];
+    double uv[2] = {0.0, 0.0};
+    if (cam >= 0) uv[0] = A.obs_uv[2 * o], uv[1] = A.obs_uv[2 * o + 1];
+    double *Q = A.lm_rec + (uint64_t)(lm_ok ? j : 0) * kBaLmStride;
+    if (flags & kUpdate) {
+        // p -= H^-1 (g_p + b_f df + sum_o Jp^T (Jx dc)), at the poses and focal length before the step
+        const int slot = cam >= 0 ? A.free_slot[cam] : -1;
+        double q[12];
+#pragma unroll
+        for (int t = 0; t < 12; ++t) q[t] = Q[kQH + t];   // H^-1, b_f, g_p
+        double v[3] = {0.0, 0.0, 0.0};
+        if (slot >= 0) {
+            const double *T = A.pose_old + 12 * slot, *dc = A.dc + 6 * slot;
+            const ObsGeom g = observe(T, p, A.pose_old[12 * (uint64_t)A.F]);
+            double x0[6], x1[6], p0[3], p1[3], e0 = 0.0, e1 = 0.0;
+            pose_rows(g, x0, x1);
+            point_rows(g, T, p0, p1);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) e0 = fma(x0[i], dc[i], e0), e1 = fma(x1[i], dc[i], e1);
+#pragma unroll
+            for (int u = 0; u < 3; ++u) v[u] = fma(p0[u], e0, p1[u] * e1);
+        }
+        const double df = A.dc[A.D - 1];
+        double d[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) v[u] = q[9 + u] + fma(q[6 + u], df, group_sum(v[u]));
+        sym3(q, v, d);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) p[u] -= d[u];
+        if (lm_ok && k == 0)
+            for (int u = 0; u < 3; ++u) A.landmarks[3 * (uint64_t)j + u] = p[u];
+    }
+    double r0 = 0.0, r1 = 0.0, xn = 0.0, yn = 0.0, p0[3] = {0.0, 0.0, 0.0}, p1[3] = {0.0, 0.0, 0.0};
     if (cam >= 0) {
-        double p[3] = {A.landmarks[3 * j], A.landmarks[3 * j + 1], A.landmarks[3 * j + 2]};
-        double uv[2] = {A.obs_uv[2 * o], A.obs_uv[2 * o + 1]};
-        g = observe(A.poses + 12 * cam, p, f, A.cx, A.cy, uv);
+        const double *T = A.poses + 12 * (uint64_t)cam;
+        const ObsGeom g = observe(T, p, f);
+        point_rows(g, T, p0, p1);
+        xn = g.xn, yn = g.yn;
+        r0 = fma(f, xn, A.cx) - uv[0];
+        r1 = fma(f, yn, A.cy) - uv[1];
     }
-    const double cost = group_sum(0.5 * (g.r[0] * g.r[0] + g.r[1] * g.r[1]));
-    if (cost_only) {
-        if (lm_ok && k == 0) A.lm_rec[(uint64_t)j * kBaLmStride + kLCost] = cost;
-        return;
-    }
-    // landmark block, gradient and focal coupling, summed over the group
-    double H[6], gp[3], bf[3];
-    {
+    // per landmark, on lane 0 of its group: Jf^T Jf, y_f . b_f, Jf^T r - y_f . g_p and the cost,
+    // summed over the block's landmarks
+    double sums[4];
+    const double cost = group_sum(0.5 * (r0 * r0 + r1 * r1));
+    const bool first = lm_ok && k == 0;
+    sums[3] = first ? cost : 0.0;
+    if (flags & kCostOnly) {
+        sums[0] = sums[1] = sums[2] = 0.0;
+    } else {
+        // landmark block, gradient and focal coupling, summed over the group
+        double H[6], gp[3], bf[3];
         int t = 0;
 #pragma unroll
         for (int u = 0; u < 3; ++u)
 #pragma unroll
-            for (int v = u; v < 3; ++v) H[t++] = group_sum(fma(g.jp[0][u], g.jp[0][v], g.jp[1][u] * g.jp[1][v]));
+            for (int v = u; v < 3; ++v) H[t++] = group_sum(fma(p0[u], p0[v], p1[u] * p1[v]));
 #pragma unroll
         for (int u = 0; u < 3; ++u) {
-            gp[u] = group_sum(fma(g.jp[0][u], g.r[0], g.jp[1][u] * g.r[1]));
-            bf[u] = group_sum(fma(g.jf[0], g.jp[0][u], g.jf[1] * g.jp[1][u]));
+            gp[u] = group_sum(fma(p0[u], r0, p1[u] * r1));
+            bf[u] = group_sum(fma(xn, p0[u], yn * p1[u]));
         }
-    }
-    const double ff = group_sum(fma(g.jf[0], g.jf[0], g.jf[1] * g.jf[1]));
-    const double sfj = group_sum(fma(g.jf[0], g.r[0], g.jf[1] * g.r[1]));
-    // H = [[H0 H1 H2], [H1 H3 H4], [H2 H4 H5]], damped; inverse by cofactors
-    const double d0 = H[0] * (1.0 + A.lambda), d1 = H[3] * (1.0 + A.lambda), d2 = H[5] * (1.0 + A.lambda);
-    const double c00 = d1 * d2 - H[4] * H[4], c01 = H[2] * H[4] - H[1] * d2, c02 = H[1] * H[4] - H[2] * d1;
-    const double c11 = d0 * d2 - H[2] * H[2], c12 = H[1] * H[2] - d0 * H[4], c22 = d0 * d1 - H[1] * H[1];
-    const double det = d0 * c00 + H[1] * c01 + H[2] * c02;
-    const double id = det != 0.0 ? 1.0 / det : 0.0;
-    const double Hi[3][3] = {{c00 * id, c01 * id, c02 * id}, {c01 * id, c11 * id, c12 * id}, {c02 * id, c12 * id, c22 * id}};
-    double yf[3], hg[3];
+        const double ff = group_sum(fma(xn, xn, yn * yn));
+        const double sfj = group_sum(fma(xn, r0, yn * r1));
+        // H = [[H0 H1 H2], [H1 H3 H4], [H2 H4 H5]], damped; inverse by cofactors
+        const double d0 = H[0] * (1.0 + A.lambda), d1 = H[3] * (1.0 + A.lambda), d2 = H[5] * (1.0 + A.lambda);
+        const double c00 = d1 * d2 - H[4] * H[4], c01 = H[2] * H[4] - H[1] * d2, c02 = H[1] * H[4] - H[2] * d1;
+        const double c11 = d0 * d2 - H[2] * H[2], c12 = H[1] * H[2] - d0 * H[4], c22 = d0 * d1 - H[1] * H[1];
+        const double det = d0 * c00 + H[1] * c01 + H[2] * c02;
+        const double id = det != 0.0 ? 1.0 / det : 0.0;
+        const double hi[6] = {c00 * id, c01 * id, c02 * id, c11 * id, c12 * id, c22 * id};
+        double yf[3];
+        sym3(hi, bf, yf);
+        if (first) {
 #pragma unroll
-    for (int u = 0; u < 3; ++u) {
-        yf[u] = fma(Hi[u][0], bf[0], fma(Hi[u][1], bf[1], Hi[u][2] * bf[2]));
-        hg[u] = fma(Hi[u][0], gp[0], fma(Hi[u][1], gp[1], Hi[u][2] * gp[2]));
-    }
-    if (lm_ok && k == 0) {
-        double *L = A.lm_rec + (uint64_t)j * kBaLmStride;
-        L[kLYf] = yf[0]; L[kLYf + 1] = yf[1]; L[kLYf + 2] = yf[2];
-        L[kLHg] = hg[0]; L[kLHg + 1] = hg[1]; L[kLHg + 2] = hg[2];
-        L[kLFf] = ff;
-        L[kLFs] = fma(yf[0], bf[0], fma(yf[1], bf[1], yf[2] * bf[2]));
-        L[kLSf] = sfj - fma(yf[0], gp[0], fma(yf[1], gp[1], yf[2] * gp[2]));
-        L[kLCost] = cost;
-    }
-    if (cam < 0 || A.free_slot[cam] < 0) return;
-    double B[6][3], Y[6][3], rec[kBaRecStride];
+            for (int u = 0; u < 3; ++u) Q[kQP + u] = p[u], Q[kQB + u] = bf[u], Q[kQG + u] = gp[u];
 #pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int u = 0; u < 3; ++u) B[i][u] = fma(g.jx[0][i], g.jp[0][u], g.jx[1][i] * g.jp[1][u]);
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int u = 0; u < 3; ++u) Y[i][u] = fma(B[i][0], Hi[0][u], fma(B[i][1], Hi[1][u], B[i][2] * Hi[2][u]));
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int u = 0; u < 3; ++u) {
-            rec[kRB + 3 * i + u] = B[i][u];
-            rec[kRY + 3 * i + u] = Y[i][u];
+            for (int u = 0; u < 6; ++u) Q[kQH + u] = hi[u];
         }
-    int t = 0;
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int q = i; q < 6; ++q) {
-            const double jj = fma(g.jx[0][i], g.jx[0][q], g.jx[1][i] * g.jx[1][q]);
-            const double yb = fma(Y[i][0], B[q][0], fma(Y[i][1], B[q][1], Y[i][2] * B[q][2]));
-            rec[kRD + t++] = jj - yb;
-            if (q == i) rec[kRDg + i] = jj;
-        }
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        rec[kRC + i] = fma(g.jx[0][i], g.jf[0], g.jx[1][i] * g.jf[1]) -
-                       fma(Y[i][0], bf[0], fma(Y[i][1], bf[1], Y[i][2] * bf[2]));
-        rec[kRS + i] = fma(g.jx[0][i], g.r[0], g.jx[1][i] * g.r[1]) -
-                       fma(Y[i][0], gp[0], fma(Y[i][1], gp[1], Y[i][2] * gp[2]));
+        sums[0] = first ? ff : 0.0;
+        sums[1] = first ? dot3(yf, bf) : 0.0;
+        sums[2] = first ? sfj - dot3(yf, gp) : 0.0;
     }
-    rec[kBaRecStride - 1] = 0.0;
-    // records (keyframe-major, see the pair lists) are 608 bytes from a
-    // 256-byte aligned base: 16-byte stores
-    double2 *R = reinterpret_cast<double2 *>(A.obs_rec + (uint64_t)A.rec_pos[o] * kBaRecStride);
-#pragma unroll
-    for (int q = 0; q < kBaRecStride / 2; ++q) R[q] = make_double2(rec[2 * q], rec[2 * q + 1]);
+    const double *sum = block_sum<kBaThreads / 64>(sums, red);
+    if (threadIdx.x < 4) A.lm_sum[4 * (uint64_t)blockIdx.x + threadIdx.x] = sum[threadIdx.x];
 }
 
-// Blocks x = 0 .. nblk-1: block (a, b) of the reduced system from its pair
-// list; block x = nblk: the focal-length diagonal entry, its right-hand side
-// and the cost.  Each is split over kBaAsmSplit workgroups (y) that take
-// consecutive parts of the list (of the landmarks) and write a partial system
-// of their own; the solve adds the partials in order.
-__global__ void __launch_bounds__(kBaThreads) k_ba_assemble(BaArgs A) {
-    __shared__ double red[5 * 39];
+// Blocks x = 0 .. nblk-1: block (a, b) of the reduced system from its list;
+// block x = nblk: the focal-length diagonal entry, its right-hand side and the
+// cost.  Each is split over kBaAsmSplit workgroups (y) that take consecutive
+// parts of the list (of the landmark blocks) and write a partial system of
+// their own; the solve adds the partials in order.
+__global__ void __launch_bounds__(kAsmThreads) k_ba_assemble(BaArgs A) {
+    __shared__ double red[(kAsmThreads / 64 + 1) * 40];
     const int D = A.D, SP = D + 1, fcol = D - 1;
     const int part = blockIdx.y;
     double *S = A.S + part * part_stride(D), *s = S + (uint64_t)D * SP;
     if ((int)blockIdx.x == A.nblk) {
-        const int j0 = (int)((int64_t)A.K * part / kBaAsmSplit), j1 = (int)((int64_t)A.K * (part + 1) / kBaAsmSplit);
+        const int nb = (A.K + kLmPerBlock - 1) / kLmPerBlock;
+        const int i0 = (int)((int64_t)nb * part / kBaAsmSplit), i1 = (int)((int64_t)nb * (part + 1) / kBaAsmSplit);
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int jb = j0 + threadIdx.x; jb < j1; jb += 4 * kBaThreads) {   // 4 landmarks' loads in flight
-            double v[4][4];
+        for (int i = i0 + threadIdx.x; i < i1; i += kAsmThreads)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int j = jb + u * kBaThreads;
-                const double *L = A.lm_rec + (uint64_t)j * kBaLmStride;
-                const bool ok = j < j1;
-                v[u][0] = ok ? L[kLFf] : 0.0;
-                v[u][1] = ok ? L[kLFs] : 0.0;
-                v[u][2] = ok ? L[kLSf] : 0.0;
-                v[u][3] = ok ? L[kLCost] : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc[t] += v[u][t];
-        }
-        const double *sum = block_sum(acc, red);
+            for (int t = 0; t < 4; ++t) acc[t] += A.lm_sum[4 * (uint64_t)i + t];
+        const double *sum = block_sum<kAsmThreads / 64>(acc, red);
         if (threadIdx.x == 0) {
             S[(uint64_t)fcol * SP + fcol] = sum[0] * (1.0 + A.lambda) - sum[1];
             s[fcol] = sum[2];
@@ -295,17 +337,46 @@ __global__ void __launch_bounds__(kBaThreads) k_ba_assemble(BaArgs A) {
     const uint32_t e0 = b0 + (uint32_t)((uint64_t)len * part / kBaAsmSplit);
     const uint32_t e1 = b0 + (uint32_t)((uint64_t)len * (part + 1) / kBaAsmSplit);
     const int ra = 6 * ab.x, rb = 6 * ab.y;
+    const double f = A.focal[0];
+    const double *Ta = A.poses + 12 * (uint64_t)A.slot_cam[ab.x];
     if (ab.x == ab.y) {
+        // 21 entries of the upper triangle, 6 of diag(Jx^T Jx), the focal column and the right-hand side
         double acc[39];
 #pragma unroll
         for (int t = 0; t < 39; ++t) acc[t] = 0.0;
-        for (uint32_t e = e0 + threadIdx.x; e < e1; e += kBaThreads) {
-            const double *R = A.obs_rec + (uint64_t)A.pairs[e].x * kBaRecStride + kRD;
+        for (uint32_t e = e0 + threadIdx.x; e < e1; e += kAsmThreads) {
+            const uint32_t o = A.pairs[e];
+            const double *Q = A.lm_rec + (uint64_t)(o / (uint32_t)A.M) * kBaLmStride;
+            double q[15];
 #pragma unroll
-            for (int t = 0; t < 39; ++t) acc[t] += R[t];
+            for (int t = 0; t < 15; ++t) q[t] = Q[t];
+            const double u0 = A.obs_uv[2 * (uint64_t)o], u1 = A.obs_uv[2 * (uint64_t)o + 1];
+            const ObsGeom g = observe(Ta, q + kQP, f);
+            double x0[6], x1[6], p0[3], p1[3], h0[3], h1[3];
+            pose_rows(g, x0, x1);
+            point_rows(g, Ta, p0, p1);
+            sym3(q + kQH, p0, h0);
+            sym3(q + kQH, p1, h1);
+            const double m00 = 1.0 - dot3(p0, h0), m01 = -dot3(p0, h1), m11 = 1.0 - dot3(p1, h1);
+            const double r0 = fma(f, g.xn, A.cx) - u0, r1 = fma(f, g.yn, A.cy) - u1;
+            const double c0 = g.xn - dot3(h0, q + kQB), c1 = g.yn - dot3(h1, q + kQB);
+            const double s0 = r0 - dot3(h0, q + kQG), s1 = r1 - dot3(h1, q + kQG);
+            int t = 0;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                const double y0 = fma(m00, x0[i], m01 * x1[i]), y1 = fma(m01, x0[i], m11 * x1[i]);
+#pragma unroll
+                for (int w = i; w < 6; ++w, ++t) acc[t] = fma(y0, x0[w], fma(y1, x1[w], acc[t]));
+            }
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                acc[21 + i] = fma(x0[i], x0[i], fma(x1[i], x1[i], acc[21 + i]));
+                acc[27 + i] = fma(x0[i], c0, fma(x1[i], c1, acc[27 + i]));
+                acc[33 + i] = fma(x0[i], s0, fma(x1[i], s1, acc[33 + i]));
+            }
         }
-        const double *sum = block_sum(acc, red);
-        for (int t = threadIdx.x; t < 36; t += kBaThreads) {
+        const double *sum = block_sum<kAsmThreads / 64>(acc, red);
+        for (int t = threadIdx.x; t < 36; t += kAsmThreads) {
             const int i = t / 6, q = t % 6;
             const int lo = i < q ? i : q, hi = i < q ? q : i;
             const int tri = lo * 6 - lo * (lo - 1) / 2 + (hi - lo);   // packed upper-triangle index
@@ -315,7 +386,6 @@ __global__ void __launch_bounds__(kBaThreads) k_ba_assemble(BaArgs A) {
         }
         if (threadIdx.x < 6) {
             const int i = threadIdx.x;
-            S[(uint64_t)(ra + i) * SP + fcol] = sum[27 + i];
             S[(uint64_t)fcol * SP + ra + i] = sum[27 + i];
             s[ra + i] = sum[33 + i];
         }
@@ -324,236 +394,60 @@ __global__ void __launch_bounds__(kBaThreads) k_ba_assemble(BaArgs A) {
     double acc[36];
 #pragma unroll
     for (int t = 0; t < 36; ++t) acc[t] = 0.0;
-    for (uint32_t e = e0 + threadIdx.x; e < e1; e += kBaThreads) {
-        const int2 pr = A.pairs[e];
-        const double *Ya = A.obs_rec + (uint64_t)pr.x * kBaRecStride + kRY;
-        const double *Bb = A.obs_rec + (uint64_t)pr.y * kBaRecStride + kRB;
-        double y[18], b[18];
+    const double *Tb = A.poses + 12 * (uint64_t)A.slot_cam[ab.y];
+    for (uint32_t e = e0 + threadIdx.x; e < e1; e += kAsmThreads) {
+        const double *Q = A.lm_rec + (uint64_t)A.pairs[e] * kBaLmStride;
+        double q[9];
 #pragma unroll
-        for (int t = 0; t < 18; ++t) {
-            y[t] = Ya[t];
-            b[t] = Bb[t];
+        for (int t = 0; t < 9; ++t) q[t] = Q[t];
+        const ObsGeom ga = observe(Ta, q + kQP, f), gb = observe(Tb, q + kQP, f);
+        double a0[3], a1[3], p0[3], p1[3], h0[3], h1[3];
+        point_rows(ga, Ta, a0, a1);
+        point_rows(gb, Tb, p0, p1);
+        sym3(q + kQH, p0, h0);
+        sym3(q + kQH, p1, h1);
+        const double m00 = dot3(a0, h0), m01 = dot3(a0, h1), m10 = dot3(a1, h0), m11 = dot3(a1, h1);
+        double x0[6], x1[6], z0[6], z1[6];
+        pose_rows(ga, x0, x1);
+        pose_rows(gb, z0, z1);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            const double y0 = fma(m00, x0[i], m10 * x1[i]), y1 = fma(m01, x0[i], m11 * x1[i]);
+#pragma unroll
+            for (int w = 0; w < 6; ++w) acc[6 * i + w] = fma(y0, z0[w], fma(y1, z1[w], acc[6 * i + w]));
         }
-#pragma unroll
-        for (int i = 0; i < 6; ++i)
-#pragma unroll
-            for (int q = 0; q < 6; ++q)
-                acc[6 * i + q] += fma(y[3 * i], b[3 * q], fma(y[3 * i + 1], b[3 * q + 1], y[3 * i + 2] * b[3 * q + 2]));
     }
-    const double *sum = block_sum(acc, red);
-    for (int t = threadIdx.x; t < 36; t += kBaThreads) {
+    const double *sum = block_sum<kAsmThreads / 64>(acc, red);
+    // (only the lower triangle is read: rows of b, columns of a < b)
+    for (int t = threadIdx.x; t < 36; t += kAsmThreads) {
         const int i = t / 6, q = t % 6;
-        S[(uint64_t)(ra + i) * SP + rb + q] = -sum[t];
         S[(uint64_t)(rb + q) * SP + ra + i] = -sum[t];
     }
 }
 
-// Cholesky S = L L^T of the reduced system (D x D, symmetric positive definite
-// after damping) in LDS, right-looking in column blocks of 8, then
-// dc = -S^-1 s.  Per block: wave 0 factors the 8 x 8 diagonal block in
-// registers (lane = row * 8 + column) and solves its part of L z = s while the
-// other waves file the previous block's panel; then 2 x 2 tiles of the
-// trailing lower triangle each solve the panel rows they need against the
-// block and take the rank-8 update, the first tile of each row band keeping
-// its rows' panel and folding them into z.  Two barriers per block.  Finally
-// wave 0 solves L^T x = z a column at a time.
-__global__ void __launch_bounds__(kSolveThreads) k_ba_solve(BaArgs A, int iter) {
-    extern __shared__ double lds[];
-    // odd row pitch: column walks (one row per lane) hit distinct LDS banks
-    const int D = A.D, P = D | 1;
-    double *M = lds, *rhs = lds + (uint64_t)D * P, *dinv = rhs + D, *pan = dinv + D;   // pan: [D][8]
-    const int tid = threadIdx.x, lane = tid & 63;
-    const size_t ps = part_stride(D);
-    // lower triangle of the sum of the partial systems, as column pairs of
-    // 16-byte loads, 2 pairs x kBaAsmSplit partials in flight per thread
-    {
-        const int SP = D + 1, half = SP / 2, items = D * half;
-        for (int base = tid; base < items; base += 2 * kSolveThreads) {
-            double2 v[2][kBaAsmSplit];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int it = base + u * kSolveThreads, r = it / half, cp = it - r * half;
-                const bool ok = it < items && 2 * cp <= r;
-#pragma unroll
-                for (int q = 0; q < kBaAsmSplit; ++q)
-                    v[u][q] = ok ? *reinterpret_cast<const double2 *>(A.S + q * ps + (size_t)r * SP + 2 * cp)
-                                 : make_double2(0.0, 0.0);
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int it = base + u * kSolveThreads, r = it / half, cp = it - r * half;
-                if (it < items && 2 * cp <= r) {
-                    double2 w = v[u][0];
-#pragma unroll
-                    for (int q = 1; q < kBaAsmSplit; ++q) {
-                        w.x += v[u][q].x;
-                        w.y += v[u][q].y;
-                    }
-                    M[r * P + 2 * cp] = w.x;
-                    if (2 * cp + 1 <= r) M[r * P + 2 * cp + 1] = w.y;
-                }
-            }
-        }
-    }
-    for (int t = tid; t <= D; t += kSolveThreads) {   // right-hand side and (t = D) the cost
-        const size_t at = (size_t)D * (D + 1) + t;
-        double v = A.S[at];
-#pragma unroll
-        for (int q = 1; q < kBaAsmSplit; ++q) v += A.S[q * ps + at];
-        if (t < D) rhs[t] = v;
-        else if (A.costs) A.costs[iter] = v;
-    }
-    __syncthreads();
-    for (int k0 = 0; k0 < D; k0 += 8) {
-        const int nb = D - k0 < 8 ? D - k0 : 8, k1 = k0 + nb;
-        if (tid < 64) {
-            // rows/columns past the block's end are padded with the identity
-            const int r = lane >> 3, c = lane & 7;
-            const bool in = r < nb && c <= r;
-            double a = in ? M[(k0 + r) * P + k0 + c] : (r == c ? 1.0 : 0.0);
-            double y = (c == 0 && r < nb) ? rhs[k0 + r] : 0.0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const double inv = rsqrt(readlane_d(a, j * 9)), ljj = readlane_d(a, j * 9) * inv;
-                if (c == j) a = r == j ? ljj : (r > j ? a * inv : a);
-                const double lrj = __shfl(a, r * 8 + j, 64), lcj = __shfl(a, c * 8 + j, 64);
-                if (c > j && r >= c) a = fma(-lrj, lcj, a);
-                const double zj = readlane_d(y, j * 8) * inv;
-                if (c == 0) y = r == j ? zj : (r > j ? fma(-lrj, zj, y) : y);
-            }
-            if (in) M[(k0 + r) * P + k0 + c] = a;
-            if (r == c && r < nb) dinv[k0 + r] = 1.0 / a;
-            if (c == 0 && r < nb) rhs[k0 + r] = y;
-        } else if (k0 > 0) {
-            // meanwhile the other waves file the previous block's panel (rows
-            // k0.., columns k0 - 8 .. k0 - 1) into the factor
-            for (int e = tid - 64; e < (D - k0) * 8; e += kSolveThreads - 64)
-                M[(k0 + (e >> 3)) * P + k0 - 8 + (e & 7)] = pan[(k0 + (e >> 3)) * 8 + (e & 7)];
-        }
-        __syncthreads();
-        const int n = D - k1;   // n > 0 implies a full block (nb = 8)
-        if (n > 0) {
-            // the factor's 8 x 8 block, its reciprocal diagonal and z entries are
-            // the same for every thread: read from LDS where used (broadcasts)
-            const double *lb = M + k0 * P + k0, *di = dinv + k0, *zb = rhs + k0;
-            const int T = (n + 1) >> 1, ntiles = T * (T + 1) / 2;
-            for (int t = tid; t < ntiles; t += kSolveThreads) {
-                int ti = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
-                while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
-                while (ti * (ti + 1) / 2 > t) --ti;
-                const int tj = t - ti * (ti + 1) / 2;
-                const int i0 = k1 + 2 * ti, j0 = k1 + 2 * tj;
-                // the panel rows of this tile (L[row][k0..k1) = A[row][k0..k1) L_blk^-T),
-                // recomputed by every tile that needs them: no panel phase, no barrier
-                double li[2][8], lj[2][8];
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int m = 0; m < 8; ++m) {
-                        li[u][m] = i0 + u < D ? M[(i0 + u) * P + k0 + m] : 0.0;
-                        lj[u][m] = j0 + u < D ? M[(j0 + u) * P + k0 + m] : 0.0;
-                    }
-                double acc[2][2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 2; ++v) {
-                        const int i = i0 + u, j = j0 + v;
-                        acc[u][v] = (i < D && j <= i) ? M[i * P + j] : 0.0;
-                    }
-#pragma unroll
-                for (int m = 0; m < 8; ++m) {
-#pragma unroll
-                    for (int q = 0; q < m; ++q) {
-                        const double l = lb[m * P + q];
-#pragma unroll
-                        for (int u = 0; u < 2; ++u) {
-                            li[u][m] = fma(-li[u][q], l, li[u][m]);
-                            lj[u][m] = fma(-lj[u][q], l, lj[u][m]);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        li[u][m] *= di[m];
-                        lj[u][m] *= di[m];
-                    }
-                }
-                if (tj == 0) {
-                    // the first tile of each row band files its rows' panel and
-                    // folds them into z (one owner per row)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-                        if (i0 + u < D) {
-                            double rr = rhs[i0 + u];
-#pragma unroll
-                            for (int m = 0; m < 8; ++m) {
-                                pan[(i0 + u) * 8 + m] = li[u][m];
-                                rr = fma(-li[u][m], zb[m], rr);
-                            }
-                            rhs[i0 + u] = rr;
-                        }
-                }
-#pragma unroll
-                for (int m = 0; m < 8; ++m)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int v = 0; v < 2; ++v) acc[u][v] = fma(-li[u][m], lj[v][m], acc[u][v]);
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 2; ++v) {
-                        const int i = i0 + u, j = j0 + v;
-                        if (i < D && j <= i) M[i * P + j] = acc[u][v];
-                    }
-            }
-        }
-        __syncthreads();
-    }
-    // L^T x = z by wave 0: lane owns entries lane and lane + 64; x_q is final
-    // once every row below q has been folded in.
-    if (tid >= 64) return;
-    const double di0 = lane < D ? dinv[lane] : 0.0, di1 = lane + 64 < D ? dinv[lane + 64] : 0.0;
-    double y0 = lane < D ? rhs[lane] : 0.0, y1 = lane + 64 < D ? rhs[lane + 64] : 0.0;
-    // rows of L read four at a time ahead of the dependent steps that use them
-    int q = D - 1;
-    for (; q >= 4; q -= 4) {
-        double m0[4], m1[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            m0[u] = lane < q - u ? M[(q - u) * P + lane] : 0.0;
-            m1[u] = lane + 64 < q - u ? M[(q - u) * P + lane + 64] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int r = q - u;
-            const double xr = r < 64 ? readlane_d(y0 * di0, r) : readlane_d(y1 * di1, r - 64);
-            y0 = fma(-m0[u], xr, y0);
-            y1 = fma(-m1[u], xr, y1);
-        }
-    }
-    for (; q > 0; --q) {
-        const double xq = q < 64 ? readlane_d(y0 * di0, q) : readlane_d(y1 * di1, q - 64);
-        if (lane < q) y0 = fma(-M[q * P + lane], xq, y0);
-        if (lane + 64 < q) y1 = fma(-M[q * P + lane + 64], xq, y1);
-    }
-    if (lane < D) A.dc[lane] = -y0 * di0;
-    if (lane + 64 < D) A.dc[lane + 64] = -y1 * di1;
-}
-
 // SE(3) exponential of (rho, phi): R = I + a [phi]x + b [phi]x^2,
 // V = I + b [phi]x + c [phi]x^2 with a = sin t / t, b = (1 - cos t) / t^2,
-// c = (t - sin t) / t^3, t = |phi| (series below t = 1e-2, error < 1e-15).
+// c = (t - sin t) / t^3, t = |phi|.  Up to t = 1/2, where the closed forms of
+// b and c cancel, by their power series in t^2 (nine terms: the next is below
+// 1e-21), which also keeps the sine and cosine out of the solve's chain.
 __device__ void se3_exp(const double xi[6], double Rm[3][3], double tv[3]) {
     const double w0 = xi[3], w1 = xi[4], w2 = xi[5];
-    const double t2 = w0 * w0 + w1 * w1 + w2 * w2, t = sqrt(t2);
+    const double t2 = w0 * w0 + w1 * w1 + w2 * w2;
     double a, b, c;
-    if (t < 1e-2) {
-        a = 1.0 - t2 / 6.0 * (1.0 - t2 / 20.0);
-        b = 0.5 - t2 / 24.0 * (1.0 - t2 / 30.0);
-        c = 1.0 / 6.0 - t2 / 120.0 * (1.0 - t2 / 42.0);
+    if (t2 < 0.25) {
+        // the k-th coefficients are (-1)^k / (2k + 1)!, / (2k + 2)! and / (2k + 3)!:
+        // each ratio to the one before is -1 / ((m - 1) m) for factorial m!
+        a = b = c = 1.0;
+#pragma unroll
+        for (int k = 8; k >= 1; --k) {
+            a = fma(-t2 * (1.0 / ((2 * k) * (2 * k + 1))), a, 1.0);
+            b = fma(-t2 * (1.0 / ((2 * k + 1) * (2 * k + 2))), b, 1.0);
+            c = fma(-t2 * (1.0 / ((2 * k + 2) * (2 * k + 3))), c, 1.0);
+        }
+        b *= 0.5;
+        c *= 1.0 / 6.0;
     } else {
-        const double sn = sin(t), cs = cos(t);
+        const double t = sqrt(t2), sn = sin(t), cs = cos(t);
         a = sn / t;
         b = (1.0 - cs) / t2;
         c = (t - sn) / (t2 * t);
@@ -572,86 +466,317 @@ __device__ void se3_exp(const double xi[6], double Rm[3][3], double tv[3]) {
     for (int r = 0; r < 3; ++r) tv[r] = V[r][0] * xi[0] + V[r][1] * xi[1] + V[r][2] * xi[2];
 }
 
-// Landmark back-substitution p_j -= h_g + sum_o Y_o^T dc_a + y_f df, and (the
-// last block) the pose retraction T_a <- exp(dc_a) T_a and f += df.
-__global__ void __launch_bounds__(kBaThreads) k_ba_update(BaArgs A) {
-    const double df = A.dc[A.D - 1];
-    if (blockIdx.x == gridDim.x - 1) {
-        const int a = threadIdx.x;
-        if (a < A.F) {
-            double xi[6], Rm[3][3], tv[3];
-            for (int q = 0; q < 6; ++q) xi[q] = A.dc[6 * a + q];
-            se3_exp(xi, Rm, tv);
-            double *T = A.poses + 12 * A.slot_cam[a];
-            double N[12];
-            for (int r = 0; r < 3; ++r) {
-                for (int q = 0; q < 4; ++q) N[4 * r + q] = Rm[r][0] * T[q] + Rm[r][1] * T[4 + q] + Rm[r][2] * T[8 + q];
-                N[4 * r + 3] += tv[r];
-            }
-            for (int q = 0; q < 12; ++q) T[q] = N[q];
+// v of lane C of this lane's row of 16 (a DPP move: a few cycles, against tens
+// for a readlane into a scalar register and back).
+template <int C>
+__device__ __forceinline__ double row_lane(double v) {
+    return __longlong_as_double(
+        __builtin_amdgcn_update_dpp((long long)0, (long long)__double_as_longlong(v), 0x150 + C, 0xf, 0xf, true));
+}
+
+// f(integral constant I) for I = I0 .. N - 1, for code whose index must be a constant
+template <int I>
+struct Index {
+    static constexpr int value = I;
+};
+template <int I0, int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+    if constexpr (I0 < N) {
+        f(Index<I0>{});
+        static_for<I0 + 1, N>(f);
+    }
+}
+
+// 1 / d to within about an ulp: the hardware's estimate and two Newton steps.
+__device__ __forceinline__ double recip(double d) {
+    double y = __builtin_amdgcn_rcp(d);
+    y = fma(y, fma(-d, y, 1.0), y);
+    return fma(y, fma(-d, y, 1.0), y);
+}
+
+// S = L D L^T of the reduced system (D x D, symmetric positive definite after
+// damping) in LDS, right-looking in column blocks of 16, with the right-hand
+// side s as one more row (row D of the factor is then w^T, w = D^-1 L^-1 s,
+// without a forward solve), then L^T dc = -w.  What it costs is the
+// serial chain of D pivots, so everything else is taken off it:
+//
+//   factor + panel  every row of 16 lanes holds the diagonal tile, a row of it
+//                   per lane, and each lane one further panel row of the
+//                   block's columns, in registers (64 panel rows; the next 64
+//                   are another wave's, which factors the diagonal tile again
+//                   rather than wait for it).  Column j: the pivot and the
+//                   column's entries come from the tile by DPP broadcasts
+//                   within the row of lanes, and one reciprocal and one
+//                   multiply-add per entry follow; no square root, no LDS and
+//                   no scalar register in the chain, and the reciprocal of
+//                   the next pivot runs between the updates of this column.
+//                   What is left in place is -L.
+//   trailing        16 x 16 tiles, C -= L_i D L_j^T, four v_mfma_f64_16x16x4
+//                   each, a wave per tile: the next block's column of tiles
+//                   at once, the others while waves 0 and 1 factor it.
+//
+// Two barriers per block of 16 columns.  D = 97: 22.5 us (load 2.3, factor
+// and panel 10, trailing 3.3, backward solve 5.1, retraction 0.8) against
+// 59 us for a blocked Cholesky by 8 columns with 2 x 2 register tiles.  A
+// factoring wave is alone on its SIMD and bound by issue, about 6 cycles an
+// FP64 instruction, not by the pivots' dependence (a shorter reciprocal chain
+// changed nothing).
+__global__ void __launch_bounds__(kSolveThreads) k_ba_solve(BaArgs A, int iter) {
+    extern __shared__ __attribute__((aligned(16))) double lds[];
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    // row pitch 16 NB + 2: 16 rows of one column lie in 16 different bank groups
+    const int D = A.D, NB = (D + 1 + kTile - 1) / kTile, N = NB * kTile, P = N + 2;
+    double *M = lds, *nd = lds + (size_t)N * P, *dcs = nd + N;   // nd: -D
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const size_t ps = part_stride(D);
+    // the lower triangle of the sum of the partial systems (row D: the
+    // right-hand side, and the cost in column D), zero in the padding: row
+    // wave + 8 i, one 16-byte column pair per lane, every load in flight
+    {
+        constexpr int W = kSolveThreads / 64, U = kMaxTiles * kTile / W;
+        double2 v[U][kBaAsmSplit];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = wave + W * u;
+            const bool ok = r <= D && 2 * lane <= r && 2 * lane < D;
+#pragma unroll
+            for (int q = 0; q < kBaAsmSplit; ++q)
+                v[u][q] = ok ? *reinterpret_cast<const double2 *>(A.S + q * ps + (size_t)r * (D + 1) + 2 * lane)
+                             : make_double2(0.0, 0.0);
         }
-        if (a == 0) A.focal[0] += df;
-        return;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = wave + W * u;
+            if (r >= N || 2 * lane >= N) continue;
+            double2 w = v[u][0];
+#pragma unroll
+            for (int q = 1; q < kBaAsmSplit; ++q) {
+                w.x += v[u][q].x;
+                w.y += v[u][q].y;
+            }
+            if (r == D && 2 * lane + 1 == D && A.costs) A.costs[iter] = w.y;
+            *reinterpret_cast<double2 *>(M + (size_t)r * P + 2 * lane) = w;
+        }
     }
-    const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t j = gid / kLanesPerLm;
-    const int k = (int)(gid % kLanesPerLm);
-    const bool lm_ok = j < (uint32_t)A.K;
-    const uint64_t o = (uint64_t)j * A.M + k;
-    const int cam = (lm_ok && k < A.M) ? A.obs_cam[o] : -1;
-    const int slot = cam >= 0 ? A.free_slot[cam] : -1;
-    double v[3] = {0.0, 0.0, 0.0};
-    if (slot >= 0) {
-        const double *Y = A.obs_rec + (uint64_t)A.rec_pos[o] * kBaRecStride + kRY;
-        const double *dc = A.dc + 6 * slot;
-        for (int i = 0; i < 6; ++i)
-            for (int u = 0; u < 3; ++u) v[u] = fma(Y[3 * i + u], dc[i], v[u]);
+    __syncthreads();
+    // tile (ti, tj) of what is left after block kb (ti, tj >= 1 past it)
+    const auto trail = [&](int kb, int ti, int tj) {
+        const int k0 = kb * kTile, i0 = k0 + kTile * ti, j0 = k0 + kTile * tj;
+        const double *Li = M + (size_t)(i0 + li) * P + k0 + lk, *Lj = M + (size_t)(j0 + li) * P + k0 + lk;
+        double *C = M + (size_t)(i0 + lk) * P + j0 + li;   // rows 4 apart per register
+        v4d acc, ac2 = {0.0, 0.0, 0.0, 0.0};
+        double x[4], y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = Li[4 * q] * nd[k0 + 4 * q + lk], y[q] = Lj[4 * q], acc[q] = C[(size_t)(4 * q) * P];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {   // two chains of two
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[q], y[q], acc, 0, 0, 0);
+            ac2 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[2 + q], y[2 + q], ac2, 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) C[(size_t)(4 * q) * P] = acc[q] + ac2[q];
+    };
+    for (int kb = 0; kb < NB; ++kb) {
+        const int k0 = kb * kTile, k1 = k0 + kTile;
+        const int rows = D + 1 - k1;   // panel rows below the block (the right-hand side's included)
+        const bool mine = wave * 64 < (rows > 1 ? rows : 1);   // (at most waves 0 and 1: D <= 121)
+        if (wave >= 2 && kb > 0) {
+            // the tiles the previous block left for now
+            const int T = NB - kb, left = T * (T - 1) / 2;
+            for (int t = wave - 2; t < left; t += kSolveThreads / 64 - 2) {
+                int ti = 0, tj = t;
+                while (tj > ti) tj -= ++ti;
+                trail(kb - 1, ti + 2, tj + 2);
+            }
+        }
+        double a[kTile];
+        if (mine) {
+            const int r = k1 + wave * 64 + lane;
+            const bool in = r <= D;
+            const double *top = M + (size_t)(k0 + li) * P + k0, *row = M + (size_t)(in ? r : k0) * P + k0;
+            double x[kTile], md = 0.0;
+#pragma unroll
+            for (int c = 0; c < kTile; c += 2) {
+                const double2 w = *reinterpret_cast<const double2 *>(top + c), v = *reinterpret_cast<const double2 *>(row + c);
+                a[c] = w.x, a[c + 1] = w.y;
+                x[c] = v.x, x[c + 1] = v.y;
+            }
+            // (columns from D on only change entries nothing reads)
+            double inv = recip(row_lane<0>(a[0]));
+            static_for<0, kTile>([&](auto J) {
+                constexpr int j = decltype(J)::value;
+                const double na = -(a[j] * inv), nx = -(x[j] * inv);
+                if (li == j) md = -a[j];
+                // the next pivot first, then its reciprocal's chain with the
+                // other columns' updates between its steps (the compiler keeps
+                // the order it is given across the barriers)
+                double y = 0.0, e = 0.0, d = 1.0;
+                if constexpr (j + 1 < kTile) {
+                    const double s = row_lane<j + 1>(a[j]);
+                    a[j + 1] = fma(s, na, a[j + 1]);
+                    d = row_lane<j + 1>(a[j + 1]);
+                    y = __builtin_amdgcn_rcp(d);
+                    x[j + 1] = fma(s, nx, x[j + 1]);
+                }
+                static_for<0, 7>([&](auto U) {
+                    constexpr int u = decltype(U)::value, c = j + 2 + 2 * u;
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (c < kTile) {
+                        const double s = row_lane<c>(a[j]);
+                        a[c] = fma(s, na, a[c]);
+                        x[c] = fma(s, nx, x[c]);
+                    }
+                    if constexpr (c + 1 < kTile) {
+                        const double s = row_lane<c + 1>(a[j]);
+                        a[c + 1] = fma(s, na, a[c + 1]);
+                        x[c + 1] = fma(s, nx, x[c + 1]);
+                    }
+                    if constexpr (j + 1 < kTile && (u == 0 || u == 2)) e = fma(-d, y, 1.0);
+                    if constexpr (j + 1 < kTile && (u == 1 || u == 3)) y = fma(y, e, y);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                a[j] = na, x[j] = nx;
+                inv = y;
+            });
+            // (computed here by every lane: sunk into the branch below, the
+            // panel's updates would keep all the broadcasts alive)
+#pragma unroll
+            for (int c = 0; c < kTile; ++c) asm volatile("" : "+v"(x[c]));
+            if (in) {
+#pragma unroll
+                for (int c = 0; c < kTile; c += 2)
+                    *reinterpret_cast<double2 *>(M + (size_t)r * P + k0 + c) = make_double2(x[c], x[c + 1]);
+            }
+            if (wave == 0 && lane < kTile) nd[k0 + lane] = md;
+        }
+        __syncthreads();
+        // the diagonal tile, which every panel wave has read by now
+        if (wave == 0 && lane < kTile) {
+#pragma unroll
+            for (int c = 0; c < kTile; c += 2)
+                *reinterpret_cast<double2 *>(M + (size_t)(k0 + lane) * P + k0 + c) = make_double2(a[c], a[c + 1]);
+        }
+        if (wave < NB - 1 - kb) trail(kb, wave + 1, 1);   // the next block's column of tiles
+        __syncthreads();
     }
-    for (int u = 0; u < 3; ++u) v[u] = group_sum(v[u]);
-    if (lm_ok && k == 0) {
-        const double *L = A.lm_rec + (uint64_t)j * kBaLmStride;
-        for (int u = 0; u < 3; ++u) A.landmarks[3 * j + u] -= L[kLHg + u] + v[u] + L[kLYf + u] * df;
+    // L^T dc = -w by wave 0, from the last block up; lane owns entries lane
+    // and lane + 64.  A block's 16 entries are solved in every row of 16 lanes
+    // alike (its rows of -L, a column per lane, and DPP broadcasts), then
+    // folded into the entries above it.
+    if (wave != 0) return;
+    double T[12];   // the pose lane a < F retracts: its load overlaps the solve
+    if (lane < A.F)
+        for (int q = 0; q < 12; ++q) T[q] = A.poses[12 * (uint64_t)A.slot_cam[lane] + q];
+    const int c0 = lane, c1 = lane + 64, a0 = c0 < N ? c0 : N - 1, a1 = c1 < N ? c1 : N - 1;
+    double y0 = M[(size_t)D * P + a0], y1 = M[(size_t)D * P + a1];
+    if (c0 < D) dcs[c0] = y0;
+    if (c1 < D) dcs[c1] = y1;
+    double lt[kTile];
+#pragma unroll
+    for (int u = 0; u < kTile; ++u) lt[u] = M[(size_t)((NB - 1) * kTile + u) * P + (NB - 1) * kTile + li];
+    for (int kb = NB - 1; kb >= 0; --kb) {
+        const int k0 = kb * kTile;
+        const bool valid = k0 + li < D, two = k0 > 64;   // (entries 64.. only matter to blocks beyond them)
+        double m0[kTile], m1[kTile];
+        double x = valid ? dcs[k0 + li] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kTile; ++u) m0[u] = M[(size_t)(k0 + u) * P + a0];
+        if (two)
+#pragma unroll
+            for (int u = 0; u < kTile; ++u) m1[u] = M[(size_t)(k0 + u) * P + a1];
+#pragma unroll
+        for (int u = 1; u < kTile; ++u) lt[u] = (valid & (li < u)) ? lt[u] : 0.0;   // (entries beyond may be anything)
+        static_for<0, kTile - 1>([&](auto U) {
+            constexpr int u = kTile - 1 - decltype(U)::value;
+            x = fma(lt[u], row_lane<u>(x), x);
+        });
+        if (lane < kTile && valid) dcs[k0 + lane] = x;
+        if (kb > 0)   // the next block's, ahead of its use
+#pragma unroll
+            for (int u = 0; u < kTile; ++u) lt[u] = M[(size_t)(k0 - kTile + u) * P + k0 - kTile + li];
+        double s0 = 0.0;
+        static_for<0, kTile / 2>([&](auto U) {
+            constexpr int u = 2 * decltype(U)::value;
+            y0 = fma(m0[u], row_lane<u>(x), y0);
+            s0 = fma(m0[u + 1], row_lane<u + 1>(x), s0);
+        });
+        y0 += s0;   // (of use to the entries above the block only)
+        if (c0 < k0) dcs[c0] = y0;
+        if (two) {
+            double s1 = 0.0;
+            static_for<0, kTile / 2>([&](auto U) {
+                constexpr int u = 2 * decltype(U)::value;
+                y1 = fma(m1[u], row_lane<u>(x), y1);
+                s1 = fma(m1[u + 1], row_lane<u + 1>(x), s1);
+            });
+            y1 += s1;
+            if (c1 < k0) dcs[c1] = y1;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    if (c0 < D) A.dc[c0] = dcs[c0];
+    if (c1 < D) A.dc[c1] = dcs[c1];
+    // T_a <- exp(dc_a) T_a and f += df; the poses and the focal length before
+    // the step stay in pose_old for the landmark update
+    if (lane < A.F) {
+        double xi[6], Rm[3][3], tv[3];
+        for (int q = 0; q < 6; ++q) xi[q] = dcs[6 * lane + q];
+        se3_exp(xi, Rm, tv);
+        double *now = A.poses + 12 * (uint64_t)A.slot_cam[lane], *old = A.pose_old + 12 * lane;
+        for (int q = 0; q < 12; ++q) old[q] = T[q];
+        for (int r = 0; r < 3; ++r)
+            for (int q = 0; q < 4; ++q)
+                now[4 * r + q] = Rm[r][0] * T[q] + Rm[r][1] * T[4 + q] + Rm[r][2] * T[8 + q] + (q == 3 ? tv[r] : 0.0);
+    }
+    if (lane == 63) {
+        const double f = A.focal[0];
+        A.pose_old[12 * (uint64_t)A.F] = f;
+        A.focal[0] = f + dcs[D - 1];
     }
 }
 
 __global__ void __launch_bounds__(kBaThreads) k_ba_cost(BaArgs A, int iter) {
-    __shared__ double red[5];
+    __shared__ double red[5 * 4];
+    const int nb = (A.K + kLmPerBlock - 1) / kLmPerBlock;
     double acc[1] = {0.0};
-    for (int j0 = threadIdx.x; j0 < A.K; j0 += 8 * kBaThreads) {   // 8 loads in flight per thread
-        double v[8];
+    for (int i0 = threadIdx.x; i0 < nb; i0 += 4 * kBaThreads) {   // 4 loads in flight per thread
+        double v[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int j = j0 + u * kBaThreads;
-            v[u] = j < A.K ? A.lm_rec[(uint64_t)j * kBaLmStride + kLCost] : 0.0;
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kBaThreads;
+            v[u] = i < nb ? A.lm_sum[4 * (uint64_t)i + 3] : 0.0;
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[0] += v[u];
+        for (int u = 0; u < 4; ++u) acc[0] += v[u];
     }
-    const double *sum = block_sum(acc, red);
+    const double *sum = block_sum<kBaThreads / 64>(acc, red);
     if (threadIdx.x == 0 && A.costs) A.costs[iter] = sum[0];
 }
 
 }  // namespace
 
-size_t ba_solve_lds_bytes(int D) { return ((size_t)D * (D | 1) + 10 * (size_t)D) * sizeof(double); }
-
-size_t ba_lds_bytes(int D) { return ba_solve_lds_bytes(D); }
+size_t ba_lds_bytes(int D) {
+    const size_t N = (size_t)(D + 1 + kTile - 1) / kTile * kTile;
+    return (N * (N + 2) + 2 * N) * sizeof(double);
+}
 
 hipError_t ba_allow_lds(int D) {
     return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ba_solve), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)ba_solve_lds_bytes(D));
+                               (int)ba_lds_bytes(D));
 }
 
+size_t ba_lm_blocks(int K) { return ((size_t)K + kLmPerBlock - 1) / kLmPerBlock; }
+
 void launch_ba_iterations(const BaArgs &A, int iterations, hipStream_t st) {
-    const unsigned lm_blocks = (unsigned)(((uint64_t)A.K * kLanesPerLm + kBaThreads - 1) / kBaThreads);
-    const size_t solve_lds = ba_solve_lds_bytes(A.D);
+    const unsigned lm_blocks = (unsigned)ba_lm_blocks(A.K);
+    const size_t solve_lds = ba_lds_bytes(A.D);
     for (int it = 0; it < iterations; ++it) {
-        hipLaunchKernelGGL(k_ba_landmark, dim3(lm_blocks), dim3(kBaThreads), 0, st, A, 0);
-        hipLaunchKernelGGL(k_ba_assemble, dim3((unsigned)A.nblk + 1, kBaAsmSplit), dim3(kBaThreads), 0, st, A);
+        hipLaunchKernelGGL(k_ba_landmark, dim3(lm_blocks), dim3(kBaThreads), 0, st, A, it > 0 ? kUpdate : 0);
+        hipLaunchKernelGGL(k_ba_assemble, dim3((unsigned)A.nblk + 1, kBaAsmSplit), dim3(kAsmThreads), 0, st, A);
         hipLaunchKernelGGL(k_ba_solve, dim3(1), dim3(kSolveThreads), solve_lds, st, A, it);
-        hipLaunchKernelGGL(k_ba_update, dim3(lm_blocks + 1), dim3(kBaThreads), 0, st, A);
     }
-    hipLaunchKernelGGL(k_ba_landmark, dim3(lm_blocks), dim3(kBaThreads), 0, st, A, 1);
+    hipLaunchKernelGGL(k_ba_landmark, dim3(lm_blocks), dim3(kBaThreads), 0, st, A, (iterations > 0 ? kUpdate : 0) | kCostOnly);
     hipLaunchKernelGGL(k_ba_cost, dim3(1), dim3(kBaThreads), 0, st, A, iterations);
 }
 
