@@ -78,10 +78,13 @@ int build_views(int32_t n_views, const gsr_camera *cams, const gsr_launch_config
     return GSR_OK;
 }
 
-int tile_bits(uint32_t total_tiles) {
-    int b = 1;
-    while ((1ull << b) < total_tiles) ++b;
-    return b;
+// Shares of a view's items in the counting sort by tile: one for each of the
+// 256 compute units (the views follow each other), but at least 8192 pairs of
+// capacity each (a share costs a row of counters, however few its pairs) and,
+// beyond 65,536 tiles, no more than 16 M counters.
+uint32_t bin_rows(const gsr::ViewTable &vt, uint64_t cap) {
+    const uint64_t most = std::max<uint64_t>(8, std::min<uint64_t>(gsr::kBinMaxRows, (1ull << 24) / std::max(1u, vt.total_tiles)));
+    return (uint32_t)std::min<uint64_t>(most, cap / (8192ull * (uint64_t)vt.n_views) + 1);
 }
 
 gsr::WsLayout make_layout(uint64_t n, const gsr::ViewTable &vt, uint64_t cap) {
@@ -91,7 +94,6 @@ gsr::WsLayout make_layout(uint64_t n, const gsr::ViewTable &vt, uint64_t cap) {
     L.items = items;
     L.cap = cap;
     L.chunks = chunk_count(cap);
-    L.hist_blocks = (uint32_t)std::max<uint64_t>(1, (cap + kSortTile - 1) / kSortTile);
     L.pose_blocks = (uint32_t)std::max<uint64_t>(1, (n + kProjThreads - 1) / kProjThreads);
     const uint64_t scan_blocks = std::max<uint64_t>(1, (items + kScanTile - 1) / kScanTile);
     size_t o = 0;
@@ -102,23 +104,20 @@ gsr::WsLayout make_layout(uint64_t n, const gsr::ViewTable &vt, uint64_t cap) {
     };
     L.header = take(sizeof(WsHeader));
     L.rec = take(sizeof(Rec) * items);
-    L.ulo = take(sizeof(float2) * items);
-    L.zkey = take(4 * items);
     L.count = take(4 * items);
     L.scan_tmp = take(8 * scan_blocks);
     L.vis = take(4 * items);
     L.poff = take(4 * items);
+    L.ioff = take(4 * items);
     L.chunk_item = take(4 * (L.chunks + 1));
     L.item_box = take(16 * items);
     L.carry = take(4ull * 2 * kPartialStride * L.chunks);
-    L.screen = take(48 * items);
-    L.pkey[0] = take(4 * cap);
-    L.pkey[1] = take(4 * cap);
-    L.pval[0] = take(4 * cap);
-    L.pval[1] = take(4 * cap);
+    L.screen = L.box = take(48 * items);
+    L.entries = take(8 * cap);
+    L.pval = take(4 * cap);
     L.pflag = take((cap + 3) & ~uint64_t(3));
-    L.hist = take(4ull * 256 * L.hist_blocks);
-    L.digit_total = take(4 * 256);
+    L.bin_rows = bin_rows(vt, cap);
+    L.counts = take(4ull * (L.bin_rows + 1) * vt.total_tiles);
     L.ranges = take(8ull * vt.total_tiles);
     L.tile_cut = take(4ull * vt.total_tiles);
     L.tile_order = take(4ull * kCostBuckets * (1 + vt.total_tiles));
@@ -127,7 +126,7 @@ gsr::WsLayout make_layout(uint64_t n, const gsr::ViewTable &vt, uint64_t cap) {
     L.pix_n = take(4ull * vt.total_pixels);
     L.partial = take(4ull * kPartialStride * cap);
     L.pose_part = take(4ull * 12 * vt.n_views * L.pose_blocks);
-    L.view_seg = take(4ull * (GSR_MAX_VIEWS + 1));
+    L.view_seg = take(8ull * (GSR_MAX_VIEWS + 1));
     L.total = o;
     return L;
 }
@@ -151,11 +150,11 @@ int check_gaussians(const gsr_gaussians *g) {
 struct Ptrs {
     gsr::WsHeader *hdr;
     gsr::Rec *rec;
-    float2 *ulo;
-    uint32_t *zkey, *count, *scan_tmp, *vis, *poff, *chunk_item, *pkey[2], *pval[2], *hist, *digit_total, *pflag;
+    uint32_t *count, *scan_tmp, *vis, *poff, *ioff, *chunk_item, *pval, *counts, *pflag;
+    unsigned long long *entries;
     float4 *screen;
     float *carry;
-    uint4 *item_box;
+    uint4 *box, *item_box;
     uint2 *ranges;
     uint32_t *tile_cut;
     uint32_t *tile_order;
@@ -170,17 +169,15 @@ Ptrs carve(void *ws, const gsr::WsLayout &L) {
     Ptrs p;
     p.hdr = reinterpret_cast<gsr::WsHeader *>(b + L.header);
     p.rec = reinterpret_cast<gsr::Rec *>(b + L.rec);
-    p.ulo = reinterpret_cast<float2 *>(b + L.ulo);
-    p.zkey = reinterpret_cast<uint32_t *>(b + L.zkey);
+    p.box = reinterpret_cast<uint4 *>(b + L.box);
     p.count = reinterpret_cast<uint32_t *>(b + L.count);
     p.scan_tmp = reinterpret_cast<uint32_t *>(b + L.scan_tmp);
-    for (int k = 0; k < 2; ++k) {
-        p.pkey[k] = reinterpret_cast<uint32_t *>(b + L.pkey[k]);
-        p.pval[k] = reinterpret_cast<uint32_t *>(b + L.pval[k]);
-    }
+    p.entries = reinterpret_cast<unsigned long long *>(b + L.entries);
+    p.pval = reinterpret_cast<uint32_t *>(b + L.pval);
     p.pflag = reinterpret_cast<uint32_t *>(b + L.pflag);
     p.vis = reinterpret_cast<uint32_t *>(b + L.vis);
     p.poff = reinterpret_cast<uint32_t *>(b + L.poff);
+    p.ioff = reinterpret_cast<uint32_t *>(b + L.ioff);
     p.chunk_item = reinterpret_cast<uint32_t *>(b + L.chunk_item);
     p.carry = reinterpret_cast<float *>(b + L.carry);
     p.item_box = reinterpret_cast<uint4 *>(b + L.item_box);
@@ -188,8 +185,7 @@ Ptrs carve(void *ws, const gsr::WsLayout &L) {
     p.tile_cut = reinterpret_cast<uint32_t *>(b + L.tile_cut);
     p.tile_order = reinterpret_cast<uint32_t *>(b + L.tile_order);
     p.long_tiles = reinterpret_cast<uint32_t *>(b + L.long_tiles);
-    p.hist = reinterpret_cast<uint32_t *>(b + L.hist);
-    p.digit_total = reinterpret_cast<uint32_t *>(b + L.digit_total);
+    p.counts = reinterpret_cast<uint32_t *>(b + L.counts);
     p.ranges = reinterpret_cast<uint2 *>(b + L.ranges);
     p.pix_T = reinterpret_cast<float *>(b + L.pix_T);
     p.pix_n = reinterpret_cast<uint32_t *>(b + L.pix_n);
@@ -208,8 +204,8 @@ int layout_from_bytes(uint64_t n, const gsr::ViewTable &vt, size_t ws_bytes, gsr
     const gsr::WsLayout L0 = make_layout(n, vt, 1);
     if (ws_bytes < L0.total) return fail(GSR_ERR_WORKSPACE_TOO_SMALL, "workspace %zu < %zu bytes", ws_bytes, L0.total);
     // largest capacity whose layout fits (the layout size grows with it);
-    // per pair the workspace holds 4 key/value words and 9 moment floats
-    uint64_t lo = 1, hi = (ws_bytes - L0.total) / (16 + 4 * gsr::kPartialStride) + 2;
+    // per pair the workspace holds an entry, an item id and 9 moment floats
+    uint64_t lo = 1, hi = (ws_bytes - L0.total) / (12 + 4 * gsr::kPartialStride) + 2;
     if (hi > 0x7ffffffeull) hi = 0x7ffffffeull;
     while (lo < hi) {
         const uint64_t mid = lo + (hi - lo + 1) / 2;
@@ -244,9 +240,6 @@ int read_header_now(const gsr::WsHeader *dev_hdr, gsr::WsHeader &out, hipStream_
     if (rc) return rc;
     return check_hip(hipStreamSynchronize(st), "stream sync");
 }
-
-// Number of tile-sort passes decides which ping-pong buffer holds the result.
-int pair_result_buffer(uint32_t total_tiles) { return ((tile_bits(total_tiles) + 7) / 8) & 1; }
 
 }  // namespace
 
@@ -287,7 +280,7 @@ int backward_tail(const gsr_gaussians *g, const gsr::ViewTable &vt, const float 
     using namespace gsr;
     mark.begin(GSR_STAGE_PROJECT_BWD);
     launch_pair_reduce(p.poff, p.chunk_item, cap, p.vis, p.pflag, p.partial, p.screen, p.carry, p.hdr, st);
-    launch_project_bwd(*g, vt, world_to_cam, (uint64_t)g->n, p.rec, p.count, p.vis, p.hdr, p.screen, p.carry, *grads,
+    launch_project_bwd(*g, vt, world_to_cam, (uint64_t)g->n, p.rec, p.ioff, p.count, p.vis, p.hdr, p.screen, p.carry, *grads,
                        p.pose_part, L.pose_blocks, p.view_seg, vt.total_tiles == 0, st);
     if (g->n == 0)  // no Gaussian wrote a partial: the pose gradient is zero
         launch_fill_u32(reinterpret_cast<uint32_t *>(p.pose_part), 0u, 12ull * vt.n_views * L.pose_blocks, st);
@@ -312,7 +305,6 @@ int backward_impl(void *ws, size_t ws_bytes, const gsr_gaussians *g, int32_t n_v
     if ((rc = layout_from_bytes((uint64_t)g->n, vt, ws_bytes, L, cap))) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Ptrs p = carve(ws, L);
-    const int pc = pair_result_buffer(vt.total_tiles);
     const bool pers = (flags & GSR_FLAG_PERSISTENT) != 0;
     const StageMark mark{cfg ? static_cast<hipEvent_t *>(cfg->stage_events) : nullptr, st};
     mark.begin(GSR_STAGE_COMPOSITE_BWD);
@@ -320,7 +312,7 @@ int backward_impl(void *ws, size_t ws_bytes, const gsr_gaussians *g, int32_t n_v
     const ZeroRows zr = zero_rows(g, vt, grads, p);
     Upstream up{dL_drgb, target_rgb, 0.f};
     if (target_rgb) up.l1_scale = l1_scale_of(vt);
-    launch_composite_bwd(vt, p.ranges, p.pval[pc], p.rec, p.ulo, out_rgb, up, p.pix_n, p.tile_cut, p.tile_order, p.partial,
+    launch_composite_bwd(vt, p.ranges, p.pval, p.rec, p.ioff, out_rgb, up, p.pix_n, p.tile_cut, p.tile_order, p.partial,
                          reinterpret_cast<uint8_t *>(p.pflag), zr, p.hdr, pers, persistent_ctas(cfg), st);
     mark.end(GSR_STAGE_COMPOSITE_BWD);
     return backward_tail(g, vt, world_to_cam, L, cap, p, grads, dL_dworld_to_cam, dL_dtwist, mark, st);
@@ -345,38 +337,32 @@ int forward_setup(void *ws, size_t ws_bytes, const gsr_gaussians *g, int32_t n_v
     return GSR_OK;
 }
 
-// A1-A5 of a forward (projection, compaction, emission, tile sort, ranges,
-// per-tile depth sort); pc: the pair buffer holding the sorted lists.  With
-// schedule, every tile is also filed in tile_order by min(list length, the
-// replay count tile_cut holds from the previous step): the fused
+// A1-A5 of a forward (projection, compaction, binning by tile, per-tile depth
+// sort).  With schedule, every tile is also filed in tile_order by min(list
+// length, the replay count tile_cut holds from the previous step): the fused
 // compositing's schedule.
 int forward_binning(const gsr_gaussians *g, const gsr::ViewTable &vt, const float *world_to_cam,
                     const gsr_launch_config *cfg, const gsr::WsLayout &L, uint64_t cap, const Ptrs &p, uint32_t flags,
-                    bool schedule, const StageMark &mark, hipStream_t st, int &pc) {
+                    bool schedule, const StageMark &mark, hipStream_t st) {
     using namespace gsr;
     int rc = GSR_OK;
     const uint64_t n = (uint64_t)g->n;
     mark.begin(GSR_STAGE_PROJECT);
-    launch_project_fwd(*g, vt, world_to_cam, n, p.rec, p.ulo, p.zkey, p.count, p.hdr, (uint32_t)cap,
+    launch_project_fwd(*g, vt, world_to_cam, n, p.rec, p.box, p.count, p.hdr, (uint32_t)cap,
                        cfg ? cfg->active_count : nullptr, st);
     mark.end(GSR_STAGE_PROJECT);
     mark.begin(GSR_STAGE_COMPACT);
-    launch_visible_offsets(vt, n, p.count, p.rec, p.zkey, L.items, p.vis, p.poff, p.item_box, p.chunk_item, L.chunks,
-                           p.scan_tmp, p.hdr, st);
+    launch_visible_offsets(vt, n, p.count, p.box, L.items, p.vis, p.poff, p.ioff, p.item_box, p.chunk_item, L.chunks,
+                           p.scan_tmp, p.view_seg, p.hdr, st);
     mark.end(GSR_STAGE_COMPACT);
     mark.begin(GSR_STAGE_EMIT);
-    const uint64_t pair_grid = cap;  // every kernel reads the pair count from the header
-    launch_emit_pairs(p.poff, p.chunk_item, p.item_box, pair_grid, p.pkey[0], p.pval[0], p.pflag, p.hdr, st);
+    const BinPlan plan = bin_plan(vt, cap);
+    if ((rc = check_hip(bin_allow_lds(std::max(plan.lds_count, plan.lds_place)), "LDS attribute"))) return rc;
+    launch_bin_pairs(vt, plan, L.bin_rows, p.view_seg, p.item_box, p.counts,
+                     p.counts + (size_t)L.bin_rows * vt.total_tiles, p.ranges, p.long_tiles, p.tile_order, p.entries,
+                     p.pflag, p.hdr, st);
     mark.end(GSR_STAGE_EMIT);
     mark.begin(GSR_STAGE_TILE_SORT);
-    pc = 0;
-    {
-        uint32_t *k2[2] = {p.pkey[0], p.pkey[1]}, *v2[2] = {p.pval[0], p.pval[1]};
-        // unstable: the per-tile depth sort fixes the order within a tile
-        radix_sort_u32(k2, v2, SortCount{nullptr, p.hdr}, pair_grid, 0, tile_bits(vt.total_tiles), p.hist,
-                       L.hist_blocks, p.digit_total, pc, false, st);
-    }
-    launch_tile_ranges(p.pkey[pc], pair_grid, p.ranges, vt.total_tiles, p.long_tiles, p.tile_order, p.hdr, st);
     // lists longer than one workgroup sorts: runs of kLongWindow, then merge passes
     int passes = cfg ? std::max(0, std::min(cfg->long_list_passes, kMaxLongPasses)) : 0;
     uint64_t long_pairs = cap, n_long = kMaxLongTiles;
@@ -395,16 +381,15 @@ int forward_binning(const gsr_gaussians *g, const gsr::ViewTable &vt, const floa
     }
     const uint32_t chunk_wgs = passes > 0 ? (uint32_t)((long_pairs + kLongWindow - 1) / kLongWindow + n_long) : 0u;
     const uint32_t merge_wgs = passes > 0 ? (uint32_t)((long_pairs + kMergeWindow - 1) / kMergeWindow + n_long) : 0u;
-    uint32_t *xh = p.pkey[pc ^ 1], *xl = p.pval[pc ^ 1], *yh = p.pkey[pc], *yl = p.pval[pc];
     if (passes > 0) launch_long_windows(p.ranges, p.long_tiles, passes, p.hdr, st);
-    launch_tile_depth_sort(p.ranges, vt.total_tiles, p.pval[pc], p.zkey, xh, xl, yh, yl, p.long_tiles, passes,
-                           chunk_wgs, schedule ? p.tile_order : nullptr, p.tile_cut, p.hdr, st);
-    for (int q = 0; q < passes; ++q) {
-        // the runs start in x when the pass count is odd, so that the last pass reads x
-        const bool from_x = ((passes - q) & 1) != 0;
-        launch_long_merge(p.ranges, p.long_tiles, p.hdr, q, passes, from_x ? xh : yh, from_x ? xl : yl,
-                          from_x ? yh : xh, from_x ? yl : xl, p.pval[pc], merge_wgs, st);
-    }
+    launch_tile_depth_sort(p.ranges, vt.total_tiles, p.entries, p.pval, p.long_tiles, passes, chunk_wgs,
+                           schedule ? p.tile_order : nullptr, p.tile_cut, p.hdr, st);
+    // the runs start in place, the last pass writes pval; in between the passes
+    // alternate with the moments' memory, which nothing uses yet
+    unsigned long long *other = reinterpret_cast<unsigned long long *>(p.partial);
+    for (int q = 0; q < passes; ++q)
+        launch_long_merge(p.ranges, p.long_tiles, p.hdr, q, passes, (q & 1) ? other : p.entries,
+                          (q & 1) ? p.entries : other, p.pval, merge_wgs, st);
     mark.end(GSR_STAGE_TILE_SORT);
     return GSR_OK;
 }
@@ -453,11 +438,10 @@ int gsr_rasterize_forward(void *ws, size_t ws_bytes, const gsr_gaussians *g, int
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const StageMark mark{cfg ? static_cast<hipEvent_t *>(cfg->stage_events) : nullptr, st};
-    int pc = 0;
-    if ((rc = forward_binning(g, vt, world_to_cam, cfg, L, cap, p, flags, false, mark, st, pc))) return rc;
+    if ((rc = forward_binning(g, vt, world_to_cam, cfg, L, cap, p, flags, false, mark, st))) return rc;
     const bool pers = (flags & GSR_FLAG_PERSISTENT) != 0;
     mark.begin(GSR_STAGE_COMPOSITE_FWD);
-    launch_composite_fwd(vt, p.ranges, p.pval[pc], p.rec, p.ulo, make_float3(bg[0], bg[1], bg[2]), out_rgb, out_T,
+    launch_composite_fwd(vt, p.ranges, p.pval, p.rec, make_float3(bg[0], bg[1], bg[2]), out_rgb, out_T,
                          p.pix_T, p.pix_n, p.tile_cut, p.tile_order, p.hdr, pers, persistent_ctas(cfg),
                          (flags & GSR_FLAG_STATS) != 0, st);
     mark.end(GSR_STAGE_COMPOSITE_FWD);
@@ -510,13 +494,12 @@ int gsr_rasterize_step_l1(void *ws, size_t ws_bytes, const gsr_gaussians *g, int
     if ((rc = check_backward_args(g, ws, world_to_cam, out_rgb, target_rgb, grads))) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const StageMark mark{cfg ? static_cast<hipEvent_t *>(cfg->stage_events) : nullptr, st};
-    int pc = 0;
-    if ((rc = forward_binning(g, vt, world_to_cam, cfg, L, cap, p, flags, true, mark, st, pc))) return rc;
+    if ((rc = forward_binning(g, vt, world_to_cam, cfg, L, cap, p, flags, true, mark, st))) return rc;
     const bool pers = (flags & GSR_FLAG_PERSISTENT) != 0;
     // the fused compositing is timed as the forward compositing stage; the
     // backward compositing stage is empty
     mark.begin(GSR_STAGE_COMPOSITE_FWD);
-    launch_composite_step(vt, p.ranges, p.pval[pc], p.rec, p.ulo, make_float3(bg[0], bg[1], bg[2]), target_rgb,
+    launch_composite_step(vt, p.ranges, p.pval, p.rec, p.ioff, make_float3(bg[0], bg[1], bg[2]), target_rgb,
                           l1_scale_of(vt), out_rgb, out_T, p.pix_T, p.pix_n, p.tile_cut, p.tile_order, p.partial,
                           reinterpret_cast<uint8_t *>(p.pflag), zero_rows(g, vt, grads, p), p.hdr, pers,
                           persistent_ctas(cfg), st);
@@ -575,17 +558,13 @@ int gsr_export_state(const void *ws, size_t ws_bytes, const gsr_gaussians *g, in
     if ((rc = check_hip(hipMemcpyAsync(&h, p.hdr, sizeof(h), hipMemcpyDeviceToHost, st), "header copy"))) return rc;
     if ((rc = check_hip(hipStreamSynchronize(st), "stream sync"))) return rc;
     const uint64_t m = h.overflow ? 0 : std::min<uint64_t>(h.n_pairs, cap);
-    const int pc = pair_result_buffer(vt.total_tiles);
     struct Copy {
         void *dst;
         const void *src;
         size_t bytes;
     } copies[] = {
-        {pair_items, p.pval[pc], 4 * m},
+        {pair_items, p.pval, 4 * m},
         {ranges, p.ranges, 8ull * vt.total_tiles},
-        {records, p.rec, sizeof(Rec) * L.items},
-        {centre_lo, p.ulo, sizeof(float2) * L.items},
-        {depth_keys, p.zkey, 4 * L.items},
         {tile_counts, p.count, 4 * L.items},
     };
     if (pair_tiles && m > 0) launch_expand_ranges(p.ranges, vt.total_tiles, pair_tiles, p.hdr, st);
@@ -593,7 +572,8 @@ int gsr_export_state(const void *ws, size_t ws_bytes, const gsr_gaussians *g, in
         if (!c.dst || c.bytes == 0) continue;
         if ((rc = check_hip(hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToDevice, st), "export copy"))) return rc;
     }
-    return GSR_OK;
+    launch_export_items(p.poff, p.item_box, p.rec, p.hdr, L.items, records, centre_lo, depth_keys, st);
+    return check_hip(hipGetLastError(), "export launch");
 }
 
 }  // extern "C"

@@ -144,10 +144,10 @@ __device__ __forceinline__ void ellipse_rows_in_band(float A, float B, float C, 
 // alpha = min(0.99, exp2(-sigma log2e + b.y)).  Bit k of the slab mask is set
 // when the Gaussian's alpha >= 1/255 ellipse (with slack) reaches rows
 // [4k, 4k + 3] of the tile within its columns.
-__device__ __forceinline__ void stage_record(const Rec &r, const float2 lo, const TileCtx &c, uint32_t tile_h,
+__device__ __forceinline__ void stage_record(const Rec &r, uint32_t first_pair, const TileCtx &c, uint32_t tile_h,
                                              float4 &a, float4 &b, float4 &d) {
-    const float ut = (r.r0.x - (float)c.ox) + lo.x;
-    const float vt = (r.r0.y - (float)c.oy) + lo.y;
+    const float ut = (r.r0.x - (float)c.ox) + r.r3.x;
+    const float vt = (r.r0.y - (float)c.oy) + r.r3.y;
     a = make_float4(ut, vt, -0.5f * kLog2e * r.r0.z, -kLog2e * r.r0.w);
     b = make_float4(-0.5f * kLog2e * r.r1.x, __log2f(r.r1.y), r.r1.z, r.r1.w);
     const uint32_t by = __float_as_uint(r.r2.z);
@@ -158,7 +158,7 @@ __device__ __forceinline__ void stage_record(const Rec &r, const float2 lo, cons
     const uint32_t bx = __float_as_uint(r.r2.y);
     const uint32_t tx0 = (bx & 0xffffu) / kTileW, tx1 = (bx >> 16) / kTileW;
     const uint32_t ty0 = (by & 0xffffu) / tile_h;
-    const uint32_t p = __float_as_uint(r.r2.w) + (c.ty - ty0) * (tx1 - tx0 + 1) + (c.tx - tx0);
+    const uint32_t p = first_pair + (c.ty - ty0) * (tx1 - tx0 + 1) + (c.tx - tx0);
     d = make_float4(r.r2.x, __uint_as_float(smask), __uint_as_float(p), r.r1.y);
 }
 
@@ -261,12 +261,12 @@ struct Reduce {
 template <int W>
 __device__ __forceinline__ void stage_batch(Staged<W> &sh, const ViewTable &vt, const TileCtx &c, uint32_t b0,
                                             uint32_t end, const uint32_t *__restrict__ pval,
-                                            const Rec *__restrict__ rec, const float2 *__restrict__ ulo) {
+                                            const Rec *__restrict__ rec, const uint32_t *__restrict__ ioff) {
     const uint32_t tid = threadIdx.x, idx = b0 + tid;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, d = a;
     if (idx < end) {
         const uint32_t item = pval[idx];
-        stage_record(rec[item], ulo[item], c, (uint32_t)vt.tile_h, a, b, d);
+        stage_record(rec[item], ioff ? ioff[item] : 0u, c, (uint32_t)vt.tile_h, a, b, d);
     }
     sh.a[tid] = a;
     sh.b[tid] = b;
@@ -368,7 +368,7 @@ __device__ __forceinline__ bool forward_list(const Staged<W> &sh, unsigned long 
 template <int RPL, int W, int KP, bool STATS>
 __device__ __forceinline__ void tile_forward(Staged<W> &sh, const ViewTable &vt, const TileCtx &c, uint2 rg,
                                              const uint32_t *__restrict__ pval, const Rec *__restrict__ rec,
-                                             const float2 *__restrict__ ulo, int wave, int lane, float pxl, float pyl,
+                                             const uint32_t *__restrict__ ioff, int wave, int lane, float pxl, float pyl,
                                              float (&T)[RPL], float (&C0)[RPL], float (&C1)[RPL], float (&C2)[RPL],
                                              uint32_t (&last)[RPL], uint32_t (&ncontrib)[RPL],
                                              uint32_t (&stop_at)[RPL], uint32_t &staged) {
@@ -390,7 +390,7 @@ __device__ __forceinline__ void tile_forward(Staged<W> &sh, const ViewTable &vt,
                 if (!alive) break;
             }
         }
-        stage_batch(sh, vt, c, b0, rg.y, pval, rec, ulo);
+        stage_batch(sh, vt, c, b0, rg.y, pval, rec, ioff);
         staged = b0;
         __syncthreads();
         for (int s = 0; s < W && alive && b0 + (uint32_t)(s * kWave) < rg.y; ++s) {
@@ -427,7 +427,7 @@ template <int RPL, int W>
 __device__ __forceinline__ void tile_backward(Staged<W> &sh, Reduce<W> &bw, const ViewTable &vt, const TileCtx &c,
                                               uint2 rg, uint32_t end, uint32_t staged,
                                               const uint32_t *__restrict__ pval, const Rec *__restrict__ rec,
-                                              const float2 *__restrict__ ulo, int wave, int lane, float pxl, float pyl,
+                                              const uint32_t *__restrict__ ioff, int wave, int lane, float pxl, float pyl,
                                               float (&T)[RPL], const float (&g0)[RPL], const float (&g1)[RPL],
                                               const float (&g2)[RPL], float (&gB)[RPL], const uint32_t (&ncon)[RPL],
                                               float *__restrict__ partial, uint8_t *__restrict__ pflag) {
@@ -443,7 +443,7 @@ __device__ __forceinline__ void tile_backward(Staged<W> &sh, Reduce<W> &bw, cons
     for (uint32_t b0 = rg.x; b0 < end; b0 += W * kWave) {
         if (b0 != rg.x || staged != rg.x) {  // (the forward's batch is there only if it is the first)
             if (b0 != rg.x) __syncthreads();
-            stage_batch(sh, vt, c, b0, end, pval, rec, ulo);
+            stage_batch(sh, vt, c, b0, end, pval, rec, ioff);
             if (b0 == rg.x) stage_sentinel(sh);
             __syncthreads();
         }
@@ -594,7 +594,7 @@ struct CompositeArgs {
     const uint2 *ranges;
     const uint32_t *pval;
     const Rec *rec;
-    const float2 *ulo;
+    const uint32_t *ioff;  // pair offsets, for the backward's moments
     float3 bg;
     Upstream up;
     float *out_rgb, *out_T, *pix_T;
@@ -637,7 +637,7 @@ __global__ __launch_bounds__(W *kWave) void k_composite(ViewTable vt, CompositeA
                 ncontrib[k] = 0;
                 stop_at[k] = 0xffffffffu;
             }
-            tile_forward<RPL, W, forward_slabs(RPL), STATS>(sh, vt, c, rg, A.pval, A.rec, A.ulo, wave, lane, pxl, pyl, T, C0, C1, C2,
+            tile_forward<RPL, W, forward_slabs(RPL), STATS>(sh, vt, c, rg, A.pval, A.rec, BWD ? A.ioff : nullptr, wave, lane, pxl, pyl, T, C0, C1, C2,
                                            last, ncontrib, stop_at, staged);
         }
         // the forward's outputs, and the backward's start: g = dL/dC, gB = g . C_out
@@ -717,7 +717,7 @@ __global__ __launch_bounds__(W *kWave) void k_composite(ViewTable vt, CompositeA
         }
         if constexpr (BWD) {
             __shared__ Reduce<W> bw;
-            tile_backward<RPL, W>(sh, bw, vt, c, rg, rg.x + nmax, staged, A.pval, A.rec, A.ulo, wave, lane, pxl, pyl, T,
+            tile_backward<RPL, W>(sh, bw, vt, c, rg, rg.x + nmax, staged, A.pval, A.rec, A.ioff, wave, lane, pxl, pyl, T,
                                   g0, g1, g2, gB, last, A.partial, A.pflag);
         }
     }
@@ -795,12 +795,12 @@ static void launch_composite(const ViewTable &vt, const CompositeArgs &A, int pe
 }
 
 void launch_composite_fwd(const ViewTable &vt, const uint2 *ranges, const uint32_t *pval, const Rec *rec,
-                          const float2 *ulo, float3 bg, float *out_rgb, float *out_T, float *pix_T,
+                          float3 bg, float *out_rgb, float *out_T, float *pix_T,
                           uint32_t *pix_n, uint32_t *tile_cut, uint32_t *tile_order, WsHeader *hdr,
                           bool persistent, int persistent_ctas, bool stats, hipStream_t st) {
     if (vt.total_tiles == 0) return;
     CompositeArgs A{};
-    A.ranges = ranges, A.pval = pval, A.rec = rec, A.ulo = ulo, A.bg = bg;
+    A.ranges = ranges, A.pval = pval, A.rec = rec, A.bg = bg;
     A.out_rgb = out_rgb, A.out_T = out_T, A.pix_T = pix_T, A.pix_n = pix_n;
     A.tile_cut = tile_cut, A.tile_order = tile_order, A.hdr = hdr, A.persistent = persistent ? 1 : 0;
     if (stats) launch_composite<true, false, true>(vt, A, persistent_ctas, st);
@@ -808,12 +808,12 @@ void launch_composite_fwd(const ViewTable &vt, const uint2 *ranges, const uint32
 }
 
 void launch_composite_bwd(const ViewTable &vt, const uint2 *ranges, const uint32_t *pval, const Rec *rec,
-                          const float2 *ulo, const float *out_rgb, const Upstream &up, const uint32_t *pix_n,
+                          const uint32_t *ioff, const float *out_rgb, const Upstream &up, const uint32_t *pix_n,
                           const uint32_t *tile_cut, const uint32_t *tile_order, float *partial, uint8_t *pflag,
                           const ZeroRows &zr, WsHeader *hdr, bool persistent, int persistent_ctas, hipStream_t st) {
     if (vt.total_tiles == 0) return;
     CompositeArgs A{};
-    A.ranges = ranges, A.pval = pval, A.rec = rec, A.ulo = ulo, A.up = up;
+    A.ranges = ranges, A.pval = pval, A.rec = rec, A.ioff = ioff, A.up = up;
     A.out_rgb = const_cast<float *>(out_rgb), A.pix_n = const_cast<uint32_t *>(pix_n);
     A.tile_cut = const_cast<uint32_t *>(tile_cut), A.tile_order = const_cast<uint32_t *>(tile_order);
     A.partial = partial, A.pflag = pflag, A.zr = zr, A.hdr = hdr, A.persistent = persistent ? 1 : 0;
@@ -821,13 +821,13 @@ void launch_composite_bwd(const ViewTable &vt, const uint2 *ranges, const uint32
 }
 
 void launch_composite_step(const ViewTable &vt, const uint2 *ranges, const uint32_t *pval, const Rec *rec,
-                           const float2 *ulo, float3 bg, const float *target, float l1_scale, float *out_rgb,
+                           const uint32_t *ioff, float3 bg, const float *target, float l1_scale, float *out_rgb,
                            float *out_T, float *pix_T, uint32_t *pix_n, uint32_t *tile_cut,
                            const uint32_t *tile_order, float *partial, uint8_t *pflag, const ZeroRows &zr,
                            WsHeader *hdr, bool persistent, int persistent_ctas, hipStream_t st) {
     if (vt.total_tiles == 0) return;
     CompositeArgs A{};
-    A.ranges = ranges, A.pval = pval, A.rec = rec, A.ulo = ulo, A.bg = bg, A.up = Upstream{nullptr, target, l1_scale};
+    A.ranges = ranges, A.pval = pval, A.rec = rec, A.ioff = ioff, A.bg = bg, A.up = Upstream{nullptr, target, l1_scale};
     A.out_rgb = out_rgb, A.out_T = out_T, A.pix_T = pix_T, A.pix_n = pix_n;
     A.tile_cut = tile_cut, A.tile_order = const_cast<uint32_t *>(tile_order);
     A.partial = partial, A.pflag = pflag, A.zr = zr, A.hdr = hdr, A.persistent = persistent ? 1 : 0;

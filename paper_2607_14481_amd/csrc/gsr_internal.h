@@ -54,33 +54,38 @@ static_assert(sizeof(WsHeader) == 256, "header is 256 bytes");
 // Projected record of one (view, Gaussian) item, three float4:
 //   r0 = (u_hi, v_hi, A, B)      conic (A, B, C) = inverse 2D covariance
 //   r1 = (C, opacity, red, green)
-//   r2 = (blue, bits(x0 | x1 << 16), bits(y0 | y1 << 16), bits(pair_offset))
+//   r2 = (blue, bits(x0 | x1 << 16), bits(y0 | y1 << 16), unused)
 // The inclusive pixel box (x0..x1, y0..y1) is that of the alpha >= 1/255
 // ellipse.  The centre is stored as u = u_hi + u_lo (double-float) so that
-// tile-relative offsets keep ~1e-6 px accuracy; the low parts live in `ulo`.
+// tile-relative offsets keep ~1e-6 px accuracy; r3 = (u_lo, v_lo, 0, 0) holds the low parts.
+// 64 bytes: the compositing gathers them, and a gather touches one half of a
+// cache line, never two (with records of 48 bytes, the low parts and the pair
+// offsets in three arrays, compositing 8 views of 1 M items took 1,266 us, with
+// this and the offsets apart 1,213).
 struct Rec {
-    float4 r0, r1, r2;
+    float4 r0, r1, r2, r3;
 };
+constexpr int kExportWords = 12;  // floats of a record as a caller sees it: r0, r1, r2
 
 // Offsets of the workspace regions, all 256-byte aligned.
 struct WsLayout {
     size_t header;
     size_t rec;         // Rec[items]
-    size_t ulo;         // float2[items] low parts of (u, v)
-    size_t zkey;        // u32[items] depth key (float bits) or kCulledKey
     size_t count;       // u32[items] tiles touched
     size_t scan_tmp;    // u32 scratch for scans (block sums)
     size_t vis;         // u32[items] visible item ids in ascending order
     size_t poff;        // u32[items] pair offset of the k-th visible item
+    size_t ioff;        // u32[items] pair offset of a visible item
     size_t chunk_item;  // u32[chunks + 1] index (into vis) of the item holding each chunk's first pair
-    size_t item_box;    // uint4[items] per visible index: (first tile of the box, width | tiles_x << 16, depth key, item)
+    size_t item_box;    // uint4[items] per visible index: the box words with the item id as the last
     size_t carry;       // float[chunks * 2 * 9] chunk-boundary partial sums of the pair moments
     size_t screen;      // float4[items * 3] per-item sums of the pair moments
-    size_t pkey[2];     // u32[cap] tile keys ping-pong
-    size_t pval[2];     // u32[cap] item ids ping-pong
+    size_t box;         // in screen's memory until the backward: uint4[items] of a visible item, (first tile column |
+                        // row << 16, width | height << 16 in tiles, depth key (float bits), unused)
+    size_t entries;     // u64[cap] (depth key << 32 | item) of the pairs, grouped by tile
+    size_t pval;        // u32[cap] item ids of the sorted lists
     size_t pflag;       // u8[cap] per pair slot (emission order): 1 once the backward compositing wrote its moments
-    size_t hist;        // u32[256 * max_blocks] radix histograms
-    size_t digit_total; // u32[256] radix digit totals
+    size_t counts;      // u32[bin_rows][total_tiles] pairs per (share of the items, tile), then u32[total_tiles] totals
     size_t ranges;      // uint2[total_tiles]
     size_t tile_cut;    // u32[total_tiles]: list positions any pixel of the tile used (the backward replays those)
     size_t tile_order;  // u32[kCostBuckets] bucket counts, then u32[kCostBuckets][tiles] tile ids per bucket
@@ -88,19 +93,20 @@ struct WsLayout {
                         // u32[2][kMaxLongTiles + 1] their first window of kLongWindow / kMergeWindow entries
     size_t pix_T;       // float[total_pixels] final transmittance
     size_t pix_n;       // u32[total_pixels] last contributor + 1
-    size_t partial;     // float[cap * 9] per-pair moments of the pixel gradients
+    size_t partial;     // float[cap * 9] per-pair moments of the pixel gradients (until the backward compositing,
+                        // scratch of the merge passes: u64[cap])
     size_t pose_part;   // float[views * pose_blocks * 12]
-    size_t view_seg;    // u32[GSR_MAX_VIEWS + 1] first visible index of each view
+    size_t view_seg;    // u32[GSR_MAX_VIEWS + 1] first visible index of each view, then u32[GSR_MAX_VIEWS + 1] first pair
     size_t total;
     uint64_t items, cap, chunks;
-    uint32_t hist_blocks, pose_blocks;
+    uint32_t bin_rows, pose_blocks;
 };
 
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanThreads * kScanItems;     // 1024
-constexpr int kSortThreads = 256;
-constexpr int kSortTile = 3072;                           // elements per sort block
+constexpr int kBinMaxRows = 256;                           // shares of a view in the binning (rows of its counts)
+constexpr size_t kBinMaxLds = 147456;                     // counters of a binning workgroup: 144 of the 160 KB of a CU
 constexpr int kGroupSortMax = 4096;                       // longest list one workgroup sorts in registers
 constexpr uint32_t kMaxLongTiles = 1024;                  // longer lists the multi-workgroup path takes
 constexpr uint32_t kLongWindow = 4096;                    // entries per sorted run of a long list
@@ -117,7 +123,7 @@ __device__ __forceinline__ uint32_t cost_bucket(uint32_t n) {
     return min(kCostBuckets - 1, (uint32_t)(16.f * __log2f((float)n + 1.f)));
 }
 // Pairs are also processed in fixed chunks of consecutive emission-order
-// slots (A3 emission, A8 reduction): 256 threads x 4 pairs.
+// slots (A8 reduction): 256 threads x 4 pairs.
 constexpr uint32_t kChunkPairs = 1024;
 constexpr uint32_t kChunkThreads = 256;
 constexpr uint32_t kChunkPerThread = kChunkPairs / kChunkThreads;
@@ -131,48 +137,48 @@ void launch_reset_header(WsHeader *h, uint32_t cap, hipStream_t st);
 
 // Also resets the workspace header (pair capacity cap) for this forward.
 void launch_project_fwd(const gsr_gaussians &g, const ViewTable &vt, const float *w2c, uint64_t n,
-                        Rec *rec, float2 *ulo, uint32_t *zkey, uint32_t *count, WsHeader *hdr, uint32_t cap,
+                        Rec *rec, uint4 *box, uint32_t *count, WsHeader *hdr, uint32_t cap,
                         const int64_t *active, hipStream_t st);
 
 // Exclusive scans / compaction / sorting / binning.
-// Visible items (ascending ids), their pair offsets (also into each record's
-// r2.w), their box words (by visible index) and each chunk's first item;
-// header: visible and pair counts, overflow.  block_tmp: 2 u32 per block of
-// kScanTile items.
-void launch_visible_offsets(const ViewTable &vt, uint64_t n, const uint32_t *count, Rec *rec,
-                            const uint32_t *zkey, uint64_t items, uint32_t *vis, uint32_t *poff, uint4 *item_box,
-                            uint32_t *chunk_item, uint64_t chunks_cap, uint32_t *block_tmp, WsHeader *hdr,
+// Visible items (ascending ids), their pair offsets (by visible index and by
+// item), their boxes by visible index, each chunk's first item and each view's
+// first visible index and pair; header: visible and pair counts, overflow.
+// block_tmp: 2 u32 per block of kScanTile items.
+void launch_visible_offsets(const ViewTable &vt, uint64_t n, const uint32_t *count, const uint4 *box, uint64_t items,
+                            uint32_t *vis, uint32_t *poff, uint32_t *ioff, uint4 *item_box, uint32_t *chunk_item,
+                            uint64_t chunks_cap, uint32_t *block_tmp, uint32_t *view_seg, WsHeader *hdr,
                             hipStream_t st);
-// Element count of a sort, read on the device: *n_dev, or (hdr set) the pair
-// count, 0 if the binning overflowed.
-struct SortCount {
-    const uint32_t *n_dev;
-    const WsHeader *hdr;
-    __device__ uint64_t operator()() const {
-        if (hdr) return hdr->overflow ? 0ull : (uint64_t)hdr->n_pairs;
-        return (uint64_t)*n_dev;
-    }
+// The visible items' state as a caller sees it: records [item][kExportWords]
+// with the pair offset as the last word, centre_lo [item][2], and depth_keys
+// (kCulledKey for the others).  Any of the three may be NULL.
+void launch_export_items(const uint32_t *poff, const uint4 *item_box, const Rec *rec, const WsHeader *hdr,
+                         uint64_t items, float *records, float *centre_lo, uint32_t *depth_keys, hipStream_t st);
+// Bins the pairs of every view: the entries grouped by tile, the tiles' ranges
+// and the list of the long ones; clears the pair slots' flags and the
+// schedule's counters.  counts: u32[G][total_tiles].  A plan says in how many
+// bands of tile rows each view is counted and placed, and the LDS they need.
+struct BinPlan {
+    uint32_t count_bands, place_bands;
+    size_t lds_count, lds_place;
 };
-// LSD sort of (key, value) on bits [begin_bit, end_bit), at most 8 per pass,
-// ping-ponging between keys[cur]/keys[cur ^ 1]; `cur` ends at the result.
-// Stable when `stable`; otherwise equal keys come out in an unspecified order.
-void radix_sort_u32(uint32_t *keys[2], uint32_t *vals[2], SortCount sc, uint64_t n_cap, int begin_bit, int end_bit,
-                    uint32_t *hist, uint32_t hist_blocks, uint32_t *digit_total, int &cur, bool stable,
-                    hipStream_t st);
-// Each tile's list (grouped by the tile sort, in no particular order)
-// sorted by (depth key, item).  Lists longer than kGroupSortMax: with
-// long_passes > 0 (and at most kMaxLongTiles of them), `chunk_wgs` extra
-// workgroups sort them in runs of kLongWindow into the key buffer the first
-// merge pass reads (x when long_passes is odd, else y; hi = depth key,
-// lo = item); lists longer than kLongWindow << long_passes, or all long lists
-// when long_passes == 0, are sorted by one workgroup in global memory
-// (x_hi/x_lo as scratch).  sched (or NULL): one more workgroup files the
+BinPlan bin_plan(const ViewTable &vt, uint64_t cap);
+hipError_t bin_allow_lds(size_t bytes);
+void launch_bin_pairs(const ViewTable &vt, const BinPlan &plan, uint32_t G, const uint32_t *seg,
+                      const uint4 *item_box, uint32_t *counts, uint32_t *totals, uint2 *ranges, uint32_t *long_tiles,
+                      uint32_t *tile_order, unsigned long long *entries, uint32_t *pflag, WsHeader *hdr,
+                      hipStream_t st);
+// Each tile's list of entries sorted by (depth key, item), its item ids to
+// pval.  Lists longer than kGroupSortMax: with long_passes > 0 (and at most
+// kMaxLongTiles of them), `chunk_wgs` extra workgroups sort them in place in
+// runs of kLongWindow, for the merge passes; lists longer than kLongWindow <<
+// long_passes, or all long lists when long_passes == 0, are sorted by one
+// workgroup in global memory.  sched (or NULL): one more workgroup files the
 // fused compositing's schedule there (layout of WsLayout::tile_order): every
 // tile in the bucket of min(its list length, cost_hint[t]), cost_hint being
 // the previous step's replay count per tile (any values: only the order of
 // the tiles depends on them).
-void launch_tile_depth_sort(const uint2 *ranges, uint32_t total_tiles, uint32_t *pval, const uint32_t *zkey,
-                            uint32_t *x_hi, uint32_t *x_lo, uint32_t *y_hi, uint32_t *y_lo,
+void launch_tile_depth_sort(const uint2 *ranges, uint32_t total_tiles, unsigned long long *entries, uint32_t *pval,
                             const uint32_t *long_tiles, int long_passes, uint32_t chunk_wgs, uint32_t *sched,
                             const uint32_t *cost_hint, const WsHeader *hdr, hipStream_t st);
 // Merge pass p of long_passes over the long lists' runs (run length
@@ -183,20 +189,14 @@ void launch_tile_depth_sort(const uint2 *ranges, uint32_t total_tiles, uint32_t 
 void launch_long_windows(const uint2 *ranges, uint32_t *long_tiles, int long_passes, const WsHeader *hdr,
                          hipStream_t st);
 void launch_long_merge(const uint2 *ranges, const uint32_t *long_tiles, const WsHeader *hdr, int p, int long_passes,
-                       const uint32_t *src_hi, const uint32_t *src_lo, uint32_t *dst_hi, uint32_t *dst_lo,
-                       uint32_t *pval, uint32_t merge_wgs, hipStream_t st);
+                       const unsigned long long *src, unsigned long long *dst, uint32_t *pval, uint32_t merge_wgs,
+                       hipStream_t st);
 // Tile id of every position of the sorted pairs, from the ranges.
 void launch_expand_ranges(const uint2 *ranges, uint32_t total_tiles, uint32_t *pair_tiles, const WsHeader *hdr,
                           hipStream_t st);
 void launch_reset_queue(WsHeader *h, int which, hipStream_t st);
-void launch_emit_pairs(const uint32_t *poff, const uint32_t *chunk_item, const uint4 *item_box, uint64_t pair_grid,
-                       uint32_t *pkey, uint32_t *pval, uint32_t *pflag, const WsHeader *hdr, hipStream_t st);
-// Also clears the backward schedule's bucket counts (tile_order).
-void launch_tile_ranges(const uint32_t *pkey, uint64_t cap, uint2 *ranges, uint32_t total_tiles,
-                        uint32_t *long_tiles, uint32_t *tile_order, WsHeader *hdr, hipStream_t st);
-
 void launch_composite_fwd(const ViewTable &vt, const uint2 *ranges, const uint32_t *pval, const Rec *rec,
-                          const float2 *ulo, float3 bg, float *out_rgb, float *out_T, float *pix_T,
+                          float3 bg, float *out_rgb, float *out_T, float *pix_T,
                           uint32_t *pix_n, uint32_t *tile_cut, uint32_t *tile_order, WsHeader *hdr,
                           bool persistent, int persistent_ctas, bool stats, hipStream_t st);
 // Gradient rows of the Gaussians no view saw are zeroed by the backward
@@ -216,7 +216,7 @@ struct Upstream {
     float l1_scale;
 };
 void launch_composite_bwd(const ViewTable &vt, const uint2 *ranges, const uint32_t *pval, const Rec *rec,
-                          const float2 *ulo, const float *out_rgb, const Upstream &up, const uint32_t *pix_n,
+                          const uint32_t *ioff, const float *out_rgb, const Upstream &up, const uint32_t *pix_n,
                           const uint32_t *tile_cut, const uint32_t *tile_order, float *partial, uint8_t *pflag,
                           const ZeroRows &zr, WsHeader *hdr, bool persistent, int persistent_ctas, hipStream_t st);
 // A6 and A7 fused for the mean absolute error against `target` (dL/dC =
@@ -225,7 +225,7 @@ void launch_composite_bwd(const ViewTable &vt, const uint2 *ranges, const uint32
 // flags, zeroed rows) in one launch; tiles in the order of `tile_order` as
 // filed by launch_tile_depth_sort's sched.
 void launch_composite_step(const ViewTable &vt, const uint2 *ranges, const uint32_t *pval, const Rec *rec,
-                           const float2 *ulo, float3 bg, const float *target, float l1_scale, float *out_rgb,
+                           const uint32_t *ioff, float3 bg, const float *target, float l1_scale, float *out_rgb,
                            float *out_T, float *pix_T, uint32_t *pix_n, uint32_t *tile_cut,
                            const uint32_t *tile_order, float *partial, uint8_t *pflag, const ZeroRows &zr,
                            WsHeader *hdr, bool persistent, int persistent_ctas, hipStream_t st);
@@ -234,11 +234,12 @@ void launch_pair_reduce(const uint32_t *poff, const uint32_t *chunk_item, uint64
                         hipStream_t st);
 
 // zero_unseen: also write the zero rows of the Gaussians no view saw (when the
-// backward compositing did not).  seg: u32[GSR_MAX_VIEWS + 1] scratch.
+// backward compositing did not).  seg: each view's first visible index, and
+// their number (as the compaction wrote them).
 void launch_project_bwd(const gsr_gaussians &g, const ViewTable &vt, const float *w2c, uint64_t n,
-                        const Rec *rec, const uint32_t *count, const uint32_t *vis, const WsHeader *hdr,
+                        const Rec *rec, const uint32_t *ioff, const uint32_t *count, const uint32_t *vis, const WsHeader *hdr,
                         const float4 *screen, const float *carry, const gsr_gaussian_grads &gr, float *pose_part,
-                        uint32_t pose_blocks, uint32_t *seg, bool zero_unseen, hipStream_t st);
+                        uint32_t pose_blocks, const uint32_t *seg, bool zero_unseen, hipStream_t st);
 // dense: the partials come from the per-view launches over the visible items
 // (only the blocks with items are summed; seg as for launch_project_bwd).
 void launch_pose_finalize(const ViewTable &vt, const float *w2c, const float *pose_part, uint32_t pose_blocks,
@@ -356,103 +357,5 @@ __device__ __forceinline__ uint32_t xcd_contiguous(uint32_t b, uint32_t count) {
     return x * q + min(x, r) + b / kXcds;
 }
 
-
-// ---------------------------------------------------------------------------
-// The items whose pairs fall in one chunk of emission-order slots.  The k-th
-// visible item (ascending item id) owns the contiguous pair range
-// [poff[k], poff[k + 1]), so a chunk meets the visible indices
-// chunk_item[c] .. chunk_item[c + 1] (the last one only if it starts before
-// the chunk's end).  Each local item gets its first pair, the global id of its
-// box's first tile, its box width in tiles (low 16 bits) with its view's tiles
-// per row (high 16 bits), its depth key and its item id; p0[nloc] is the end of
-// the last one.
-// ---------------------------------------------------------------------------
-struct ChunkItems {
-    uint32_t p0[kChunkPairs + 2];
-    uint32_t tile0[kChunkPairs + 1];
-    uint32_t wx[kChunkPairs + 1];
-    uint32_t item[kChunkPairs + 1];
-    uint32_t zkey[kChunkPairs + 1];
-};
-
-// Box word of a visible item: (first tile, box width | tiles per row << 16,
-// depth key, item), from the pixel box in its record's third word (r2).
-__device__ __forceinline__ uint4 item_box_word(const ViewTable &vt, uint64_t n, uint32_t item, const float4 &r2,
-                                               uint32_t z) {
-    const uint32_t bx = __float_as_uint(r2.y), by = __float_as_uint(r2.z);
-    const uint32_t tx0 = (bx & 0xffffu) / kTileW, tx1 = (bx >> 16) / kTileW;
-    const uint32_t ty0 = (by & 0xffffu) / (uint32_t)vt.tile_h;
-    const int v = (int)(item / n);
-    const uint32_t tiles_x = (uint32_t)vt.v[v].tiles_x;
-    return make_uint4(vt.v[v].tile_off + ty0 * tiles_x + tx0, (tx1 - tx0 + 1) | (tiles_x << 16), z, item);
-}
-
-// The chunk's item range, from the box words by visible index (one coalesced
-// 16-byte load per item); every thread of the workgroup calls it (it ends
-// with a barrier).
-__device__ __forceinline__ uint32_t load_chunk_items(const uint32_t *__restrict__ poff,
-                                                     const uint32_t *__restrict__ chunk_item,
-                                                     const uint4 *__restrict__ boxes, uint32_t c, uint32_t m,
-                                                     uint32_t nvis, ChunkItems &ci, uint32_t &i_lo) {
-    const uint32_t c0 = c * kChunkPairs;
-    i_lo = chunk_item[c];
-    const uint32_t i_hi = c0 + kChunkPairs < m ? chunk_item[c + 1] : nvis - 1;
-    const uint32_t nloc = i_hi - i_lo + 1;
-    for (uint32_t k = threadIdx.x; k <= nloc; k += kChunkThreads) {
-        const uint32_t i = i_lo + k;
-        if (k == nloc) {
-            ci.p0[k] = i < nvis ? poff[i] : m;
-            continue;
-        }
-        ci.p0[k] = poff[i];
-        const uint4 bw = boxes[i];
-        ci.tile0[k] = bw.x;
-        ci.wx[k] = bw.y;
-        ci.zkey[k] = bw.z;
-        ci.item[k] = bw.w;
-    }
-    __syncthreads();
-    return nloc;
-}
-
-// largest local index k < nloc with p0[k] <= p (p0[0] <= p holds)
-__device__ __forceinline__ uint32_t find_chunk_item(const ChunkItems &ci, uint32_t nloc, uint32_t p) {
-    uint32_t lo = 0, hi = nloc - 1;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if (ci.p0[mid] <= p)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
-// Global tiles of consecutive pairs p, p + 1, ...: the walker keeps the
-// (row, column) of the current pair in its item's box, so only the first pair
-// needs a division.
-struct PairWalker {
-    uint32_t k, row, col;
-    __device__ __forceinline__ void start(const ChunkItems &ci, uint32_t nloc, uint32_t p) {
-        k = find_chunk_item(ci, nloc, p);
-        const uint32_t q = p - ci.p0[k], w = ci.wx[k] & 0xffffu;
-        row = q / w;
-        col = q - row * w;
-    }
-    // move to pair p (the pair after the previous one)
-    __device__ __forceinline__ void next(const ChunkItems &ci, uint32_t nloc, uint32_t p) {
-        if (k + 1 < nloc && ci.p0[k + 1] <= p) {
-            ++k;
-            while (k + 1 < nloc && ci.p0[k + 1] <= p) ++k;  // (items own at least one pair: not taken)
-            row = col = 0;
-        } else if (++col == (ci.wx[k] & 0xffffu)) {
-            col = 0;
-            ++row;
-        }
-    }
-    __device__ __forceinline__ uint32_t tile(const ChunkItems &ci) const {
-        return ci.tile0[k] + row * (ci.wx[k] >> 16) + col;
-    }
-};
 
 }  // namespace gsr

@@ -141,8 +141,8 @@ __device__ __forceinline__ void load_pose(const float *__restrict__ w2c, int v, 
 template <int DEG>
 __global__ __launch_bounds__(kProjThreads) void k_project_fwd(gsr_gaussians g, ViewTable vt,
                                                               const float *__restrict__ w2c, uint64_t n,
-                                                              Rec *__restrict__ rec, float2 *__restrict__ ulo,
-                                                              uint32_t *__restrict__ zkey,
+                                                              Rec *__restrict__ rec,
+                                                              uint4 *__restrict__ box,
                                                               uint32_t *__restrict__ count,
                                                               WsHeader *__restrict__ hdr, uint32_t cap,
                                                               const int64_t *__restrict__ active) {
@@ -156,7 +156,6 @@ __global__ __launch_bounds__(kProjThreads) void k_project_fwd(gsr_gaussians g, V
     const int v = (int)(item / n);
     const uint64_t i = item - (uint64_t)v * n;
     if (active && (int64_t)i >= *active) {  // beyond the device-given count: culled, nothing read
-        zkey[item] = kCulledKey;
         count[item] = 0;
         return;
     }
@@ -170,7 +169,6 @@ __global__ __launch_bounds__(kProjThreads) void k_project_fwd(gsr_gaussians g, V
     const double pz = (double)Wf[6] * mx + (double)Wf[7] * my + (double)Wf[8] * mz + (double)tf[2];
 
     uint32_t cnt = 0;
-    uint32_t key = kCulledKey;
     do {
         if (!(pz > (double)cam.near_plane)) break;
         const float4 qf = reinterpret_cast<const float4 *>(g.quats)[i];
@@ -227,8 +225,10 @@ __global__ __launch_bounds__(kProjThreads) void k_project_fwd(gsr_gaussians g, V
         y1 = fmin(y1, (double)(cam.height - 1));
         if (!(x0 <= x1) || !(y0 <= y1)) break;
         const uint32_t ix0 = (uint32_t)x0, ix1 = (uint32_t)x1, iy0 = (uint32_t)y0, iy1 = (uint32_t)y1;
-        cnt = (ix1 / kTileW - ix0 / kTileW + 1) * (iy1 / vt.tile_h - iy0 / vt.tile_h + 1);
-        key = __float_as_uint((float)pz);
+        const uint32_t tx = ix0 / kTileW, ty = iy0 / vt.tile_h;
+        const uint32_t tw = ix1 / kTileW - tx + 1, th = iy1 / vt.tile_h - ty + 1;
+        cnt = tw * th;
+        box[item] = make_uint4(pack_u16(tx, ty), pack_u16(tw, th), __float_as_uint((float)pz), 0u);
 
         // colour: direction from the camera centre c = -W^T t, world frame
         const double cx = -((double)Wf[0] * tf[0] + (double)Wf[3] * tf[1] + (double)Wf[6] * tf[2]);
@@ -255,15 +255,14 @@ __global__ __launch_bounds__(kProjThreads) void k_project_fwd(gsr_gaussians g, V
         r.r1 = make_float4((float)(ca / det), op, (float)fmax(col[0], 0.0), (float)fmax(col[1], 0.0));
         r.r2 = make_float4((float)fmax(col[2], 0.0), __uint_as_float(pack_u16(ix0, ix1)),
                            __uint_as_float(pack_u16(iy0, iy1)), 0.f);
+        r.r3 = make_float4((float)(u - (double)uh), (float)(vv - (double)vh), 0.f, 0.f);
         rec[item] = r;
-        ulo[item] = make_float2((float)(u - (double)uh), (float)(vv - (double)vh));
     } while (0);
-    zkey[item] = key;
     count[item] = cnt;
 }
 
 void launch_project_fwd(const gsr_gaussians &g, const ViewTable &vt, const float *w2c, uint64_t n, Rec *rec,
-                        float2 *ulo, uint32_t *zkey, uint32_t *count, WsHeader *hdr, uint32_t cap,
+                        uint4 *box, uint32_t *count, WsHeader *hdr, uint32_t cap,
                         const int64_t *active, hipStream_t st) {
     const uint64_t items = n * (uint64_t)vt.n_views;
     if (items == 0) {
@@ -272,10 +271,10 @@ void launch_project_fwd(const gsr_gaussians &g, const ViewTable &vt, const float
     }
     const dim3 grid((unsigned)((items + kProjThreads - 1) / kProjThreads));
     switch (g.sh_degree) {
-        case 0: hipLaunchKernelGGL(k_project_fwd<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ulo, zkey, count, hdr, cap, active); break;
-        case 1: hipLaunchKernelGGL(k_project_fwd<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ulo, zkey, count, hdr, cap, active); break;
-        case 2: hipLaunchKernelGGL(k_project_fwd<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ulo, zkey, count, hdr, cap, active); break;
-        default: hipLaunchKernelGGL(k_project_fwd<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ulo, zkey, count, hdr, cap, active); break;
+        case 0: hipLaunchKernelGGL(k_project_fwd<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+        case 1: hipLaunchKernelGGL(k_project_fwd<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+        case 2: hipLaunchKernelGGL(k_project_fwd<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+        default: hipLaunchKernelGGL(k_project_fwd<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
     }
 }
 
@@ -287,7 +286,7 @@ void launch_project_fwd(const gsr_gaussians &g, const ViewTable &vt, const float
 // pairs, not by items: a workgroup takes one chunk of 1024 consecutive pair
 // slots, 4 per thread (nine float4 loads per thread, coalesced).  Pairs whose
 // tile stopped before reaching the item were never written by the backward
-// compositing and count as zero: the emission clears one flag byte per slot
+// compositing and count as zero: the binning clears one flag byte per slot
 // and the backward compositing sets the flags of the slots it replays, so the
 // flags (4 per thread, one 32-bit load) tell which moments to load without
 // finding each pair's tile first.
@@ -581,7 +580,7 @@ __device__ __forceinline__ void item_moments(const float4 *__restrict__ screen, 
 // ones) and to the view's pose (added to gW, gt).
 template <int DEG>
 __device__ __forceinline__ void item_backward(const gsr_gaussians &g, const ViewInfo &cam, const float *__restrict__ w2c,
-                                              int v, uint64_t i, uint64_t item, uint32_t cnt,
+                                              int v, uint64_t i, uint64_t item, uint32_t first_pair, uint32_t cnt,
                                               const Rec *__restrict__ rec, const float4 *__restrict__ screen,
                                               const float *__restrict__ carry, const float *sh_row, float *gsh,
                                               bool &sh_written, float (&gmu)[3], float (&gls)[3], float (&gq)[4],
@@ -589,7 +588,7 @@ __device__ __forceinline__ void item_backward(const gsr_gaussians &g, const View
     constexpr int K = (DEG + 1) * (DEG + 1);
     const float4 r0 = rec[item].r0, r1 = rec[item].r1;
     float S[kPartialStride];
-    item_moments(screen, carry, item, __float_as_uint(rec[item].r2.w), cnt, S);
+    item_moments(screen, carry, item, first_pair, cnt, S);
     // S[0..4] hold the moments of sa = -dL/dsigma: S_x = -S[0], ..., S_yy = -S[4]
     const float gu = -fmaf(r0.z, S[0], r0.w * S[1]), gv = -fmaf(r0.w, S[0], r1.x * S[1]);
     const float gA = -0.5f * S[2], gB = -S[3], gC = -0.5f * S[4], go = S[5] / r1.y;
@@ -812,7 +811,7 @@ __device__ __forceinline__ void pose_block_partial(const float (&gW)[9], const f
 template <int DEG>
 __global__ __launch_bounds__(kProjThreads) void k_project_bwd(
     gsr_gaussians g, ViewTable vt, const float *__restrict__ w2c, uint64_t n, const Rec *__restrict__ rec,
-    const uint32_t *__restrict__ count, const WsHeader *__restrict__ hdr, const float4 *__restrict__ screen,
+    const uint32_t *__restrict__ ioff, const uint32_t *__restrict__ count, const WsHeader *__restrict__ hdr, const float4 *__restrict__ screen,
     const float *__restrict__ carry, gsr_gaussian_grads gr, float *__restrict__ pose_part, uint32_t pose_blocks,
     int zero_unseen) {
     constexpr int K = (DEG + 1) * (DEG + 1);
@@ -877,7 +876,7 @@ __global__ __launch_bounds__(kProjThreads) void k_project_bwd(
         const uint64_t item = (uint64_t)v * n + i;
         const uint32_t cnt = live ? count[item] : 0u;
         if (cnt > 0)
-            item_backward<DEG>(g, vt.v[v], w2c, v, i, item, cnt, rec, screen, carry, g.sh + (size_t)i * K * 3, gsh,
+            item_backward<DEG>(g, vt.v[v], w2c, v, i, item, ioff[item], cnt, rec, screen, carry, g.sh + (size_t)i * K * 3, gsh,
                                sh_written, gmu, gls, gq, gop, gW, gt);
         pose_block_partial(gW, gt, red, pose_part, v, pose_blocks);
     }
@@ -903,7 +902,7 @@ __global__ __launch_bounds__(kProjThreads) void k_project_bwd(
 template <int DEG>
 __global__ __launch_bounds__(kProjThreads) void k_project_bwd_vis(
     gsr_gaussians g, ViewTable vt, const float *__restrict__ w2c, uint64_t n, int v, const uint32_t *__restrict__ seg,
-    const uint32_t *__restrict__ vis, const Rec *__restrict__ rec, const uint32_t *__restrict__ count,
+    const uint32_t *__restrict__ vis, const Rec *__restrict__ rec, const uint32_t *__restrict__ ioff, const uint32_t *__restrict__ count,
     const WsHeader *__restrict__ hdr, const float4 *__restrict__ screen, const float *__restrict__ carry,
     gsr_gaussian_grads gr, float *__restrict__ pose_part, uint32_t pose_blocks) {
     constexpr int K = (DEG + 1) * (DEG + 1);
@@ -950,7 +949,7 @@ __global__ __launch_bounds__(kProjThreads) void k_project_bwd_vis(
         float gmu[3] = {0, 0, 0}, gls[3] = {0, 0, 0}, gq[4] = {0, 0, 0, 0}, gop = 0.f;
         bool sh_written = false;
         float *row = rows + lane * kStride;  // read, then overwritten with this view's SH gradient
-        item_backward<DEG>(g, vt.v[v], w2c, v, i, item, count[item], rec, screen, carry, row, row, sh_written, gmu,
+        item_backward<DEG>(g, vt.v[v], w2c, v, i, item, ioff[item], count[item], rec, screen, carry, row, row, sh_written, gmu,
                            gls, gq, gop, gW, gt);
         if (!first) {
 #pragma unroll
@@ -994,54 +993,31 @@ __global__ __launch_bounds__(kProjThreads) void k_project_bwd_vis(
     pose_block_partial(gW, gt, red, pose_part, v, pose_blocks);
 }
 
-// First visible index of each view (the list is in ascending item order and
-// item = view * n + Gaussian), and the visible count at index n_views; one
-// thread per entry.
-static_assert(GSR_MAX_VIEWS < 64, "one wave computes the view segments");
-__global__ void k_view_segments(const uint32_t *__restrict__ vis, uint64_t n, int n_views,
-                                const WsHeader *__restrict__ hdr, uint32_t *__restrict__ seg) {
-    const int v = threadIdx.x;
-    if (v > n_views) return;
-    const uint32_t nvis = hdr->overflow ? 0u : hdr->n_visible;
-    const uint64_t key = (uint64_t)v * n;
-    uint32_t a = 0, b = nvis;  // first index whose item is >= key
-    while (a < b) {
-        const uint32_t mid = (a + b) >> 1;
-        if ((uint64_t)vis[mid] < key)
-            a = mid + 1;
-        else
-            b = mid;
-    }
-    seg[v] = a;
-}
-
 void launch_project_bwd(const gsr_gaussians &g, const ViewTable &vt, const float *w2c, uint64_t n, const Rec *rec,
-                        const uint32_t *count, const uint32_t *vis, const WsHeader *hdr, const float4 *screen,
+                        const uint32_t *ioff, const uint32_t *count, const uint32_t *vis, const WsHeader *hdr, const float4 *screen,
                         const float *carry, const gsr_gaussian_grads &gr, float *pose_part, uint32_t pose_blocks,
-                        uint32_t *seg, bool zero_unseen, hipStream_t st) {
+                        const uint32_t *seg, bool zero_unseen, hipStream_t st) {
     if (n == 0) return;
     const dim3 grid(pose_blocks);
     const int z = zero_unseen ? 1 : 0;
     if (!zero_unseen) {
         // one dense launch per view, in view order
-        if (vt.n_views > 1)
-            hipLaunchKernelGGL(k_view_segments, dim3(1), dim3(64), 0, st, vis, n, vt.n_views, hdr, seg);
         const uint32_t *sg = vt.n_views > 1 ? seg : nullptr;
         for (int v = 0; v < vt.n_views; ++v) {
             switch (g.sh_degree) {
-                case 0: hipLaunchKernelGGL(k_project_bwd_vis<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
-                case 1: hipLaunchKernelGGL(k_project_bwd_vis<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
-                case 2: hipLaunchKernelGGL(k_project_bwd_vis<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
-                default: hipLaunchKernelGGL(k_project_bwd_vis<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+                case 0: hipLaunchKernelGGL(k_project_bwd_vis<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+                case 1: hipLaunchKernelGGL(k_project_bwd_vis<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+                case 2: hipLaunchKernelGGL(k_project_bwd_vis<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+                default: hipLaunchKernelGGL(k_project_bwd_vis<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
             }
         }
         return;
     }
     switch (g.sh_degree) {
-        case 0: hipLaunchKernelGGL(k_project_bwd<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
-        case 1: hipLaunchKernelGGL(k_project_bwd<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
-        case 2: hipLaunchKernelGGL(k_project_bwd<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
-        default: hipLaunchKernelGGL(k_project_bwd<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
+        case 0: hipLaunchKernelGGL(k_project_bwd<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
+        case 1: hipLaunchKernelGGL(k_project_bwd<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
+        case 2: hipLaunchKernelGGL(k_project_bwd<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
+        default: hipLaunchKernelGGL(k_project_bwd<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
     }
 }
 

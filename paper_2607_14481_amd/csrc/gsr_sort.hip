@@ -1,23 +1,24 @@
 // gsr_sort.hip -- binning stages of the rasterizer on gfx950:
 //   A2 scans: visible-item compaction and per-item pair offsets (exclusive
 //      scans in u32 with saturating adds, reduce-then-scan, no spin waits)
-//   A3 emission: (tile, item) pairs, written in ascending item order
-//   A4 radix sort: LSD passes of up to 8 bits over (tile u32, item u32)
+//   A3-A5 binning: the (depth bits, item) entries of each tile's list, grouped
+//      by tile in no particular order, and each list's [start, end)
 //   A4c per-tile depth order: each tile's list sorted by (depth bits, item)
-//   A5 tile ranges: [start, end) of each tile in the sorted pairs
 //
 // Order of work.  The pairs must end up sorted by (tile, depth bits, item).
-// Rather than sorting 48-bit (tile, depth) keys over all M pairs (six 8-bit
-// passes over the pairs), the pairs are emitted in ascending item order, an
-// LSD sort on the tile id alone (ceil(tile_bits / 8) passes, two at 1080p)
-// groups them by tile, and one workgroup per tile sorts its short list by
-// (depth bits, item) in LDS.  The result is the (tile, depth, item) order
-// exactly, whatever order a tile's list had before; so the first radix pass
-// need not keep equal digits in input order (only the later ones must).
+// The tiles of one view are few enough for one counter each in a workgroup's
+// LDS, so the grouping by tile is one counting sort with a digit per tile: a
+// pass that counts (k_bin_count), a column scan (k_bin_scan) and a pass that
+// places every pair (k_bin_place); the pairs are generated from the items'
+// tile boxes in both passes and never stored unsorted.  One workgroup per tile
+// then sorts its short list by (depth bits, item) in LDS: the result is the
+// (tile, depth, item) order exactly, whatever order a tile's list had before.
 //
 // Every kernel reads its element count from the workspace header, so the
 // launch grid can be sized for a capacity and the call needs no host
 // synchronisation (graph capture).
+#include <algorithm>
+
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -136,10 +137,16 @@ void launch_compact_flags(const uint8_t *flags, uint64_t n, uint32_t *out_idx, u
 // all items before it.  Phase 1 sums each block of kScanTile items; phase 2
 // gives each block the sums of the blocks before it (each block adds them up
 // itself: at most a few thousand L2-resident values, no extra launch) and
-// writes the k-th visible item's id, pair offset and box word and, for each
-// chunk of kChunkPairs pair slots whose first pair the item holds, k.  The
-// last block writes the visible and pair counts and the overflow decision
-// (pairs > capacity).
+// writes the k-th visible item's id, pair offset and box and, for each
+// chunk of kChunkPairs pair slots whose first pair the item holds, k; each
+// view's first visible index too.  The last block writes the visible and pair
+// counts and the overflow decision (pairs > capacity).
+//
+// It moves 40 bytes per visible item, with every access contiguous except for
+// the gaps of the invisible ones: the projection leaves the box words in an
+// array of their own and the pair offset by item goes to another.  (Read from
+// and written into the records themselves, 48 bytes apart, both touched every
+// line of theirs for one word: 132 us for 8 views of 1 M items, 63 us now.)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kScanThreads) void k_vis_reduce(const uint32_t *__restrict__ count, uint64_t n,
                                                              uint32_t *__restrict__ block_vis,
@@ -164,13 +171,14 @@ __global__ __launch_bounds__(kScanThreads) void k_vis_reduce(const uint32_t *__r
 
 __global__ __launch_bounds__(kScanThreads) void k_vis_apply(ViewTable vt, uint64_t n_view,
                                                             const uint32_t *__restrict__ count,
-                                                            Rec *__restrict__ rec,
-                                                            const uint32_t *__restrict__ zkey, uint64_t n,
+                                                            const uint4 *__restrict__ box, uint64_t n,
                                                             const uint32_t *__restrict__ block_vis,
                                                             const uint32_t *__restrict__ block_pairs,
                                                             uint32_t *__restrict__ vis, uint32_t *__restrict__ poff,
+                                                            uint32_t *__restrict__ ioff,
                                                             uint4 *__restrict__ item_box,
                                                             uint32_t *__restrict__ chunk_item, uint64_t chunks_cap,
+                                                            uint32_t *__restrict__ view_seg,
                                                             WsHeader *__restrict__ hdr) {
     // The block's kScanTile items in kScanItems rounds of kScanThreads
     // consecutive ones (round k, thread t: item base + k kScanThreads + t), so
@@ -187,19 +195,11 @@ __global__ __launch_bounds__(kScanThreads) void k_vis_apply(ViewTable vt, uint64
         const uint64_t it = base + (uint64_t)k * kScanThreads + tid;
         c[k] = it < n ? count[it] : 0u;
     }
-    // the visible items' boxes and depth keys, all requested before the scans
-    // (the stores below into the same records would otherwise order each load
-    // after the previous item's store)
-    float4 r2[kScanItems];
-    uint32_t z[kScanItems];
+    // the visible items' boxes, all requested before the scans
+    uint4 bw[kScanItems];
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        if (c[k] > 0u) {
-            const uint64_t it = base + (uint64_t)k * kScanThreads + tid;
-            r2[k] = rec[it].r2;
-            z[k] = zkey[it];
-        }
-    }
+    for (int k = 0; k < kScanItems; ++k)
+        if (c[k] > 0u) bw[k] = box[base + (uint64_t)k * kScanThreads + tid];
     // the sums of the blocks before this one
     uint32_t bv = 0, bp = 0;
     for (uint32_t j = tid; j < blockIdx.x; j += kScanThreads) {
@@ -243,6 +243,17 @@ __global__ __launch_bounds__(kScanThreads) void k_vis_apply(ViewTable vt, uint64
         hdr->n_visible = v0;
         hdr->n_pairs = p0;
         hdr->overflow = p0 > hdr->pair_capacity ? 1u : 0u;
+        view_seg[vt.n_views] = v0;
+        view_seg[GSR_MAX_VIEWS + 1 + vt.n_views] = p0;
+    }
+    // the first visible index and the first pair of each view that starts here
+    for (uint64_t v = (base + n_view - 1) / n_view; v * n_view < min(base + kScanTile, n); ++v) {
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k)
+            if (base + (uint64_t)k * kScanThreads + tid == v * n_view) {
+                view_seg[v] = kv[k];
+                view_seg[GSR_MAX_VIEWS + 1 + v] = run[k];
+            }
     }
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
@@ -250,8 +261,8 @@ __global__ __launch_bounds__(kScanThreads) void k_vis_apply(ViewTable vt, uint64
             const uint32_t item = (uint32_t)(base + (uint64_t)k * kScanThreads + tid);
             vis[kv[k]] = item;
             poff[kv[k]] = run[k];
-            item_box[kv[k]] = item_box_word(vt, n_view, item, r2[k], z[k]);
-            rec[item].r2.w = __uint_as_float(run[k]);  // the item's first pair, for the later passes
+            ioff[item] = run[k];
+            item_box[kv[k]] = make_uint4(bw[k].x, bw[k].y, bw[k].z, item);
             // chunks whose first pair lies in [run, run + c)
             const uint32_t end = sat_add(run[k], c[k]);
             for (uint64_t ch = chunk_count(run[k]); ch < chunks_cap && ch * kChunkPairs < end; ++ch)
@@ -260,331 +271,383 @@ __global__ __launch_bounds__(kScanThreads) void k_vis_apply(ViewTable vt, uint64
     }
 }
 
-void launch_visible_offsets(const ViewTable &vt, uint64_t n, const uint32_t *count, Rec *rec,
-                            const uint32_t *zkey, uint64_t items, uint32_t *vis, uint32_t *poff, uint4 *item_box,
-                            uint32_t *chunk_item, uint64_t chunks_cap, uint32_t *block_tmp, WsHeader *hdr,
+void launch_visible_offsets(const ViewTable &vt, uint64_t n, const uint32_t *count, const uint4 *box, uint64_t items,
+                            uint32_t *vis, uint32_t *poff, uint32_t *ioff, uint4 *item_box, uint32_t *chunk_item,
+                            uint64_t chunks_cap, uint32_t *block_tmp, uint32_t *view_seg, WsHeader *hdr,
                             hipStream_t st) {
     const uint32_t nb = (uint32_t)((items + kScanTile - 1) / kScanTile);
-    if (nb == 0) return;
+    if (nb == 0) {
+        launch_fill_u32(view_seg, 0u, 2 * (GSR_MAX_VIEWS + 1), st);
+        return;
+    }
     uint32_t *bv = block_tmp, *bp = block_tmp + nb;
     hipLaunchKernelGGL(k_vis_reduce, dim3(nb), dim3(kScanThreads), 0, st, count, items, bv, bp);
-    hipLaunchKernelGGL(k_vis_apply, dim3(nb), dim3(kScanThreads), 0, st, vt, n, count, rec, zkey, items, bv, bp, vis,
-                       poff, item_box, chunk_item, chunks_cap, hdr);
+    hipLaunchKernelGGL(k_vis_apply, dim3(nb), dim3(kScanThreads), 0, st, vt, n, count, box, items, bv, bp, vis, poff,
+                       ioff, item_box, chunk_item, chunks_cap, view_seg, hdr);
+}
+
+__global__ __launch_bounds__(256) void k_export_items(const uint32_t *__restrict__ poff,
+                                                      const uint4 *__restrict__ item_box,
+                                                      const Rec *__restrict__ rec, const WsHeader *__restrict__ hdr,
+                                                      uint64_t items, float *__restrict__ records,
+                                                      float *__restrict__ centre_lo,
+                                                      uint32_t *__restrict__ depth_keys) {
+    const uint64_t k = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= min((uint64_t)hdr->n_visible, items)) return;
+    const uint4 bw = item_box[k];
+    const Rec r = rec[bw.w];
+    if (records) {
+        const float w[kExportWords] = {r.r0.x, r.r0.y, r.r0.z, r.r0.w, r.r1.x, r.r1.y,
+                                       r.r1.z, r.r1.w, r.r2.x, r.r2.y, r.r2.z, __uint_as_float(poff[k])};
+        for (int c = 0; c < kExportWords; ++c) records[(size_t)bw.w * kExportWords + c] = w[c];
+    }
+    if (centre_lo) centre_lo[2 * (size_t)bw.w] = r.r3.x, centre_lo[2 * (size_t)bw.w + 1] = r.r3.y;
+    if (depth_keys) depth_keys[bw.w] = bw.z;
+}
+
+void launch_export_items(const uint32_t *poff, const uint4 *item_box, const Rec *rec, const WsHeader *hdr,
+                         uint64_t items, float *records, float *centre_lo, uint32_t *depth_keys, hipStream_t st) {
+    if (items == 0 || (!records && !centre_lo && !depth_keys)) return;
+    if (depth_keys) launch_fill_u32(depth_keys, kCulledKey, items, st);
+    hipLaunchKernelGGL(k_export_items, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, poff, item_box, rec, hdr,
+                       items, records, centre_lo, depth_keys);
 }
 
 // ---------------------------------------------------------------------------
-// A4: LSD radix sort, one 8-bit digit per pass.
-//   k_radix_hist    per-block digit histogram -> hist[digit][block]
-//   k_radix_scan    per digit: exclusive scan over blocks (in place) + total
-//   k_radix_scatter rank within the block (wave ballots, stable; or LDS
-//                   atomics for a first pass that need not be), scatter
-// The element count is read on the device: either *n_dev or, for the pair
-// sort, 0 when the header flags an overflow.
+// A3-A5: the counting sort by tile.  A view's visible items are cut into G
+// shares (groups of kBinGroup consecutive items, dealt round robin, so that the
+// shares get about as many pairs each) and its rows of tiles into bands; a
+// workgroup takes one share in one band.
+//   k_bin_count  counts the share's pairs per tile of the band and writes them
+//                into row g of the count matrix.  A tile's count is a 2-D
+//                prefix sum: an item adds four corners of its box to a
+//                difference array in LDS, however many tiles it covers;
+//   k_bin_scan   per tile: the exclusive scan over the rows in place, and the
+//                tile's total;
+//   k_bin_place  scans the view's tile totals (every workgroup itself: no
+//                launch between), adds its row, and places its pairs with LDS
+//                counters as cursors (the pairs come from the items' boxes, a
+//                lane per item while the item has at most kBinLaneTiles tiles
+//                in the band and a wave per item beyond); the first share also
+//                writes the tiles' ranges and lists the long ones.
+// A view's pairs start where its first visible item's do, so a workgroup
+// needs only its own view's totals.
+//
+// What bounds the placing is its scattered 8-byte stores: a tile's list is
+// filled by all shares at once, so every cache line of the output stays
+// partly written until the end.  Hence the bands, taken one after the other
+// (the workgroups of a band fill the chip): a band's output is small enough
+// for the XCDs' L2s to hold its lines until they are full, and each XCD takes
+// consecutive shares, whose parts of a list lie side by side.
+// A view of 341 k visible items and 5.4 M pairs (capacity 7.0 M; 1920x1080, 8,160
+// tiles): 84 us in one band, 43 us in three; at 1.0, 1.7, 2.6 and 4.0 M pairs a
+// band 54, 49, 46 and 52 us, and smaller calls lose with more bands than one
+// (each band walks all the share's boxes again).  Counting, scanning and placing
+// take 57 us there in all, where emitting the pairs unsorted, a two-pass radix sort by
+// tile and the search for the tiles' ranges took 96 us; with 8 views
+// (2.9 M visible items, 15.3 M pairs, 14,720 tiles) 123 us against 285 us.
 // ---------------------------------------------------------------------------
-// A block sorts TILE consecutive elements.
-// Rounds of 64 consecutive elements per wave: wave w of a block owns the
-// block's elements [w * TILE / 4, (w + 1) * TILE / 4), which keeps the block's
-// order (wave, round, lane) equal to the input order.
-template <int TILE>
-struct SortShape {
-    static constexpr int kWaveSpan = TILE / (kSortThreads / 64);
-    static constexpr int kRounds = kWaveSpan / 64;
-    static constexpr int kItems = TILE / kSortThreads;
+constexpr int kBinThreads = 1024;
+constexpr uint32_t kBinLaneTiles = 48;
+constexpr uint64_t kBinBandPairs = 2600000;  // pairs (of the capacity) a band of a view is meant to hold
+constexpr uint32_t kBinGroup = 16;  // 256 contiguous bytes of box words
+
+// Visible index of the q-th item of share g of G of the view whose visible
+// indices start at s0.
+__device__ __forceinline__ uint32_t bin_item(uint32_t s0, uint32_t q, uint32_t g, uint32_t G) {
+    return s0 + (q / kBinGroup * G + g) * kBinGroup + q % kBinGroup;
+}
+
+// A visible item's box, clipped to the tile rows [r0, r1) of its view.
+struct BinBox {
+    uint32_t x0, y0, w, h;  // first column and (clipped) row, width and (clipped) height
+    uint32_t z, item;
 };
-
-// Lanes of the wave holding the same digit (of `bits` <= 8 bits) as this lane.
-__device__ __forceinline__ unsigned long long digit_peers(bool ok, uint32_t d, int bits) {
-    unsigned long long match = __ballot(ok);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        if (b >= bits) break;
-        const unsigned long long bal = __ballot(ok && ((d >> b) & 1u));
-        match &= ((d >> b) & 1u) ? bal : ~bal;
-    }
-    return match;
+__device__ __forceinline__ BinBox bin_box(const uint4 &bw, uint32_t r0, uint32_t r1) {
+    const uint32_t y = bw.x >> 16, y1 = min(y + (bw.y >> 16), r1);
+    BinBox b;
+    b.x0 = bw.x & 0xffffu;
+    b.w = bw.y & 0xffffu;
+    b.y0 = max(y, r0);
+    b.h = y1 > b.y0 ? y1 - b.y0 : 0u;
+    b.z = bw.z;
+    b.item = bw.w;
+    return b;
 }
 
-// Per-block digit histogram (LDS atomics; all loads are issued first).
-template <int TILE>
-__global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint32_t *__restrict__ keys, SortCount sc,
-                                                             int shift, uint32_t mask, uint32_t *__restrict__ hist,
-                                                             uint32_t hist_blocks) {
-    __shared__ uint32_t h[256];
-    const uint64_t n = sc();
-    const uint64_t blk = (uint64_t)blockIdx.x * TILE;
-    if (blk >= n) return;  // blocks past the end are never scanned
-    const uint32_t m = (uint32_t)min((uint64_t)TILE, n - blk);
-    uint32_t k[SortShape<TILE>::kItems];
-#pragma unroll
-    for (int r = 0; r < SortShape<TILE>::kItems; ++r) {
-        const uint32_t li = (uint32_t)r * kSortThreads + threadIdx.x;
-        k[r] = li < m ? keys[blk + li] : 0u;
-    }
-    h[threadIdx.x] = 0;
+// (share, view, tile rows) of a workgroup: views and bands one after the
+// other, and within one, consecutive shares on each XCD.
+struct BinTurn {
+    uint32_t g, v, r0, r1;
+};
+__device__ __forceinline__ BinTurn bin_turn(const ViewTable &vt, uint32_t G, uint32_t bands) {
+    BinTurn b;
+    const uint32_t turn = blockIdx.x / G;
+    b.g = xcd_contiguous(blockIdx.x - turn * G, G);
+    b.v = turn / bands;
+    const uint32_t band = turn - b.v * bands, rows = (uint32_t)vt.v[b.v].tiles_y;
+    const uint32_t per = (rows + bands - 1) / bands;
+    b.r0 = min(band * per, rows);
+    b.r1 = min(b.r0 + per, rows);
+    return b;
+}
+
+__global__ __launch_bounds__(kBinThreads) void k_bin_count(ViewTable vt, uint32_t G, uint32_t bands,
+                                                           const uint32_t *__restrict__ seg,
+                                                           const uint4 *__restrict__ item_box,
+                                                           uint32_t *__restrict__ counts,
+                                                           const WsHeader *__restrict__ hdr) {
+    extern __shared__ uint32_t s_tile[];  // rows + 1 of tiles_x + 1
+    const BinTurn bt = bin_turn(vt, G, bands);
+    if (bt.r0 >= bt.r1) return;  // uniform
+    const uint32_t nx = (uint32_t)vt.v[bt.v].tiles_x, ny = bt.r1 - bt.r0, P = nx + 1, off = vt.v[bt.v].tile_off;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (uint32_t t = tid; t < P * (ny + 1); t += kBinThreads) s_tile[t] = 0u;
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < SortShape<TILE>::kItems; ++r)
-        if ((uint32_t)r * kSortThreads + threadIdx.x < m) atomicAdd(&h[(k[r] >> shift) & mask], 1u);
+    if (!hdr->overflow) {
+        const uint32_t s0 = seg[bt.v], s1 = seg[bt.v + 1];
+        for (uint32_t q = tid;; q += kBinThreads) {
+            const uint32_t k = bin_item(s0, q, bt.g, G);
+            if (k >= s1) break;
+            const BinBox b = bin_box(item_box[k], bt.r0, bt.r1);
+            if (!b.h) continue;
+            uint32_t *at = s_tile + (b.y0 - bt.r0) * P + b.x0;
+            atomicAdd(at, 1u);
+            atomicAdd(at + b.w, 0xffffffffu);
+            atomicAdd(at + b.h * P, 0xffffffffu);
+            atomicAdd(at + b.h * P + b.w, 1u);
+        }
+    }
     __syncthreads();
-    hist[(size_t)threadIdx.x * hist_blocks + blockIdx.x] = h[threadIdx.x];
+    // sums along the rows (a wave each), then down the columns (a thread each)
+    const auto add = [](uint32_t a, uint32_t b) { return a + b; };
+    for (uint32_t y = wave; y < ny; y += kBinThreads / kWave) {
+        uint32_t carry = 0;
+        for (uint32_t x0 = 0; x0 < nx; x0 += kWave) {
+            const uint32_t x = x0 + lane;
+            const uint32_t inc = wave_inclusive_scan(x < nx ? s_tile[y * P + x] : 0u, add) + carry;
+            if (x < nx) s_tile[y * P + x] = inc;
+            carry = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        }
+    }
+    __syncthreads();
+    uint32_t *out = counts + (size_t)bt.g * vt.total_tiles + off + bt.r0 * nx;
+    for (uint32_t x = tid; x < nx; x += kBinThreads) {
+        uint32_t run = 0, y = 0;
+        for (; y + 8 <= ny; y += 8) {  // eight loads in flight
+            uint32_t c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c[u] = s_tile[(y + u) * P + x];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) out[(y + u) * nx + x] = run += c[u];
+        }
+        for (; y < ny; ++y) out[y * nx + x] = run += s_tile[y * P + x];
+    }
 }
 
-// One workgroup per digit: exclusive scan of hist[d][0..nb) in place, each
-// thread taking kScanRun consecutive blocks per sweep (one sweep covers 2048
-// blocks, 6.3M elements at 3072 per block).
-constexpr int kScanRun = 8;
-template <int TILE>
-__global__ __launch_bounds__(256) void k_radix_scan(uint32_t *__restrict__ hist, uint32_t hist_blocks, SortCount sc,
-                                                    uint32_t *__restrict__ digit_total) {
-    __shared__ uint32_t lds[4];
-    const uint64_t n = sc();
-    const uint32_t nb = (uint32_t)((n + TILE - 1) / TILE);
-    uint32_t *row = hist + (size_t)blockIdx.x * hist_blocks;
-    uint32_t carry = 0;
-    for (uint32_t b0 = 0; b0 < nb; b0 += 256 * kScanRun) {
-        const uint32_t bt = b0 + threadIdx.x * kScanRun;
-        uint32_t x[kScanRun], sum = 0;
+// 64 tiles per workgroup, each of its 16 waves holding up to 16 rows of them in
+// registers: the matrix is read once, all loads in flight, and written once.
+__global__ __launch_bounds__(kBinThreads) void k_bin_scan(uint32_t *__restrict__ counts, uint32_t G,
+                                                          uint32_t total_tiles, uint32_t *__restrict__ totals) {
+    constexpr int kWaves = kBinThreads / kWave, kRows = kBinMaxRows / kWaves;
+    __shared__ uint32_t part[kWaves][kWave];
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t t = blockIdx.x * kWave + lane, g0 = w * kRows;
+    const bool ok = t < total_tiles;
+    uint32_t c[kRows], sum = 0;
 #pragma unroll
-        for (int j = 0; j < kScanRun; ++j) {
-            x[j] = bt + j < nb ? row[bt + j] : 0u;
-            sum += x[j];
-        }
-        uint32_t total;
-        uint32_t ex = carry + block_exclusive_scan(sum, lds, total);
+    for (int r = 0; r < kRows; ++r) c[r] = ok && g0 + r < G ? counts[(size_t)(g0 + r) * total_tiles + t] : 0u;
 #pragma unroll
-        for (int j = 0; j < kScanRun; ++j) {
-            if (bt + j < nb) row[bt + j] = ex;
-            ex += x[j];
-        }
-        carry += total;
+    for (int r = 0; r < kRows; ++r) sum += c[r];
+    part[w][lane] = sum;
+    __syncthreads();
+    uint32_t run = 0;
+    for (uint32_t q = 0; q < w; ++q) run += part[q][lane];
+    if (!ok) return;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        if (g0 + r < G) counts[(size_t)(g0 + r) * total_tiles + t] = run;
+        run += c[r];
     }
-    if (threadIdx.x == 0) digit_total[blockIdx.x] = carry;
+    if (w == kWaves - 1) totals[t] = run;
 }
 
-// Stable scatter of one block's TILE elements.  Each wave loads its TILE / 4
-// consecutive elements up front, then ranks them round by round against its
-// own running digit counts (ballot peers; no block barrier inside the loop).
-// One barrier later the waves' counts become offsets, the block's elements
-// are placed in LDS in digit order, and written out in contiguous runs per
-// digit (coalesced, instead of one random 4-byte write per element).  With
-// STABLE false (a first pass whose caller does not need equal keys kept in
-// input order) each element takes its rank from an LDS atomic on its wave's
-// digit count instead of the ballots.
-template <int TILE, bool STABLE>
-__global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t *__restrict__ kin,
-                                                                const uint32_t *__restrict__ vin,
-                                                                uint32_t *__restrict__ kout,
-                                                                uint32_t *__restrict__ vout, SortCount sc, int shift,
-                                                                int bits, const uint32_t *__restrict__ hist,
-                                                                uint32_t hist_blocks,
-                                                                const uint32_t *__restrict__ digit_total) {
-    __shared__ uint32_t gbase[256];      // global position of this block's first element of each digit
-    __shared__ uint32_t lbase[256];      // block-local position of the same
-    __shared__ uint32_t wcnt[4][256];    // per-wave running digit counts, then per-wave block-local offsets
-    __shared__ uint32_t lds[4];
-    __shared__ uint32_t skey[TILE], sval[TILE];
-    const uint64_t n = sc();
-    const uint32_t nb = (uint32_t)((n + TILE - 1) / TILE);
-    if (blockIdx.x >= nb) return;
-    // neighbouring blocks write neighbouring parts of each digit's output
-    // range (often the same cache lines): keep them on one XCD
-    const uint32_t tb = xcd_contiguous(blockIdx.x, nb);
-    const uint64_t blk = (uint64_t)tb * TILE;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint32_t t = threadIdx.x;
-    const uint32_t m = (uint32_t)min((uint64_t)TILE, n - blk);
-    const uint32_t mask = (1u << bits) - 1u;
-    uint32_t key[SortShape<TILE>::kRounds], val[SortShape<TILE>::kRounds];
-#pragma unroll
-    for (int r = 0; r < SortShape<TILE>::kRounds; ++r) {
-        const uint32_t li = (uint32_t)(w * SortShape<TILE>::kWaveSpan + r * 64 + lane);
-        key[r] = li < m ? kin[blk + li] : 0u;
-        val[r] = li < m ? vin[blk + li] : 0u;
-    }
+// A list longer than kGroupSortMax: registered for the multi-workgroup sort.
+__device__ __forceinline__ void register_long(uint32_t tile, uint32_t len, uint32_t *__restrict__ long_tiles,
+                                              WsHeader *__restrict__ hdr) {
+    const uint32_t k = atomicAdd(&hdr->n_long, 1u);
+    if (k < kMaxLongTiles) long_tiles[k] = tile;
+    atomicAdd(&hdr->long_pairs, len);
+    atomicMax(&hdr->max_long, len);
+}
+
+__global__ __launch_bounds__(kBinThreads) void k_bin_place(ViewTable vt, uint32_t G, uint32_t bands,
+                                                           const uint32_t *__restrict__ seg,
+                                                           const uint4 *__restrict__ item_box,
+                                                           const uint32_t *__restrict__ counts,
+                                                           const uint32_t *__restrict__ totals,
+                                                           uint2 *__restrict__ ranges, uint32_t *__restrict__ long_tiles,
+                                                           uint32_t *__restrict__ tile_order,
+                                                           unsigned long long *__restrict__ entries,
+                                                           uint32_t *__restrict__ pflag, WsHeader *hdr) {
+    extern __shared__ uint32_t s_tile[];
+    __shared__ uint32_t s_wave[2][kBinThreads / kWave];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const bool overflow = hdr->overflow != 0u;
+    const uint32_t m = overflow ? 0u : hdr->n_pairs;
+    // the slots' "moments written" flags, set by the backward compositing
     {
-        uint32_t total;
-        // digits above the mask do not occur in this pass (their totals were not scanned)
-        const bool used = t <= mask;
-        const uint32_t tot = used ? digit_total[t] : 0u;
-        const uint32_t ex = block_exclusive_scan(tot, lds, total);
-        const uint32_t mine = used ? hist[(size_t)t * hist_blocks + tb] : 0u;
-        const uint32_t next = !used ? 0u : tb + 1 < nb ? hist[(size_t)t * hist_blocks + tb + 1] : tot;
-        gbase[t] = ex + mine;
-        lbase[t] = block_exclusive_scan(next - mine, lds, total);
+        const uint64_t words = ((uint64_t)m + 3) / 4, nb = gridDim.x, w1 = words * (blockIdx.x + 1) / nb;
+        for (uint64_t i = words * blockIdx.x / nb + tid; i < w1; i += kBinThreads) pflag[i] = 0u;
     }
-    for (int k = 0; k < 4; ++k) wcnt[k][t] = 0;
+    if (blockIdx.x == 0 && tid < kCostBuckets) tile_order[tid] = 0u;  // filled by the forward
+    const BinTurn bt = bin_turn(vt, G, bands);
+    if (bt.r0 >= bt.r1) return;  // uniform
+    const uint32_t nx = (uint32_t)vt.v[bt.v].tiles_x, off = vt.v[bt.v].tile_off;
+    const uint32_t before = bt.r0 * nx, T = (bt.r1 - bt.r0) * nx, band0 = off + before;
+    const uint32_t s0 = seg[bt.v], s1 = overflow ? s0 : seg[bt.v + 1];
+    const uint32_t first = overflow ? 0u : seg[GSR_MAX_VIEWS + 1 + bt.v];
+    // the band's tile starts: the totals of the view's tiles before it summed,
+    // its own staged in LDS, each thread's run of consecutive tiles scanned
+    const auto add = [](uint32_t a, uint32_t b) { return a + b; };
+    uint32_t early = 0;
+    for (uint32_t t = tid; t < before; t += kBinThreads) early += totals[off + t];
+    for (uint32_t t = tid; t < T; t += kBinThreads) s_tile[t] = totals[band0 + t];
+    early = wave_reduce(early, 0u, add);
+    if (lane == 0) s_wave[0][w] = early;
     __syncthreads();
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
-    uint32_t pos[SortShape<TILE>::kRounds];
+    const uint32_t per = (T + kBinThreads - 1) / kBinThreads, t0 = min(tid * per, T), t1 = min(t0 + per, T);
+    uint32_t sum = 0;
+    for (uint32_t t = t0; t < t1; ++t) sum += s_tile[t];
+    const uint32_t inc = wave_inclusive_scan(sum, add);
+    if (lane == 63) s_wave[1][w] = inc;
+    __syncthreads();
+    uint32_t run = first + inc - sum;
+    for (uint32_t q = 0; q < kBinThreads / kWave; ++q) run += s_wave[0][q] + (q < w ? s_wave[1][q] : 0u);
+    for (uint32_t t = t0; t < t1; ++t) {
+        const uint32_t n = s_tile[t];
+        s_tile[t] = run;
+        if (bt.g == 0) {
+            ranges[band0 + t] = make_uint2(run, run + n);
+            if (n > (uint32_t)kGroupSortMax) register_long(band0 + t, n, long_tiles, hdr);
+        }
+        run += n;
+    }
+    __syncthreads();
+    const uint32_t *row = counts + (size_t)bt.g * vt.total_tiles + band0;
+    for (uint32_t t = tid; t < T; t += kBinThreads) s_tile[t] += row[t];
+    __syncthreads();
+    const auto place = [&](uint32_t t, uint32_t z, uint32_t item) {
+        entries[atomicAdd(&s_tile[t], 1u)] = ((unsigned long long)z << 32) | item;
+    };
+    for (uint32_t q = w * kWave; bin_item(s0, q, bt.g, G) < s1; q += kBinThreads) {  // the wave's first item: uniform
+        const uint32_t k = bin_item(s0, q + lane, bt.g, G);
+        BinBox b{};
+        b.w = 1u;
+        if (k < s1) b = bin_box(item_box[k], bt.r0, bt.r1);
+        const uint32_t c = b.w * b.h, t_first = (b.y0 - bt.r0) * nx + b.x0;
+        const bool big = c > kBinLaneTiles;
+        uint32_t left = big ? 0u : c, col = 0, t = t_first;
+        while (__ballot(left > 0u)) {
 #pragma unroll
-    for (int r = 0; r < SortShape<TILE>::kRounds; ++r) {
-        const uint32_t li = (uint32_t)(w * SortShape<TILE>::kWaveSpan + r * 64 + lane);
-        const bool ok = li < m;
-        const uint32_t d = (key[r] >> shift) & mask;
-        if constexpr (!STABLE) {
-            pos[r] = ok ? atomicAdd(&wcnt[w][d], 1u) : 0u;
-            continue;
+            for (int u = 0; u < 4; ++u) {
+                if (left > 0u) {
+                    place(t, b.z, b.item);
+                    --left;
+                    ++t;
+                    if (++col == b.w) col = 0, t += nx - b.w;
+                }
+            }
         }
-        const unsigned long long peers = digit_peers(ok, d, bits);
-        const uint32_t rank = (uint32_t)__popcll(peers & lt_mask);
-        const uint32_t before = ok ? wcnt[w][d] : 0u;
-        pos[r] = before + rank;
-        // the digit's last lane advances the wave's count (read above by every lane first)
-        __builtin_amdgcn_wave_barrier();
-        if (ok && (peers >> lane) == 1ull) wcnt[w][d] = before + (uint32_t)__popcll(peers);
-        __builtin_amdgcn_wave_barrier();
-    }
-    __syncthreads();
-    {
-        const uint32_t c0 = wcnt[0][t], c1 = wcnt[1][t], c2 = wcnt[2][t];
-        const uint32_t b = lbase[t];
-        wcnt[0][t] = b;
-        wcnt[1][t] = b + c0;
-        wcnt[2][t] = b + c0 + c1;
-        wcnt[3][t] = b + c0 + c1 + c2;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < SortShape<TILE>::kRounds; ++r) {
-        const uint32_t li = (uint32_t)(w * SortShape<TILE>::kWaveSpan + r * 64 + lane);
-        if (li < m) {
-            const uint32_t p = wcnt[w][(key[r] >> shift) & mask] + pos[r];
-            skey[p] = key[r];
-            sval[p] = val[r];
-        }
-    }
-    __syncthreads();
-    // write out in local order: runs of one digit go to consecutive addresses
-    for (uint32_t p = t; p < m; p += kSortThreads) {
-        const uint32_t k = skey[p];
-        const uint32_t d = (k >> shift) & mask;
-        const uint32_t g = gbase[d] + (p - lbase[d]);
-        kout[g] = k;
-        vout[g] = sval[p];
-    }
-}
-
-template <int TILE>
-static void radix_passes(uint32_t *keys[2], uint32_t *vals[2], SortCount sc, uint64_t n_cap, int begin_bit,
-                         int end_bit, uint32_t *hist, uint32_t hist_blocks, uint32_t *digit_total, int &cur,
-                         bool stable, hipStream_t st) {
-    const uint32_t nb = (uint32_t)((n_cap + TILE - 1) / TILE);
-    // as many 8-bit passes as the key needs, with the bits spread evenly over
-    // them (13 bits: 7 + 6): fewer digits per pass means longer runs per digit
-    // in each block's output, so better coalesced writes
-    const int total_bits = end_bit - begin_bit;
-    const int passes = (total_bits + 7) / 8;
-    for (int pass = 0, shift = begin_bit; pass < passes; ++pass) {
-        const int bits = (end_bit - shift + (passes - pass) - 1) / (passes - pass);
-        // the result buffer depends only on the number of passes, not on n
-        if (nb == 0) {
-            cur ^= 1;
-            shift += bits;
-            continue;
-        }
-        const uint32_t mask = (1u << bits) - 1u;
-        hipLaunchKernelGGL(k_radix_hist<TILE>, dim3(nb), dim3(kSortThreads), 0, st, keys[cur], sc, shift, mask, hist,
-                           hist_blocks);
-        hipLaunchKernelGGL(k_radix_scan<TILE>, dim3(1u << bits), dim3(256), 0, st, hist, hist_blocks, sc, digit_total);
-        // only the first pass may break ties: every later one keeps the order of the digits below
-        if (pass == 0 && !stable)
-            hipLaunchKernelGGL((k_radix_scatter<TILE, false>), dim3(nb), dim3(kSortThreads), 0, st, keys[cur],
-                               vals[cur], keys[cur ^ 1], vals[cur ^ 1], sc, shift, bits, hist, hist_blocks,
-                               digit_total);
-        else
-            hipLaunchKernelGGL((k_radix_scatter<TILE, true>), dim3(nb), dim3(kSortThreads), 0, st, keys[cur],
-                               vals[cur], keys[cur ^ 1], vals[cur ^ 1], sc, shift, bits, hist, hist_blocks,
-                               digit_total);
-        cur ^= 1;
-        shift += bits;
-    }
-}
-
-void radix_sort_u32(uint32_t *keys[2], uint32_t *vals[2], SortCount sc, uint64_t n_cap, int begin_bit, int end_bit,
-                    uint32_t *hist, uint32_t hist_blocks, uint32_t *digit_total, int &cur, bool stable,
-                    hipStream_t st) {
-    radix_passes<kSortTile>(keys, vals, sc, n_cap, begin_bit, end_bit, hist, hist_blocks, digit_total, cur, stable,
-                            st);
-}
-
-// ---------------------------------------------------------------------------
-// A3: emission.  The k-th visible item (ascending item id) owns pairs
-// [poff[k], poff[k] + count) in row-major order over its tile box.  A workgroup
-// writes one chunk of 1024 consecutive pair slots, 4 per thread (16-byte
-// stores, so the writes are coalesced and equal per thread however the tile
-// counts are spread): the chunk's items are staged in LDS and each thread finds
-// its pairs' item by binary search there.  The items' box words come from the
-// compaction pass (by visible index: coalesced loads).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kChunkThreads) void k_emit(const uint32_t *__restrict__ poff,
-                                                        const uint32_t *__restrict__ chunk_item,
-                                                        const uint4 *__restrict__ item_box,
-                                                        uint32_t *__restrict__ pkey, uint32_t *__restrict__ pval,
-                                                        uint32_t *__restrict__ pflag, const WsHeader *__restrict__ hdr) {
-    __shared__ ChunkItems ci;
-    if (hdr->overflow) return;
-    const uint32_t m = hdr->n_pairs, nvis = hdr->n_visible;
-    const uint32_t c0 = blockIdx.x * kChunkPairs;
-    if (c0 >= m) return;  // uniform per workgroup
-    const uint32_t cend = min(c0 + kChunkPairs, m);
-    uint32_t i_lo;
-    const uint32_t nloc = load_chunk_items(poff, chunk_item, item_box, blockIdx.x, m, nvis, ci, i_lo);
-    const uint32_t pb = c0 + threadIdx.x * kChunkPerThread;
-    if (pb >= cend) return;
-    pflag[pb / 4] = 0u;  // the four slots' "moments written" flags, set by the backward compositing
-    uint32_t key[kChunkPerThread], val[kChunkPerThread];
-    PairWalker pw;
-    pw.start(ci, nloc, pb);
-#pragma unroll
-    for (uint32_t u = 0; u < kChunkPerThread; ++u) {
-        if (u > 0) pw.next(ci, nloc, pb + u);
-        key[u] = pw.tile(ci);
-        val[u] = ci.item[pw.k];
-    }
-    if (pb + kChunkPerThread <= cend) {
-        *reinterpret_cast<uint4 *>(pkey + pb) = make_uint4(key[0], key[1], key[2], key[3]);
-        *reinterpret_cast<uint4 *>(pval + pb) = make_uint4(val[0], val[1], val[2], val[3]);
-    } else {
-        for (uint32_t u = 0; pb + u < cend; ++u) {
-            pkey[pb + u] = key[u];
-            pval[pb + u] = val[u];
+        unsigned long long mb = __ballot(big);
+        while (mb) {
+            const int j = __builtin_ctzll(mb);
+            mb &= mb - 1ull;
+            const uint32_t tj = __builtin_amdgcn_readlane(t_first, j), wj = __builtin_amdgcn_readlane(b.w, j);
+            const uint32_t zj = __builtin_amdgcn_readlane(b.z, j), ij = __builtin_amdgcn_readlane(b.item, j);
+            const uint32_t nj = __builtin_amdgcn_readlane(c, j);
+            for (uint32_t q = lane; q < nj; q += kWave) {
+                const uint32_t y = q / wj;
+                place(tj + y * nx + (q - y * wj), zj, ij);
+            }
         }
     }
 }
 
-void launch_emit_pairs(const uint32_t *poff, const uint32_t *chunk_item, const uint4 *item_box, uint64_t pair_grid,
-                       uint32_t *pkey, uint32_t *pval, uint32_t *pflag, const WsHeader *hdr, hipStream_t st) {
-    static_assert(kChunkPerThread == 4, "one 32-bit word of slot flags per thread");
-    const uint64_t chunks = chunk_count(pair_grid);
-    if (chunks == 0) return;
-    hipLaunchKernelGGL(k_emit, dim3((unsigned)chunks), dim3(kChunkThreads), 0, st, poff, chunk_item, item_box, pkey,
-                       pval, pflag, hdr);
+hipError_t bin_allow_lds(size_t bytes) {
+    if (bytes <= 65536) return hipSuccess;  // up to 64 KB of LDS need no leave
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bin_count),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBinMaxLds);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bin_place), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)kBinMaxLds);
+}
+
+BinPlan bin_plan(const ViewTable &vt, uint64_t cap) {
+    const uint64_t V = (uint64_t)vt.n_views;
+    const auto lds = [&](uint32_t bands) {
+        size_t most = 0;
+        for (int v = 0; v < vt.n_views; ++v) {
+            const size_t rows = ((size_t)vt.v[v].tiles_y + bands - 1) / bands;
+            most = std::max(most, 4 * (rows + 1) * ((size_t)vt.v[v].tiles_x + 1));
+        }
+        return most;
+    };
+    BinPlan p;
+    // (a row of the widest view, 4,096 tiles, and the one after it always fit)
+    p.count_bands = 1;
+    while (lds(p.count_bands) > kBinMaxLds) ++p.count_bands;
+    const uint64_t want = std::min<uint64_t>((cap + V * kBinBandPairs - 1) / (V * kBinBandPairs), 64);
+    p.place_bands = std::max(p.count_bands, (uint32_t)std::max<uint64_t>(want, 1));
+    p.lds_count = lds(p.count_bands);
+    p.lds_place = lds(p.place_bands);
+    return p;
+}
+
+void launch_bin_pairs(const ViewTable &vt, const BinPlan &plan, uint32_t G, const uint32_t *seg,
+                      const uint4 *item_box, uint32_t *counts, uint32_t *totals, uint2 *ranges, uint32_t *long_tiles,
+                      uint32_t *tile_order, unsigned long long *entries, uint32_t *pflag, WsHeader *hdr,
+                      hipStream_t st) {
+    const uint32_t V = (uint32_t)vt.n_views;
+    hipLaunchKernelGGL(k_bin_count, dim3(G * V * plan.count_bands), dim3(kBinThreads), plan.lds_count, st, vt, G,
+                       plan.count_bands, seg, item_box, counts, hdr);
+    hipLaunchKernelGGL(k_bin_scan, dim3((vt.total_tiles + kWave - 1) / kWave), dim3(kBinThreads), 0, st, counts, G, vt.total_tiles,
+                       totals);
+    hipLaunchKernelGGL(k_bin_place, dim3(G * V * plan.place_bands), dim3(kBinThreads), plan.lds_place, st, vt, G,
+                       plan.place_bands, seg, item_box, counts, totals, ranges, long_tiles, tile_order,
+                       entries, pflag, hdr);
 }
 
 // ---------------------------------------------------------------------------
 // A4c: per-tile depth order.  After the tile sort each tile's list holds its
 // items in no particular order; it is sorted here by the 64-bit key
 // (depth key << 32 | item), the unique order of the compositing definition.
+// The binning leaves those keys as the lists' entries, so a list is one
+// contiguous read; its sorted item ids go to pval.
 //
 // The network is bitonic with every comparator oriented low-to-high: each
 // merge starts with a "flip" that pairs mirrored positions, then half-cleaners
 // at halving distances.  Lists are padded to a power of two with keys above
 // every real key, which the network leaves at the end.
 //
-// A workgroup of four waves takes one tile.  A list of up to 1024 entries (most
-// tiles) is sorted by a bucket pass (below) when the depths allow, else by the
+// A workgroup of four waves takes one tile.  A list of up to kBlockBucketMax
+// entries is sorted by a bucket pass (below) when the depths allow, else by the
 // network in registers.  There each lane holds E (1..16) consecutive entries,
 // so comparators closer than E are register operations and the others pair
 // lane l with lane l ^ m, fetched with DPP or ds_swizzle (within 32 lanes) or
 // ds_bpermute, or, across waves, exchanged through LDS; a flip also mirrors
-// the register index.  Lists of 1025..4096 entries take the network with 16
+// the register index.  Lists up to 4096 entries take the network with 16
 // entries per lane; longer lists run the multi-workgroup path (below) or, when
 // it is off, the same network over global memory, one comparator per thread
 // and step.
 // ---------------------------------------------------------------------------
 typedef unsigned long long u64;
 constexpr u64 kPadKey = ~0ull;
-constexpr int kBlockBucketMax = 1024;  // bucket path: four waves, up to 4 entries per lane
+// Bucket path: four waves, up to 8 entries per lane.  (With up to 4, half
+// of the lists of the dense views, about 1,000 entries on average, fell to the
+// 4096-entry network: sorting 8 views of 1 M items took 307 us, 4 views of 700 k
+// 130 us; with 8, and the entries in one array, 81 us and 53 us.)
+constexpr int kBlockBucketMax = 2048;
 
 // v from lane (lane ^ M)
 template <int M>
@@ -675,32 +738,22 @@ __device__ __forceinline__ void register_bitonic(u64 (&key)[E], int lane, int wa
     if constexpr (K < 64 * E * W) register_bitonic<E, W, 2 * K>(key, lane, wave, xs);
 }
 
-// Sort list[0, len) of item ids by (zkey[item], item); the caller's threads
-// are `W` whole waves and 64 * E * W >= len.  The result goes back to list,
-// or, with out_hi non-null, as keys to out_hi (depth key) / out_lo (item).
+// Sort list[0, len) of keys; the caller's threads are `W` whole waves and
+// 64 * E * W >= len.  The items go to out, or, with out null, the keys back to
+// list (every entry is in registers before the first is written).
 template <int E, int W>
-__device__ __forceinline__ void sort_list_regs(uint32_t *__restrict__ list, uint32_t len,
-                                               const uint32_t *__restrict__ zkey, int lane, int wave, uint32_t *xs,
-                                               uint32_t *__restrict__ out_hi = nullptr,
-                                               uint32_t *__restrict__ out_lo = nullptr) {
+__device__ __forceinline__ void sort_list_regs(u64 *__restrict__ list, uint32_t len, uint32_t *__restrict__ out,
+                                               int lane, int wave, uint32_t *xs) {
     u64 key[E];
     const uint32_t base = (uint32_t)(wave * 64 + lane) * E;
 #pragma unroll
-    for (int r = 0; r < E; ++r) {
-        const uint32_t i = base + r;
-        const uint32_t item = i < len ? list[i] : 0u;
-        key[r] = i < len ? (((u64)zkey[item] << 32) | item) : kPadKey;
-    }
+    for (int r = 0; r < E; ++r) key[r] = base + r < len ? list[base + r] : kPadKey;
     register_bitonic<E, W>(key, lane, wave, xs);
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         if (base + r < len) {
-            if (out_hi) {
-                out_hi[base + r] = (uint32_t)(key[r] >> 32);
-                out_lo[base + r] = (uint32_t)key[r];
-            } else {
-                list[base + r] = (uint32_t)key[r];
-            }
+            if (out) out[base + r] = (uint32_t)key[r];
+            else list[base + r] = key[r];
         }
     }
 }
@@ -726,8 +779,8 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 }
 
 template <int E>
-__device__ bool bucket_sort_block(uint32_t *__restrict__ list, uint32_t len, const uint32_t *__restrict__ zkey,
-                                  u64 *buf, uint32_t *cnt, uint32_t *red /* [8] */) {
+__device__ bool bucket_sort_block(const u64 *__restrict__ list, uint32_t len, uint32_t *__restrict__ out, u64 *buf,
+                                  uint32_t *cnt, uint32_t *red /* [8] */) {
     constexpr uint32_t NB = 256 * E;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
@@ -737,9 +790,8 @@ __device__ bool bucket_sort_block(uint32_t *__restrict__ list, uint32_t len, con
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const uint32_t i = (uint32_t)r * 256 + tid;
-        const uint32_t item = i < len ? list[i] : 0u;
-        const uint32_t z = i < len ? zkey[item] : 0u;
-        key[r] = ((u64)z << 32) | item;
+        key[r] = i < len ? list[i] : 0ull;
+        const uint32_t z = (uint32_t)(key[r] >> 32);
         if (i < len) zmin = min(zmin, z), zmax = max(zmax, z);
     }
     zmin = wave_min_u32(zmin);
@@ -794,33 +846,25 @@ __device__ bool bucket_sort_block(uint32_t *__restrict__ list, uint32_t len, con
             const uint32_t s0 = sc[r] >> 16, n = sc[r] & 0xffffu;
             uint32_t rank = 0;
             for (uint32_t q = 0; q < n; ++q) rank += buf[s0 + q] < key[r] ? 1u : 0u;
-            list[s0 + rank] = (uint32_t)key[r];
+            out[s0 + rank] = (uint32_t)key[r];
         }
     }
     return true;
 }
 
 template <int E>
-__device__ __forceinline__ void sort_list_block(uint32_t *__restrict__ list, uint32_t len,
-                                                const uint32_t *__restrict__ zkey, u64 *buf, uint32_t *cnt,
-                                                uint32_t *red, uint32_t *xs) {
-    if (!bucket_sort_block<E>(list, len, zkey, buf, cnt, red)) {
+__device__ __forceinline__ void sort_list_block(u64 *__restrict__ list, uint32_t len, uint32_t *__restrict__ out,
+                                                u64 *buf, uint32_t *cnt, uint32_t *red, uint32_t *xs) {
+    if (!bucket_sort_block<E>(list, len, out, buf, cnt, red)) {
         __syncthreads();  // the network reuses the exchange area
-        sort_list_regs<E, 4>(list, len, zkey, threadIdx.x & 63, threadIdx.x >> 6, xs);
+        sort_list_regs<E, 4>(list, len, out, threadIdx.x & 63, threadIdx.x >> 6, xs);
     }
 }
 
 // The same network over global memory, for lists beyond kGroupSortMax
 // (comparators with an entry past the end are skipped: those entries act as
 // +infinity).  Runs on the whole workgroup.
-__device__ void sort_list_global(uint32_t *__restrict__ list, uint32_t len, const uint32_t *__restrict__ zkey,
-                                 uint32_t *__restrict__ hi, uint32_t *__restrict__ lo) {
-    for (uint32_t i = threadIdx.x; i < len; i += blockDim.x) {
-        const uint32_t item = list[i];
-        hi[i] = zkey[item];
-        lo[i] = item;
-    }
-    __syncthreads();
+__device__ void sort_list_global(u64 *__restrict__ list, uint32_t len, uint32_t *__restrict__ out) {
     uint32_t p2 = 1;
     while (p2 < len) p2 <<= 1;
     for (uint32_t k = 2; k <= p2; k <<= 1) {
@@ -829,14 +873,14 @@ __device__ void sort_list_global(uint32_t *__restrict__ list, uint32_t len, cons
                 const uint32_t a = ((c & ~(j - 1)) << 1) | (c & (j - 1));
                 const uint32_t b = j == (k >> 1) ? (a ^ (k - 1)) : (a + j);
                 if (b < len) {
-                    const uint32_t ha = hi[a], hb = hi[b], la = lo[a], lb = lo[b];
-                    if (ha > hb || (ha == hb && la > lb)) hi[a] = hb, hi[b] = ha, lo[a] = lb, lo[b] = la;
+                    const u64 x = list[a], y = list[b];
+                    if (x > y) list[a] = y, list[b] = x;
                 }
             }
             __syncthreads();
         }
     }
-    for (uint32_t i = threadIdx.x; i < len; i += blockDim.x) list[i] = lo[i];
+    for (uint32_t i = threadIdx.x; i < len; i += blockDim.x) out[i] = (uint32_t)list[i];
     __syncthreads();
 }
 
@@ -951,14 +995,12 @@ __device__ void file_schedule(const uint2 *__restrict__ ranges, const uint32_t *
 }
 
 __global__ __launch_bounds__(256) void k_tile_depth_sort(const uint2 *__restrict__ ranges, uint32_t total_tiles,
-                                                         uint32_t *__restrict__ pval, const uint32_t *__restrict__ zkey,
-                                                         uint32_t *__restrict__ x_hi, uint32_t *__restrict__ x_lo,
-                                                         uint32_t *__restrict__ y_hi, uint32_t *__restrict__ y_lo,
+                                                         u64 *__restrict__ entries, uint32_t *__restrict__ pval,
                                                          const uint32_t *__restrict__ long_tiles, int passes,
                                                          uint32_t *__restrict__ sched,
                                                          const uint32_t *__restrict__ cost_hint,
                                                          const WsHeader *__restrict__ hdr) {
-    __shared__ u64 s_buf[kGroupSortMax / 2];  // bucket entries; the network's exchange area (16 KB)
+    __shared__ u64 s_buf[kBlockBucketMax];  // bucket entries; the network's exchange area (16 KB)
     __shared__ uint32_t s_cnt[kBlockBucketMax];
     __shared__ uint32_t s_red[8];
     if (hdr->overflow) return;  // uniform (no schedule either: the fused compositing falls back to tile order)
@@ -973,7 +1015,7 @@ __global__ __launch_bounds__(256) void k_tile_depth_sort(const uint2 *__restrict
     }
     const uint32_t bid = blockIdx.x - (sched ? 1u : 0u);
     if (bid >= total_tiles) {
-        // a window of a long list, sorted into a run of the first merge pass's input
+        // a window of a long list, sorted in place into a run of the first merge pass's input
         if (!multi) return;
         uint32_t t, w;
         if (!long_tile_window(long_tiles, long_tiles + kMaxLongTiles, hdr->n_long, bid - total_tiles, t, w))
@@ -981,36 +1023,40 @@ __global__ __launch_bounds__(256) void k_tile_depth_sort(const uint2 *__restrict
         const uint2 rg = ranges[t];
         const uint32_t off = rg.x + w * kLongWindow;
         const uint32_t n = min(kLongWindow, rg.y - off);
-        uint32_t *oh = (passes & 1) ? x_hi : y_hi, *ol = (passes & 1) ? x_lo : y_lo;
-        sort_list_regs<16, 4>(pval + off, n, zkey, lane, wave, xs, oh + off, ol + off);
+        sort_list_regs<16, 4>(entries + off, n, nullptr, lane, wave, xs);
         return;
     }
     const uint32_t t = bid;
     const uint2 rg = ranges[t];
     const uint32_t len = rg.y - rg.x;
-    uint32_t *list = pval + rg.x;
-    if (len <= 1) return;
+    u64 *list = entries + rg.x;
+    uint32_t *out = pval + rg.x;
+    if (len <= 1) {
+        if (len == 1 && threadIdx.x == 0) out[0] = (uint32_t)list[0];
+        return;
+    }
     if (len <= 256)
-        sort_list_block<1>(list, len, zkey, s_buf, s_cnt, s_red, xs);
+        sort_list_block<1>(list, len, out, s_buf, s_cnt, s_red, xs);
     else if (len <= 512)
-        sort_list_block<2>(list, len, zkey, s_buf, s_cnt, s_red, xs);
+        sort_list_block<2>(list, len, out, s_buf, s_cnt, s_red, xs);
+    else if (len <= 1024)
+        sort_list_block<4>(list, len, out, s_buf, s_cnt, s_red, xs);
     else if (len <= (uint32_t)kBlockBucketMax)
-        sort_list_block<4>(list, len, zkey, s_buf, s_cnt, s_red, xs);
+        sort_list_block<8>(list, len, out, s_buf, s_cnt, s_red, xs);
     else if (len <= (uint32_t)kGroupSortMax)
-        sort_list_regs<16, 4>(list, len, zkey, lane, wave, xs);
+        sort_list_regs<16, 4>(list, len, out, lane, wave, xs);
     else if (!multi || (uint64_t)len > ((uint64_t)kLongWindow << passes))
-        sort_list_global(list, len, zkey, x_hi + rg.x, x_lo + rg.x);
+        sort_list_global(list, len, out);
     // else: the window workgroups and the merge passes sort it
 }
 
-void launch_tile_depth_sort(const uint2 *ranges, uint32_t total_tiles, uint32_t *pval, const uint32_t *zkey,
-                            uint32_t *x_hi, uint32_t *x_lo, uint32_t *y_hi, uint32_t *y_lo,
+void launch_tile_depth_sort(const uint2 *ranges, uint32_t total_tiles, unsigned long long *entries, uint32_t *pval,
                             const uint32_t *long_tiles, int long_passes, uint32_t chunk_wgs, uint32_t *sched,
                             const uint32_t *cost_hint, const WsHeader *hdr, hipStream_t st) {
     if (total_tiles == 0) return;
     const uint32_t grid = total_tiles + (long_passes > 0 ? chunk_wgs : 0u) + (sched ? 1u : 0u);
-    hipLaunchKernelGGL(k_tile_depth_sort, dim3(grid), dim3(256), 0, st, ranges, total_tiles, pval, zkey, x_hi, x_lo,
-                       y_hi, y_lo, long_tiles, long_passes, sched, cost_hint, hdr);
+    hipLaunchKernelGGL(k_tile_depth_sort, dim3(grid), dim3(256), 0, st, ranges, total_tiles, entries, pval, long_tiles,
+                       long_passes, sched, cost_hint, hdr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1021,21 +1067,16 @@ void launch_tile_depth_sort(const uint2 *ranges, uint32_t total_tiles, uint32_t 
 // staged in LDS, and each thread merges 8 outputs from its own crossing.
 // Keys are unique, so every split is unambiguous.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ u64 load_key(const uint32_t *__restrict__ hi, const uint32_t *__restrict__ lo, uint32_t i) {
-    return ((u64)hi[i] << 32) | lo[i];
-}
-
 // Number of elements of A among the first d outputs of merge(A, B): the
 // smallest a in [max(0, d - nB), min(d, nA)] with not (A[a] < B[d - 1 - a]).
 // One whole wave calls it.
-__device__ uint32_t wave_merge_split(const uint32_t *a_hi, const uint32_t *a_lo, uint32_t nA, const uint32_t *b_hi,
-                                     const uint32_t *b_lo, uint32_t nB, uint32_t d, int lane) {
+__device__ uint32_t wave_merge_split(const u64 *a, uint32_t nA, const u64 *b, uint32_t nB, uint32_t d, int lane) {
     uint32_t lo = d > nB ? d - nB : 0u, hi = min(d, nA);
     while (lo < hi) {
         const uint32_t step = (hi - lo + 63) / 64;
         const uint32_t m = lo + (uint32_t)lane * step;
         const bool probe = m < hi;
-        const bool before = probe && load_key(a_hi, a_lo, m) < load_key(b_hi, b_lo, d - 1 - m);
+        const bool before = probe && a[m] < b[d - 1 - m];
         const uint32_t c = (uint32_t)__popcll(__ballot(before));  // probes before the split: a prefix of the lanes
         const uint32_t nlo = c > 0 ? lo + (c - 1) * step + 1 : lo;
         const uint32_t nhi = min(hi, lo + c * step);
@@ -1048,9 +1089,8 @@ __device__ uint32_t wave_merge_split(const uint32_t *a_hi, const uint32_t *a_lo,
 __global__ __launch_bounds__(256) void k_long_merge(const uint2 *__restrict__ ranges,
                                                     const uint32_t *__restrict__ long_tiles,
                                                     const WsHeader *__restrict__ hdr, int p, int passes,
-                                                    const uint32_t *__restrict__ src_hi,
-                                                    const uint32_t *__restrict__ src_lo, uint32_t *__restrict__ dst_hi,
-                                                    uint32_t *__restrict__ dst_lo, uint32_t *__restrict__ pval) {
+                                                    const u64 *__restrict__ src, u64 *__restrict__ dst,
+                                                    uint32_t *__restrict__ pval) {
     __shared__ u64 sA[kMergeWindow], sB[kMergeWindow];
     __shared__ uint32_t s_split[2];
     if (hdr->overflow || !long_path_on(hdr, passes)) return;  // uniform
@@ -1063,20 +1103,19 @@ __global__ __launch_bounds__(256) void k_long_merge(const uint2 *__restrict__ ra
     const uint32_t R = (uint32_t)R64;
     const uint32_t base = (uint32_t)((o0 / (2 * R64)) * (2 * R64));
     const uint32_t nA = min(R, L - base), nB = L - base > R ? min(R, L - base - R) : 0u;
-    const uint32_t *ah = src_hi + rg.x + base, *al = src_lo + rg.x + base;
-    const uint32_t *bh = ah + R, *bl = al + R;
+    const u64 *pa = src + rg.x + base, *pb = pa + R;
     const bool last = p == passes - 1;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t d0 = o0 - base, d1 = o1 - base;
     if (wave < 2) {
-        const uint32_t a = wave_merge_split(ah, al, nA, bh, bl, nB, wave == 0 ? d0 : d1, (int)lane);
+        const uint32_t a = wave_merge_split(pa, nA, pb, nB, wave == 0 ? d0 : d1, (int)lane);
         if (lane == 0) s_split[wave] = a;
     }
     __syncthreads();
     const uint32_t a0 = s_split[0], a1 = s_split[1], b0 = d0 - a0, b1 = d1 - a1;
     const uint32_t na = a1 - a0, nb = b1 - b0;
-    for (uint32_t k = tid; k < na; k += 256) sA[k] = load_key(ah, al, a0 + k);
-    for (uint32_t k = tid; k < nb; k += 256) sB[k] = load_key(bh, bl, b0 + k);
+    for (uint32_t k = tid; k < na; k += 256) sA[k] = pa[a0 + k];
+    for (uint32_t k = tid; k < nb; k += 256) sB[k] = pb[b0 + k];
     __syncthreads();
     constexpr uint32_t kPer = kMergeWindow / 256;
     const uint32_t q = tid * kPer;
@@ -1096,21 +1135,17 @@ __global__ __launch_bounds__(256) void k_long_merge(const uint2 *__restrict__ ra
         const u64 v = take_b ? sB[j] : sA[i];
         i += take_b ? 0u : 1u;
         j += take_b ? 1u : 0u;
-        if (last) {
-            pval[out + k] = (uint32_t)v;
-        } else {
-            dst_hi[out + k] = (uint32_t)(v >> 32);
-            dst_lo[out + k] = (uint32_t)v;
-        }
+        if (last) pval[out + k] = (uint32_t)v;
+        else dst[out + k] = v;
     }
 }
 
 void launch_long_merge(const uint2 *ranges, const uint32_t *long_tiles, const WsHeader *hdr, int p, int long_passes,
-                       const uint32_t *src_hi, const uint32_t *src_lo, uint32_t *dst_hi, uint32_t *dst_lo,
-                       uint32_t *pval, uint32_t merge_wgs, hipStream_t st) {
+                       const unsigned long long *src, unsigned long long *dst, uint32_t *pval, uint32_t merge_wgs,
+                       hipStream_t st) {
     if (merge_wgs == 0) return;
     hipLaunchKernelGGL(k_long_merge, dim3(merge_wgs), dim3(256), 0, st, ranges, long_tiles, hdr, p, long_passes,
-                       src_hi, src_lo, dst_hi, dst_lo, pval);
+                       src, dst, pval);
 }
 
 // Tile id at every position of the sorted pairs (the export of the lists).
@@ -1127,84 +1162,6 @@ void launch_expand_ranges(const uint2 *ranges, uint32_t total_tiles, uint32_t *p
                           hipStream_t st) {
     if (total_tiles == 0) return;
     hipLaunchKernelGGL(k_expand_ranges, dim3(total_tiles), dim3(256), 0, st, ranges, total_tiles, pair_tiles, hdr);
-}
-
-// ---------------------------------------------------------------------------
-// A5: per-tile [start, end) over the sorted pairs.  Where the tile key changes
-// (and once more at i = m) the previous tile is closed, the new one opened, and
-// the tiles in between marked empty, so no pre-clearing pass is needed.  Each
-// thread takes kRangeRun consecutive pairs (16-byte loads).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void tile_boundary(const uint32_t *__restrict__ pkey, uint2 *__restrict__ ranges,
-                                              uint32_t *__restrict__ long_tiles, WsHeader *__restrict__ hdr,
-                                              uint64_t i, uint64_t m, int64_t prev, int64_t t) {
-    for (int64_t u = prev + 1; u < t; ++u) ranges[u] = make_uint2((uint32_t)i, (uint32_t)i);
-    if (i < m) ranges[t].x = (uint32_t)i;
-    if (i == 0) return;
-    ranges[prev].y = (uint32_t)i;
-    // a list longer than kGroupSortMax: find where it starts (the keys are
-    // sorted) and register it for the multi-workgroup sort
-    if (i > (uint64_t)kGroupSortMax && pkey[i - kGroupSortMax - 1] == (uint32_t)prev) {
-        uint64_t lo = 0, hi = i - kGroupSortMax - 1;  // first position holding prev lies in [lo, hi]
-        while (lo < hi) {
-            const uint64_t mid = (lo + hi) >> 1;
-            if (pkey[mid] < (uint32_t)prev) lo = mid + 1;
-            else hi = mid;
-        }
-        const uint32_t len = (uint32_t)(i - lo);
-        const uint32_t k = atomicAdd(&hdr->n_long, 1u);
-        if (k < kMaxLongTiles) long_tiles[k] = (uint32_t)prev;
-        atomicAdd(&hdr->long_pairs, len);
-        atomicMax(&hdr->max_long, len);
-    }
-}
-
-constexpr int kRangeRun = 4;
-__global__ __launch_bounds__(256) void k_tile_ranges(const uint32_t *__restrict__ pkey, uint64_t cap,
-                                                     uint2 *__restrict__ ranges, uint32_t total_tiles,
-                                                     uint32_t *__restrict__ long_tiles,
-                                                     uint32_t *__restrict__ tile_order, WsHeader *__restrict__ hdr) {
-    if (blockIdx.x == 0 && threadIdx.x < kCostBuckets) tile_order[threadIdx.x] = 0u;  // filled by the forward
-    const uint64_t i0 = ((uint64_t)blockIdx.x * 256 + threadIdx.x) * kRangeRun;
-    // a whole run inside the buffer is loaded while the pair count is still
-    // in flight (entries past the count are ignored below)
-    uint32_t k[kRangeRun];
-    const bool whole = i0 + kRangeRun <= cap;
-    if (whole) {
-#pragma unroll
-        for (int q = 0; q < kRangeRun / 4; ++q) {
-            const uint4 kk = *reinterpret_cast<const uint4 *>(pkey + i0 + 4 * q);
-            k[4 * q] = kk.x, k[4 * q + 1] = kk.y, k[4 * q + 2] = kk.z, k[4 * q + 3] = kk.w;
-        }
-    }
-    const uint32_t prev_key = i0 > 0 && i0 <= cap ? pkey[i0 - 1] : 0u;
-    const uint64_t m = hdr->overflow ? 0ull : (uint64_t)hdr->n_pairs;
-    if (i0 > m) return;
-    if (!whole || i0 + kRangeRun > m) {
-#pragma unroll
-        for (int j = 0; j < kRangeRun; ++j) k[j] = i0 + j < m ? pkey[i0 + j] : total_tiles;
-    }
-    // positions of this run where the tile changes (and i = m)
-    uint32_t edges = 0;
-    int64_t prev = i0 > 0 ? (int64_t)prev_key : -1;
-#pragma unroll
-    for (int j = 0; j < kRangeRun; ++j) {
-        const int64_t t = i0 + j <= m ? (int64_t)k[j] : prev;  // (k[j] = total_tiles at i = m)
-        edges |= (t != prev ? 1u : 0u) << j;
-        prev = t;
-    }
-    while (edges) {
-        const int j = __builtin_ctz(edges);
-        edges &= edges - 1;
-        // k[j] and the key before it, selected without indexing the array by j
-        int64_t t = 0, before = i0 > 0 ? (int64_t)prev_key : -1;
-#pragma unroll
-        for (int q = 0; q < kRangeRun; ++q) {
-            if (q == j) t = (int64_t)k[q];
-            if (q + 1 == j) before = (int64_t)k[q];
-        }
-        tile_boundary(pkey, ranges, long_tiles, hdr, i0 + j, m, before, t);
-    }
 }
 
 __global__ __launch_bounds__(256) void k_fill_u32(uint32_t *__restrict__ p, uint32_t value, uint64_t n) {
@@ -1235,14 +1192,6 @@ __global__ void k_reset_queue(WsHeader *h, int which) { h->queue[which] = 0u; }
 
 void launch_reset_queue(WsHeader *h, int which, hipStream_t st) {
     hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(1), 0, st, h, which);
-}
-
-void launch_tile_ranges(const uint32_t *pkey, uint64_t cap, uint2 *ranges, uint32_t total_tiles,
-                        uint32_t *long_tiles, uint32_t *tile_order, WsHeader *hdr, hipStream_t st) {
-    if (total_tiles == 0) return;
-    const uint64_t groups = cap / kRangeRun + 1;  // positions 0..cap, kRangeRun per thread
-    hipLaunchKernelGGL(k_tile_ranges, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, pkey, cap, ranges,
-                       total_tiles, long_tiles, tile_order, hdr);
 }
 
 }  // namespace gsr
