@@ -94,7 +94,7 @@ gsr::WsLayout make_layout(uint64_t n, const gsr::ViewTable &vt, uint64_t cap) {
     L.items = items;
     L.cap = cap;
     L.chunks = chunk_count(cap);
-    L.pose_blocks = (uint32_t)std::max<uint64_t>(1, (n + kProjThreads - 1) / kProjThreads);
+    L.pose_blocks = project_bwd_blocks(n, vt.n_views);
     const uint64_t scan_blocks = std::max<uint64_t>(1, (items + kScanTile - 1) / kScanTile);
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -281,10 +281,11 @@ int backward_tail(const gsr_gaussians *g, const gsr::ViewTable &vt, const float 
     mark.begin(GSR_STAGE_PROJECT_BWD);
     launch_pair_reduce(p.poff, p.chunk_item, cap, p.vis, p.pflag, p.partial, p.screen, p.carry, p.hdr, st);
     launch_project_bwd(*g, vt, world_to_cam, (uint64_t)g->n, p.rec, p.ioff, p.count, p.vis, p.hdr, p.screen, p.carry, *grads,
-                       p.pose_part, L.pose_blocks, p.view_seg, vt.total_tiles == 0, st);
+                       p.pose_part, L.pose_blocks, p.view_seg, st);
     if (g->n == 0)  // no Gaussian wrote a partial: the pose gradient is zero
         launch_fill_u32(reinterpret_cast<uint32_t *>(p.pose_part), 0u, 12ull * vt.n_views * L.pose_blocks, st);
-    launch_pose_finalize(vt, world_to_cam, p.pose_part, L.pose_blocks, p.hdr, p.view_seg, vt.total_tiles != 0,
+    launch_pose_finalize(vt, world_to_cam, p.pose_part, L.pose_blocks, p.hdr, p.view_seg,
+                         project_bwd_groups((uint64_t)g->n, vt.n_views) == 0,
                          dL_dworld_to_cam, dL_dtwist, st);
     mark.end(GSR_STAGE_PROJECT_BWD);
     return check_hip(hipGetLastError(), "backward launch");

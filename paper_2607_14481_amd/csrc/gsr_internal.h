@@ -233,13 +233,18 @@ void launch_pair_reduce(const uint32_t *poff, const uint32_t *chunk_item, uint64
                         const uint32_t *pflag, const float *partial, float4 *screen, float *carry, const WsHeader *hdr,
                         hipStream_t st);
 
-// zero_unseen: also write the zero rows of the Gaussians no view saw (when the
-// backward compositing did not).  seg: each view's first visible index, and
-// their number (as the compaction wrote them).
+// The gradient rows of Gaussians no view saw are left as they are (the backward
+// compositing zeroed them).  seg: each view's first visible index, and their
+// number (as the compaction wrote them).  project_bwd_groups: groups of
+// Gaussians per workgroup of the multi-view form, 0 for a launch per view;
+// project_bwd_blocks: workgroups, each with a partial of every view's pose
+// gradient.
+uint32_t project_bwd_groups(uint64_t n, int n_views);
+uint32_t project_bwd_blocks(uint64_t n, int n_views);
 void launch_project_bwd(const gsr_gaussians &g, const ViewTable &vt, const float *w2c, uint64_t n,
                         const Rec *rec, const uint32_t *ioff, const uint32_t *count, const uint32_t *vis, const WsHeader *hdr,
                         const float4 *screen, const float *carry, const gsr_gaussian_grads &gr, float *pose_part,
-                        uint32_t pose_blocks, const uint32_t *seg, bool zero_unseen, hipStream_t st);
+                        uint32_t pose_blocks, const uint32_t *seg, hipStream_t st);
 // dense: the partials come from the per-view launches over the visible items
 // (only the blocks with items are summed; seg as for launch_project_bwd).
 void launch_pose_finalize(const ViewTable &vt, const float *w2c, const float *pose_part, uint32_t pose_blocks,

@@ -1,14 +1,14 @@
 // gsr_project.hip -- per-Gaussian stages of the rasterizer on gfx950:
 //   A1 k_project_fwd  : EWA projection, SH colour, alpha >= 1/255 box, tile count
-//   A8+A9 k_project_bwd: per-Gaussian sum of the per-pair screen-space
-//                        gradients, chain rule to every parameter, per-block
-//                        partial sums of each view's pose gradient
+//   A8 k_pair_reduce : per-item sum of the per-pair screen-space gradients
+//   A9 k_project_bwd_vis, k_project_bwd_multi: chain rule to every parameter,
+//                        per-block partial sums of each view's pose gradient
 //   k_pose_finalize    : fixed-order sum of those partials, 4x4 and 6-DoF twist
 //
-// The geometric part of A1 runs in FP64: it is HBM-bound (~100-300 bytes per
-// Gaussian against a few hundred flops), so double precision costs nothing
-// measurable and keeps the centre, box and depth key within an ulp of the exact
-// values (world coordinates of tens of metres otherwise cost ~1e-4 px).
+// A1 runs in FP64, which keeps the centre, box and depth key within an ulp of
+// the exact values (world coordinates of tens of metres otherwise cost ~1e-4 px).
+#include <algorithm>
+
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -136,129 +136,176 @@ __device__ __forceinline__ void load_pose(const float *__restrict__ w2c, int v, 
 }
 
 // ---------------------------------------------------------------------------
-// A1: projection forward.  One thread per (view, Gaussian) item, item = v n + i.
+// A1: projection forward.  One thread per Gaussian and slice of the views
+// (item = v n + i): what does not depend on the view is formed once for them.
+// Slices: as few as keep the chip filled.
+//
+// STAGE (a workgroup has several views): the SH rows go through LDS, loaded
+// with row-contiguous accesses when a view first sees the Gaussian.  Read by
+// each lane from its own row instead, an access of a wave touches 64 cache
+// lines, and 12 such accesses per view bound the kernel: 231 us for 8 views of
+// 1 M Gaussians (2.9 M visible items), staged 184 us; 4 views of 700 k (2.4 M
+// visible) 146 and 102 us.  A thread per item, with every view forming the
+// covariance again, took 267 us and 160 us.  With one view the rows are read
+// once, and the waves that the LDS costs count for more: 1 M Gaussians (341 k
+// visible) 45 us from the rows, 51 us staged.  The doubles are bound by FP64
+// issue next: quotients are one reciprocal and products.
 // ---------------------------------------------------------------------------
-template <int DEG>
-__global__ __launch_bounds__(kProjThreads) void k_project_fwd(gsr_gaussians g, ViewTable vt,
-                                                              const float *__restrict__ w2c, uint64_t n,
-                                                              Rec *__restrict__ rec,
-                                                              uint4 *__restrict__ box,
-                                                              uint32_t *__restrict__ count,
-                                                              WsHeader *__restrict__ hdr, uint32_t cap,
-                                                              const int64_t *__restrict__ active) {
+constexpr uint64_t kProjBlocks = 2048;  // workgroups that keep the chip filled (8 per compute unit)
+
+template <int DEG, bool STAGE>
+__global__ __launch_bounds__(kProjThreads, STAGE ? 3 : 4) void k_project_fwd(
+    gsr_gaussians g, ViewTable vt, const float *__restrict__ w2c, uint64_t n, Rec *__restrict__ rec,
+    uint4 *__restrict__ box, uint32_t *__restrict__ count, WsHeader *__restrict__ hdr, uint32_t cap,
+    const int64_t *__restrict__ active) {
     constexpr int K = (DEG + 1) * (DEG + 1);
-    if (blockIdx.x == 0 && threadIdx.x < sizeof(WsHeader) / 4) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < sizeof(WsHeader) / 4) {
         // a fresh header for this forward (read first by the visible-item scan)
         reinterpret_cast<uint32_t *>(hdr)[threadIdx.x] = threadIdx.x == offsetof(WsHeader, pair_capacity) / 4 ? cap : 0u;
     }
-    const uint64_t item = (uint64_t)blockIdx.x * kProjThreads + threadIdx.x;
-    if (item >= n * (uint64_t)vt.n_views) return;
-    const int v = (int)(item / n);
-    const uint64_t i = item - (uint64_t)v * n;
-    if (active && (int64_t)i >= *active) {  // beyond the device-given count: culled, nothing read
-        count[item] = 0;
-        return;
+    // SH rows of the wave's Gaussians, staged when a view first sees them
+    constexpr bool kVec = (3 * K) % 4 == 0;
+    constexpr int kUnits = kVec ? 3 * K / 4 : 3 * K;              // accesses per row
+    constexpr int kRow = kVec && kUnits % 2 == 0 ? 3 * K + 4 : 3 * K;  // odd in accesses: no bank conflicts
+    __shared__ __align__(16) float s_sh[kProjThreads / kWave][STAGE ? kWave * kRow : 4];
+    __shared__ uint8_t s_list[kProjThreads / kWave][kWave];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t i = (uint64_t)blockIdx.x * kProjThreads + threadIdx.x, first = i - lane;
+    if (first >= n) return;  // the whole wave
+    const int v0 = (int)(blockIdx.y * vt.n_views / gridDim.y), v1 = (int)((blockIdx.y + 1) * vt.n_views / gridDim.y);
+    // Gaussians beyond the device-given count are culled, nothing of them is read
+    bool bad = i >= n || (active && (int64_t)i >= *active);  // never visible
+    unsigned long long staged = 0ull;                        // (uniform)
+    float *rows = s_sh[wave];
+    double mx = 0.0, my = 0.0, mz = 0.0;
+    if (!bad) mx = g.means[3 * i + 0], my = g.means[3 * i + 1], mz = g.means[3 * i + 2];
+    double Sg[6] = {}, k2 = 0.0;
+    float op = 0.f;
+    bool have = false;  // what no view changes is formed
+    for (int v = v0; v < v1; ++v) {
+        const ViewInfo &cam = vt.v[v];
+        const uint64_t item = (uint64_t)v * n + i;
+        float Wf[9], tf[3];
+        load_pose(w2c, v, Wf, tf);
+        const double px = (double)Wf[0] * mx + (double)Wf[1] * my + (double)Wf[2] * mz + (double)tf[0];
+        const double py = (double)Wf[3] * mx + (double)Wf[4] * my + (double)Wf[5] * mz + (double)tf[1];
+        const double pz = (double)Wf[6] * mx + (double)Wf[7] * my + (double)Wf[8] * mz + (double)tf[2];
+        uint32_t cnt = 0, bx = 0, by = 0;
+        double u = 0.0, vv = 0.0, ca = 0.0, cb = 0.0, cc = 0.0, det = 1.0;
+        do {
+            if (!(pz > (double)cam.near_plane) || bad) break;
+            if (!have) {
+                const float4 qf = reinterpret_cast<const float4 *>(g.quats)[i];
+                op = g.opacities[i];
+                const double qn =
+                    sqrt((double)qf.x * qf.x + (double)qf.y * qf.y + (double)qf.z * qf.z + (double)qf.w * qf.w);
+                bad = !(qn > 0.0) || !(op >= kAlphaMin);
+                if (bad) break;
+                const double iqn = 1.0 / qn;
+                double R[9];
+                quat_rot<double>(qf.x * iqn, qf.y * iqn, qf.z * iqn, qf.w * iqn, R);
+                const double s0 = exp((double)g.log_scales[3 * i + 0]);
+                const double s1 = exp((double)g.log_scales[3 * i + 1]);
+                const double s2 = exp((double)g.log_scales[3 * i + 2]);
+                // M = R diag(s); Sigma = M M^T (symmetric: 00, 01, 02, 11, 12, 22)
+                const double M[9] = {R[0] * s0, R[1] * s1, R[2] * s2, R[3] * s0, R[4] * s1,
+                                     R[5] * s2, R[6] * s0, R[7] * s1, R[8] * s2};
+#pragma unroll
+                for (int a = 0, e = 0; a < 3; ++a)
+#pragma unroll
+                    for (int b = a; b < 3; ++b, ++e)
+                        Sg[e] = M[3 * a] * M[3 * b] + M[3 * a + 1] * M[3 * b + 1] + M[3 * a + 2] * M[3 * b + 2];
+                k2 = 2.0 * log(255.0 * (double)op);
+                have = true;
+            }
+            const double iz = 1.0 / pz;
+            const double rx = px * iz, ry = py * iz;
+            const double rxc = fmin(fmax(rx, -(double)cam.limx), (double)cam.limx);
+            const double ryc = fmin(fmax(ry, -(double)cam.limy), (double)cam.limy);
+            const double j00 = cam.fx * iz, j02 = -j00 * rxc;
+            const double j11 = cam.fy * iz, j12 = -j11 * ryc;
+            // T = J W (2x3)
+            double T0[3], T1[3];
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                T0[b] = j00 * Wf[b] + j02 * Wf[6 + b];
+                T1[b] = j11 * Wf[3 + b] + j12 * Wf[6 + b];
+            }
+            const double TS0[3] = {T0[0] * Sg[0] + T0[1] * Sg[1] + T0[2] * Sg[2],
+                                   T0[0] * Sg[1] + T0[1] * Sg[3] + T0[2] * Sg[4],
+                                   T0[0] * Sg[2] + T0[1] * Sg[4] + T0[2] * Sg[5]};
+            const double TS1[3] = {T1[0] * Sg[0] + T1[1] * Sg[1] + T1[2] * Sg[2],
+                                   T1[0] * Sg[1] + T1[1] * Sg[3] + T1[2] * Sg[4],
+                                   T1[0] * Sg[2] + T1[1] * Sg[4] + T1[2] * Sg[5]};
+            ca = TS0[0] * T0[0] + TS0[1] * T0[1] + TS0[2] * T0[2] + (double)kLowPass;
+            cb = TS0[0] * T1[0] + TS0[1] * T1[1] + TS0[2] * T1[2];
+            cc = TS1[0] * T1[0] + TS1[1] * T1[1] + TS1[2] * T1[2] + (double)kLowPass;
+            det = ca * cc - cb * cb;
+            if (!(det > 0.0)) break;
+            u = cam.fx * rx + cam.cx, vv = cam.fy * ry + cam.cy;
+            // exact box of the alpha >= 1/255 ellipse, pixel centres at i + 1/2
+            const double ex = sqrt(k2 * ca), ey = sqrt(k2 * cc);
+            double x0 = ceil(u - ex - 0.5), x1 = floor(u + ex - 0.5);
+            double y0 = ceil(vv - ey - 0.5), y1 = floor(vv + ey - 0.5);
+            x0 = fmax(x0, 0.0);
+            y0 = fmax(y0, 0.0);
+            x1 = fmin(x1, (double)(cam.width - 1));
+            y1 = fmin(y1, (double)(cam.height - 1));
+            if (!(x0 <= x1) || !(y0 <= y1)) break;
+            const uint32_t ix0 = (uint32_t)x0, ix1 = (uint32_t)x1, iy0 = (uint32_t)y0, iy1 = (uint32_t)y1;
+            const uint32_t tx = ix0 / kTileW, ty = iy0 / vt.tile_h;
+            const uint32_t tw = ix1 / kTileW - tx + 1, th = iy1 / vt.tile_h - ty + 1;
+            cnt = tw * th;
+            box[item] = make_uint4(pack_u16(tx, ty), pack_u16(tw, th), __float_as_uint((float)pz), 0u);
+            bx = pack_u16(ix0, ix1);
+            by = pack_u16(iy0, iy1);
+        } while (0);
+        if (i < n) count[item] = cnt;
+        const unsigned long long seen = __ballot(cnt > 0u), need = seen & ~staged;
+        if (STAGE && need) {
+            if (need >> lane & 1ull) s_list[wave][__popcll(need & ((1ull << lane) - 1ull))] = (uint8_t)lane;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int m = __popcll(need) * kUnits;
+#pragma unroll 4
+            for (int a = lane; a < m; a += kWave) {
+                const int j = a / kUnits, c = a - j * kUnits, r = s_list[wave][j];
+                if constexpr (kVec)
+                    *reinterpret_cast<float4 *>(rows + r * kRow + 4 * c) =
+                        reinterpret_cast<const float4 *>(g.sh)[(first + r) * kUnits + c];
+                else
+                    rows[r * kRow + c] = g.sh[(first + r) * kUnits + c];
+            }
+            staged |= need;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (cnt > 0u) {
+            // colour: direction from the camera centre c = -W^T t, world frame
+            const double dx = mx + ((double)Wf[0] * tf[0] + (double)Wf[3] * tf[1] + (double)Wf[6] * tf[2]);
+            const double dy = my + ((double)Wf[1] * tf[0] + (double)Wf[4] * tf[1] + (double)Wf[7] * tf[2]);
+            const double dz = mz + ((double)Wf[2] * tf[0] + (double)Wf[5] * tf[1] + (double)Wf[8] * tf[2]);
+            const double idn = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
+            double Y[K];
+            sh_eval<DEG, double>(dx * idn, dy * idn, dz * idn, Y);
+            double col[3] = {0.5, 0.5, 0.5};
+            const float *shp = STAGE ? rows + lane * kRow : g.sh + (size_t)i * K * 3;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                col[0] += (double)shp[3 * k + 0] * Y[k];
+                col[1] += (double)shp[3 * k + 1] * Y[k];
+                col[2] += (double)shp[3 * k + 2] * Y[k];
+            }
+            const double idet = 1.0 / det;
+            const float uh = (float)u, vh = (float)vv;
+            Rec r;
+            r.r0 = make_float4(uh, vh, (float)(cc * idet), (float)(-cb * idet));
+            r.r1 = make_float4((float)(ca * idet), op, (float)fmax(col[0], 0.0), (float)fmax(col[1], 0.0));
+            r.r2 = make_float4((float)fmax(col[2], 0.0), __uint_as_float(bx), __uint_as_float(by), 0.f);
+            r.r3 = make_float4((float)(u - (double)uh), (float)(vv - (double)vh), 0.f, 0.f);
+            rec[item] = r;
+        }
     }
-    const ViewInfo cam = vt.v[v];
-
-    float Wf[9], tf[3];
-    load_pose(w2c, v, Wf, tf);
-    const double mx = g.means[3 * i + 0], my = g.means[3 * i + 1], mz = g.means[3 * i + 2];
-    const double px = (double)Wf[0] * mx + (double)Wf[1] * my + (double)Wf[2] * mz + (double)tf[0];
-    const double py = (double)Wf[3] * mx + (double)Wf[4] * my + (double)Wf[5] * mz + (double)tf[1];
-    const double pz = (double)Wf[6] * mx + (double)Wf[7] * my + (double)Wf[8] * mz + (double)tf[2];
-
-    uint32_t cnt = 0;
-    do {
-        if (!(pz > (double)cam.near_plane)) break;
-        const float4 qf = reinterpret_cast<const float4 *>(g.quats)[i];
-        const double qn = sqrt((double)qf.x * qf.x + (double)qf.y * qf.y + (double)qf.z * qf.z + (double)qf.w * qf.w);
-        if (!(qn > 0.0)) break;
-        double R[9];
-        quat_rot<double>(qf.x / qn, qf.y / qn, qf.z / qn, qf.w / qn, R);
-        const double s0 = exp((double)g.log_scales[3 * i + 0]);
-        const double s1 = exp((double)g.log_scales[3 * i + 1]);
-        const double s2 = exp((double)g.log_scales[3 * i + 2]);
-        // M = R diag(s); Sigma = M M^T (symmetric, 6 entries)
-        const double M[9] = {R[0] * s0, R[1] * s1, R[2] * s2, R[3] * s0, R[4] * s1,
-                             R[5] * s2, R[6] * s0, R[7] * s1, R[8] * s2};
-        double Sg[9];
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b)
-                Sg[3 * a + b] = M[3 * a] * M[3 * b] + M[3 * a + 1] * M[3 * b + 1] + M[3 * a + 2] * M[3 * b + 2];
-        const double rx = px / pz, ry = py / pz;
-        const double rxc = fmin(fmax(rx, -(double)cam.limx), (double)cam.limx);
-        const double ryc = fmin(fmax(ry, -(double)cam.limy), (double)cam.limy);
-        const double j00 = cam.fx / pz, j02 = -cam.fx * rxc / pz;
-        const double j11 = cam.fy / pz, j12 = -cam.fy * ryc / pz;
-        // T = J W (2x3)
-        double T0[3], T1[3];
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            T0[b] = j00 * Wf[b] + j02 * Wf[6 + b];
-            T1[b] = j11 * Wf[3 + b] + j12 * Wf[6 + b];
-        }
-        double TS0[3], TS1[3];
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            TS0[b] = T0[0] * Sg[b] + T0[1] * Sg[3 + b] + T0[2] * Sg[6 + b];
-            TS1[b] = T1[0] * Sg[b] + T1[1] * Sg[3 + b] + T1[2] * Sg[6 + b];
-        }
-        const double ca = TS0[0] * T0[0] + TS0[1] * T0[1] + TS0[2] * T0[2] + (double)kLowPass;
-        const double cb = TS0[0] * T1[0] + TS0[1] * T1[1] + TS0[2] * T1[2];
-        const double cc = TS1[0] * T1[0] + TS1[1] * T1[1] + TS1[2] * T1[2] + (double)kLowPass;
-        const double det = ca * cc - cb * cb;
-        if (!(det > 0.0)) break;
-        const float op = g.opacities[i];
-        if (!(op >= kAlphaMin)) break;
-        const double u = cam.fx * rx + cam.cx, vv = cam.fy * ry + cam.cy;
-        // exact box of the alpha >= 1/255 ellipse, pixel centres at i + 1/2
-        const double k2 = 2.0 * log(255.0 * (double)op);
-        const double ex = sqrt(k2 * ca), ey = sqrt(k2 * cc);
-        double x0 = ceil(u - ex - 0.5), x1 = floor(u + ex - 0.5);
-        double y0 = ceil(vv - ey - 0.5), y1 = floor(vv + ey - 0.5);
-        x0 = fmax(x0, 0.0);
-        y0 = fmax(y0, 0.0);
-        x1 = fmin(x1, (double)(cam.width - 1));
-        y1 = fmin(y1, (double)(cam.height - 1));
-        if (!(x0 <= x1) || !(y0 <= y1)) break;
-        const uint32_t ix0 = (uint32_t)x0, ix1 = (uint32_t)x1, iy0 = (uint32_t)y0, iy1 = (uint32_t)y1;
-        const uint32_t tx = ix0 / kTileW, ty = iy0 / vt.tile_h;
-        const uint32_t tw = ix1 / kTileW - tx + 1, th = iy1 / vt.tile_h - ty + 1;
-        cnt = tw * th;
-        box[item] = make_uint4(pack_u16(tx, ty), pack_u16(tw, th), __float_as_uint((float)pz), 0u);
-
-        // colour: direction from the camera centre c = -W^T t, world frame
-        const double cx = -((double)Wf[0] * tf[0] + (double)Wf[3] * tf[1] + (double)Wf[6] * tf[2]);
-        const double cy = -((double)Wf[1] * tf[0] + (double)Wf[4] * tf[1] + (double)Wf[7] * tf[2]);
-        const double cz = -((double)Wf[2] * tf[0] + (double)Wf[5] * tf[1] + (double)Wf[8] * tf[2]);
-        double dx = mx - cx, dy = my - cy, dz = mz - cz;
-        const double dn = sqrt(dx * dx + dy * dy + dz * dz);
-        dx /= dn;
-        dy /= dn;
-        dz /= dn;
-        double Y[K];
-        sh_eval<DEG, double>(dx, dy, dz, Y);
-        double col[3] = {0.5, 0.5, 0.5};
-        const float *shp = g.sh + (size_t)i * K * 3;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            col[0] += (double)shp[3 * k + 0] * Y[k];
-            col[1] += (double)shp[3 * k + 1] * Y[k];
-            col[2] += (double)shp[3 * k + 2] * Y[k];
-        }
-        const float uh = (float)u, vh = (float)vv;
-        Rec r;
-        r.r0 = make_float4(uh, vh, (float)(cc / det), (float)(-cb / det));
-        r.r1 = make_float4((float)(ca / det), op, (float)fmax(col[0], 0.0), (float)fmax(col[1], 0.0));
-        r.r2 = make_float4((float)fmax(col[2], 0.0), __uint_as_float(pack_u16(ix0, ix1)),
-                           __uint_as_float(pack_u16(iy0, iy1)), 0.f);
-        r.r3 = make_float4((float)(u - (double)uh), (float)(vv - (double)vh), 0.f, 0.f);
-        rec[item] = r;
-    } while (0);
-    count[item] = cnt;
 }
 
 void launch_project_fwd(const gsr_gaussians &g, const ViewTable &vt, const float *w2c, uint64_t n, Rec *rec,
@@ -269,12 +316,23 @@ void launch_project_fwd(const gsr_gaussians &g, const ViewTable &vt, const float
         launch_reset_header(hdr, cap, st);
         return;
     }
-    const dim3 grid((unsigned)((items + kProjThreads - 1) / kProjThreads));
-    switch (g.sh_degree) {
-        case 0: hipLaunchKernelGGL(k_project_fwd<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
-        case 1: hipLaunchKernelGGL(k_project_fwd<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
-        case 2: hipLaunchKernelGGL(k_project_fwd<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
-        default: hipLaunchKernelGGL(k_project_fwd<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+    const uint64_t blocks = (n + kProjThreads - 1) / kProjThreads;
+    const uint64_t slices = std::min<uint64_t>((uint64_t)vt.n_views, (kProjBlocks + blocks - 1) / blocks);
+    const dim3 grid((unsigned)blocks, (unsigned)slices);
+    if (2 * slices <= (uint64_t)vt.n_views) {  // two views or more a workgroup
+        switch (g.sh_degree) {
+            case 0: hipLaunchKernelGGL((k_project_fwd<0, true>), grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+            case 1: hipLaunchKernelGGL((k_project_fwd<1, true>), grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+            case 2: hipLaunchKernelGGL((k_project_fwd<2, true>), grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+            default: hipLaunchKernelGGL((k_project_fwd<3, true>), grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+        }
+    } else {
+        switch (g.sh_degree) {
+            case 0: hipLaunchKernelGGL((k_project_fwd<0, false>), grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+            case 1: hipLaunchKernelGGL((k_project_fwd<1, false>), grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+            case 2: hipLaunchKernelGGL((k_project_fwd<2, false>), grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+            default: hipLaunchKernelGGL((k_project_fwd<3, false>), grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, box, count, hdr, cap, active); break;
+        }
     }
 }
 
@@ -542,11 +600,11 @@ void launch_pair_reduce(const uint32_t *poff, const uint32_t *chunk_item, uint64
 }
 
 // ---------------------------------------------------------------------------
-// A9: projection backward.  One thread per Gaussian; loops over views and
-// chains each visible item's screen-space gradient back to the parameters and
-// to the view's pose.  The item's pair moments come from A8 (or, when its
-// pairs span several chunks, from their chunk-boundary parts added in chunk
-// order) and turn into the gradient of (u, v, A, B, C, opacity, colour) with
+// A9: projection backward.  One thread per visible item; chains the item's
+// screen-space gradient back to the parameters and to the view's pose.  The
+// item's pair moments come from A8 (or, when its pairs span several chunks,
+// from their chunk-boundary parts added in chunk order) and turn into the
+// gradient of (u, v, A, B, C, opacity, colour) with
 // the item's own conic and opacity: sigma = A dx^2 / 2 + B dx dy + C dy^2 / 2
 // with (dx, dy) = (u, v) - pixel, so dL/du = A S_x + B S_y,
 // dL/dv = B S_x + C S_y, dL/d(A, B, C) = (S_xx / 2, S_xy, S_yy / 2) and
@@ -576,14 +634,14 @@ __device__ __forceinline__ void item_moments(const float4 *__restrict__ screen, 
 
 // Chain rule of one visible (view, Gaussian) item: its screen-space gradient
 // (from the pair moments) back to the Gaussian's parameters (added to gmu, gls,
-// gq, gop and to the SH row gsh: stored by the first view, added to by later
-// ones) and to the view's pose (added to gW, gt).
+// gq, gop; the SH row's gradient is gc outer Y(dir)) and to the view's pose
+// (added to gW, gt).
 template <int DEG>
 __device__ __forceinline__ void item_backward(const gsr_gaussians &g, const ViewInfo &cam, const float *__restrict__ w2c,
                                               int v, uint64_t i, uint64_t item, uint32_t first_pair, uint32_t cnt,
                                               const Rec *__restrict__ rec, const float4 *__restrict__ screen,
-                                              const float *__restrict__ carry, const float *sh_row, float *gsh,
-                                              bool &sh_written, float (&gmu)[3], float (&gls)[3], float (&gq)[4],
+                                              const float *__restrict__ carry, const float *sh_row,
+                                              float (&gc)[3], float (&dir)[3], float (&gmu)[3], float (&gls)[3], float (&gq)[4],
                                               float &gop, float (&gW)[9], float (&gt)[3]) {
     constexpr int K = (DEG + 1) * (DEG + 1);
     const float4 r0 = rec[item].r0, r1 = rec[item].r1;
@@ -610,7 +668,8 @@ __device__ __forceinline__ void item_backward(const gsr_gaussians &g, const View
     const float czw = -(W[2] * t[0] + W[5] * t[1] + W[8] * t[2]);
     float dvec[3] = {mu[0] - cxw, mu[1] - cyw, mu[2] - czw};
     const float dn = sqrtf(dvec[0] * dvec[0] + dvec[1] * dvec[1] + dvec[2] * dvec[2]);
-    const float dir[3] = {dvec[0] / dn, dvec[1] / dn, dvec[2] / dn};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dir[c] = dvec[c] / dn;
     float Y[K];
     sh_eval<DEG, float>(dir[0], dir[1], dir[2], Y);
     // colour, to know which channels the forward clamped at 0 (the row is read
@@ -622,24 +681,13 @@ __device__ __forceinline__ void item_backward(const gsr_gaussians &g, const View
         col[1] = fmaf(sh_row[3 * k + 1], Y[k], col[1]);
         col[2] = fmaf(sh_row[3 * k + 2], Y[k], col[2]);
     }
-    float gc[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) gc[c] = col[c] < 0.f ? 0.f : grgb[c];
-    // coefficient gradients (added to an earlier view's) and the weights of
-    // dRGB/ddir; gsh may be sh_row itself: each coefficient is read before it
-    // is overwritten
+    // the weights of dRGB/ddir
     float wdir[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const float s0 = sh_row[3 * k], s1 = sh_row[3 * k + 1], s2 = sh_row[3 * k + 2];
-        wdir[k] = fmaf(gc[0], s0, fmaf(gc[1], s1, gc[2] * s2));
-        float o0 = gc[0] * Y[k], o1 = gc[1] * Y[k], o2 = gc[2] * Y[k];
-        if (sh_written) o0 += gsh[3 * k], o1 += gsh[3 * k + 1], o2 += gsh[3 * k + 2];
-        gsh[3 * k] = o0;
-        gsh[3 * k + 1] = o1;
-        gsh[3 * k + 2] = o2;
-    }
-    sh_written = true;
+    for (int k = 0; k < K; ++k)
+        wdir[k] = fmaf(gc[0], sh_row[3 * k], fmaf(gc[1], sh_row[3 * k + 1], gc[2] * sh_row[3 * k + 2]));
     float gdx, gdy, gdz;
     sh_grad_dir<DEG>(dir[0], dir[1], dir[2], wdir, gdx, gdy, gdz);
     const float dd = gdx * dir[0] + gdy * dir[1] + gdz * dir[2];
@@ -808,96 +856,192 @@ __device__ __forceinline__ void pose_block_partial(const float (&gW)[9], const f
     __syncthreads();
 }
 
+// The multi-view backward.  A workgroup takes groups of 64 consecutive
+// Gaussians, one after the other: which of them each view sees (a ballot per
+// view) gives the group's list of visible items in (view, Gaussian) order, and
+// passes of 256 of them run the chain rule, one per thread, on full waves.  Each
+// leaves its gradients in LDS, where they are added up per Gaussian in view
+// order (each wave a quarter of the SH coefficients and some of the other
+// parameters) and per view for the pose.  So an SH row and every gradient row
+// cross the memory once, whatever the number of views.  (Per-view launches read
+// and add to the rows again for each view that sees the Gaussian: 754 us for 8
+// views of 1 M Gaussians, 2.9 M visible items; 372 us here.)  It moves 590 MB
+// there, 125 us; most of the time is the chain rule's issue, at three waves per
+// SIMD (registers, LDS) with 183 of 256 threads busy in an average pass.
+constexpr int kMultiGroup = 64, kMultiViews = 3;
 template <int DEG>
-__global__ __launch_bounds__(kProjThreads) void k_project_bwd(
-    gsr_gaussians g, ViewTable vt, const float *__restrict__ w2c, uint64_t n, const Rec *__restrict__ rec,
-    const uint32_t *__restrict__ ioff, const uint32_t *__restrict__ count, const WsHeader *__restrict__ hdr, const float4 *__restrict__ screen,
-    const float *__restrict__ carry, gsr_gaussian_grads gr, float *__restrict__ pose_part, uint32_t pose_blocks,
-    int zero_unseen) {
-    constexpr int K = (DEG + 1) * (DEG + 1);
-    constexpr bool kVecSH = (3 * K) % 4 == 0;  // SH rows of 16-byte multiples: float4 loads and stores
-    __shared__ float red[4 * 12];
-    __shared__ uint32_t s_list[kProjThreads];  // block-local indices of the Gaussians seen by some view
-    __shared__ uint32_t s_wcnt[4];
-    __shared__ uint8_t s_vis[kProjThreads];
-    const uint64_t base = (uint64_t)blockIdx.x * kProjThreads;
-    const uint32_t nb = (uint32_t)min((uint64_t)kProjThreads, n - base);
-    // after a pair overflow no pair gradient exists: every Gaussian gets zero
-    const bool ovf = hdr->overflow != 0u;
+struct MultiBwd {
+    static constexpr int K = (DEG + 1) * (DEG + 1);
+    static constexpr bool kVec = (3 * K) % 4 == 0;       // SH rows of 16-byte multiples
+    static constexpr int kUnit = kVec ? 4 : 1;
+    static constexpr int kUnits = 3 * K / kUnit;         // cooperative accesses per row
+    static constexpr int kRow = kVec ? 3 * K + 4 : 3 * K;  // LDS row stride in floats
+    static constexpr int kPart = (K + 3) / 4;            // SH coefficients whose gradients a wave adds up
+    static constexpr int kOut = 29;  // floats an item leaves (odd: no bank conflicts): 3 + 3 + 4 + 1 parameter gradients,
+                                     // gc, dir, 12 of the pose
+    alignas(16) float sh[kMultiGroup * kRow];
+    float out[kProjThreads * kOut];
+    float pose[GSR_MAX_VIEWS * 12];
+    unsigned long long mask[GSR_MAX_VIEWS];
+    uint32_t base[GSR_MAX_VIEWS + 1];
+    uint16_t list[GSR_MAX_VIEWS * kMultiGroup];  // view << 6 | Gaussian of the group
+};
 
-    // ---- the block's Gaussians that some view sees, compacted so that the
-    // chain rule below runs on full waves (most Gaussians are off-screen)
-    {
-        bool vis = false;
-        if (!ovf && threadIdx.x < nb)
-            for (int v = 0; v < vt.n_views; ++v) vis |= count[(uint64_t)v * n + base + threadIdx.x] > 0u;
-        const unsigned long long bal = __ballot(vis);
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        if (lane == 0) s_wcnt[wv] = (uint32_t)__popcll(bal);
-        s_vis[threadIdx.x] = vis ? 1 : 0;
-        __syncthreads();
-        uint32_t off = 0;
-        for (int w = 0; w < wv; ++w) off += s_wcnt[w];
-        if (vis) s_list[off + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull))] = threadIdx.x;
-        __syncthreads();
+// Adds an item's gradients o to the part of wave P: SH coefficients
+// [P kPart, (P + 1) kPart) of the three channels, and one of means, log-scales,
+// quaternion and opacity.
+template <int DEG, int P>
+__device__ __forceinline__ void add_part(const float *o, float (&acc)[3 * MultiBwd<DEG>::kPart], float (&par)[4]) {
+    constexpr int K = MultiBwd<DEG>::K, kPart = MultiBwd<DEG>::kPart;
+    if constexpr (P * kPart < K) {
+        float Y[K];
+        sh_eval<DEG, float>(o[14], o[15], o[16], Y);  // (the compiler drops the other parts')
+#pragma unroll
+        for (int k = 0; k < kPart && P * kPart + k < K; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) acc[3 * k + c] = fmaf(o[11 + c], Y[P * kPart + k], acc[3 * k + c]);
     }
-    const uint32_t nlist = s_wcnt[0] + s_wcnt[1] + s_wcnt[2] + s_wcnt[3];
-    // ---- zero rows of the others, block-wide and coalesced (unless the backward
-    // compositing already did)
-    if (zero_unseen) {
-        float *zm = gr.means + 3 * base, *zl = gr.log_scales + 3 * base;
-        for (uint32_t f = threadIdx.x; f < 3 * nb; f += kProjThreads)
-            if (!s_vis[f / 3]) zm[f] = 0.f, zl[f] = 0.f;
-        for (uint32_t f = threadIdx.x; f < nb; f += kProjThreads)
-            if (!s_vis[f]) {
-                reinterpret_cast<float4 *>(gr.quats)[base + f] = make_float4(0.f, 0.f, 0.f, 0.f);
-                gr.opacities[base + f] = 0.f;
-            }
-        if constexpr (kVecSH) {
-            constexpr uint32_t R4 = 3 * K / 4;  // float4 per SH row
-            float4 *zs = reinterpret_cast<float4 *>(gr.sh) + base * R4;
-            for (uint32_t f = threadIdx.x; f < R4 * nb; f += kProjThreads)
-                if (!s_vis[f / R4]) zs[f] = make_float4(0.f, 0.f, 0.f, 0.f);
-        } else {
-            float *zs = gr.sh + base * 3 * K;
-            for (uint32_t f = threadIdx.x; f < 3 * K * nb; f += kProjThreads)
-                if (!s_vis[f / (3 * K)]) zs[f] = 0.f;
-        }
-    }
-    const bool live = threadIdx.x < nlist;
-    const uint64_t i = base + (live ? s_list[threadIdx.x] : 0u);
-
-    float gmu[3] = {0, 0, 0}, gls[3] = {0, 0, 0}, gq[4] = {0, 0, 0, 0}, gop = 0.f;
-    bool sh_written = false;  // SH gradient rows are stored by the first visible view, added to by later ones
-    float *gsh = gr.sh + (size_t)i * K * 3;
-
-    for (int v = 0; v < vt.n_views; ++v) {
-        float gW[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, gt[3] = {0, 0, 0};
-        const uint64_t item = (uint64_t)v * n + i;
-        const uint32_t cnt = live ? count[item] : 0u;
-        if (cnt > 0)
-            item_backward<DEG>(g, vt.v[v], w2c, v, i, item, ioff[item], cnt, rec, screen, carry, g.sh + (size_t)i * K * 3, gsh,
-                               sh_written, gmu, gls, gq, gop, gW, gt);
-        pose_block_partial(gW, gt, red, pose_part, v, pose_blocks);
-    }
-    if (!live) return;  // its rows were zeroed above (or it is one of the zeroed ones)
-    gr.means[3 * i] = gmu[0];
-    gr.means[3 * i + 1] = gmu[1];
-    gr.means[3 * i + 2] = gmu[2];
-    gr.log_scales[3 * i] = gls[0];
-    gr.log_scales[3 * i + 1] = gls[1];
-    gr.log_scales[3 * i + 2] = gls[2];
-    reinterpret_cast<float4 *>(gr.quats)[i] = make_float4(gq[0], gq[1], gq[2], gq[3]);
-    gr.opacities[i] = gop;
+    constexpr int kFirst[4] = {0, 3, 6, 10}, kNum[4] = {3, 3, 4, 1};
+#pragma unroll
+    for (int k = 0; k < kNum[P]; ++k) par[k] += o[kFirst[P] + k];
 }
 
-// The same for one view, over its segment of the visible-item list instead of
-// over all Gaussians: every thread of a block has a seen Gaussian (the list is
-// dense), where the per-block compaction above leaves two of every three
-// threads idle when a third of the Gaussians is seen.  Several views run one
-// launch each, in view order: a Gaussian's gradient rows are stored by the
-// first view that sees it and added to by the later ones (the order of the
-// sums above), and rows no view sees were zeroed by the backward compositing.
+template <int DEG>
+__global__ __launch_bounds__(kProjThreads, 3) void k_project_bwd_multi(
+    gsr_gaussians g, ViewTable vt, const float *__restrict__ w2c, uint64_t n, uint32_t groups,
+    const Rec *__restrict__ rec, const uint32_t *__restrict__ ioff, const uint32_t *__restrict__ count,
+    const WsHeader *__restrict__ hdr, const float4 *__restrict__ screen, const float *__restrict__ carry,
+    gsr_gaussian_grads gr, float *__restrict__ pose_part, uint32_t pose_blocks) {
+    using L = MultiBwd<DEG>;
+    constexpr int K = L::K, kOut = L::kOut;
+    __shared__ L s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V = vt.n_views;
+    for (int e = tid; e < 12 * V; e += kProjThreads) s.pose[e] = 0.f;
+    // (after a pair overflow no pair gradient exists: nothing is seen)
+    for (uint32_t q = 0; q < (hdr->overflow ? 0u : groups); ++q) {
+        const uint64_t base = ((uint64_t)blockIdx.x * groups + q) * kMultiGroup;
+        if (base >= n) break;  // uniform
+        for (int v = wave; v < V; v += 4) {
+            const bool seen = base + lane < n && count[(uint64_t)v * n + base + lane] > 0u;
+            const unsigned long long m = __ballot(seen);
+            if (lane == 0) s.mask[v] = m;
+        }
+        __syncthreads();
+        unsigned long long any = 0ull;
+        uint32_t P = 0;
+        for (int v = 0; v < V; ++v) {
+            const unsigned long long m = s.mask[v];
+            if (tid == 0) s.base[v] = P;
+            if ((v & 3) == wave && (m >> lane & 1ull))
+                s.list[P + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(v << 6 | lane);
+            P += (uint32_t)__popcll(m);
+            any |= m;
+        }
+        if (tid == 0) s.base[V] = P;
+        // the seen Gaussians' SH rows
+        for (int u = tid; u < kMultiGroup * L::kUnits; u += kProjThreads) {
+            const int r = u / L::kUnits, c = u - r * L::kUnits;
+            if (any >> r & 1ull) {
+                if constexpr (L::kVec)
+                    *reinterpret_cast<float4 *>(s.sh + r * L::kRow + 4 * c) =
+                        reinterpret_cast<const float4 *>(g.sh)[(base + r) * L::kUnits + c];
+                else
+                    s.sh[r * L::kRow + c] = g.sh[(base + r) * L::kUnits + c];
+            }
+        }
+        __syncthreads();
+        float acc[3 * L::kPart] = {}, par[4] = {};  // the wave's part of the Gaussian's (lane's) gradients
+        for (uint32_t p0 = 0; p0 < P; p0 += kProjThreads) {
+            if (p0 + tid < P) {
+                const uint32_t w = s.list[p0 + tid];
+                const int v = (int)(w >> 6), r = (int)(w & 63u);
+                const uint64_t i = base + r, item = (uint64_t)v * n + i;
+                float gW[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, gt[3] = {0, 0, 0};
+                float gmu[3] = {0, 0, 0}, gls[3] = {0, 0, 0}, gq[4] = {0, 0, 0, 0}, gop = 0.f, gc[3], dir[3];
+                item_backward<DEG>(g, vt.v[v], w2c, v, i, item, ioff[item], count[item], rec, screen, carry,
+                                   s.sh + r * L::kRow, gc, dir, gmu, gls, gq, gop, gW, gt);
+                float *o = s.out + tid * kOut;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    o[c] = gmu[c];
+                    o[3 + c] = gls[c];
+                    o[11 + c] = gc[c];
+                    o[14 + c] = dir[c];
+                    o[20 + 4 * c] = gt[c];
+#pragma unroll
+                    for (int b = 0; b < 3; ++b) o[17 + 4 * c + b] = gW[3 * c + b];
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) o[6 + c] = gq[c];
+                o[10] = gop;
+            }
+            __syncthreads();
+            const uint32_t p1 = min(p0 + (uint32_t)kProjThreads, P);
+            for (int v = 0; v < V; ++v) {
+                const uint32_t b0 = s.base[v];
+                if (b0 >= p1 || s.base[v + 1] <= p0) continue;  // uniform
+                const unsigned long long m = s.mask[v];
+                const uint32_t p = b0 + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                if (!(m >> lane & 1ull) || p < p0 || p >= p1) continue;
+                const float *o = s.out + (p - p0) * kOut;
+                switch (wave) {  // uniform
+                    case 0: add_part<DEG, 0>(o, acc, par); break;
+                    case 1: add_part<DEG, 1>(o, acc, par); break;
+                    case 2: add_part<DEG, 2>(o, acc, par); break;
+                    default: add_part<DEG, 3>(o, acc, par); break;
+                }
+            }
+            for (int e = tid; e < 12 * V; e += kProjThreads) {
+                const int v = e / 12, k = e - 12 * v;
+                uint32_t p = max(s.base[v], p0);
+                const uint32_t end = min(s.base[v + 1], p1);
+                const float *o = s.out + 17 + k;
+                float sum[4] = {0.f, 0.f, 0.f, 0.f};  // independent loads in flight
+                for (; p + 4 <= end; p += 4)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) sum[u] += o[(p - p0 + u) * kOut];
+                for (; p < end; ++p) sum[0] += o[(p - p0) * kOut];
+                s.pose[e] += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+            }
+            __syncthreads();
+        }
+        // the rows: through LDS for the SH gradients, so that they are stored row-contiguous
+#pragma unroll
+        for (int k = 0; k < L::kPart; ++k)
+            if (wave * L::kPart + k < K) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) s.sh[lane * L::kRow + 3 * (wave * L::kPart + k) + c] = acc[3 * k + c];
+            }
+        if (any >> lane & 1ull) {
+            const uint64_t i = base + lane;
+            if (wave == 0) gr.means[3 * i] = par[0], gr.means[3 * i + 1] = par[1], gr.means[3 * i + 2] = par[2];
+            if (wave == 1)
+                gr.log_scales[3 * i] = par[0], gr.log_scales[3 * i + 1] = par[1], gr.log_scales[3 * i + 2] = par[2];
+            if (wave == 2) reinterpret_cast<float4 *>(gr.quats)[i] = make_float4(par[0], par[1], par[2], par[3]);
+            if (wave == 3) gr.opacities[i] = par[0];
+        }
+        __syncthreads();
+        for (int u = tid; u < kMultiGroup * L::kUnits; u += kProjThreads) {
+            const int r = u / L::kUnits, c = u - r * L::kUnits;
+            if (any >> r & 1ull) {
+                if constexpr (L::kVec)
+                    reinterpret_cast<float4 *>(gr.sh)[(base + r) * L::kUnits + c] =
+                        *reinterpret_cast<const float4 *>(s.sh + r * L::kRow + 4 * c);
+                else
+                    gr.sh[(base + r) * L::kUnits + c] = s.sh[r * L::kRow + c];
+            }
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+    for (int e = tid; e < 12 * V; e += kProjThreads) pose_part[(size_t)e * pose_blocks + blockIdx.x] = s.pose[e];
+}
+
+// One view, over its segment of the visible-item list: every thread of a block
+// has a seen Gaussian.  Two views run one launch each, in view order: a
+// Gaussian's gradient rows are stored by the first view that sees it and added
+// to by the later one; rows no view sees were zeroed by the backward
+// compositing.
 // seg (several views): first visible index of each view, and the total.
 template <int DEG>
 __global__ __launch_bounds__(kProjThreads) void k_project_bwd_vis(
@@ -947,10 +1091,16 @@ __global__ __launch_bounds__(kProjThreads) void k_project_bwd_vis(
     float gW[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, gt[3] = {0, 0, 0};
     if (live) {
         float gmu[3] = {0, 0, 0}, gls[3] = {0, 0, 0}, gq[4] = {0, 0, 0, 0}, gop = 0.f;
-        bool sh_written = false;
+        float gc[3], dir[3];
         float *row = rows + lane * kStride;  // read, then overwritten with this view's SH gradient
-        item_backward<DEG>(g, vt.v[v], w2c, v, i, item, ioff[item], count[item], rec, screen, carry, row, row, sh_written, gmu,
+        item_backward<DEG>(g, vt.v[v], w2c, v, i, item, ioff[item], count[item], rec, screen, carry, row, gc, dir, gmu,
                            gls, gq, gop, gW, gt);
+        float Y[K];
+        sh_eval<DEG, float>(dir[0], dir[1], dir[2], Y);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) row[3 * k + c] = gc[c] * Y[k];
         if (!first) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) gmu[c] += gr.means[3 * i + c], gls[c] += gr.log_scales[3 * i + c];
@@ -993,31 +1143,47 @@ __global__ __launch_bounds__(kProjThreads) void k_project_bwd_vis(
     pose_block_partial(gW, gt, red, pose_part, v, pose_blocks);
 }
 
+// Groups of 64 Gaussians a workgroup of the multi-view backward takes, or 0
+// where the views run one dense launch each.  A group's visible items should
+// fill a good part of the workgroup: whole fused steps of 3 and 6 views take
+// 149 and 232 us against 184 and 316 us (20 k Gaussians), 911 and 1,553 us
+// against 926 and 1,724 us (600 k), but of 2 views 669 us against 632 us (600 k).
+uint32_t project_bwd_groups(uint64_t n, int n_views) {
+    if (n_views < kMultiViews) return 0;
+    return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(4, n / (kMultiGroup * 1024)));
+}
+
+uint32_t project_bwd_blocks(uint64_t n, int n_views) {
+    const uint64_t per = n_views < kMultiViews ? kProjThreads : kMultiGroup * project_bwd_groups(n, n_views);
+    return (uint32_t)std::max<uint64_t>(1, (n + per - 1) / per);
+}
+
 void launch_project_bwd(const gsr_gaussians &g, const ViewTable &vt, const float *w2c, uint64_t n, const Rec *rec,
                         const uint32_t *ioff, const uint32_t *count, const uint32_t *vis, const WsHeader *hdr, const float4 *screen,
                         const float *carry, const gsr_gaussian_grads &gr, float *pose_part, uint32_t pose_blocks,
-                        const uint32_t *seg, bool zero_unseen, hipStream_t st) {
+                        const uint32_t *seg, hipStream_t st) {
     if (n == 0) return;
-    const dim3 grid(pose_blocks);
-    const int z = zero_unseen ? 1 : 0;
-    if (!zero_unseen) {
-        // one dense launch per view, in view order
-        const uint32_t *sg = vt.n_views > 1 ? seg : nullptr;
-        for (int v = 0; v < vt.n_views; ++v) {
-            switch (g.sh_degree) {
-                case 0: hipLaunchKernelGGL(k_project_bwd_vis<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
-                case 1: hipLaunchKernelGGL(k_project_bwd_vis<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
-                case 2: hipLaunchKernelGGL(k_project_bwd_vis<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
-                default: hipLaunchKernelGGL(k_project_bwd_vis<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
-            }
+    if (project_bwd_groups(n, vt.n_views)) {
+        const uint32_t groups = project_bwd_groups(n, vt.n_views);
+        const dim3 grid(pose_blocks);
+        switch (g.sh_degree) {
+            case 0: hipLaunchKernelGGL(k_project_bwd_multi<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, groups, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+            case 1: hipLaunchKernelGGL(k_project_bwd_multi<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, groups, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+            case 2: hipLaunchKernelGGL(k_project_bwd_multi<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, groups, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+            default: hipLaunchKernelGGL(k_project_bwd_multi<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, groups, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
         }
         return;
     }
-    switch (g.sh_degree) {
-        case 0: hipLaunchKernelGGL(k_project_bwd<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
-        case 1: hipLaunchKernelGGL(k_project_bwd<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
-        case 2: hipLaunchKernelGGL(k_project_bwd<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
-        default: hipLaunchKernelGGL(k_project_bwd<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks, z); break;
+    // one dense launch per view, in view order
+    const dim3 grid(pose_blocks);
+    const uint32_t *sg = vt.n_views > 1 ? seg : nullptr;
+    for (int v = 0; v < vt.n_views; ++v) {
+        switch (g.sh_degree) {
+            case 0: hipLaunchKernelGGL(k_project_bwd_vis<0>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+            case 1: hipLaunchKernelGGL(k_project_bwd_vis<1>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+            case 2: hipLaunchKernelGGL(k_project_bwd_vis<2>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+            default: hipLaunchKernelGGL(k_project_bwd_vis<3>, grid, dim3(kProjThreads), 0, st, g, vt, w2c, n, v, sg, vis, rec, ioff, count, hdr, screen, carry, gr, pose_part, pose_blocks); break;
+        }
     }
 }
 
@@ -1032,7 +1198,7 @@ __global__ __launch_bounds__(768) void k_pose_finalize(const float *__restrict__
                                                        const uint32_t *__restrict__ seg, int dense,
                                                        float *__restrict__ dL_dw2c, float *__restrict__ dL_dtwist) {
     // one workgroup per view, one wave per entry of the top 3x4 block
-    __shared__ float G[16];
+    __shared__ double G[16];
     const int v = blockIdx.x;
     const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // the dense backward's grid is sized by capacity: only the blocks that had
@@ -1044,7 +1210,7 @@ __global__ __launch_bounds__(768) void k_pose_finalize(const float *__restrict__
         used = min(pose_blocks, (hi - lo + (uint32_t)kProjThreads - 1u) / (uint32_t)kProjThreads);
     }
     const float *src = pose_part + ((size_t)v * 12 + k) * pose_blocks;
-    float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f, acc3 = 0.f;  // independent loads in flight
+    double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;  // independent loads in flight
     uint32_t b = lane;
     for (; b + 192 < used; b += 256) {
         acc0 += src[b];
@@ -1053,25 +1219,27 @@ __global__ __launch_bounds__(768) void k_pose_finalize(const float *__restrict__
         acc3 += src[b + 192];
     }
     for (; b < used; b += 64) acc0 += src[b];
-    const float acc = wave_sum((acc0 + acc1) + (acc2 + acc3));
+    double acc = (acc0 + acc1) + (acc2 + acc3);
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) acc += __shfl_xor(acc, m, kWave);
     if (lane == 0) G[k] = acc;
-    if (threadIdx.x == 0) G[12] = G[13] = G[14] = G[15] = 0.f;
+    if (threadIdx.x == 0) G[12] = G[13] = G[14] = G[15] = 0.0;
     __syncthreads();
-    if (threadIdx.x < 16 && dL_dw2c) dL_dw2c[16 * v + threadIdx.x] = G[threadIdx.x];
+    if (threadIdx.x < 16 && dL_dw2c) dL_dw2c[16 * v + threadIdx.x] = (float)G[threadIdx.x];
     if (threadIdx.x == 0 && dL_dtwist) {
         const float *T = w2c + 16 * v;
-        float M[16];
+        double M[16];
         for (int a = 0; a < 4; ++a)
             for (int b = 0; b < 4; ++b)
                 M[4 * a + b] = G[4 * a] * T[4 * b] + G[4 * a + 1] * T[4 * b + 1] + G[4 * a + 2] * T[4 * b + 2] +
                                G[4 * a + 3] * T[4 * b + 3];
         float *o = dL_dtwist + 6 * v;
-        o[0] = M[3];
-        o[1] = M[7];
-        o[2] = M[11];
-        o[3] = M[9] - M[6];
-        o[4] = M[2] - M[8];
-        o[5] = M[4] - M[1];
+        o[0] = (float)M[3];
+        o[1] = (float)M[7];
+        o[2] = (float)M[11];
+        o[3] = (float)(M[9] - M[6]);
+        o[4] = (float)(M[2] - M[8]);
+        o[5] = (float)(M[4] - M[1]);
     }
 }
 
