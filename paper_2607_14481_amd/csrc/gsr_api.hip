@@ -863,11 +863,13 @@ int gsr_hierarchy_build(const gsr_param_set *nodes, int32_t sh_degree, int64_t n
     const float *const ptrs[5] = {nodes->means, nodes->log_scales, nodes->quats, nodes->opacities, nodes->sh};
     if ((rc = check_param_set(ptrs, ((sh_degree + 1) * (sh_degree + 1) * 3) % 4 == 0, "nodes"))) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    launch_fill_i32(child_count, 0, (uint64_t)n_leaves, st);                          // leaves
-    launch_fill_i32(parent + ls[nl - 1], -1, (uint64_t)(ls[nl] - ls[nl - 1]), st);  // roots
+    if (nl == 1) {  // the leaves are the roots (else the levels' launches write these)
+        launch_fill_i32(child_count, 0, (uint64_t)n_leaves, st);
+        launch_fill_i32(parent, -1, (uint64_t)n_leaves, st);
+    }
     for (int32_t l = 0; l + 1 < nl; ++l)
         launch_hierarchy_level(*nodes, sh_degree, (uint64_t)ls[l], (uint64_t)(ls[l + 1] - ls[l]), (uint64_t)ls[l + 1],
-                               (uint32_t)branching, parent, child_count, st);
+                               (uint32_t)branching, l == 0, l + 2 == nl, parent, child_count, st);
     return check_hip(hipGetLastError(), "hierarchy build launch");
 }
 

@@ -10,6 +10,8 @@
 // ancestor chain (a few levels), and an ordered compaction lists the cut in
 // ascending node order.  S is evaluated in double precision so that the
 // decision agrees with the FP64 reference away from ties.
+#include <algorithm>
+
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -137,19 +139,35 @@ void launch_store_count_i64(const uint32_t *count, int64_t *out, hipStream_t st)
 // The covariance is stored factored: eigenvalues ascending -> log-scales,
 // eigenvectors (determinant +1) -> quaternion with w >= 0.
 //
-// k_merge_geometry: one thread per parent, FP64.  Moments are accumulated
-// about the first child's mean, so the spread term does not cancel against
-// the coordinates' magnitude (a street 2 km long).  The 3x3 eigenproblem is
-// solved by cyclic Jacobi rotations (quadratic convergence; a sweep limit of
-// 12 is never reached).  The thread also writes its node's child count and its
-// children's parent index.  k_merge_sh: one thread per float4 (or float) of
-// a parent's SH row, coalesced over consecutive parents.
+// One launch per level; its workgroups are of two kinds, dealt in turn so that
+// the arithmetic of one runs under the memory traffic of the other.
+//
+// Geometry, FP64: a thread per child forms its weighted moments (about the
+// first child's mean, so the spread term does not cancel against the
+// coordinates' magnitude on a street 2 km long), the sums over each parent's
+// children are taken from LDS in child order, and then a thread per parent
+// solves the 3x3 eigenproblem by cyclic Jacobi rotations (quadratic
+// convergence; a sweep limit of 12 is never reached).  It also writes the
+// children's parent index and the nodes' child counts.
+//
+// SH: one thread per float4 (or float) of a parent's SH row, coalesced over
+// consecutive parents; this is what bounds the large levels (two million
+// leaves of degree 3: 432 MB of SH rows and 103 MB of the rest, 114 us at the
+// rate of a copy).
+//
+// Two million leaves, seven levels of branching 8: 318 us with a thread per
+// parent, whose serial loads of eight children (113 us alone) the SH rows of a
+// launch of their own (87 us) did not cover; 180 us now.  The upper levels take
+// 7 to 12 us each, the latency of one eigenproblem.  Two chunks of children to
+// a geometry workgroup (64 parents) rather than one or four (more LDS: fewer
+// waves for the SH rows): 180, 218 and 222 us; geometry workgroups dealt in
+// turn rather than first: 180 and 193 us.
 // ---------------------------------------------------------------------------
 constexpr double kMergeMinVar = 1e-12;
 
 __device__ inline void quat_to_rot_d(double w, double x, double y, double z, double R[9]) {
-    const double n = sqrt(w * w + x * x + y * y + z * z);
-    w /= n, x /= n, y /= n, z /= n;
+    const double in = 1.0 / sqrt(w * w + x * x + y * y + z * z);
+    w *= in, x *= in, y *= in, z *= in;
     R[0] = 1 - 2 * (y * y + z * z), R[1] = 2 * (x * y - w * z), R[2] = 2 * (x * z + w * y);
     R[3] = 2 * (x * y + w * z), R[4] = 1 - 2 * (x * x + z * z), R[5] = 2 * (y * z - w * x);
     R[6] = 2 * (x * z - w * y), R[7] = 2 * (y * z + w * x), R[8] = 1 - 2 * (x * x + y * y);
@@ -168,8 +186,11 @@ __device__ inline void sym3_eig(double a[9], double lam[3], double V[9]) {
             const int p = r == 2 ? 1 : 0, q = r == 0 ? 1 : 2;
             const double apq = a[3 * p + q];
             if (apq == 0.0) continue;
-            const double theta = (a[3 * q + q] - a[3 * p + p]) / (2.0 * apq);
-            const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
+            // tan of the rotation: the smaller root of t^2 + 2 theta t - 1 with theta = d / h
+            // (any t gives a rotation; where the squares underflow it is a smaller one)
+            const double d = a[3 * q + q] - a[3 * p + p], h = 2.0 * apq;
+            const double root = fmax(sqrt(d * d + h * h), fabs(h));
+            const double t = h / (d >= 0.0 ? d + root : d - root);
             const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
             // A <- J^T A J with J the rotation in the (p, q) plane
             for (int k = 0; k < 3; ++k) {  // columns p, q
@@ -233,73 +254,106 @@ __device__ inline void rot_to_quat_d(const double R[9], double q[4]) {
     for (int i = 0; i < 4; ++i) q[i] *= sg / n;
 }
 
-__global__ __launch_bounds__(256) void k_merge_geometry(gsr_param_set nodes, uint64_t child_base, uint64_t n_child,
-                                                        uint64_t parent_base, uint32_t branching,
-                                                        int32_t *__restrict__ parent, int32_t *__restrict__ child_count) {
-    const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;  // parent within its level
-    const uint64_t first = (uint64_t)j * branching;
-    if (first >= n_child) return;
-    const uint32_t k = (uint32_t)min((uint64_t)branching, n_child - first);
-    const uint64_t c0 = child_base + first, p = parent_base + j;
-    const double ox = nodes.means[3 * c0], oy = nodes.means[3 * c0 + 1], oz = nodes.means[3 * c0 + 2];
-    double wsum = 0.0, keep = 1.0, d[3] = {0.0, 0.0, 0.0}, S[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (uint32_t i = 0; i < k; ++i) {
-        const uint64_t c = c0 + i;
-        parent[c] = (int32_t)p;
-        const double o = nodes.opacities[c];
-        const float4 qf = reinterpret_cast<const float4 *>(nodes.quats)[c];
-        double R[9];
-        quat_to_rot_d(qf.x, qf.y, qf.z, qf.w, R);
-        const double e0 = exp(2.0 * (double)nodes.log_scales[3 * c]), e1 = exp(2.0 * (double)nodes.log_scales[3 * c + 1]),
-                     e2 = exp(2.0 * (double)nodes.log_scales[3 * c + 2]);
-        const double dx = (double)nodes.means[3 * c] - ox, dy = (double)nodes.means[3 * c + 1] - oy,
-                     dz = (double)nodes.means[3 * c + 2] - oz;
-        // o (Sigma_c + d d^T), upper triangle: 00 01 02 11 12 22
-        const int ia[6] = {0, 0, 0, 1, 1, 2}, ib[6] = {0, 1, 2, 1, 2, 2};
-        const double dd[3] = {dx, dy, dz};
+constexpr uint32_t kMergeThreads = 256, kMergeMaxParents = 64, kMergeTerms = 11;
+
+struct MergeLevel {
+    gsr_param_set nodes;
+    uint64_t child_base, n_child, parent_base, n_parent;
+    uint32_t branching, per, chunks;  // parents per 256 children; such chunks per geometry workgroup
+    uint32_t geometry, period;        // geometry workgroups; every period-th workgroup is one
+    bool leaves, roots;               // the children are leaves; the parents are roots
+    int32_t *parent, *child_count;
+};
+
+// Geometry workgroup wg: parents [wg * chunks * per, + chunks * per).
+__device__ __forceinline__ void merge_geometry(const MergeLevel &L, uint64_t wg, double (*child)[kMergeTerms],
+                                               double (*sums)[kMergeTerms]) {
+    const gsr_param_set &nodes = L.nodes;
+    const uint32_t tid = threadIdx.x, b = L.branching;
+    const uint64_t j0 = wg * L.chunks * L.per;  // the first parent
+    const uint32_t np = (uint32_t)min((uint64_t)(L.chunks * L.per), L.n_parent - j0);
+    for (uint32_t q0 = 0; q0 < np; q0 += L.per) {
+        const uint32_t q = q0 + tid / b;  // the child's parent within the workgroup
+        const uint64_t in = (j0 + q0) * b + tid;
+        if (tid < L.per * b && q < np && in < L.n_child) {
+            const uint64_t c = L.child_base + in, c0 = L.child_base + (j0 + q) * b;
+            L.parent[c] = (int32_t)(L.parent_base + j0 + q);
+            if (L.leaves) L.child_count[c] = 0;
+            const double o = nodes.opacities[c];
+            const float4 qf = reinterpret_cast<const float4 *>(nodes.quats)[c];
+            double R[9];
+            quat_to_rot_d(qf.x, qf.y, qf.z, qf.w, R);
+            const double e0 = exp(2.0 * (double)nodes.log_scales[3 * c]),
+                         e1 = exp(2.0 * (double)nodes.log_scales[3 * c + 1]),
+                         e2 = exp(2.0 * (double)nodes.log_scales[3 * c + 2]);
+            const double d[3] = {(double)nodes.means[3 * c] - (double)nodes.means[3 * c0],
+                                 (double)nodes.means[3 * c + 1] - (double)nodes.means[3 * c0 + 1],
+                                 (double)nodes.means[3 * c + 2] - (double)nodes.means[3 * c0 + 2]};
+            double *t = child[tid];
+            t[0] = o;
 #pragma unroll
-        for (int t = 0; t < 6; ++t) {
-            const int a = ia[t], b = ib[t];
-            const double sig = R[3 * a] * R[3 * b] * e0 + R[3 * a + 1] * R[3 * b + 1] * e1 + R[3 * a + 2] * R[3 * b + 2] * e2;
-            S[t] += o * (sig + dd[a] * dd[b]);
+            for (int a = 0; a < 3; ++a) t[1 + a] = o * d[a];
+            // o (Sigma_c + d d^T), upper triangle: 00 01 02 11 12 22
+#pragma unroll
+            for (int a = 0, e = 4; a < 3; ++a)
+#pragma unroll
+                for (int k = a; k < 3; ++k, ++e)
+                    t[e] = o * (R[3 * a] * R[3 * k] * e0 + R[3 * a + 1] * R[3 * k + 1] * e1 +
+                                R[3 * a + 2] * R[3 * k + 2] * e2 + d[a] * d[k]);
+            t[10] = 1.0 - o;
         }
-        d[0] += o * dx, d[1] += o * dy, d[2] += o * dz;
-        wsum += o;
-        keep *= 1.0 - o;
+        __syncthreads();
+        const uint32_t nq = min(L.per, np - q0);
+        for (uint32_t e = tid; e < nq * kMergeTerms; e += kMergeThreads) {
+            const uint32_t r = e / kMergeTerms, t = e - r * kMergeTerms;
+            const uint32_t k = (uint32_t)min((uint64_t)b, L.n_child - (j0 + q0 + r) * b);
+            double x = child[r * b][t];
+            if (t < 10)
+                for (uint32_t i = 1; i < k; ++i) x += child[r * b + i][t];
+            else
+                for (uint32_t i = 1; i < k; ++i) x *= child[r * b + i][t];
+            sums[q0 + r][t] = x;
+        }
+        __syncthreads();
     }
-    child_count[p] = (int32_t)k;
-    const double inv = 1.0 / wsum;
-    const double m[3] = {d[0] * inv, d[1] * inv, d[2] * inv};  // mean about the first child
+    if (tid >= np) return;
+    const double *S = sums[tid];
+    const uint64_t j = j0 + tid, p = L.parent_base + j, c0 = L.child_base + j * b;
+    L.child_count[p] = (int32_t)min((uint64_t)b, L.n_child - j * b);
+    if (L.roots) L.parent[p] = -1;
+    const double inv = 1.0 / S[0];
+    const double m[3] = {S[1] * inv, S[2] * inv, S[3] * inv};  // mean about the first child
     double A[9];
-    A[0] = S[0] * inv - m[0] * m[0], A[1] = A[3] = S[1] * inv - m[0] * m[1], A[2] = A[6] = S[2] * inv - m[0] * m[2];
-    A[4] = S[3] * inv - m[1] * m[1], A[5] = A[7] = S[4] * inv - m[1] * m[2], A[8] = S[5] * inv - m[2] * m[2];
+    A[0] = S[4] * inv - m[0] * m[0], A[1] = A[3] = S[5] * inv - m[0] * m[1], A[2] = A[6] = S[6] * inv - m[0] * m[2];
+    A[4] = S[7] * inv - m[1] * m[1], A[5] = A[7] = S[8] * inv - m[1] * m[2], A[8] = S[9] * inv - m[2] * m[2];
     double lam[3], V[9], q[4];
     sym3_eig(A, lam, V);
     rot_to_quat_d(V, q);
-    nodes.means[3 * p] = (float)(ox + m[0]);
-    nodes.means[3 * p + 1] = (float)(oy + m[1]);
-    nodes.means[3 * p + 2] = (float)(oz + m[2]);
-    for (int a = 0; a < 3; ++a) nodes.log_scales[3 * p + a] = (float)(0.5 * log(fmax(lam[a], kMergeMinVar)));
+    for (int a = 0; a < 3; ++a) {
+        nodes.means[3 * p + a] = (float)((double)nodes.means[3 * c0 + a] + m[a]);
+        nodes.log_scales[3 * p + a] = (float)(0.5 * log(fmax(lam[a], kMergeMinVar)));
+    }
     reinterpret_cast<float4 *>(nodes.quats)[p] = make_float4((float)q[0], (float)q[1], (float)q[2], (float)q[3]);
-    nodes.opacities[p] = (float)(1.0 - keep);
+    nodes.opacities[p] = (float)(1.0 - S[10]);
 }
 
-// SH rows of the parents: unit u of parent j (K3 / 4 float4 units, or K3
-// floats when a row is not a whole number of float4).
+// Unit t of the parents' SH rows (K3 / 4 float4 units a row, or K3 floats when
+// a row is not a whole number of float4).
 template <int K3, bool VEC>
-__global__ __launch_bounds__(256) void k_merge_sh(gsr_param_set nodes, uint64_t child_base, uint64_t n_child,
-                                                  uint64_t parent_base, uint64_t n_parent, uint32_t branching) {
+__device__ __forceinline__ void merge_sh(const MergeLevel &L, uint64_t t) {
     constexpr uint32_t kUnits = VEC ? K3 / 4 : K3;
-    const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= n_parent * kUnits) return;
+    const gsr_param_set &nodes = L.nodes;
+    if (t >= L.n_parent * kUnits) return;
     const uint64_t j = t / kUnits, u = t - j * kUnits;
-    const uint64_t first = j * branching, c0 = child_base + first, p = parent_base + j;
-    const uint32_t k = (uint32_t)min((uint64_t)branching, n_child - first);
+    const uint64_t first = j * L.branching, c0 = L.child_base + first, p = L.parent_base + j;
+    const uint32_t k = (uint32_t)min((uint64_t)L.branching, L.n_child - first);
     float wsum = 0.f;
+#pragma unroll 8
     for (uint32_t i = 0; i < k; ++i) wsum += nodes.opacities[c0 + i];
     const float inv = 1.f / wsum;
     if constexpr (VEC) {
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
         for (uint32_t i = 0; i < k; ++i) {
             const float w = nodes.opacities[c0 + i] * inv;
             const float4 v = reinterpret_cast<const float4 *>(nodes.sh)[(c0 + i) * kUnits + u];
@@ -309,9 +363,23 @@ __global__ __launch_bounds__(256) void k_merge_sh(gsr_param_set nodes, uint64_t 
         reinterpret_cast<float4 *>(nodes.sh)[p * kUnits + u] = acc;
     } else {
         float acc = 0.f;
+#pragma unroll 8
         for (uint32_t i = 0; i < k; ++i) acc = fmaf(nodes.opacities[c0 + i] * inv, nodes.sh[(c0 + i) * kUnits + u], acc);
         nodes.sh[p * kUnits + u] = acc;
     }
+}
+
+template <int K3, bool VEC>
+__global__ __launch_bounds__(kMergeThreads, 4) void k_merge_level(MergeLevel L) {
+    __shared__ double child[kMergeThreads][kMergeTerms], sums[kMergeMaxParents][kMergeTerms];
+    const uint32_t turn = blockIdx.x / L.period;
+    if (turn * L.period == blockIdx.x && turn < L.geometry) {  // uniform
+        merge_geometry(L, turn, child, sums);
+        return;
+    }
+    // the SH workgroups are those between, numbered through
+    const uint64_t wg = blockIdx.x - min(L.geometry, turn + 1);
+    merge_sh<K3, VEC>(L, wg * kMergeThreads + threadIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_fill_i32(int32_t *__restrict__ p, int32_t value, uint64_t n) {
@@ -320,21 +388,32 @@ __global__ __launch_bounds__(256) void k_fill_i32(int32_t *__restrict__ p, int32
 }
 
 void launch_hierarchy_level(const gsr_param_set &nodes, int sh_degree, uint64_t child_base, uint64_t n_child,
-                            uint64_t parent_base, uint32_t branching, int32_t *parent, int32_t *child_count,
-                            hipStream_t st) {
-    const uint64_t n_parent = (n_child + branching - 1) / branching;
-    if (n_parent == 0) return;
-    hipLaunchKernelGGL(k_merge_geometry, dim3((unsigned)((n_parent + 255) / 256)), dim3(256), 0, st, nodes, child_base,
-                       n_child, parent_base, branching, parent, child_count);
-    auto sh = [&](auto kernel, uint64_t units) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((n_parent * units + 255) / 256)), dim3(256), 0, st, nodes,
-                           child_base, n_child, parent_base, n_parent, branching);
+                            uint64_t parent_base, uint32_t branching, bool leaves, bool roots, int32_t *parent,
+                            int32_t *child_count, hipStream_t st) {
+    MergeLevel L{};
+    L.nodes = nodes;
+    L.child_base = child_base, L.n_child = n_child, L.parent_base = parent_base;
+    L.n_parent = (n_child + branching - 1) / branching;
+    if (L.n_parent == 0) return;
+    L.branching = branching;
+    L.per = std::min(kMergeThreads / branching, kMergeMaxParents);
+    // two chunks to a workgroup, so that the parents' part runs on a full wave,
+    // once that leaves four workgroups per compute unit
+    L.chunks = (uint32_t)std::max<uint64_t>(
+        1, std::min<uint64_t>(kMergeMaxParents / L.per, L.n_parent / (L.per * 1024ull)));
+    L.geometry = (uint32_t)((L.n_parent + L.per * L.chunks - 1) / (L.per * L.chunks));
+    L.leaves = leaves, L.roots = roots;
+    L.parent = parent, L.child_count = child_count;
+    auto run = [&](auto kernel, uint64_t units) {
+        const uint32_t sh = (uint32_t)((L.n_parent * units + kMergeThreads - 1) / kMergeThreads);
+        L.period = (L.geometry + sh) / L.geometry;
+        hipLaunchKernelGGL(kernel, dim3(L.geometry + sh), dim3(kMergeThreads), 0, st, L);
     };
     switch (sh_degree) {
-        case 0: sh(k_merge_sh<3, false>, 3); break;
-        case 1: sh(k_merge_sh<12, true>, 3); break;
-        case 2: sh(k_merge_sh<27, false>, 27); break;
-        default: sh(k_merge_sh<48, true>, 12); break;
+        case 0: run(k_merge_level<3, false>, 3); break;
+        case 1: run(k_merge_level<12, true>, 3); break;
+        case 2: run(k_merge_level<27, false>, 27); break;
+        default: run(k_merge_level<48, true>, 12); break;
     }
 }
 
