@@ -1,0 +1,49 @@
+"""Edges of two kernels' work split: the Adam step's groups of 64 Gaussians and
+row forms, against the FP64 update oracle with the tolerances of the update
+tests; the cut's four nodes per thread, over forests whose siblings lie
+anywhere, where the cut is the FP64 reference's exactly."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+
+from oracle import update as U
+from paper_2607_14481_amd import gsr
+from paper_2607_14481_amd import scenes as S
+
+from .test_gpu_hierarchy import _check
+from .test_gpu_update import LRS, _acfg, _compare, _dev, _host, _random_state
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("deg", [0, 1, 2, 3])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 200])
+def test_adam_groups(n, deg):
+    import torch
+    rng = np.random.default_rng(100 * n + deg)
+    p, shapes = _random_state(rng, n, deg)
+    zero = {k: np.zeros(s, np.float32) for k, s in shapes.items()}
+    P, M, V = _dev(p), _dev(zero), _dev(zero)
+    g = {k: rng.standard_normal(s).astype(np.float32) for k, s in shapes.items()}
+    gsr.adam_step(P, _dev(g), M, V, deg, 1, _acfg(gsr))
+    torch.cuda.synchronize()
+    refP, refM, refV = U.adam(p, g, zero, zero, 1, LRS, 0.9, 0.999, 1e-8)
+    _compare(_host(P), refP, "params")
+    _compare(_host(M), refM, "exp_avg")
+    _compare(_host(V), refV, "exp_avg_sq", rtol=1e-4, atol=1e-9)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 1023, 1025, 5002])
+def test_cut_of_any_forest(n):
+    rng = np.random.default_rng(n)
+    means = np.c_[rng.uniform(0, 60, n), rng.uniform(-3, 3, n), rng.uniform(0, 3, n)]
+    nodes = S._gaussian_body(rng, means, 0)
+    # parents anywhere behind their children, runs of siblings and single nodes mixed; some roots
+    up = np.minimum(np.arange(n) // rng.integers(1, 6, n) + n // 3 + 1, n)
+    parent = np.where((up > np.arange(n)) & (up < n) & (rng.random(n) < 0.97), up, -1)
+    h = SimpleNamespace(nodes=nodes, parent=parent, child_count=np.bincount(parent[parent >= 0], minlength=n))
+    eye = np.array([-1.0, 0.0, 1.5])
+    cam = S.pinhole(160, 120, S.look_at(eye, eye + [1.0, 0.0, 0.0]))
+    for tau in (0.5, 8.0):
+        _check(h, cam, f"forest of {n}, tau {tau}", tau)
