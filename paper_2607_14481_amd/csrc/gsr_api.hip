@@ -357,7 +357,7 @@ int forward_binning(const gsr_gaussians *g, const gsr::ViewTable &vt, const floa
                            p.scan_tmp, p.view_seg, p.hdr, st);
     mark.end(GSR_STAGE_COMPACT);
     mark.begin(GSR_STAGE_EMIT);
-    const BinPlan plan = bin_plan(vt, cap);
+    const BinPlan plan = bin_plan(vt, n, cap);
     if ((rc = check_hip(bin_allow_lds(std::max(plan.lds_count, plan.lds_place)), "LDS attribute"))) return rc;
     launch_bin_pairs(vt, plan, L.bin_rows, p.view_seg, p.item_box, p.counts,
                      p.counts + (size_t)L.bin_rows * vt.total_tiles, p.ranges, p.long_tiles, p.tile_order, p.entries,

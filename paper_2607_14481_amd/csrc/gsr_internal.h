@@ -159,10 +159,11 @@ void launch_export_items(const uint32_t *poff, const uint4 *item_box, const Rec 
 // schedule's counters.  counts: u32[G][total_tiles].  A plan says in how many
 // bands of tile rows each view is counted and placed, and the LDS they need.
 struct BinPlan {
-    uint32_t count_bands, place_bands;
+    uint32_t count_bands, place_bands;  // of the three launches, or
+    uint32_t small_bands;               // of the one launch (0: not taken)
     size_t lds_count, lds_place;
 };
-BinPlan bin_plan(const ViewTable &vt, uint64_t cap);
+BinPlan bin_plan(const ViewTable &vt, uint64_t n, uint64_t cap);
 hipError_t bin_allow_lds(size_t bytes);
 void launch_bin_pairs(const ViewTable &vt, const BinPlan &plan, uint32_t G, const uint32_t *seg,
                       const uint4 *item_box, uint32_t *counts, uint32_t *totals, uint2 *ranges, uint32_t *long_tiles,

@@ -169,6 +169,11 @@ __global__ __launch_bounds__(kScanThreads) void k_vis_reduce(const uint32_t *__r
     }
 }
 
+// Blocks up to which phase 2 reads the counts of the blocks before it itself,
+// which saves phase 1's launch (2 us in a trace of 1,000 items); with 16 blocks
+// (16,000 items) a forward was 1.5 us slower so.
+constexpr uint32_t kScanFewBlocks = 8;
+
 __global__ __launch_bounds__(kScanThreads) void k_vis_apply(ViewTable vt, uint64_t n_view,
                                                             const uint32_t *__restrict__ count,
                                                             const uint4 *__restrict__ box, uint64_t n,
@@ -200,11 +205,21 @@ __global__ __launch_bounds__(kScanThreads) void k_vis_apply(ViewTable vt, uint64
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k)
         if (c[k] > 0u) bw[k] = box[base + (uint64_t)k * kScanThreads + tid];
-    // the sums of the blocks before this one
+    // the sums of the blocks before this one, from phase 1 or, without it, from
+    // their counts
     uint32_t bv = 0, bp = 0;
-    for (uint32_t j = tid; j < blockIdx.x; j += kScanThreads) {
-        bv += block_vis[j];
-        bp = sat_add(bp, block_pairs[j]);
+    if (block_vis) {
+        for (uint32_t j = tid; j < blockIdx.x; j += kScanThreads) {
+            bv += block_vis[j];
+            bp = sat_add(bp, block_pairs[j]);
+        }
+    } else {
+        const uint4 *c4 = reinterpret_cast<const uint4 *>(count);
+        for (uint32_t j = 0; j < blockIdx.x; ++j) {  // (kScanTile items are kScanThreads words)
+            const uint4 x = c4[(size_t)j * kScanThreads + tid];
+            bv += (x.x > 0u ? 1u : 0u) + (x.y > 0u ? 1u : 0u) + (x.z > 0u ? 1u : 0u) + (x.w > 0u ? 1u : 0u);
+            bp = sat_add(bp, sat_add(sat_add(x.x, x.y), sat_add(x.z, x.w)));
+        }
     }
     bv = wave_reduce(bv, 0u, sat_add);
     bp = wave_reduce(bp, 0u, sat_add);
@@ -280,8 +295,12 @@ void launch_visible_offsets(const ViewTable &vt, uint64_t n, const uint32_t *cou
         launch_fill_u32(view_seg, 0u, 2 * (GSR_MAX_VIEWS + 1), st);
         return;
     }
+    static_assert(kScanItems == 4, "a block's counts are one uint4 a thread");
     uint32_t *bv = block_tmp, *bp = block_tmp + nb;
-    hipLaunchKernelGGL(k_vis_reduce, dim3(nb), dim3(kScanThreads), 0, st, count, items, bv, bp);
+    if (nb <= kScanFewBlocks)
+        bv = bp = nullptr;
+    else
+        hipLaunchKernelGGL(k_vis_reduce, dim3(nb), dim3(kScanThreads), 0, st, count, items, bv, bp);
     hipLaunchKernelGGL(k_vis_apply, dim3(nb), dim3(kScanThreads), 0, st, vt, n, count, box, items, bv, bp, vis, poff,
                        ioff, item_box, chunk_item, chunks_cap, view_seg, hdr);
 }
@@ -349,6 +368,13 @@ void launch_export_items(const uint32_t *poff, const uint4 *item_box, const Rec 
 // ---------------------------------------------------------------------------
 constexpr int kBinThreads = 1024;
 constexpr uint32_t kBinLaneTiles = 48;
+// The one launch: its bands, items of a view and pairs of capacity per band at
+// most.  Forwards of three launches and of one: 1,000 items 37.8 / 30.4 us
+// (128x128) and 169 / 131 us (1920x1080 in 32,400 tiles), 8,000 items 46.5 / 41.5
+// us (640x480) and 169 / 164 us (1920x1080, capacity 520 k); of 16,000 items 55.5 /
+// 57.8 us and 78 / 92 us, each band walking all of them.
+constexpr uint32_t kBinSmallBands = 32;
+constexpr uint64_t kBinSmallItems = 8192, kBinSmallPairs = 32768;
 constexpr uint64_t kBinBandPairs = 2600000;  // pairs (of the capacity) a band of a view is meant to hold
 constexpr uint32_t kBinGroup = 16;  // 256 contiguous bytes of box words
 
@@ -373,6 +399,40 @@ __device__ __forceinline__ BinBox bin_box(const uint4 &bw, uint32_t r0, uint32_t
     b.z = bw.z;
     b.item = bw.w;
     return b;
+}
+
+// Adds a box to the difference array of the band that starts at row r0 (rows of
+// P words).
+__device__ __forceinline__ void bin_add_corners(uint32_t *s_tile, uint32_t P, const BinBox &b, uint32_t r0) {
+    if (!b.h) return;
+    uint32_t *at = s_tile + (b.y0 - r0) * P + b.x0;
+    atomicAdd(at, 1u);
+    atomicAdd(at + b.w, 0xffffffffu);
+    atomicAdd(at + b.h * P, 0xffffffffu);
+    atomicAdd(at + b.h * P + b.w, 1u);
+}
+
+// Sums along the rows of a difference array of ny rows of nx tiles, a wave each.
+__device__ __forceinline__ void bin_row_sums(uint32_t *s_tile, uint32_t nx, uint32_t ny) {
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, P = nx + 1;
+    const auto add = [](uint32_t a, uint32_t b) { return a + b; };
+    for (uint32_t y = wave; y < ny; y += kBinThreads / kWave) {
+        uint32_t carry = 0;
+        for (uint32_t x0 = 0; x0 < nx; x0 += kWave) {
+            const uint32_t x = x0 + lane;
+            const uint32_t inc = wave_inclusive_scan(x < nx ? s_tile[y * P + x] : 0u, add) + carry;
+            if (x < nx) s_tile[y * P + x] = inc;
+            carry = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        }
+    }
+}
+
+// Clears the slots' "moments written" flags, set by the backward compositing,
+// and the schedule's counters, filled by the forward; the grid shares the work.
+__device__ __forceinline__ void bin_clear(uint32_t m, uint32_t *__restrict__ pflag, uint32_t *__restrict__ tile_order) {
+    const uint64_t words = ((uint64_t)m + 3) / 4, nb = gridDim.x, w1 = words * (blockIdx.x + 1) / nb;
+    for (uint64_t i = words * blockIdx.x / nb + threadIdx.x; i < w1; i += kBinThreads) pflag[i] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < kCostBuckets) tile_order[threadIdx.x] = 0u;
 }
 
 // (share, view, tile rows) of a workgroup: views and bands one after the
@@ -401,7 +461,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(ViewTable vt, uint32_
     const BinTurn bt = bin_turn(vt, G, bands);
     if (bt.r0 >= bt.r1) return;  // uniform
     const uint32_t nx = (uint32_t)vt.v[bt.v].tiles_x, ny = bt.r1 - bt.r0, P = nx + 1, off = vt.v[bt.v].tile_off;
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t tid = threadIdx.x;
     for (uint32_t t = tid; t < P * (ny + 1); t += kBinThreads) s_tile[t] = 0u;
     __syncthreads();
     if (!hdr->overflow) {
@@ -409,27 +469,11 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(ViewTable vt, uint32_
         for (uint32_t q = tid;; q += kBinThreads) {
             const uint32_t k = bin_item(s0, q, bt.g, G);
             if (k >= s1) break;
-            const BinBox b = bin_box(item_box[k], bt.r0, bt.r1);
-            if (!b.h) continue;
-            uint32_t *at = s_tile + (b.y0 - bt.r0) * P + b.x0;
-            atomicAdd(at, 1u);
-            atomicAdd(at + b.w, 0xffffffffu);
-            atomicAdd(at + b.h * P, 0xffffffffu);
-            atomicAdd(at + b.h * P + b.w, 1u);
+            bin_add_corners(s_tile, P, bin_box(item_box[k], bt.r0, bt.r1), bt.r0);
         }
     }
     __syncthreads();
-    // sums along the rows (a wave each), then down the columns (a thread each)
-    const auto add = [](uint32_t a, uint32_t b) { return a + b; };
-    for (uint32_t y = wave; y < ny; y += kBinThreads / kWave) {
-        uint32_t carry = 0;
-        for (uint32_t x0 = 0; x0 < nx; x0 += kWave) {
-            const uint32_t x = x0 + lane;
-            const uint32_t inc = wave_inclusive_scan(x < nx ? s_tile[y * P + x] : 0u, add) + carry;
-            if (x < nx) s_tile[y * P + x] = inc;
-            carry = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-        }
-    }
+    bin_row_sums(s_tile, nx, ny);  // then down the columns (a thread each)
     __syncthreads();
     uint32_t *out = counts + (size_t)bt.g * vt.total_tiles + off + bt.r0 * nx;
     for (uint32_t x = tid; x < nx; x += kBinThreads) {
@@ -481,6 +525,51 @@ __device__ __forceinline__ void register_long(uint32_t tile, uint32_t len, uint3
     atomicMax(&hdr->max_long, len);
 }
 
+// Places the pairs of share g of G of the visible indices [s0, s1) in the tile
+// rows [r0, r1): s_tile holds each tile's next free entry, a row of the band
+// every `pitch` words.
+__device__ __forceinline__ void bin_place_items(uint32_t *s_tile, uint32_t pitch, uint32_t r0, uint32_t r1,
+                                                uint32_t s0, uint32_t s1, uint32_t g, uint32_t G,
+                                                const uint4 *__restrict__ item_box,
+                                                unsigned long long *__restrict__ entries) {
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const auto place = [&](uint32_t t, uint32_t z, uint32_t item) {
+        entries[atomicAdd(&s_tile[t], 1u)] = ((unsigned long long)z << 32) | item;
+    };
+    for (uint32_t q = w * kWave; bin_item(s0, q, g, G) < s1; q += kBinThreads) {  // the wave's first item: uniform
+        const uint32_t k = bin_item(s0, q + lane, g, G);
+        BinBox b{};
+        b.w = 1u;
+        if (k < s1) b = bin_box(item_box[k], r0, r1);
+        const uint32_t c = b.w * b.h, t_first = (b.y0 - r0) * pitch + b.x0;
+        const bool big = c > kBinLaneTiles;
+        uint32_t left = big ? 0u : c, col = 0, t = t_first;
+        while (__ballot(left > 0u)) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (left > 0u) {
+                    place(t, b.z, b.item);
+                    --left;
+                    ++t;
+                    if (++col == b.w) col = 0, t += pitch - b.w;
+                }
+            }
+        }
+        unsigned long long mb = __ballot(big);
+        while (mb) {
+            const int j = __builtin_ctzll(mb);
+            mb &= mb - 1ull;
+            const uint32_t tj = __builtin_amdgcn_readlane(t_first, j), wj = __builtin_amdgcn_readlane(b.w, j);
+            const uint32_t zj = __builtin_amdgcn_readlane(b.z, j), ij = __builtin_amdgcn_readlane(b.item, j);
+            const uint32_t nj = __builtin_amdgcn_readlane(c, j);
+            for (uint32_t q = lane; q < nj; q += kWave) {
+                const uint32_t y = q / wj;
+                place(tj + y * pitch + (q - y * wj), zj, ij);
+            }
+        }
+    }
+}
+
 __global__ __launch_bounds__(kBinThreads) void k_bin_place(ViewTable vt, uint32_t G, uint32_t bands,
                                                            const uint32_t *__restrict__ seg,
                                                            const uint4 *__restrict__ item_box,
@@ -495,12 +584,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_place(ViewTable vt, uint32_
     const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const bool overflow = hdr->overflow != 0u;
     const uint32_t m = overflow ? 0u : hdr->n_pairs;
-    // the slots' "moments written" flags, set by the backward compositing
-    {
-        const uint64_t words = ((uint64_t)m + 3) / 4, nb = gridDim.x, w1 = words * (blockIdx.x + 1) / nb;
-        for (uint64_t i = words * blockIdx.x / nb + tid; i < w1; i += kBinThreads) pflag[i] = 0u;
-    }
-    if (blockIdx.x == 0 && tid < kCostBuckets) tile_order[tid] = 0u;  // filled by the forward
+    bin_clear(m, pflag, tile_order);
     const BinTurn bt = bin_turn(vt, G, bands);
     if (bt.r0 >= bt.r1) return;  // uniform
     const uint32_t nx = (uint32_t)vt.v[bt.v].tiles_x, off = vt.v[bt.v].tile_off;
@@ -537,41 +621,71 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_place(ViewTable vt, uint32_
     const uint32_t *row = counts + (size_t)bt.g * vt.total_tiles + band0;
     for (uint32_t t = tid; t < T; t += kBinThreads) s_tile[t] += row[t];
     __syncthreads();
-    const auto place = [&](uint32_t t, uint32_t z, uint32_t item) {
-        entries[atomicAdd(&s_tile[t], 1u)] = ((unsigned long long)z << 32) | item;
-    };
-    for (uint32_t q = w * kWave; bin_item(s0, q, bt.g, G) < s1; q += kBinThreads) {  // the wave's first item: uniform
-        const uint32_t k = bin_item(s0, q + lane, bt.g, G);
-        BinBox b{};
-        b.w = 1u;
-        if (k < s1) b = bin_box(item_box[k], bt.r0, bt.r1);
-        const uint32_t c = b.w * b.h, t_first = (b.y0 - bt.r0) * nx + b.x0;
-        const bool big = c > kBinLaneTiles;
-        uint32_t left = big ? 0u : c, col = 0, t = t_first;
-        while (__ballot(left > 0u)) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (left > 0u) {
-                    place(t, b.z, b.item);
-                    --left;
-                    ++t;
-                    if (++col == b.w) col = 0, t += nx - b.w;
-                }
-            }
-        }
-        unsigned long long mb = __ballot(big);
-        while (mb) {
-            const int j = __builtin_ctzll(mb);
-            mb &= mb - 1ull;
-            const uint32_t tj = __builtin_amdgcn_readlane(t_first, j), wj = __builtin_amdgcn_readlane(b.w, j);
-            const uint32_t zj = __builtin_amdgcn_readlane(b.z, j), ij = __builtin_amdgcn_readlane(b.item, j);
-            const uint32_t nj = __builtin_amdgcn_readlane(c, j);
-            for (uint32_t q = lane; q < nj; q += kWave) {
-                const uint32_t y = q / wj;
-                place(tj + y * nx + (q - y * wj), zj, ij);
-            }
-        }
+    bin_place_items(s_tile, nx, bt.r0, bt.r1, s0, s1, bt.g, G, item_box, entries);
+}
+
+// All three in one launch, for calls of few items: a workgroup takes a band of
+// tile rows of a view and all of the view's items, so that its counters are the
+// tiles' totals; the pairs of the rows above come from the items' boxes.
+__global__ __launch_bounds__(kBinThreads) void k_bin_small(ViewTable vt, uint32_t bands,
+                                                           const uint32_t *__restrict__ seg,
+                                                           const uint4 *__restrict__ item_box,
+                                                           uint2 *__restrict__ ranges, uint32_t *__restrict__ long_tiles,
+                                                           uint32_t *__restrict__ tile_order,
+                                                           unsigned long long *__restrict__ entries,
+                                                           uint32_t *__restrict__ pflag, WsHeader *hdr) {
+    extern __shared__ uint32_t s_tile[];  // rows + 1 of tiles_x + 1
+    __shared__ uint32_t s_wave[2][kBinThreads / kWave];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const bool overflow = hdr->overflow != 0u;
+    bin_clear(overflow ? 0u : hdr->n_pairs, pflag, tile_order);
+    const BinTurn bt = bin_turn(vt, 1, bands);
+    if (bt.r0 >= bt.r1) return;  // uniform
+    const uint32_t nx = (uint32_t)vt.v[bt.v].tiles_x, ny = bt.r1 - bt.r0, P = nx + 1, T = nx * ny;
+    const uint32_t band0 = vt.v[bt.v].tile_off + bt.r0 * nx;
+    const uint32_t s0 = seg[bt.v], s1 = overflow ? s0 : seg[bt.v + 1];
+    for (uint32_t t = tid; t < P * (ny + 1); t += kBinThreads) s_tile[t] = 0u;
+    __syncthreads();
+    const auto add = [](uint32_t a, uint32_t b) { return a + b; };
+    uint32_t early = 0;  // pairs in the rows above
+    for (uint32_t k = s0 + tid; k < s1; k += kBinThreads) {
+        const uint4 bw = item_box[k];
+        const uint32_t y = bw.x >> 16, above = min(y + (bw.y >> 16), bt.r0);
+        if (above > y) early += (above - y) * (bw.y & 0xffffu);
+        bin_add_corners(s_tile, P, bin_box(bw, bt.r0, bt.r1), bt.r0);
     }
+    early = wave_reduce(early, 0u, add);
+    if (lane == 0) s_wave[0][w] = early;
+    __syncthreads();
+    bin_row_sums(s_tile, nx, ny);
+    __syncthreads();
+    for (uint32_t x = tid; x < nx; x += kBinThreads) {
+        uint32_t run = 0;
+        for (uint32_t y = 0; y < ny; ++y) s_tile[y * P + x] = run += s_tile[y * P + x];
+    }
+    __syncthreads();
+    // counts to starts, each thread a run of consecutive tiles
+    const uint32_t per = (T + kBinThreads - 1) / kBinThreads, t0 = min(tid * per, T), t1 = min(t0 + per, T);
+    uint32_t sum = 0;
+    for (uint32_t t = t0, at = t0 / nx * P + t0 % nx, x = t0 % nx; t < t1; ++t) {
+        sum += s_tile[at++];
+        if (++x == nx) x = 0, ++at;
+    }
+    const uint32_t inc = wave_inclusive_scan(sum, add);
+    if (lane == 63) s_wave[1][w] = inc;
+    __syncthreads();
+    uint32_t run = (overflow ? 0u : seg[GSR_MAX_VIEWS + 1 + bt.v]) + inc - sum;
+    for (uint32_t q = 0; q < kBinThreads / kWave; ++q) run += s_wave[0][q] + (q < w ? s_wave[1][q] : 0u);
+    for (uint32_t t = t0, at = t0 / nx * P + t0 % nx, x = t0 % nx; t < t1; ++t) {
+        const uint32_t n = s_tile[at];
+        s_tile[at++] = run;
+        ranges[band0 + t] = make_uint2(run, run + n);
+        if (n > (uint32_t)kGroupSortMax) register_long(band0 + t, n, long_tiles, hdr);
+        run += n;
+        if (++x == nx) x = 0, ++at;
+    }
+    __syncthreads();
+    bin_place_items(s_tile, P, bt.r0, bt.r1, s0, s1, 0, 1, item_box, entries);
 }
 
 hipError_t bin_allow_lds(size_t bytes) {
@@ -583,7 +697,7 @@ hipError_t bin_allow_lds(size_t bytes) {
                                (int)kBinMaxLds);
 }
 
-BinPlan bin_plan(const ViewTable &vt, uint64_t cap) {
+BinPlan bin_plan(const ViewTable &vt, uint64_t n, uint64_t cap) {
     const uint64_t V = (uint64_t)vt.n_views;
     const auto lds = [&](uint32_t bands) {
         size_t most = 0;
@@ -593,7 +707,17 @@ BinPlan bin_plan(const ViewTable &vt, uint64_t cap) {
         }
         return most;
     };
-    BinPlan p;
+    BinPlan p{};
+    // one launch: few items and no more pairs than its bands, a row of tiles each
+    // at least, place in a few us
+    uint32_t rows = 1;
+    for (int v = 0; v < vt.n_views; ++v) rows = std::max(rows, (uint32_t)vt.v[v].tiles_y);
+    const uint32_t bands = std::min(rows, kBinSmallBands);
+    if (n <= kBinSmallItems && cap <= V * bands * kBinSmallPairs && lds(bands) <= 65536) {
+        p.small_bands = bands;
+        p.lds_place = lds(bands);
+        return p;
+    }
     // (a row of the widest view, 4,096 tiles, and the one after it always fit)
     p.count_bands = 1;
     while (lds(p.count_bands) > kBinMaxLds) ++p.count_bands;
@@ -609,6 +733,11 @@ void launch_bin_pairs(const ViewTable &vt, const BinPlan &plan, uint32_t G, cons
                       uint32_t *tile_order, unsigned long long *entries, uint32_t *pflag, WsHeader *hdr,
                       hipStream_t st) {
     const uint32_t V = (uint32_t)vt.n_views;
+    if (plan.small_bands) {
+        hipLaunchKernelGGL(k_bin_small, dim3(V * plan.small_bands), dim3(kBinThreads), plan.lds_place, st, vt,
+                           plan.small_bands, seg, item_box, ranges, long_tiles, tile_order, entries, pflag, hdr);
+        return;
+    }
     hipLaunchKernelGGL(k_bin_count, dim3(G * V * plan.count_bands), dim3(kBinThreads), plan.lds_count, st, vt, G,
                        plan.count_bands, seg, item_box, counts, hdr);
     hipLaunchKernelGGL(k_bin_scan, dim3((vt.total_tiles + kWave - 1) / kWave), dim3(kBinThreads), 0, st, counts, G, vt.total_tiles,

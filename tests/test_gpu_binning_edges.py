@@ -75,3 +75,12 @@ def test_many_tiles(n):
     # 256 x 300 tiles of 16x8: counters for 76,800 tiles exceed one workgroup's LDS
     _check(n, [_camera(4096, 2400), _camera(40, 24)], 8, 9_000_000 if n > 100 else 600_000, f"{n} items, 76,800 tiles",
            reach=3.0, every=37 if n < 100 else 2000)
+
+
+@pytest.mark.parametrize("n,width,height,tile_h,capacity", [
+    (8192, 120, 150, 4, 32 * 32768), (8192, 120, 150, 4, 32 * 32768 + 1),  # 38 rows of tiles: bands of two
+    (8193, 120, 150, 4, 32 * 32768), (1, 17, 4, 4, 32768), (300, 17, 4, 4, 32769),
+    (1023, 2000, 40, 8, 5 * 32768), (1025, 2000, 40, 8, 5 * 32768 + 1), (9000, 64, 64, 16, 70_000)])
+def test_one_launch_lines(n, width, height, tile_h, capacity):
+    _check(n, [_camera(width, height)], tile_h, capacity, f"{n} items, {width}x{height}/{tile_h}, capacity {capacity}",
+           every=400)
