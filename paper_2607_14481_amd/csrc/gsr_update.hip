@@ -4,9 +4,11 @@
 //   * the pose step: Adam on each view's 6-DoF twist, then the SE(3)
 //     retraction of its world-to-camera transform,
 //   * the loop-closure Sim(3) relocation of Gaussians (or hierarchy nodes).
-// The first and last are elementwise and HBM-bound: the arrays are walked as
-// sequences of float4 (or float) units, so loads and stores are coalesced
-// whatever the row length of an array.
+// The first and last are elementwise and HBM-bound: every array is walked as
+// one flat sequence of float4 (or float) units, so loads and stores are
+// coalesced whatever the row length of an array.
+#include <algorithm>
+
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -50,24 +52,76 @@ __device__ __forceinline__ void adam_units(float *p, const float *g, float *m, f
     }
 }
 
-// A workgroup takes 64 Gaussians: the ones to update (all, or those some view
-// saw) are listed first, and the rows of the listed ones are then walked as
-// float4 (or float) units with every lane busy: the SH rows by the whole
-// workgroup, the other arrays by a wave each.
+// Segments of the flat walk: means (3n floats), log-scales (3n floats),
+// quaternions (n float4), opacities (n floats, on the logit), SH (n 3K/4
+// float4 when 3K is a multiple of 4, else n 3K floats).
 //
-// HBM-bound: 24 bytes a parameter.  The row length is a constant of the kernel,
-// since finding a unit's Gaussian and its place in the row by division by a
-// variable was what bound it: 136 k seen of 400 k Gaussians of degree 3 (225 MB)
-// took 71 us in one flat walk over all arrays, 55 us here.
-constexpr int kAdamGroup = 64;
-template <int K>
+// HBM-bound: 24 bytes a parameter, each array one ascending sweep.  The row
+// length is a constant and the unit index 32 bits wide wherever it fits: finding
+// a unit's Gaussian and its place in the row by 64-bit division by a variable
+// bound the smaller calls: 30 k Gaussians of degree 3 7.8 -> 7.2 us, 300 k of
+// degree 2 51.4 -> 49.8 us, 1 M as before (307 and 192 -> 188 us).
+template <int K, typename U>
 __global__ __launch_bounds__(256) void k_adam_step(AdamArgs A) {
+    constexpr bool kVec = (3 * K) % 4 == 0;
+    constexpr U kUnits = kVec ? 3 * K / 4 : 3 * K;  // units per SH row
+    const U n = (U)A.n, s0 = 3 * n, s1 = s0 + 3 * n, s2 = s1 + n, s3 = s2 + n, total = s3 + n * kUnits;
+    const U stride = (U)gridDim.x * 256;
+    for (U u = (U)blockIdx.x * 256 + threadIdx.x; u < total; u += stride) {
+        // Gaussian of this unit
+        const U gi = u < s0 ? u / 3 : u < s1 ? (u - s0) / 3 : u < s2 ? u - s1 : u < s3 ? u - s2 : (u - s3) / kUnits;
+        if (A.count && !seen(A.count, A.n, A.n_views, gi)) continue;
+        if (u < s0) {
+            adam_units<1>(A.p.means, A.g.means, A.m.means, A.v.means, u, A.a, A.step_size[0]);
+        } else if (u < s1) {
+            adam_units<1>(A.p.log_scales, A.g.log_scales, A.m.log_scales, A.v.log_scales, u - s0, A.a,
+                          A.step_size[1]);
+        } else if (u < s2) {
+            adam_units<4>(A.p.quats, A.g.quats, A.m.quats, A.v.quats, u - s1, A.a, A.step_size[2]);
+        } else if (u < s3) {
+            // opacity: the step is on l = ln(o / (1 - o)), with dL/dl = o (1 - o) dL/do
+            const U i = u - s2;
+            const float o = fminf(fmaxf(A.p.opacities[i], kOpacityLo), kOpacityHi);
+            float l = logf(o) - log1pf(-o);
+            float m = A.m.opacities[i], v = A.v.opacities[i];
+            adam_elem(l, o * (1.f - o) * A.g.opacities[i], m, v, A.a, A.step_size[3]);
+            A.p.opacities[i] = 1.f / (1.f + expf(-l));
+            A.m.opacities[i] = m;
+            A.v.opacities[i] = v;
+        } else {
+            const U w = u - s3, c = w - gi * kUnits;  // unit of the row
+            if constexpr (kVec) {
+                // (the first unit of a row holds the three DC floats and one float of k = 1)
+                const float rate = A.step_size[5], first = c == 0 ? A.step_size[4] : rate;
+                float4 P = reinterpret_cast<float4 *>(A.p.sh)[w], G = reinterpret_cast<const float4 *>(A.g.sh)[w];
+                float4 M = reinterpret_cast<float4 *>(A.m.sh)[w], V = reinterpret_cast<float4 *>(A.v.sh)[w];
+                adam_elem(P.x, G.x, M.x, V.x, A.a, first);
+                adam_elem(P.y, G.y, M.y, V.y, A.a, first);
+                adam_elem(P.z, G.z, M.z, V.z, A.a, first);
+                adam_elem(P.w, G.w, M.w, V.w, A.a, rate);
+                reinterpret_cast<float4 *>(A.p.sh)[w] = P;
+                reinterpret_cast<float4 *>(A.m.sh)[w] = M;
+                reinterpret_cast<float4 *>(A.v.sh)[w] = V;
+            } else {
+                adam_units<1>(A.p.sh, A.g.sh, A.m.sh, A.v.sh, w, A.a, c < 3 ? A.step_size[4] : A.step_size[5]);
+            }
+        }
+    }
+}
+
+// The sparse step of mid-sized calls: a workgroup takes 64 Gaussians, lists the
+// ones some view saw and walks their rows with every lane busy, the SH rows by
+// the whole workgroup, the other arrays by a wave each.
+constexpr int kAdamGroup = 64;
+constexpr uint64_t kAdamListMin = 32768, kAdamListSpan = 512ull << 20;
+template <int K>
+__global__ __launch_bounds__(256) void k_adam_listed(AdamArgs A) {
     constexpr bool kVec = (3 * K) % 4 == 0;
     constexpr uint32_t kW = kVec ? 4 : 1, kUnits = 3 * K / kW;  // floats a unit; units an SH row
     __shared__ uint8_t list[kAdamGroup];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t base = (uint64_t)blockIdx.x * kAdamGroup;
-    const bool on = base + lane < A.n && (!A.count || seen(A.count, A.n, A.n_views, base + lane));
+    const bool on = base + lane < A.n && seen(A.count, A.n, A.n_views, base + lane);
     const unsigned long long m = __ballot(on);
     if (wave == 0 && on) list[__popcll(m & ((1ull << lane) - 1ull))] = (uint8_t)lane;
     __syncthreads();
@@ -118,14 +172,35 @@ __global__ __launch_bounds__(256) void k_adam_step(AdamArgs A) {
     }
 }
 
+template <int K>
+static void launch_adam(const AdamArgs &A, hipStream_t st) {
+    // The lanes of unseen Gaussians cost the flat walk most of its time, but from
+    // about half a gigabyte of arrays on (parameters, gradients, moments) five
+    // ascending sweeps use the memory better than runs of rows dealt over all of
+    // them.  Listed and flat: 400 k (378 MB, 191 k seen) 73 / 78 us, 560 k (529 MB)
+    // 80.5 / 99 us, 700 k (661 MB) 125.3 / 124.3 us, 1 M (944 MB, 478 k seen) 251 /
+    // 235 us; 20 k Gaussians 6.1 / 5.1 us.
+    const uint64_t span = A.n * (11 + 3 * K) * 16;
+    if (A.count && A.n >= kAdamListMin && span <= kAdamListSpan) {
+        hipLaunchKernelGGL(k_adam_listed<K>, dim3((unsigned)((A.n + kAdamGroup - 1) / kAdamGroup)), dim3(256), 0, st, A);
+        return;
+    }
+    constexpr uint64_t kUnits = (3 * K) % 4 == 0 ? 3 * K / 4 : 3 * K;
+    const uint64_t total = A.n * (8 + kUnits), blocks = std::min<uint64_t>((total + 255) / 256, 65536);
+    // (an index that steps past the end by a stride must not wrap)
+    if (total + blocks * 256 < (1ull << 32))
+        hipLaunchKernelGGL((k_adam_step<K, uint32_t>), dim3((unsigned)blocks), dim3(256), 0, st, A);
+    else
+        hipLaunchKernelGGL((k_adam_step<K, uint64_t>), dim3((unsigned)blocks), dim3(256), 0, st, A);
+}
+
 void launch_adam_step(const AdamArgs &A, hipStream_t st) {
     if (A.n == 0) return;
-    const dim3 grid((unsigned)((A.n + kAdamGroup - 1) / kAdamGroup));
     switch (A.sh_k) {
-        case 1: hipLaunchKernelGGL(k_adam_step<1>, grid, dim3(256), 0, st, A); break;
-        case 4: hipLaunchKernelGGL(k_adam_step<4>, grid, dim3(256), 0, st, A); break;
-        case 9: hipLaunchKernelGGL(k_adam_step<9>, grid, dim3(256), 0, st, A); break;
-        default: hipLaunchKernelGGL(k_adam_step<16>, grid, dim3(256), 0, st, A); break;
+        case 1: launch_adam<1>(A, st); break;
+        case 4: launch_adam<4>(A, st); break;
+        case 9: launch_adam<9>(A, st); break;
+        default: launch_adam<16>(A, st); break;
     }
 }
 

@@ -1,5 +1,5 @@
-"""Edges of two kernels' work split: the Adam step's groups of 64 Gaussians and
-row forms, against the FP64 update oracle with the tolerances of the update
+"""Edges of two kernels' work split: the Adam step's row forms and its groups of
+64 listed Gaussians (bitwise the dense step's rows), against the FP64 update oracle with the tolerances of the update
 tests; the cut's four nodes per thread, over forests whose siblings lie
 anywhere, where the cut is the FP64 reference's exactly."""
 from types import SimpleNamespace
@@ -32,6 +32,32 @@ def test_adam_groups(n, deg):
     _compare(_host(P), refP, "params")
     _compare(_host(M), refM, "exp_avg")
     _compare(_host(V), refV, "exp_avg_sq", rtol=1e-4, atol=1e-9)
+
+
+@pytest.mark.parametrize("deg", [0, 1, 2, 3])
+@pytest.mark.parametrize("n", [32_767, 32_768, 32_831])  # the flat walk; listed rows, whole and ragged last groups
+def test_sparse_adam_is_the_dense_step_on_the_seen(n, deg):
+    import torch
+    from paper_2607_14481_amd.rasterizer import GaussianRasterizer
+    from ._util import params_to_device, poses_to_device
+    wl = S.small_view(seed=n + deg, n=n, width=96, height=72, sh_degree=deg, xy_half=5.0, log_scale_mean=-4.0)
+    rast = GaussianRasterizer(wl.cameras, deg)
+    params = params_to_device(wl.scene)
+    _, ws = rast.forward(params, poses_to_device(wl.cameras))
+    st = gsr.export_state(ws, params, deg, wl.cameras, rast.cfg)
+    seen = torch.tensor(st["tile_counts"].astype(np.int64) > 0, device="cuda")
+    assert 0 < int(seen.sum()) < n
+    g = [torch.randn_like(t) for t in params]
+    both = []
+    for sparse in (True, False):
+        p, m, v = [t.clone() for t in params], [0.1 * t for t in g], [t * t for t in g]
+        kw = dict(ws=ws, cams=wl.cameras, cfg=rast.cfg) if sparse else {}
+        gsr.adam_step(p, g, m, v, deg, 2, _acfg(gsr, sparse=sparse), **kw)
+        both.append((p, m, v))
+    start = (params, [0.1 * t for t in g], [t * t for t in g])
+    for a, b, c in zip(*both, start):
+        for x, y, z in zip(a, b, c):
+            assert torch.equal(x[seen], y[seen]) and torch.equal(x[~seen], z[~seen])
 
 
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 1023, 1025, 5002])
