@@ -49,10 +49,10 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def measured_traffic(workload, kernel):
+def measured_traffic(workload, kernel, tile_h):
     """HBM bytes per dispatch of `kernel` from the committed byte-counter
-    profile, if it covers this workload and the kernel sources it was taken on
-    are the current ones (else None)."""
+    profile, if it covers this workload at this tile height and the kernel
+    sources it was taken on are the current ones (else None)."""
     import hashlib
     path = os.path.join(ROOT, "profiles", f"{TRAFFIC_PROFILES.get(workload, '-')}_hbm_traffic.md")
     if not os.path.exists(path):
@@ -61,7 +61,7 @@ def measured_traffic(workload, kernel):
     for line in open(path):
         if line.startswith("traffic-json: "):
             info = json.loads(line[len("traffic-json: "):])
-    if info is None or kernel not in info["kernel"]:
+    if info is None or kernel not in info["kernel"] or info.get("tile_h", tile_h) != tile_h:
         return None
     h = hashlib.sha256()
     for f in info["sources"]:
@@ -806,19 +806,17 @@ def run_local_ba(iters=10, repeats=30, cpu_baseline=True):
         log(f"[bench] BA graph capture failed: {e}")
         same = None
     n_obs = int((P.obs_cam >= 0).sum())
-    # algorithmic bytes of one iteration: the landmark kernel reads pose, landmark
-    # and pixel per observation and writes a 608-B record per observation in a
-    # free keyframe and 80 B per landmark; the assembly reads 312 B per such
-    # observation (diagonal blocks) and 2 x 144 B per pair of them in one landmark
-    # (off-diagonal blocks); the update reads 144 B per such observation plus
-    # 48 B per landmark and writes 24 B per landmark.
+    # algorithmic bytes of one iteration: the landmark kernel reads pixel and camera
+    # index of every observation (20 B) and every landmark, which it writes back
+    # with a 128-B record (24 + 24 + 128 B); the assembly reads the observation, its
+    # landmark and the record again per observation of a free keyframe (diagonal
+    # blocks, 172 B) and per pair of them in one landmark (off-diagonal blocks, one
+    # record, one landmark and two observations: 192 B).
     free_obs = (P.obs_cam >= 0) & (P.free_slot[np.maximum(P.obs_cam, 0)] >= 0)
     per_lm = free_obs.sum(axis=1)
     n_free_obs, n_pairs = int(per_lm.sum()), int((per_lm * (per_lm - 1) // 2).sum())
     K = P.n_landmarks
-    it_bytes = (n_obs * (96 + 24 + 16) + n_free_obs * 608 + K * 80
-                + n_free_obs * 312 + n_pairs * 288
-                + n_free_obs * 144 + K * (48 + 24))
+    it_bytes = n_obs * 20 + K * (24 + 24 + 128) + n_free_obs * 172 + n_pairs * 192
     it_ms = eager_med / iters
     out = {"workload": f"local BA: 20 keyframes (4 fixed), 10,000 landmarks, {n_obs} observations (2-8 consecutive "
                        f"keyframes per landmark), focal length optimised, {iters} LM iterations, FP64",
@@ -832,8 +830,8 @@ def run_local_ba(iters=10, repeats=30, cpu_baseline=True):
            "paper_ms_rtx4090": 15.9,
            "iteration_traffic": {"algorithmic_bytes": it_bytes, "GB_per_s": round(it_bytes / (it_ms * 1e-3) / 1e9, 1),
                                  "frac_of_hbm_peak": round(it_bytes / (it_ms * 1e-3) / 8e12, 4),
-                                 "note": "whole iteration (4 launches); the dominant kernel, the one-workgroup "
-                                         "Cholesky of the 97-unknown reduced system, is bound by its serial "
+                                 "note": "whole iteration (3 launches); the dominant kernel, the one-workgroup "
+                                         "factorisation of the 97-unknown reduced system, is bound by its serial "
                                          "chain, not by HBM or the FP64 units"}}
     if cpu_baseline:
         from oracle import ba as B
@@ -990,7 +988,7 @@ def main():
         dom = max(comp, key=comp.get)
         flops, dom_ms = (bwd_flops if dom == "composite_bwd" else fwd_flops), comp[dom]
     achieved = flops / (dom_ms * 1e-3) / 1e12
-    traffic = measured_traffic(args.workload, dom)
+    traffic = measured_traffic(args.workload, dom, tile_h)
     roofline = {"kernel": dom, "bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4),
                 "traffic": traffic["bytes"] if traffic else None,
