@@ -42,34 +42,43 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t *l
 }
 
 // ---------------------------------------------------------------------------
-// Generic reduce-then-scan.  Phase 1: per-block sums of a per-element value.
-// Phase 2: one block scans the block sums.  Phase 3: per-block scan + offset,
-// handing each element its exclusive prefix to an epilogue.
+// Ordered compaction of byte flags, reduce-then-scan: out_idx receives, in
+// ascending order, the indices i < n with flags[i] != 0; their number goes to
+// *out_count.  Phase 1 counts each block of kScanTile flags; phase 2 writes a
+// block's indices from the sum of the blocks before it, which each block adds
+// up itself while they are few (kFlagFewBlocks) and a launch between scans
+// otherwise: 4.6 M flags, 4,464 blocks, take 14.6 us with the one and 20.6 us with
+// the other.
 // ---------------------------------------------------------------------------
-template <class F>
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(F f, const uint32_t *__restrict__ n_dev, uint64_t n_host,
-                                                              uint32_t *__restrict__ block_sums) {
-    __shared__ uint32_t lds[4];
-    const uint64_t n = n_dev ? (uint64_t)*n_dev : n_host;
-    const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
-    uint32_t acc = 0;
-    if (base < n) {
+constexpr uint32_t kFlagFewBlocks = 8192;
+
+// The flags of items [base, base + 4) (base a multiple of 4, flags aligned) as
+// bits; none past n.
+__device__ __forceinline__ uint32_t four_flags(const uint8_t *__restrict__ flags, uint64_t base, uint64_t n) {
+    static_assert(kScanItems == 4, "a thread's flags are one word");
+    uint32_t bits = 0;
+    if (base + 4 <= n) {
+        const uint32_t w = *reinterpret_cast<const uint32_t *>(flags + base);
 #pragma unroll
-        for (int k = 0; k < kScanItems; ++k) {
-            const uint64_t i = base + (uint64_t)threadIdx.x * kScanItems + k;
-            if (i < n) acc = sat_add(acc, f(i));
-        }
+        for (int k = 0; k < 4; ++k) bits |= ((w >> (8 * k) & 0xffu) ? 1u : 0u) << k;
+    } else {
+        for (int k = 0; k < 4; ++k) bits |= (base + k < n && flags[base + k] ? 1u : 0u) << k;
     }
+    return bits;
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_flag_count(const uint8_t *__restrict__ flags, uint64_t n,
+                                                             uint32_t *__restrict__ block_sums) {
+    __shared__ uint32_t lds[4];
     uint32_t total;
-    block_exclusive_scan(acc, lds, total);
+    block_exclusive_scan(
+        (uint32_t)__popc(four_flags(flags, (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems, n)),
+        lds, total);
     if (threadIdx.x == 0) block_sums[blockIdx.x] = total;
 }
 
-// Single workgroup: exclusive scan of nb block sums in place; total -> *out_total.
-// With `cap_hdr` set the total is the pair count and the overflow decision
-// (total > capacity) is taken here too.
-__global__ __launch_bounds__(1024) void k_scan_blocks(uint32_t *__restrict__ block_sums, uint32_t nb,
-                                                      uint32_t *__restrict__ out_total, WsHeader *cap_hdr) {
+// Single workgroup: exclusive scan of nb block sums in place.
+__global__ __launch_bounds__(1024) void k_scan_blocks(uint32_t *__restrict__ block_sums, uint32_t nb) {
     __shared__ uint32_t lds[16];
     __shared__ uint32_t carry;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -88,46 +97,43 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(uint32_t *__restrict__ blo
         if (threadIdx.x == 1023) carry = sat_add(before, inc);
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        *out_total = carry;
-        if (cap_hdr) cap_hdr->overflow = carry > cap_hdr->pair_capacity ? 1u : 0u;
-    }
 }
 
-// Ordered compaction of byte flags: out_idx receives, in ascending order, the
-// indices i < n with flags[i] != 0; their number goes to *out_count.
-struct ByteFlag {
-    const uint8_t *f;
-    __device__ uint32_t operator()(uint64_t i) const { return f[i] ? 1u : 0u; }
-};
-
+// scanned: block_sums holds the sums of the blocks before, not the blocks' own.
 __global__ __launch_bounds__(kScanThreads) void k_flag_compact_apply(const uint8_t *__restrict__ flags, uint64_t n,
                                                                      const uint32_t *__restrict__ block_sums,
-                                                                     uint32_t *__restrict__ out_idx) {
-    __shared__ uint32_t lds[4];
+                                                                     int scanned, uint32_t *__restrict__ out_idx,
+                                                                     uint32_t *__restrict__ out_count) {
+    __shared__ uint32_t lds[4], s_before[4];
     const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
-    uint32_t bits = 0, cnt = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        const bool on = base + k < n && flags[base + k] != 0;
-        bits |= (on ? 1u : 0u) << k;
-        cnt += on;
+    const uint32_t bits = four_flags(flags, base, n);
+    uint32_t before = 0;
+    if (scanned) {
+        before = block_sums[blockIdx.x];
+    } else {
+        for (uint32_t j = threadIdx.x; j < blockIdx.x; j += kScanThreads) before += block_sums[j];
+        before = wave_reduce(before, 0u, sat_add);
+        if ((threadIdx.x & 63) == 0) s_before[threadIdx.x >> 6] = before;
+        __syncthreads();
+        before = s_before[0] + s_before[1] + s_before[2] + s_before[3];
     }
     uint32_t total;
-    uint32_t pos = block_sums[blockIdx.x] + block_exclusive_scan(cnt, lds, total);
+    uint32_t pos = before + block_exclusive_scan((uint32_t)__popc(bits), lds, total);
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k)
         if (bits & (1u << k)) out_idx[pos++] = (uint32_t)(base + k);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *out_count = before + total;
 }
 
 void launch_compact_flags(const uint8_t *flags, uint64_t n, uint32_t *out_idx, uint32_t *block_tmp,
                           uint32_t *out_count, hipStream_t st) {
     const uint32_t nb = (uint32_t)((n + kScanTile - 1) / kScanTile);
     if (nb == 0) return;
-    hipLaunchKernelGGL(k_scan_reduce<ByteFlag>, dim3(nb), dim3(kScanThreads), 0, st, ByteFlag{flags},
-                       (const uint32_t *)nullptr, n, block_tmp);
-    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, block_tmp, nb, out_count, (WsHeader *)nullptr);
-    hipLaunchKernelGGL(k_flag_compact_apply, dim3(nb), dim3(kScanThreads), 0, st, flags, n, block_tmp, out_idx);
+    const bool few = nb <= kFlagFewBlocks;
+    hipLaunchKernelGGL(k_flag_count, dim3(nb), dim3(kScanThreads), 0, st, flags, n, block_tmp);
+    if (!few) hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(1024), 0, st, block_tmp, nb);
+    hipLaunchKernelGGL(k_flag_compact_apply, dim3(nb), dim3(kScanThreads), 0, st, flags, n, block_tmp, few ? 0 : 1,
+                       out_idx, out_count);
 }
 
 // ---------------------------------------------------------------------------

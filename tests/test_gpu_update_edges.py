@@ -73,3 +73,19 @@ def test_cut_of_any_forest(n):
     cam = S.pinhole(160, 120, S.look_at(eye, eye + [1.0, 0.0, 0.0]))
     for tau in (0.5, 8.0):
         _check(h, cam, f"forest of {n}, tau {tau}", tau)
+
+
+@pytest.mark.parametrize("n", [8192 * 1024, 8192 * 1024 + 1])  # blocks of flags added up by each block, or scanned
+def test_cut_of_many_nodes(n):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    big = torch.rand(n, generator=g, device="cuda") < 0.4  # inner nodes far coarser than the threshold: they descend
+    means = torch.zeros((n, 3), device="cuda")
+    means[:, 2] = 10.0
+    log_scales = torch.where(big, 3.0, -8.0)[:, None].repeat(1, 3).contiguous()
+    nodes = [means, log_scales, torch.ones((n, 4), device="cuda"), torch.ones(n, device="cuda"),
+             torch.zeros((n, 1, 3), device="cuda")]
+    parent = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    cam = S.Camera(64, 48, 50.0, 50.0, 32.0, 24.0, np.eye(4, dtype=np.float32))
+    cut = gsr.hierarchy_cut(nodes, 0, parent, big.to(torch.int32), cam, torch.eye(4, device="cuda"), 1.5)
+    assert torch.equal(cut.to(torch.int64), torch.nonzero(~big)[:, 0])
