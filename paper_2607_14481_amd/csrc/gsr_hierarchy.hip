@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void k_cut_select(const int32_t *__restrict__ 
 #pragma unroll
     for (int q = 0; q < kSelectNodes; ++q) a[q] = q < m ? parent[i0 + q] : -1;
     uint32_t out = 0;
-    int64_t walked = -2;
+    int64_t walked = INT64_MIN;  // (no 32-bit parent: any negative one marks a root)
     bool all = false;  // every ancestor from `walked` up descends
 #pragma unroll
     for (int q = 0; q < kSelectNodes; ++q) {
