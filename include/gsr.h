@@ -204,7 +204,9 @@ int gsr_rasterize_forward(void *ws, size_t ws_bytes, const gsr_gaussians *g, int
 /*
  * Backward pass of the most recent forward on this workspace (same g, views,
  * cams, world_to_cam, bg, cfg).  out_rgb: the forward's output image, unchanged.
- * dL_drgb: device, same layout as out_rgb.  grads: device outputs, overwritten.
+ * dL_drgb: device, same layout as out_rgb; a value of it that is not finite spoils
+ * the gradients of the Gaussians that composite on its pixel (and the view's pose
+ * gradient) and of no others.  grads: device outputs, overwritten.
  * dL_dworld_to_cam: device [n_views][16] (row-major, last row zero), may be
  * NULL.  dL_dtwist: device [n_views][6], gradient of a left perturbation
  * exp(xi^) T with xi = (rho, phi), translation first, may be NULL.
