@@ -1,6 +1,7 @@
 """Values that are not finite stay where they belong, in every form of the
 compositing (waves per tile, slabs per wave): an upstream gradient of a pixel
-reaches the Gaussians that composite on that pixel.  The footprints come from
+reaches the Gaussians that composite on that pixel, and a Gaussian at infinity
+no pixel.  The footprints come from
 the projection formula in FP64; everything outside them is bit for bit what it is
 with a finite value in that place."""
 import numpy as np
@@ -68,3 +69,33 @@ def test_upstream_of_one_pixel(w, h, tile_h, value):
         grads.append([t.clone() for t in g])
     _same(*grads, ~on, "not on the pixel")
     assert not torch.isfinite(grads[0][4].cpu()[torch.tensor(on)]).all(dim=-1).any()
+
+
+@pytest.mark.parametrize("w,h,tile_h", FORMS)
+def test_gaussian_at_infinity(w, h, tile_h):
+    """A mean at infinity in front of the camera has no centre on the image and
+    composites nowhere: the image, the other Gaussians' gradients and its own of
+    the shape and the opacity (zero) are those without it."""
+    import torch
+    sc, cam, _ = _scene(w, h)
+    params, w2c = params_to_device(sc), poses_to_device([cam])
+    last = torch.arange(len(sc.means), device="cuda") == len(sc.means) - 1
+    target = torch.rand(3 * h * w, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    out = []
+    for far in (True, False):
+        p = [t.clone() for t in params]
+        if far:
+            p[0][last] = torch.tensor([0.0, 0.0, np.inf], device="cuda")
+        else:
+            p[3][last] = 0.0  # culled
+        rast = GaussianRasterizer([cam], 0, tile_h=tile_h)
+        rgb, ws = rast.forward(p, w2c)
+        grads, _, _ = rast.backward(ws, p, w2c, (0.0, 0.0, 0.0), rgb, target - 0.5)
+        step = rast.step_l1(p, w2c, (0.0, 0.0, 0.0), target)
+        out.append(([rgb, step[0]], grads, step[2]))
+    for x, y in zip(out[0][0], out[1][0]):
+        np.testing.assert_array_equal(x.cpu().numpy(), y.cpu().numpy())
+    for k in (1, 2):
+        _same(out[0][k], out[1][k], ~last.cpu().numpy(), "the others")
+        for g in out[0][k][1:4]:
+            assert (g[last] == 0).all()
