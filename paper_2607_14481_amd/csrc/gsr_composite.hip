@@ -433,6 +433,11 @@ __device__ __forceinline__ float swap_add16(float x, float y) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// x y, and 0 where either is 0, whatever the other (v_mul_legacy_f32; as the
+// compiler's intrinsic, so that it keeps the waits before the lane swaps that
+// read the product).
+__device__ float mul_legacy(float x, float y) __asm("llvm.amdgcn.fmul.legacy");
+
 // A record's part of the lanes of `on` and of no others: with w = alpha T, the
 // colour gradient sums (zero before the first of RPL rows), gB (g . the colour
 // behind the record, grgb = g . its own) and T.  w is undefined elsewhere.  By
@@ -447,9 +452,9 @@ __device__ __forceinline__ void backward_add(unsigned long long on, float alpha,
     if constexpr (RPL == 1) {
         const bool ok = __builtin_amdgcn_inverse_ballot_w64(on);
         w = ok ? alpha * T : 0.f;
-        asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(a_c0) : "v"(w), "v"(g0));
-        asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(a_c1) : "v"(w), "v"(g1));
-        asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(a_c2) : "v"(w), "v"(g2));
+        a_c0 = mul_legacy(w, g0);
+        a_c1 = mul_legacy(w, g1);
+        a_c2 = mul_legacy(w, g2);
         gB = ok ? fmaf(-w, grgb, gB) : gB;
         T -= w;  // T (1 - alpha)
     } else {
