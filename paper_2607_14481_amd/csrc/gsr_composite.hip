@@ -62,10 +62,8 @@
 // spoils the gradients of the Gaussians that composite on its pixel, and of no
 // others.  (The steps of one view cost up
 // to 0.5 % for it: 70.5 against 70.2 us at 128 x 128, 428 against 426 us at
-// 720p, 520 against 521 us at 1080p with 1M Gaussians.)  A Gaussian whose centre
-// or exponent is not a number (a mean at infinity in front of the camera) reaches
-// no pixel: the clamp to 0.99 would make an opaque one of it, so alpha is tested
-// before the clamp.
+// 720p, 520 against 521 us at 1080p with 1M Gaussians.)  An exponent
+// that is not a number reaches no pixel.
 //
 // Schedule.  The forward files every tile in a bucket of its replay count
 // (nmax), and the backward's workgroups take the tiles heaviest first: in
@@ -164,9 +162,7 @@ __device__ __forceinline__ void stage_record(const Rec &r, uint32_t first_pair, 
     const uint32_t by = __float_as_uint(r.r2.z);
     int y0 = max((int)(by & 0xffffu) - (int)c.oy, 0), y1 = min((int)(by >> 16) - (int)c.oy, (int)tile_h - 1);
     ellipse_rows_in_band(r.r0.z, r.r0.w, r.r1.x, r.r1.y, ut, vt, y0, y1);
-    // (a centre that is not a number, as of a Gaussian at infinity, reaches nothing)
-    const bool centred = ut == ut && vt == vt;
-    const uint32_t smask = y0 <= y1 && centred ? ((2u << (y1 >> 2)) - 1u) & ~((1u << (y0 >> 2)) - 1u) : 0u;
+    const uint32_t smask = y0 <= y1 ? ((2u << (y1 >> 2)) - 1u) & ~((1u << (y0 >> 2)) - 1u) : 0u;
     // pair index in emission order: offset + row-major position in the tile box
     const uint32_t bx = __float_as_uint(r.r2.y);
     const uint32_t tx0 = (bx & 0xffffu) / kTileW, tx1 = (bx >> 16) / kTileW;
@@ -219,6 +215,13 @@ __device__ __forceinline__ RowQuad row_quad(const float4 &a, const float4 &b, fl
 }
 __device__ __forceinline__ float alpha_exponent(const RowQuad &rq, const float4 &b, float dy) {
     return fmaf(fmaf(b.x, dy, rq.q), dy, rq.p);
+}
+
+// Alpha before the clamp to 0.99: exp2(ex), and 0 where that is not a number (of
+// which the clamp would make 0.99).  The median with 0 and 1 is a modifier of the
+// instruction, and what it cuts off the clamp would too.
+__device__ __forceinline__ float raw_alpha(float ex) {
+    return __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(ex), 0.f, 1.f);
 }
 
 // Zero gradient rows of the Gaussians of tile t's slice that no view saw, one
@@ -337,7 +340,7 @@ __device__ __forceinline__ bool forward_list(const Staged<W> &sh, unsigned long 
 #pragma unroll
             for (int k = 0; k < KP; ++k) {
                 const float dy = a.y - (pyl + (float)(4 * k));
-                al[q][k] = __builtin_amdgcn_exp2f(alpha_exponent(rq, b[q], dy));
+                al[q][k] = fminf(kAlphaMax, raw_alpha(alpha_exponent(rq, b[q], dy)));
             }
         }
 #pragma unroll
@@ -345,9 +348,8 @@ __device__ __forceinline__ bool forward_list(const Staged<W> &sh, unsigned long 
             const uint32_t pos = pos0 + (uint32_t)j[q];
 #pragma unroll
             for (int k = 0; k < KP; ++k) {
-                // (tested before the clamp, which makes 0.99 of a value that is not a number)
                 const bool ok = al[q][k] >= kAlphaMin;
-                const float wa = fminf(kAlphaMax, al[q][k]) * T[k];
+                const float wa = al[q][k] * T[k];
                 const float Tn = T[k] - wa;  // T (1 - alpha)
                 // a stopped pixel has Tn <= 0 < kTMin, so it never adds again; the
                 // pixel stops where ok holds and add does not
@@ -533,9 +535,9 @@ __device__ __forceinline__ void tile_backward(Staged<W> &sh, Reduce<W> &bw, cons
                     for (int k = 0; k < RPL; ++k) {
                         if (RPL > 1 && !(smask & (1u << k))) continue;
                         const float dy = a.y - (pyl + (float)(4 * k));
-                        const float araw = __builtin_amdgcn_exp2f(alpha_exponent(rq, b, dy));
+                        const float araw = raw_alpha(alpha_exponent(rq, b, dy));
                         const float alpha = fminf(kAlphaMax, araw);
-                        const unsigned long long on = __ballot(pos < ncon[k]) & __ballot(araw >= kAlphaMin);
+                        const unsigned long long on = __ballot(pos < ncon[k]) & __ballot(alpha >= kAlphaMin);
                         const float grgb = fmaf(g0[k], b.z, fmaf(g1[k], b.w, g2[k] * d.x));
                         // alpha dL/dalpha = alpha T g.c - alpha g.B / (1 - alpha), with
                         // B the colour behind this Gaussian; with w = alpha T and

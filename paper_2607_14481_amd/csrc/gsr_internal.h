@@ -58,6 +58,8 @@ static_assert(sizeof(WsHeader) == 256, "header is 256 bytes");
 // The inclusive pixel box (x0..x1, y0..y1) is that of the alpha >= 1/255
 // ellipse.  The centre is stored as u = u_hi + u_lo (double-float) so that
 // tile-relative offsets keep ~1e-6 px accuracy; r3 = (u_lo, v_lo, 0, 0) holds the low parts.
+// A centre that is no finite float (of a mean at infinity) is put at minus
+// infinity, where no slab of a tile lists it.
 // 64 bytes: the compositing gathers them, and a gather touches one half of a
 // cache line, never two (with records of 48 bytes, the low parts and the pair
 // offsets in three arrays, compositing 8 views of 1 M items took 1,266 us, with

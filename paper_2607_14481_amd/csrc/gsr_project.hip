@@ -297,12 +297,13 @@ __global__ __launch_bounds__(kProjThreads, STAGE ? 3 : 4) void k_project_fwd(
                 col[2] += (double)shp[3 * k + 2] * Y[k];
             }
             const double idet = 1.0 / det;
-            const float uh = (float)u, vh = (float)vv;
+            const bool centred = fabs(u) < 1e38 && fabs(vv) < 1e38;
+            const float uh = centred ? (float)u : -__builtin_inff(), vh = (float)vv;
             Rec r;
             r.r0 = make_float4(uh, vh, (float)(cc * idet), (float)(-cb * idet));
             r.r1 = make_float4((float)(ca * idet), op, (float)fmax(col[0], 0.0), (float)fmax(col[1], 0.0));
             r.r2 = make_float4((float)fmax(col[2], 0.0), __uint_as_float(bx), __uint_as_float(by), 0.f);
-            r.r3 = make_float4((float)(u - (double)uh), (float)(vv - (double)vh), 0.f, 0.f);
+            r.r3 = make_float4(centred ? (float)(u - (double)uh) : 0.f, (float)(vv - (double)vh), 0.f, 0.f);
             rec[item] = r;
         }
     }
