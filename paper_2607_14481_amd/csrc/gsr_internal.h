@@ -47,9 +47,11 @@ struct WsHeader {
     uint32_t n_long;         // tiles whose list is longer than kGroupSortMax
     uint32_t long_pairs;     // entries in those lists
     uint32_t max_long;       // the longest of them
-    uint32_t pad[47];
+    uint32_t pad[15];
+    uint32_t infinite;       // some visible item has an infinite colour channel (on a cache line apart from the queues)
+    uint32_t pad1[31];
 };
-static_assert(sizeof(WsHeader) == 256, "header is 256 bytes");
+static_assert(sizeof(WsHeader) == 256 && offsetof(WsHeader, infinite) == 128, "header is 256 bytes");
 
 // Projected record of one (view, Gaussian) item, three float4:
 //   r0 = (u_hi, v_hi, A, B)      conic (A, B, C) = inverse 2D covariance
@@ -59,7 +61,10 @@ static_assert(sizeof(WsHeader) == 256, "header is 256 bytes");
 // ellipse.  The centre is stored as u = u_hi + u_lo (double-float) so that
 // tile-relative offsets keep ~1e-6 px accuracy; r3 = (u_lo, v_lo, 0, 0) holds the low parts.
 // A centre that is no finite float (of a mean at infinity) is put at minus
-// infinity, where no slab of a tile lists it.
+// infinity, where no slab of a tile lists it.  An infinite colour channel is held
+// as kColourMax, so that a weight of 0 adds 0 of it; in a forward with such an item
+// (header: infinite) the compositing puts a pixel's channel to infinity from
+// kColourInfinite on, less than the least weight (1/255 x 1e-4) of kColourMax.
 // 64 bytes: the compositing gathers them, and a gather touches one half of a
 // cache line, never two (with records of 48 bytes, the low parts and the pair
 // offsets in three arrays, compositing 8 views of 1 M items took 1,266 us, with
@@ -67,6 +72,7 @@ static_assert(sizeof(WsHeader) == 256, "header is 256 bytes");
 struct Rec {
     float4 r0, r1, r2, r3;
 };
+constexpr float kColourMax = 3.402823466e38f, kColourInfinite = 1e32f;
 constexpr int kExportWords = 12;  // floats of a record as a caller sees it: r0, r1, r2
 
 // Offsets of the workspace regions, all 256-byte aligned.
@@ -83,7 +89,7 @@ struct WsLayout {
     size_t carry;       // float[chunks * 2 * 9] chunk-boundary partial sums of the pair moments
     size_t screen;      // float4[items * 3] per-item sums of the pair moments
     size_t box;         // in screen's memory until the backward: uint4[items] of a visible item, (first tile column |
-                        // row << 16, width | height << 16 in tiles, depth key (float bits), unused)
+                        // row << 16, width | height << 16 in tiles, depth key (float bits), 1 if a channel is infinite)
     size_t entries;     // u64[cap] (depth key << 32 | item) of the pairs, grouped by tile
     size_t pval;        // u32[cap] item ids of the sorted lists
     size_t pflag;       // u8[cap] per pair slot (emission order): 1 once the backward compositing wrote its moments

@@ -298,11 +298,14 @@ __global__ __launch_bounds__(kProjThreads, STAGE ? 3 : 4) void k_project_fwd(
             }
             const double idet = 1.0 / det;
             const bool centred = fabs(u) < 1e38 && fabs(vv) < 1e38;
+            // an infinite channel is held as the largest float, and the box word tells of it
+            const float cr = (float)fmax(col[0], 0.0), cg = (float)fmax(col[1], 0.0), cl = (float)fmax(col[2], 0.0);
+            if (fmaxf(fmaxf(cr, cg), cl) > kColourMax) box[item].w = 1u;
             const float uh = centred ? (float)u : -__builtin_inff(), vh = (float)vv;
             Rec r;
             r.r0 = make_float4(uh, vh, (float)(cc * idet), (float)(-cb * idet));
-            r.r1 = make_float4((float)(ca * idet), op, (float)fmax(col[0], 0.0), (float)fmax(col[1], 0.0));
-            r.r2 = make_float4((float)fmax(col[2], 0.0), __uint_as_float(bx), __uint_as_float(by), 0.f);
+            r.r1 = make_float4((float)(ca * idet), op, fminf(cr, kColourMax), fminf(cg, kColourMax));
+            r.r2 = make_float4(fminf(cl, kColourMax), __uint_as_float(bx), __uint_as_float(by), 0.f);
             r.r3 = make_float4(centred ? (float)(u - (double)uh) : 0.f, (float)(vv - (double)vh), 0.f, 0.f);
             rec[item] = r;
         }

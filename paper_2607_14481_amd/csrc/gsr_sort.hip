@@ -284,6 +284,7 @@ __global__ __launch_bounds__(kScanThreads) void k_vis_apply(ViewTable vt, uint64
             poff[kv[k]] = run[k];
             ioff[item] = run[k];
             item_box[kv[k]] = make_uint4(bw[k].x, bw[k].y, bw[k].z, item);
+            if (bw[k].w) hdr->infinite = 1u;  // (whoever writes it writes the same)
             // chunks whose first pair lies in [run, run + c)
             const uint32_t end = sat_add(run[k], c[k]);
             for (uint64_t ch = chunk_count(run[k]); ch < chunks_cap && ch * kChunkPairs < end; ++ch)
@@ -322,8 +323,9 @@ __global__ __launch_bounds__(256) void k_export_items(const uint32_t *__restrict
     const uint4 bw = item_box[k];
     const Rec r = rec[bw.w];
     if (records) {
-        const float w[kExportWords] = {r.r0.x, r.r0.y, r.r0.z, r.r0.w, r.r1.x, r.r1.y,
-                                       r.r1.z, r.r1.w, r.r2.x, r.r2.y, r.r2.z, __uint_as_float(poff[k])};
+        const auto colour = [](float c) { return c == kColourMax ? __builtin_inff() : c; };
+        const float w[kExportWords] = {r.r0.x, r.r0.y, r.r0.z, r.r0.w, r.r1.x, r.r1.y, colour(r.r1.z), colour(r.r1.w),
+                                       colour(r.r2.x), r.r2.y, r.r2.z, __uint_as_float(poff[k])};
         for (int c = 0; c < kExportWords; ++c) records[(size_t)bw.w * kExportWords + c] = w[c];
     }
     if (centre_lo) centre_lo[2 * (size_t)bw.w] = r.r3.x, centre_lo[2 * (size_t)bw.w + 1] = r.r3.y;

@@ -1,12 +1,13 @@
 """Values that are not finite stay where they belong, in every form of the
 compositing (waves per tile, slabs per wave): an upstream gradient of a pixel
-reaches the Gaussians that composite on that pixel, and a Gaussian at infinity
-no pixel.  The footprints come from
+reaches the Gaussians that composite on that pixel, an infinite colour the
+pixels its Gaussian composites on, and a Gaussian at infinity no pixel.  The footprints come from
 the projection formula in FP64; everything outside them is bit for bit what it is
 with a finite value in that place."""
 import numpy as np
 import pytest
 
+from paper_2607_14481_amd import gsr
 from paper_2607_14481_amd import scenes as S
 from paper_2607_14481_amd.rasterizer import GaussianRasterizer
 
@@ -99,3 +100,40 @@ def test_gaussian_at_infinity(w, h, tile_h):
         _same(out[0][k], out[1][k], ~last.cpu().numpy(), "the others")
         for g in out[0][k][1:4]:
             assert (g[last] == 0).all()
+
+
+@pytest.mark.parametrize("w,h,tile_h", FORMS)
+def test_infinite_colour(w, h, tile_h):
+    """One Gaussian with an infinite red: the pixels outside its footprint and the
+    gradients of the Gaussians that share none of its pixels are those with a
+    finite red."""
+    import torch
+    sc, cam, alpha = _scene(w, h)
+    near = np.abs(255 * alpha - 1) < 1e-4
+    on = alpha >= 1 / 255
+    shares = ((on | near)[:, None] & (on | near)[None]).any((2, 3))
+    j = int(np.argmin(shares.sum(1) + 1000.0 * (on.sum((1, 2)) < 20)))
+    assert not near[j].any() and (~shares[j]).sum() > 20
+    outside = np.ones((h, w), bool)
+    a, b = min(50, h // 2), min(50, w // 2)  # (the alphas' window is 100 x 100, the image may be smaller)
+    outside[h // 2 - a:h // 2 + a, w // 2 - b:w // 2 + b] = ~on[j][50 - a:50 + a, 50 - b:50 + b]
+    params, w2c = params_to_device(sc), poses_to_device([cam])
+    target = torch.rand(3 * h * w, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    up = torch.rand(3 * h * w, generator=torch.Generator("cuda").manual_seed(2), device="cuda") - 0.5
+    out = []
+    for red in (np.inf, 0.2):
+        p = [t.clone() for t in params]
+        p[4][j, 0, 0] = red
+        rast = GaussianRasterizer([cam], 0, tile_h=tile_h)
+        rgb, ws = rast.forward(p, w2c)
+        grads, _, _ = rast.backward(ws, p, w2c, (0.0, 0.0, 0.0), rgb, up)
+        records = gsr.export_state(ws, p, 0, [cam], cfg=rast.cfg)["records"]
+        assert np.isinf(records[j, 6]) == (red == np.inf) and np.isfinite(records[:, 7:9]).all()
+        step = rast.step_l1(p, w2c, (0.0, 0.0, 0.0), target)
+        out.append(([rgb, step[0]], grads, step[2]))
+    for x, y in zip(out[0][0], out[1][0]):
+        x, y = (t.cpu().numpy().reshape(3, h, w) for t in (x, y))
+        np.testing.assert_array_equal(x[:, outside], y[:, outside])
+        assert np.isinf(x[0, ~outside]).all() and np.isfinite(x[1:]).all()
+    for k in (1, 2):
+        _same(out[0][k], out[1][k], ~shares[j], "the others")
