@@ -419,14 +419,17 @@ __global__ __launch_bounds__(256) void k_fill_i32(int32_t *__restrict__ p, int32
     if (i < n) p[i] = value;
 }
 
-void launch_hierarchy_level(const gsr_param_set &nodes, int sh_degree, uint64_t child_base, uint64_t n_child,
-                            uint64_t parent_base, uint32_t branching, bool leaves, bool roots, int32_t *parent,
-                            int32_t *child_count, hipStream_t st) {
+// Parents of a launch: at most 2^32 threads are launched at a time, of up to 27 a
+// parent for the SH rows and 4 or so for the geometry.
+constexpr uint64_t kMergeMaxLaunch = 1ull << 26;
+
+static void launch_level_part(const gsr_param_set &nodes, int sh_degree, uint64_t child_base, uint64_t n_child,
+                              uint64_t parent_base, uint32_t branching, bool leaves, bool roots, int32_t *parent,
+                              int32_t *child_count, hipStream_t st) {
     MergeLevel L{};
     L.nodes = nodes;
     L.child_base = child_base, L.n_child = n_child, L.parent_base = parent_base;
     L.n_parent = (n_child + branching - 1) / branching;
-    if (L.n_parent == 0) return;
     L.branching = branching;
     L.per = std::min(kMergeThreads / branching, kMergeMaxParents);
     // two chunks to a workgroup, so that the parents' part runs on a full wave,
@@ -447,6 +450,15 @@ void launch_hierarchy_level(const gsr_param_set &nodes, int sh_degree, uint64_t 
         case 2: run(k_merge_level<27, false>, 27); break;
         default: run(k_merge_level<48, true>, 12); break;
     }
+}
+
+void launch_hierarchy_level(const gsr_param_set &nodes, int sh_degree, uint64_t child_base, uint64_t n_child,
+                            uint64_t parent_base, uint32_t branching, bool leaves, bool roots, int32_t *parent,
+                            int32_t *child_count, hipStream_t st) {
+    const uint64_t step = kMergeMaxLaunch * branching;  // whole parents
+    for (uint64_t c = 0; c < n_child; c += step)
+        launch_level_part(nodes, sh_degree, child_base + c, std::min(step, n_child - c), parent_base + c / branching,
+                          branching, leaves, roots, parent, child_count, st);
 }
 
 void launch_fill_i32(int32_t *p, int32_t value, uint64_t n, hipStream_t st) {
