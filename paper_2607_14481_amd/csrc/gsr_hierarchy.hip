@@ -171,8 +171,9 @@ void launch_store_count_i64(const uint32_t *count, int64_t *out, hipStream_t st)
 // The covariance is stored factored: eigenvalues ascending -> log-scales,
 // eigenvectors (determinant +1) -> quaternion with w >= 0.
 //
-// One launch per level; its workgroups are of two kinds, dealt in turn so that
-// the arithmetic of one runs under the memory traffic of the other.
+// One launch per level (large levels of few children a parent: two); its
+// workgroups are of two kinds, dealt in turn so that the arithmetic of one runs
+// under the memory traffic of the other.
 //
 // Geometry, FP64: a thread per child forms its weighted moments (about the
 // first child's mean, so the spread term does not cancel against the
@@ -189,11 +190,11 @@ void launch_store_count_i64(const uint32_t *count, int64_t *out, hipStream_t st)
 //
 // Two million leaves, seven levels of branching 8: 318 us with a thread per
 // parent, whose serial loads of eight children (113 us alone) the SH rows of a
-// launch of their own (87 us) did not cover; 180 us now.  The upper levels take
+// launch of their own (87 us) did not cover; 170 us now.  The upper levels take
 // 7 to 12 us each, the latency of one eigenproblem.  Two chunks of children to
 // a geometry workgroup (64 parents) rather than one or four (more LDS: fewer
-// waves for the SH rows): 180, 218 and 222 us; geometry workgroups dealt in
-// turn rather than first: 180 and 193 us.
+// waves for the SH rows): 180, 218 and 222 us, measured before the period was
+// made odd; geometry workgroups dealt in turn rather than first: 180 and 193 us.
 // ---------------------------------------------------------------------------
 constexpr double kMergeMinVar = 1e-12;
 
@@ -297,6 +298,28 @@ struct MergeLevel {
     int32_t *parent, *child_count;
 };
 
+// Parent j of the level from its eleven sums.
+__device__ __forceinline__ void merge_parent(const MergeLevel &L, uint64_t j, const double *S) {
+    const gsr_param_set &nodes = L.nodes;
+    const uint64_t b = L.branching, p = L.parent_base + j, c0 = L.child_base + j * b;
+    L.child_count[p] = (int32_t)min((uint64_t)b, L.n_child - j * b);
+    if (L.roots) L.parent[p] = -1;
+    const double inv = 1.0 / S[0];
+    const double m[3] = {S[1] * inv, S[2] * inv, S[3] * inv};  // mean about the first child
+    double A[9];
+    A[0] = S[4] * inv - m[0] * m[0], A[1] = A[3] = S[5] * inv - m[0] * m[1], A[2] = A[6] = S[6] * inv - m[0] * m[2];
+    A[4] = S[7] * inv - m[1] * m[1], A[5] = A[7] = S[8] * inv - m[1] * m[2], A[8] = S[9] * inv - m[2] * m[2];
+    double lam[3], V[9], q[4];
+    sym3_eig(A, lam, V);
+    rot_to_quat_d(V, q);
+    for (int a = 0; a < 3; ++a) {
+        nodes.means[3 * p + a] = (float)((double)nodes.means[3 * c0 + a] + m[a]);
+        nodes.log_scales[3 * p + a] = (float)(0.5 * log(fmax(lam[a], kMergeMinVar)));
+    }
+    reinterpret_cast<float4 *>(nodes.quats)[p] = make_float4((float)q[0], (float)q[1], (float)q[2], (float)q[3]);
+    nodes.opacities[p] = (float)(1.0 - S[10]);
+}
+
 // Geometry workgroup wg: parents [wg * chunks * per, + chunks * per).
 __device__ __forceinline__ void merge_geometry(const MergeLevel &L, uint64_t wg, double (*child)[kMergeTerms],
                                                double (*sums)[kMergeTerms]) {
@@ -348,30 +371,47 @@ __device__ __forceinline__ void merge_geometry(const MergeLevel &L, uint64_t wg,
         }
         __syncthreads();
     }
-    if (tid >= np) return;
-    const double *S = sums[tid];
-    const uint64_t j = j0 + tid, p = L.parent_base + j, c0 = L.child_base + j * b;
-    L.child_count[p] = (int32_t)min((uint64_t)b, L.n_child - j * b);
-    if (L.roots) L.parent[p] = -1;
-    const double inv = 1.0 / S[0];
-    const double m[3] = {S[1] * inv, S[2] * inv, S[3] * inv};  // mean about the first child
-    double A[9];
-    A[0] = S[4] * inv - m[0] * m[0], A[1] = A[3] = S[5] * inv - m[0] * m[1], A[2] = A[6] = S[6] * inv - m[0] * m[2];
-    A[4] = S[7] * inv - m[1] * m[1], A[5] = A[7] = S[8] * inv - m[1] * m[2], A[8] = S[9] * inv - m[2] * m[2];
-    double lam[3], V[9], q[4];
-    sym3_eig(A, lam, V);
-    rot_to_quat_d(V, q);
-    for (int a = 0; a < 3; ++a) {
-        nodes.means[3 * p + a] = (float)((double)nodes.means[3 * c0 + a] + m[a]);
-        nodes.log_scales[3 * p + a] = (float)(0.5 * log(fmax(lam[a], kMergeMinVar)));
+    if (tid < np) merge_parent(L, j0 + tid, sums[tid]);
+}
+
+// Parent j by a thread of its own, its children one after the other.
+__global__ __launch_bounds__(kMergeThreads) void k_merge_serial(MergeLevel L) {
+    const uint64_t j = (uint64_t)blockIdx.x * kMergeThreads + threadIdx.x;
+    if (j >= L.n_parent) return;
+    const gsr_param_set &nodes = L.nodes;
+    const uint64_t first = j * L.branching, c0 = L.child_base + first;
+    const uint32_t k = (uint32_t)min((uint64_t)L.branching, L.n_child - first);
+    const double ox = nodes.means[3 * c0], oy = nodes.means[3 * c0 + 1], oz = nodes.means[3 * c0 + 2];
+    double S[kMergeTerms] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 1.0};
+    for (uint32_t i = 0; i < k; ++i) {
+        const uint64_t c = c0 + i;
+        L.parent[c] = (int32_t)(L.parent_base + j);
+        if (L.leaves) L.child_count[c] = 0;
+        const double o = nodes.opacities[c];
+        const float4 qf = reinterpret_cast<const float4 *>(nodes.quats)[c];
+        double R[9];
+        quat_to_rot_d(qf.x, qf.y, qf.z, qf.w, R);
+        const double e0 = exp(2.0 * (double)nodes.log_scales[3 * c]), e1 = exp(2.0 * (double)nodes.log_scales[3 * c + 1]),
+                     e2 = exp(2.0 * (double)nodes.log_scales[3 * c + 2]);
+        const double d[3] = {(double)nodes.means[3 * c] - ox, (double)nodes.means[3 * c + 1] - oy,
+                             (double)nodes.means[3 * c + 2] - oz};
+        S[0] += o;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) S[1 + a] += o * d[a];
+#pragma unroll
+        for (int a = 0, e = 4; a < 3; ++a)
+#pragma unroll
+            for (int q = a; q < 3; ++q, ++e)
+                S[e] += o * (R[3 * a] * R[3 * q] * e0 + R[3 * a + 1] * R[3 * q + 1] * e1 +
+                             R[3 * a + 2] * R[3 * q + 2] * e2 + d[a] * d[q]);
+        S[10] *= 1.0 - o;
     }
-    reinterpret_cast<float4 *>(nodes.quats)[p] = make_float4((float)q[0], (float)q[1], (float)q[2], (float)q[3]);
-    nodes.opacities[p] = (float)(1.0 - S[10]);
+    merge_parent(L, j, S);
 }
 
 // Unit t of the parents' SH rows (K3 / 4 float4 units a row, or K3 floats when
 // a row is not a whole number of float4).
-template <int K3, bool VEC>
+template <int K3, bool VEC, int UNROLL>
 __device__ __forceinline__ void merge_sh(const MergeLevel &L, uint64_t t) {
     constexpr uint32_t kUnits = VEC ? K3 / 4 : K3;
     const gsr_param_set &nodes = L.nodes;
@@ -380,12 +420,12 @@ __device__ __forceinline__ void merge_sh(const MergeLevel &L, uint64_t t) {
     const uint64_t first = j * L.branching, c0 = L.child_base + first, p = L.parent_base + j;
     const uint32_t k = (uint32_t)min((uint64_t)L.branching, L.n_child - first);
     float wsum = 0.f;
-#pragma unroll 8
+#pragma unroll UNROLL
     for (uint32_t i = 0; i < k; ++i) wsum += nodes.opacities[c0 + i];
     const float inv = 1.f / wsum;
     if constexpr (VEC) {
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8
+#pragma unroll UNROLL
         for (uint32_t i = 0; i < k; ++i) {
             const float w = nodes.opacities[c0 + i] * inv;
             const float4 v = reinterpret_cast<const float4 *>(nodes.sh)[(c0 + i) * kUnits + u];
@@ -395,7 +435,7 @@ __device__ __forceinline__ void merge_sh(const MergeLevel &L, uint64_t t) {
         reinterpret_cast<float4 *>(nodes.sh)[p * kUnits + u] = acc;
     } else {
         float acc = 0.f;
-#pragma unroll 8
+#pragma unroll UNROLL
         for (uint32_t i = 0; i < k; ++i) acc = fmaf(nodes.opacities[c0 + i] * inv, nodes.sh[(c0 + i) * kUnits + u], acc);
         nodes.sh[p * kUnits + u] = acc;
     }
@@ -411,7 +451,12 @@ __global__ __launch_bounds__(kMergeThreads, 4) void k_merge_level(MergeLevel L) 
     }
     // the SH workgroups are those between, numbered through
     const uint64_t wg = blockIdx.x - min(L.geometry, turn + 1);
-    merge_sh<K3, VEC>(L, wg * kMergeThreads + threadIdx.x);
+    merge_sh<K3, VEC, 8>(L, wg * kMergeThreads + threadIdx.x);
+}
+
+template <int K3, bool VEC>
+__global__ __launch_bounds__(kMergeThreads) void k_merge_sh(MergeLevel L) {
+    merge_sh<K3, VEC, 4>(L, (uint64_t)blockIdx.x * kMergeThreads + threadIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_fill_i32(int32_t *__restrict__ p, int32_t value, uint64_t n) {
@@ -439,16 +484,40 @@ static void launch_level_part(const gsr_param_set &nodes, int sh_degree, uint64_
     L.geometry = (uint32_t)((L.n_parent + L.per * L.chunks - 1) / (L.per * L.chunks));
     L.leaves = leaves, L.roots = roots;
     L.parent = parent, L.child_count = child_count;
-    auto run = [&](auto kernel, uint64_t units) {
+    // Large levels of few children a parent: the SH rows in a launch of their own, where
+    // no LDS keeps waves away, and up to five children the geometry by a thread per
+    // parent (64 threads of a workgroup would have a parent, and few a child).  One
+    // launch / apart, us: 1 M parents of three 160 / 121, 181 / 147, 419 / 268 and 319 / 239
+    // (degrees 0 to 3); 1.6 M of five 513 / 484 (degree 0, with the levels above); 500 k of
+    // six 358 / 232 and 270 / 251 (2 and 3); 375 k of eight 167 / 215 (3); 66 k of three 17.2 /
+    // 19.9, 34.5 / 28.1 and 27.1 / 26.8 (0, 2 and 3); 33 k of six 28.9 / 25.6 and 17.0 / 23.9 (2 and 3).
+    const bool rows = sh_degree >= 2, serial = branching <= 5;
+    const bool apart = branching <= (rows ? 7u : L.n_parent >= 1ull << 20 ? 5u : 4u) &&
+                       L.n_parent >= (sh_degree == 2 || (rows && serial) ? 1ull << 15 : 1ull << 18);
+    auto run = [&](auto level, auto sh_rows, uint64_t units) {
         const uint32_t sh = (uint32_t)((L.n_parent * units + kMergeThreads - 1) / kMergeThreads);
-        L.period = (L.geometry + sh) / L.geometry;
-        hipLaunchKernelGGL(kernel, dim3(L.geometry + sh), dim3(kMergeThreads), 0, st, L);
+        if (!apart) {
+            // an odd period: workgroups go to the XCDs and their shader engines in turn, and an
+            // even one gives the geometry to some of them only (8 M leaves of degree 3,
+            // branching 8: 1,036 us with a period of 4, 556 us with 3)
+            L.period = (L.geometry + sh) / L.geometry;
+            if (L.period % 2 == 0) --L.period;
+            hipLaunchKernelGGL(level, dim3(L.geometry + sh), dim3(kMergeThreads), 0, st, L);
+            return;
+        }
+        L.period = 1;
+        if (serial)
+            hipLaunchKernelGGL(k_merge_serial, dim3((unsigned)((L.n_parent + kMergeThreads - 1) / kMergeThreads)),
+                               dim3(kMergeThreads), 0, st, L);
+        else
+            hipLaunchKernelGGL(level, dim3(L.geometry), dim3(kMergeThreads), 0, st, L);
+        hipLaunchKernelGGL(sh_rows, dim3(sh), dim3(kMergeThreads), 0, st, L);
     };
     switch (sh_degree) {
-        case 0: run(k_merge_level<3, false>, 3); break;
-        case 1: run(k_merge_level<12, true>, 3); break;
-        case 2: run(k_merge_level<27, false>, 27); break;
-        default: run(k_merge_level<48, true>, 12); break;
+        case 0: run(k_merge_level<3, false>, k_merge_sh<3, false>, 3); break;
+        case 1: run(k_merge_level<12, true>, k_merge_sh<12, true>, 3); break;
+        case 2: run(k_merge_level<27, false>, k_merge_sh<27, false>, 27); break;
+        default: run(k_merge_level<48, true>, k_merge_sh<48, true>, 12); break;
     }
 }
 

@@ -61,3 +61,12 @@ def test_every_level(n_leaves, levels, branching, deg):
             ref = M.merge_group(*[g[c].astype(np.float64) for g in got])
             _compare_node([g[int(ls[l]) + j].astype(np.float64) for g in got], ref, f"level {l} node {j}")
     log(f"build {n_leaves} leaves, {levels} levels, branching {branching}, degree {deg}: {total} nodes")
+
+
+@pytest.mark.parametrize("n_leaves,branching,deg", [
+    (65_535, 2, 3), (65_533, 2, 3), (98_303, 3, 2), (98_301, 3, 2), (163_836, 5, 3), (524_287, 2, 0), (1_048_573, 4, 1),
+    (1_835_003, 7, 2), (1_572_862, 6, 3)])
+def test_levels_in_launches_apart(n_leaves, branching, deg):
+    """Levels at and above the sizes from which the SH rows have a launch of their own
+    (32,768 and 262,144 parents), and below."""
+    test_every_level(n_leaves, 1, branching, deg)
