@@ -602,13 +602,18 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_place(ViewTable vt, uint32_
     // the band's tile starts: the totals of the view's tiles before it summed,
     // its own staged in LDS, each thread's run of consecutive tiles scanned
     const auto add = [](uint32_t a, uint32_t b) { return a + b; };
+    // (eight loads in flight: with many tiles and few items these loops count)
     uint32_t early = 0;
+#pragma unroll 8
     for (uint32_t t = tid; t < before; t += kBinThreads) early += totals[off + t];
+#pragma unroll 8
     for (uint32_t t = tid; t < T; t += kBinThreads) s_tile[t] = totals[band0 + t];
     early = wave_reduce(early, 0u, add);
     if (lane == 0) s_wave[0][w] = early;
     __syncthreads();
-    const uint32_t per = (T + kBinThreads - 1) / kBinThreads, t0 = min(tid * per, T), t1 = min(t0 + per, T);
+    // (runs of an odd length: the lanes' starts then lie in different banks; 100 k items
+    // in 129,600 tiles: 158 us with even runs and a load at a time above, 79 us)
+    const uint32_t per = (T + kBinThreads - 1) / kBinThreads | 1u, t0 = min(tid * per, T), t1 = min(t0 + per, T);
     uint32_t sum = 0;
     for (uint32_t t = t0; t < t1; ++t) sum += s_tile[t];
     const uint32_t inc = wave_inclusive_scan(sum, add);
@@ -627,6 +632,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_place(ViewTable vt, uint32_
     }
     __syncthreads();
     const uint32_t *row = counts + (size_t)bt.g * vt.total_tiles + band0;
+#pragma unroll 8
     for (uint32_t t = tid; t < T; t += kBinThreads) s_tile[t] += row[t];
     __syncthreads();
     bin_place_items(s_tile, nx, bt.r0, bt.r1, s0, s1, bt.g, G, item_box, entries);
@@ -673,7 +679,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_small(ViewTable vt, uint32_
     }
     __syncthreads();
     // counts to starts, each thread a run of consecutive tiles
-    const uint32_t per = (T + kBinThreads - 1) / kBinThreads, t0 = min(tid * per, T), t1 = min(t0 + per, T);
+    const uint32_t per = (T + kBinThreads - 1) / kBinThreads | 1u, t0 = min(tid * per, T), t1 = min(t0 + per, T);
     uint32_t sum = 0;
     for (uint32_t t = t0, at = t0 / nx * P + t0 % nx, x = t0 % nx; t < t1; ++t) {
         sum += s_tile[at++];

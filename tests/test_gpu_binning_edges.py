@@ -84,3 +84,9 @@ def test_many_tiles(n):
 def test_one_launch_lines(n, width, height, tile_h, capacity):
     _check(n, [_camera(width, height)], tile_h, capacity, f"{n} items, {width}x{height}/{tile_h}, capacity {capacity}",
            every=400)
+
+
+@pytest.mark.parametrize("tiles_x,tiles_y", [(32, 32), (25, 41), (64, 32), (61, 34), (64, 33), (96, 32), (81, 38)])
+def test_thread_runs(tiles_x, tiles_y):
+    """Bands of 1,024, 2,048 and 3,072 tiles and one or a few more: a thread's run is of one or three."""
+    _check(9000, [_camera(16 * tiles_x, 16 * tiles_y - 5)], 16, 900_000, f"{tiles_x * tiles_y} tiles", every=900)
