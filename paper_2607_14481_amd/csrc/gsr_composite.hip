@@ -784,11 +784,20 @@ __global__ __launch_bounds__(W *kWave) void k_composite(ViewTable vt, CompositeA
     }
 }
 
-// Waves per tile.  The forward always takes as many as it can: at every size
-// it measured faster (16 x 16 tiles, W = 1 / 2 / 4: 136 / 95 / 74 us at 1,200
-// tiles, 151 / 151 / 142 us at 8,160; 16 x 8 tiles, W = 1 / 2: 197 / 184 us at
-// 16,200).
-static int forward_waves(const ViewTable &vt) { return vt.tile_h / 4 < 4 ? vt.tile_h / 4 : 4; }
+// Waves per tile.  The forward takes as many as it can (16 x 16 tiles, W = 1 / 2 /
+// 4: 136 / 95 / 74 us at 1,200 tiles, 151 / 151 / 142 us at 8,160; 16 x 8 tiles, W = 1 /
+// 2: 197 / 184 us at 16,200) but where the tiles alone fill the chip many times over:
+// there, what each wave repeats counts for more.  Whole forwards, us, of 300 k
+// Gaussians evenly spread, 1.5 M, and 300 k in the middle, whose longest lists take
+// most of the time: 16 x 16, W = 1 / 4: 302 / 288, 504 / 508 and 779 / 632 at 14,400
+// tiles, 471 / 508, 852 / 917 and 5,324 / 5,135 at 32,400, 1,377 / 1,631, 2,985 / 3,345
+// and 16,877 / 16,865 at 129,600; 16 x 32, W = 2 / 4: 434 / 439, 707 / 728 and 773 / 696
+// at 16,200, 1,225 / 1,343, 2,137 / 2,316 and 9,303 / 9,324 at 64,800; 16 x 8, W = 1 / 2: no
+// difference.  The line is where no scene loses.
+static int forward_waves(const ViewTable &vt) {
+    if (vt.tile_h >= 16 && vt.total_tiles > 40000u) return vt.tile_h == 16 ? 1 : 2;
+    return vt.tile_h / 4 < 4 ? vt.tile_h / 4 : 4;
+}
 
 // The backward and the fused step (one rule: both must add up a pair's moments
 // in the same order) give a wave fewer slabs the fewer tiles there are.
@@ -833,16 +842,22 @@ static void launch_composite(const ViewTable &vt, const CompositeArgs &A, int pe
                                          : vt.total_tiles),                                                         \
                        dim3(W * kWave), 0, st, vt, A)
     const int waves = BWD ? backward_waves(vt) : forward_waves(vt);
-    if constexpr (BWD) {  // (the forward alone is never split less than it can be)
+    if (waves == 1 && vt.tile_h == 16) {
+        GSR_COMPOSITE(4, 1);
+        return;
+    }
+    if (waves == 2 && vt.tile_h == 32) {
+        GSR_COMPOSITE(4, 2);
+        return;
+    }
+    if constexpr (BWD) {  // (forms the forward alone does not take)
         if (waves == 1 && vt.tile_h > 4) {
             if (vt.tile_h == 8) GSR_COMPOSITE(2, 1);
-            else if (vt.tile_h == 16) GSR_COMPOSITE(4, 1);
             else GSR_COMPOSITE(8, 1);
             return;
         }
-        if (waves == 2 && vt.tile_h > 8) {
-            if (vt.tile_h == 16) GSR_COMPOSITE(2, 2);
-            else GSR_COMPOSITE(4, 2);
+        if (waves == 2 && vt.tile_h == 16) {
+            GSR_COMPOSITE(2, 2);
             return;
         }
     }

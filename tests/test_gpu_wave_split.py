@@ -57,3 +57,29 @@ def test_list_lengths(n, height):
                     rng.uniform(0.008, 0.025, n).astype(np.float32), sc.sh, 0)
     log(f"list of {n} records, image {width}x{height}")
     _check(scene, cam, 16, f"list {n} h{height}")
+
+
+@pytest.mark.parametrize("tile_h", [16, 32])
+@pytest.mark.parametrize("tiles_x,tiles_y", [(200, 200), (201, 200)])
+def test_forward_tile_count_line(tile_h, tiles_x, tiles_y):
+    """40,000 tiles and more: the forward takes fewer waves a tile, the same image to the bit (the one-call
+    step, whose waves the rule leaves alone, against it, and the work it counts)."""
+    import torch
+    from paper_2607_14481_amd import gsr
+    from paper_2607_14481_amd.rasterizer import GaussianRasterizer
+    w, h = 16 * tiles_x - 5, tile_h * tiles_y - 3
+    wl = S.small_view(seed=23, n=3000, width=w, height=h, sh_degree=0, log_scale_mean=-2.0)
+    cam = wl.cameras[0]
+    params, w2c = params_to_device(wl.scene), poses_to_device([cam])
+    target = torch.full((3 * w * h,), 0.35, device="cuda")
+    rast = GaussianRasterizer([cam], 0, tile_h=tile_h)
+    rgb, ws = rast.forward(params, w2c)
+    grads, _, twist = rast.backward_l1(ws, params, w2c, (0.0, 0.0, 0.0), rgb, target)
+    step = rast.step_l1(params, w2c, (0.0, 0.0, 0.0), target)
+    for a, b in zip([rgb, *grads, twist], [step[0], *step[2], step[4]]):
+        assert torch.equal(a, b)
+    other = GaussianRasterizer([cam], 0, tile_h=8)
+    rast.stats = other.stats = True
+    counts = [gsr.query_stats(r.forward(params, w2c)[1])["contributors"] for r in (rast, other)]
+    log(f"{tiles_x * tiles_y} tiles of 16x{tile_h}: {counts} contributors")
+    assert counts[0] > 0 and abs(counts[0] - counts[1]) <= 1e-5 * counts[1]
