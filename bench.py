@@ -806,17 +806,18 @@ def run_local_ba(iters=10, repeats=30, cpu_baseline=True):
         log(f"[bench] BA graph capture failed: {e}")
         same = None
     n_obs = int((P.obs_cam >= 0).sum())
-    # algorithmic bytes of one iteration: the landmark kernel reads pixel and camera
-    # index of every observation (20 B) and every landmark, which it writes back
-    # with a 128-B record (24 + 24 + 128 B); the assembly reads the observation, its
-    # landmark and the record again per observation of a free keyframe (diagonal
-    # blocks, 172 B) and per pair of them in one landmark (off-diagonal blocks, one
-    # record, one landmark and two observations: 192 B).
+    # bytes the kernels of one iteration ask for: the landmark kernel reads pixel and
+    # camera index of every observation (20 B), and of every landmark its position
+    # and 12 doubles of its record, and writes the position back and the record of
+    # 15 doubles (24 + 96 + 24 + 120 B); the assembly reads a list word, a pixel and the
+    # record per observation of a free keyframe (diagonal blocks, 4 + 16 + 120 B), and
+    # a list word and 9 doubles of the record per pair of them in one landmark
+    # (off-diagonal blocks, 4 + 72 B).
     free_obs = (P.obs_cam >= 0) & (P.free_slot[np.maximum(P.obs_cam, 0)] >= 0)
     per_lm = free_obs.sum(axis=1)
     n_free_obs, n_pairs = int(per_lm.sum()), int((per_lm * (per_lm - 1) // 2).sum())
     K = P.n_landmarks
-    it_bytes = n_obs * 20 + K * (24 + 24 + 128) + n_free_obs * 172 + n_pairs * 192
+    it_bytes = n_obs * 20 + K * (24 + 96 + 24 + 120) + n_free_obs * (4 + 16 + 120) + n_pairs * (4 + 72)
     it_ms = eager_med / iters
     out = {"workload": f"local BA: 20 keyframes (4 fixed), 10,000 landmarks, {n_obs} observations (2-8 consecutive "
                        f"keyframes per landmark), focal length optimised, {iters} LM iterations, FP64",
