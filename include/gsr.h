@@ -126,8 +126,8 @@ typedef struct gsr_gaussian_grads {
 /* Stages of the two passes, for the optional per-stage timing events. */
 #define GSR_STAGE_PROJECT 0        /* forward: per-Gaussian projection */
 #define GSR_STAGE_COMPACT 1        /* forward: visible-item compaction and pair offsets */
-#define GSR_STAGE_EMIT 2           /* forward: pairs generated and grouped by tile */
-#define GSR_STAGE_TILE_SORT 3      /* forward: tile sort, tile ranges, per-tile depth sort */
+#define GSR_STAGE_EMIT 2           /* forward: pairs generated and grouped by tile, tile ranges */
+#define GSR_STAGE_TILE_SORT 3      /* forward: per-tile depth sort, merges of the long lists */
 #define GSR_STAGE_COMPOSITE_FWD 4  /* forward: compositing */
 #define GSR_STAGE_COMPOSITE_BWD 5  /* backward: compositing */
 #define GSR_STAGE_PROJECT_BWD 6    /* backward: per-Gaussian reduction, chain rule, pose */
@@ -278,8 +278,8 @@ int gsr_query_stats(const void *ws, size_t ws_bytes, gsr_stats *out, void *strea
  *     id = tile offset of the view + ty * tiles_x + tx; item = v n + i);
  *   ranges [2 * total tiles]: [start, end) of each tile in the sorted pairs;
  *   records [n_views n][12]: per item (u_hi, v_hi, A, B, C, opacity, r, g, b,
- *     bits(x0 | x1 << 16), bits(y0 | y1 << 16), bits(pair offset)), meaningful
- *     only where tile_counts > 0; centre_lo [n_views n][2]: (u_lo, v_lo);
+ *     bits(x0 | x1 << 16), bits(y0 | y1 << 16), bits(pair offset)), written
+ *     only where tile_counts > 0; centre_lo [n_views n][2]: (u_lo, v_lo), likewise;
  *   depth_keys [n_views n]: float32 bits of camera-space depth (culled:
  *     0xffffffff); tile_counts [n_views n]: tiles touched (0 = culled).
  */

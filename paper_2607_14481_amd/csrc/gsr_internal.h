@@ -53,7 +53,7 @@ struct WsHeader {
 };
 static_assert(sizeof(WsHeader) == 256 && offsetof(WsHeader, infinite) == 128, "header is 256 bytes");
 
-// Projected record of one (view, Gaussian) item, three float4:
+// Projected record of one (view, Gaussian) item, four float4:
 //   r0 = (u_hi, v_hi, A, B)      conic (A, B, C) = inverse 2D covariance
 //   r1 = (C, opacity, red, green)
 //   r2 = (blue, bits(x0 | x1 << 16), bits(y0 | y1 << 16), unused)

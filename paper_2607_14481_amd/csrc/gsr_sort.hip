@@ -148,8 +148,8 @@ void launch_compact_flags(const uint8_t *flags, uint64_t n, uint32_t *out_idx, u
 // view's first visible index too.  The last block writes the visible and pair
 // counts and the overflow decision (pairs > capacity).
 //
-// It moves 40 bytes per visible item, with every access contiguous except for
-// the gaps of the invisible ones: the projection leaves the box words in an
+// It moves 44 bytes per visible item and 4 per item (8 with phase 1), with every
+// access contiguous except for the gaps of the invisible ones: the projection leaves the box words in an
 // array of their own and the pair offset by item goes to another.  (Read from
 // and written into the records themselves, 48 bytes apart, both touched every
 // line of theirs for one word: 132 us for 8 views of 1 M items, 63 us now.)
@@ -762,8 +762,8 @@ void launch_bin_pairs(const ViewTable &vt, const BinPlan &plan, uint32_t G, cons
 }
 
 // ---------------------------------------------------------------------------
-// A4c: per-tile depth order.  After the tile sort each tile's list holds its
-// items in no particular order; it is sorted here by the 64-bit key
+// A4c: per-tile depth order.  The binning leaves each tile's items in no
+// particular order; they are sorted here by the 64-bit key
 // (depth key << 32 | item), the unique order of the compositing definition.
 // The binning leaves those keys as the lists' entries, so a list is one
 // contiguous read; its sorted item ids go to pval.
@@ -1032,7 +1032,7 @@ __device__ void sort_list_global(u64 *__restrict__ list, uint32_t len, uint32_t 
 // once they fit the list).  k_long_windows numbers their windows (of
 // kLongWindow entries for the run sort, of kMergeWindow outputs for the merge
 // passes) in list order once per forward; a workgroup then finds its window
-// by a binary search over those offsets.
+// among those offsets.
 __device__ __forceinline__ bool long_path_on(const WsHeader *hdr, int passes) {
     return passes > 0 && passes <= kMaxLongPasses && hdr->n_long <= kMaxLongTiles;
 }

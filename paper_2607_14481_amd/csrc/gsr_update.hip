@@ -6,7 +6,8 @@
 //   * the loop-closure Sim(3) relocation of Gaussians (or hierarchy nodes).
 // The first and last are elementwise and HBM-bound: every array is walked as
 // one flat sequence of float4 (or float) units, so loads and stores are
-// coalesced whatever the row length of an array.
+// coalesced whatever the row length of an array (but for the sparse Adam step of
+// mid-sized calls, which walks the rows of listed Gaussians).
 #include <algorithm>
 
 #include "gsr_internal.h"
@@ -56,7 +57,7 @@ __device__ __forceinline__ void adam_units(float *p, const float *g, float *m, f
 // quaternions (n float4), opacities (n floats, on the logit), SH (n 3K/4
 // float4 when 3K is a multiple of 4, else n 3K floats).
 //
-// HBM-bound: 24 bytes a parameter, each array one ascending sweep.  The row
+// HBM-bound: 28 bytes a parameter (four read, three written), each array one ascending sweep.  The row
 // length is a constant and the unit index 32 bits wide wherever it fits: finding
 // a unit's Gaussian and its place in the row by 64-bit division by a variable
 // bound the smaller calls: 30 k Gaussians of degree 3 7.8 -> 7.2 us, 300 k of
@@ -179,7 +180,8 @@ static void launch_adam(const AdamArgs &A, hipStream_t st) {
     // ascending sweeps use the memory better than runs of rows dealt over all of
     // them.  Listed and flat: 400 k (378 MB, 191 k seen) 73 / 78 us, 560 k (529 MB)
     // 80.5 / 99 us, 700 k (661 MB) 125.3 / 124.3 us, 1 M (944 MB, 478 k seen) 251 /
-    // 235 us; 20 k Gaussians 6.1 / 5.1 us.
+    // 235 us; 20 k Gaussians 6.1 / 5.1 us.  With every Gaussian seen, which the host
+    // cannot know, 400 k take 124 / 121 us (degree 2: 64 / 74), with few 12 / 23 us.
     const uint64_t span = A.n * (11 + 3 * K) * 16;
     if (A.count && A.n >= kAdamListMin && span <= kAdamListSpan) {
         hipLaunchKernelGGL(k_adam_listed<K>, dim3((unsigned)((A.n + kAdamGroup - 1) / kAdamGroup)), dim3(256), 0, st, A);
