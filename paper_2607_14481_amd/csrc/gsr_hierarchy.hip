@@ -45,11 +45,15 @@ __global__ __launch_bounds__(256) void k_cut_descend(const float *__restrict__ m
 // share their ancestors: a chain, a run of dependent gathers whose address
 // processing is what bounds the kernel, is walked once for them.  A hop fetches
 // the ancestor's flag and its parent together.  4.6 M nodes, 1.4 M of them in
-// the cut: 35 us with a thread and a chain per node, 20 us.
-constexpr int kSelectNodes = 4;
-__global__ __launch_bounds__(256) void k_cut_select(const int32_t *__restrict__ parent, uint64_t n,
+// the cut: 35 us with a thread and a chain per node, 20 us.  Nodes in random order
+// have four chains to a thread; workgroups of one wave keep the end of such a launch
+// short (whole cuts of 2.3 M and 4.6 M: 119 and 287 us with a node per thread, 137 and
+// 302 with four and workgroups of four waves, 132 and 295; in order 39 and 73, 26 and
+// 47, 26 and 46; with two nodes random ones take 120 and 284, but ordered ones 28 and 52).
+constexpr int kSelectNodes = 4, kSelectThreads = 64;
+__global__ __launch_bounds__(kSelectThreads) void k_cut_select(const int32_t *__restrict__ parent, uint64_t n,
                                                     const uint8_t *__restrict__ descend, uint8_t *__restrict__ in_cut) {
-    const uint64_t i0 = ((uint64_t)blockIdx.x * 256 + threadIdx.x) * kSelectNodes;
+    const uint64_t i0 = ((uint64_t)blockIdx.x * kSelectThreads + threadIdx.x) * kSelectNodes;
     if (i0 >= n) return;
     const int m = (int)min((uint64_t)kSelectNodes, n - i0);
     uint32_t flags = 0;  // a byte per node (the arrays are scratch: whole words are in bounds and aligned)
@@ -95,8 +99,9 @@ void launch_hierarchy_cut_flags(const float *means, const float *log_scales, con
     const dim3 grid((unsigned)((n + 255) / 256));
     hipLaunchKernelGGL(k_cut_descend, grid, dim3(256), 0, st, means, log_scales, child_count, n, w2c, (double)focal,
                        (double)tau, descend);
-    hipLaunchKernelGGL(k_cut_select, dim3((unsigned)((n + 256 * kSelectNodes - 1) / (256 * kSelectNodes))), dim3(256), 0,
-                       st, parent, n, descend, in_cut);
+    constexpr uint64_t per = kSelectThreads * kSelectNodes;
+    hipLaunchKernelGGL(k_cut_select, dim3((unsigned)((n + per - 1) / per)), dim3(kSelectThreads), 0, st, parent, n,
+                       descend, in_cut);
 }
 
 // Row gather as one flat walk over output units (consecutive lanes copy
