@@ -52,7 +52,8 @@ __global__ __launch_bounds__(256) void k_cut_descend(const float *__restrict__ m
 // 47, 26 and 46; with two nodes random ones take 120 and 284, but ordered ones 28 and 52).
 constexpr int kSelectNodes = 4, kSelectThreads = 64;
 __global__ __launch_bounds__(kSelectThreads) void k_cut_select(const int32_t *__restrict__ parent, uint64_t n,
-                                                    const uint8_t *__restrict__ descend, uint8_t *__restrict__ in_cut) {
+                                                               const uint8_t *__restrict__ descend,
+                                                               uint8_t *__restrict__ in_cut) {
     const uint64_t i0 = ((uint64_t)blockIdx.x * kSelectThreads + threadIdx.x) * kSelectNodes;
     if (i0 >= n) return;
     const int m = (int)min((uint64_t)kSelectNodes, n - i0);
